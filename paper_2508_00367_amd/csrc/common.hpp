@@ -165,6 +165,9 @@ constexpr int kShiftLanes = 3;  // floats per slot (L2/L1 use the first, cosine 
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials,
                        const void* ref, bool post, int64_t M, int N, int K, hipStream_t s);
+hipError_t launch_gemm_f32(GemmEpilogue epi, rs_dist dist, const void* a, const void* w, const void* bias,
+                           const void* res, void* out, float* partials, const void* ref, bool post, int64_t M, int N,
+                           int K, hipStream_t s);
 // bf16 GEMM behind a LayerNorm (EPI_LN_BIAS / EPI_LN_BIAS_GELU).
 hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded, GemmLnFold ln, void* out,
                           int64_t M, int N, int K, hipStream_t s);

@@ -9,7 +9,7 @@
 // row and 4 consecutive output features per register quad: row-wise epilogue work
 // (residual, shift partial sums) stays inside a lane, and stores are 8-byte vectors.
 //
-// fp32 path: plain FMA tiles (parity configuration, true fp32 products).
+// fp32 path: gemm_f32.hip.
 #include <stdlib.h>
 
 #include <atomic>
@@ -1063,123 +1063,6 @@ static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, c
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// fp32 GEMM: out[m, n] = epi( sum_k a[m, k] * w[k, n] ), w as given by the caller ([K, N]).
-// 64 x 64 tile, 256 threads, each a 4 x 4 micro tile; K % 16 == 0, N % 4 == 0.
-// The shift partial sums are reduced over the 16 threads that share a row.
-// ---------------------------------------------------------------------------
-template <int EPI, int DIST>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ a,
-                                                       const float* __restrict__ w,
-                                                       const float* __restrict__ bias,
-                                                       const float* __restrict__ res,
-                                                       float* __restrict__ out,
-                                                       float* __restrict__ partials,
-                                                       const float* __restrict__ ref, int post, int M,
-                                                       int N, int K, int slots) {
-    constexpr int T = 64, KS = 16;
-    __shared__ float sa[KS][T + 4];  // a tile transposed: sa[k][m]
-    __shared__ float sw[KS][T + 4];  // sw[k][n]
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;  // tx: column quad, ty: row quad
-    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-    float acc[4][4] = {};
-    // loaders: a tile 64 rows x 16 k = 256 float4 -> one per thread; w tile 16 k x 64 n = 256 float4
-    const int a_row = tid >> 2, a_k4 = (tid & 3) * 4;
-    const int w_k = tid >> 4, w_n4 = (tid & 15) * 4;
-    for (int k0 = 0; k0 < K; k0 += KS) {
-        {
-            int r = m0 + a_row;
-            r = r < M ? r : M - 1;
-            float4 v = *reinterpret_cast<const float4*>(a + (int64_t)r * K + k0 + a_k4);
-            sa[a_k4 + 0][a_row] = v.x; sa[a_k4 + 1][a_row] = v.y;
-            sa[a_k4 + 2][a_row] = v.z; sa[a_k4 + 3][a_row] = v.w;
-            int n = n0 + w_n4;
-            float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (n < N) u = *reinterpret_cast<const float4*>(w + (int64_t)(k0 + w_k) * N + n);
-            *reinterpret_cast<float4*>(&sw[w_k][w_n4]) = u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            float4 av = *reinterpret_cast<const float4*>(&sa[k][ty * 4]);
-            float4 wv = *reinterpret_cast<const float4*>(&sw[k][tx * 4]);
-            float ar[4] = {av.x, av.y, av.z, av.w}, wr[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(ar[i], wr[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    const int n = n0 + tx * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        const bool m_ok = m < M;
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-        if (n < N) {
-            float v[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-            if (bias) {
-                float4 b = *reinterpret_cast<const float4*>(bias + n);
-                v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
-            }
-            if (EPI == EPI_BIAS_GELU) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
-            }
-            if (EPI == EPI_BIAS_RES || EPI == EPI_BIAS_RES_SHIFT) {
-                float r[4] = {0.f, 0.f, 0.f, 0.f};
-                if (m_ok) {
-                    float4 rr = *reinterpret_cast<const float4*>(res + (int64_t)m * N + n);
-                    r[0] = rr.x; r[1] = rr.y; r[2] = rr.z; r[3] = rr.w;
-                }
-                if (EPI == EPI_BIAS_RES_SHIFT && m_ok) {
-                    float fi[4] = {r[0], r[1], r[2], r[3]};
-                    if (ref) {
-                        float4 q = *reinterpret_cast<const float4*>(ref + (int64_t)m * N + n);
-                        fi[0] = q.x; fi[1] = q.y; fi[2] = q.z; fi[3] = q.w;
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float fo = post ? v[e] + r[e] : v[e];
-                        if (DIST == RS_DIST_L2) { float d = fo - fi[e]; p0 += d * d; }
-                        else if (DIST == RS_DIST_L1) { p0 += fabsf(fo - fi[e]); }
-                        else { p0 += fo * fi[e]; p1 += fo * fo; p2 += fi[e] * fi[e]; }
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += r[e];
-            }
-            if (m_ok) *reinterpret_cast<float4*>(out + (int64_t)m * N + n) = make_float4(v[0], v[1], v[2], v[3]);
-        }
-        if (EPI == EPI_BIAS_RES_SHIFT) {
-            // threads tx = 0..15 of one ty share row m: they are 16 consecutive lanes
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-                p0 += __shfl_xor(p0, off, 64);
-                if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
-            }
-            if (tx == 0 && m_ok) {
-                float* dst = partials + ((int64_t)m * slots + blockIdx.x) * kShiftLanes;
-                dst[0] = p0;
-                if (DIST == RS_DIST_COS) { dst[1] = p1; dst[2] = p2; }
-            }
-        }
-    }
-}
-
-template <int EPI, int DIST>
-static hipError_t launch_f32(const void* a, const void* w, const void* bias, const void* res,
-                             void* out, float* partials, const void* ref, bool post, int64_t M, int N,
-                             int K, hipStream_t s) {
-    dim3 grid((N + 63) / 64, (unsigned)((M + 63) / 64));
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI, DIST>), grid, dim3(256), 0, s, (const float*)a,
-                       (const float*)w, (const float*)bias, (const float*)res, (float*)out, partials,
-                       (const float*)ref, post ? 1 : 0, (int)M, N, K, (N + 63) / 64);
-    return hipGetLastError();
-}
-
 #define RS_STR2(...) #__VA_ARGS__
 #define RS_STR(...) RS_STR2(__VA_ARGS__)
 const char* gemm_build_info() {
@@ -1213,30 +1096,24 @@ hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int cou
 }
 
 int gemm_shift_slots(rs_dtype dt, int N) {
-    if (dt == RS_F32) return (N + 63) / 64;
-    return (N + 63) / 64;  // one slot per 64 features, whatever the tile variant
-}
-
-template <int EPI, int DIST>
-static hipError_t launch_any(rs_dtype dt, const void* a, const void* w, const void* bias,
-                             const void* res, void* out, float* partials, const void* ref, bool post,
-                             int64_t M, int N, int K, hipStream_t s) {
-    return dt == RS_F32 ? launch_f32<EPI, DIST>(a, w, bias, res, out, partials, ref, post, M, N, K, s)
-                        : launch_bf16<EPI, DIST>(a, w, bias, res, out, partials, ref, post, GemmLnFold{}, M, N, K, s);
+    (void)dt;
+    return (N + 63) / 64;  // one slot per 64 features, whatever the type and the tile variant
 }
 
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials, const void* ref,
                        bool post, int64_t M, int N, int K, hipStream_t s) {
     if (M == 0) return hipSuccess;
+    if (dt == RS_F32) return launch_gemm_f32(epi, dist, a, w, bias, res, out, partials, ref, post, M, N, K, s);
+    const GemmLnFold ln{};
     switch (epi) {
-        case EPI_BIAS: return launch_any<EPI_BIAS, 0>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
-        case EPI_BIAS_GELU: return launch_any<EPI_BIAS_GELU, 0>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
-        case EPI_BIAS_RES: return launch_any<EPI_BIAS_RES, 0>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
+        case EPI_BIAS: return launch_bf16<EPI_BIAS, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+        case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+        case EPI_BIAS_RES: return launch_bf16<EPI_BIAS_RES, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
         case EPI_BIAS_RES_SHIFT:
-            if (dist == RS_DIST_L2) return launch_any<EPI_BIAS_RES_SHIFT, RS_DIST_L2>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
-            if (dist == RS_DIST_L1) return launch_any<EPI_BIAS_RES_SHIFT, RS_DIST_L1>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
-            return launch_any<EPI_BIAS_RES_SHIFT, RS_DIST_COS>(dt, a, w, bias, res, out, partials, ref, post, M, N, K, s);
+            if (dist == RS_DIST_L2) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L2>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+            if (dist == RS_DIST_L1) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L1>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+            return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_COS>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
         default: break;  // the LayerNorm-folded epilogues go through launch_gemm_ln
     }
     return hipErrorInvalidValue;

@@ -1,0 +1,43 @@
+"""The fp32 matrix-core kernels at the edges of their tiles, against the fp64 checker.
+
+Bound of the linear layers: a product is exact to 2^-24 relative and every one of the K / 4 + 2
+additions behind an element rounds once, so |error| <= (K / 4 + 3) 2^-24 sum_k |a w| in the worst
+case; asserted with the largest such sum of the sampled rows."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2508_00367_amd as rs
+import synth_inputs as si
+from rs_testlib import TOL, norm_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+# rows around the 32- and 64-row tiles; 1, 2, 3, 4 and 7 slices of 64; one column tile and several; the
+# last two make more than 1024 64 x 64 tiles, which is where the taller tile takes over
+@pytest.mark.parametrize("M,K,N", [(1, 64, 64), (31, 128, 64), (32, 192, 128), (33, 256, 64), (63, 448, 192), (65, 64, 320),
+                                   (65473, 64, 64), (21900, 192, 192)])
+def test_fp32_linear_tile_edges(M, K, N):
+    _say("fp32 linear", M, K, N)
+    a, w = si.generic(41, 1, (M, K)), si.generic(41, 2, (K, N), std=0.05)
+    b, res = si.generic(41, 3, (N,)), si.generic(41, 4, (M, N))
+    out = torch.full((M, N), float("nan"), device="cuda")
+    rs.rs_linear_fwd(to_dev(a, "f32"), to_dev(w, "f32"), to_dev(b, "f32"), to_dev(res, "f32"), out, rs.RS_EPI_BIAS_RES)
+    torch.cuda.synchronize()
+    got = to_host(out)
+    assert np.isfinite(got).all()
+    rows = np.unique(np.r_[0:min(M, 70), max(0, M - 70):M])
+    ref = oracle.linear(a[rows], w, b) + res[rows]
+    bound = (K / 4 + 3) * 2.0 ** -24 * (np.abs(a[rows]).astype(np.float64) @ np.abs(w) + np.abs(b) + np.abs(res[rows])).max()
+    err = np.abs(got[rows] - ref).max()
+    _say("  err %.2e bound %.2e" % (err, bound))
+    assert err <= bound
