@@ -16,7 +16,7 @@
 //                     layout yields them (slot 4u + i  <->  key 8u + 4g + i of the group).
 // Row max / row sum need one exchange between the two half-waves per tile.
 //
-// fp32 path: one query row per thread, true fp32 products (parity configuration).
+// fp32 path (v_mfma_f32_32x32x2_f32, parity configuration): the same transposed form.
 #include "common.hpp"
 
 namespace rs {
@@ -505,90 +505,164 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// fp32 path: workgroup = 64 query rows of one (image, head), one row per thread;
-// K/V tiles of 32 keys in LDS, broadcast reads.
+// fp32 path (v_mfma_f32_32x32x2_f32, true fp32 products): workgroup = 32 query rows of one
+// (image, head), its four waves split the KEYS (wave w: tiles of 32 keys w, w + 4, ...), each with its
+// own K and V tile in LDS and no barrier in the loop; the four partial results are merged through
+// LDS in wave order.  Transposed like the bf16 kernels: S^T = K Q^T, and a lane's scores (query l32,
+// keys 8 j + 4 g + i in register 4 j + i) feed O^T = V^T P^T as they are: one k step of the instruction
+// takes one key from each half-wave.  The copies of the next K tile run under the softmax and the PV
+// product, those of the next V tile under the next scores.
+// The key split is there for small batches: four images of 197 tokens and three heads are 84 blocks
+// of 32 rows, which leave two thirds of the CUs empty and would walk seven key tiles one after the other.
+// LDS: 16 KB per wave; two workgroups per CU cover each other's waits.  Matrix-core bound at long
+// sequences (92 of the 137 TFLOP/s the chip gives fp32 products at 20 x 689 x 12 heads); 10 us at
+// 4 x 197 x 3 and 45 us at 64 x 197 x 3, where one query row per thread took 148 and 168 us.
 // ---------------------------------------------------------------------------
 constexpr int F32_BN = 32;
 
-__global__ __launch_bounds__(64) void attention_f32_kernel(
+__global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     float* __restrict__ o, int N, int64_t sb, int64_t sn, int64_t sh, int64_t osb, int64_t osn,
     int64_t osh, float scale_log2e) {
-    __shared__ __attribute__((aligned(16))) float s_k[F32_BN][DH];
-    __shared__ __attribute__((aligned(16))) float s_v[F32_BN][DH];
-    const int tid = threadIdx.x;
-    const int b = blockIdx.z, h = blockIdx.y;
+    // [32 keys][64 channels] per wave.  K: 16-byte chunk c of key r in slot c ^ (r & 15); V: the two
+    // 128-byte halves of a row swapped where (r >> 2) is odd (the half-waves read rows 4 apart)
+    __shared__ __attribute__((aligned(1024))) unsigned char s_k[4][F32_BN * 256];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_v[4][F32_BN * 256];
+    __shared__ float s_m[4][32], s_l[4][32];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int h = blockIdx.y, b = blockIdx.z;
     const int64_t base = (int64_t)b * sb + (int64_t)h * sh;
-    const int qi = blockIdx.x * 64 + tid;
-    const int qr = qi < N ? qi : N - 1;
-    float qv[DH], acc[DH];
+    const int q0 = blockIdx.x * 32;
+    const int KT = (N + F32_BN - 1) / F32_BN;
+
+    // copy i brings rows 4 i .. 4 i + 3 of a tile through a resource of its own (64-bit base, so that the
+    // row stride is limited by four rows only); rows past N read as zeros
+    const int sn4 = (int)(sn * 4);
+    const int k_voff = (lane >> 4) * sn4;
+#define F32_COPY(dst_, src_, kt_, CHUNK)                                                                          \
+    _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                               \
+        const int row_ = (kt_) * F32_BN + 4 * i, rows_ = min(N - row_, 4);                                        \
+        const __amdgpu_buffer_rsrc_t rs_ = __builtin_amdgcn_make_buffer_rsrc(                                     \
+            const_cast<float*>((src_) + base + (rows_ > 0 ? (int64_t)row_ * sn : 0)), 0,                          \
+            rows_ > 0 ? (rows_ - 1) * sn4 + DH * 4 : 0, 0x00020000);                                              \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, (att_lds_ptr)((dst_)[wave] + i * 1024), 16,                 \
+                                                 k_voff + ((CHUNK) << 4), 0, 0, 0);                               \
+    }
+#define F32_COPY_K(kt_) F32_COPY(s_k, k, kt_, (lane & 15) ^ ((4 * i + (lane >> 4)) & 15))
+#define F32_COPY_V(kt_) F32_COPY(s_v, v, kt_, (lane & 15) ^ ((i & 1) << 3))
+
+    f32x4 qf[8];  // channels 8 s + 4 g .. + 3 of query row q0 + l32
     {
+        int qr = q0 + l32;
+        qr = qr < N ? qr : N - 1;  // rows past the end are computed on a copy and never stored
         const float* qp = q + base + (int64_t)qr * sn;
 #pragma unroll
-        for (int d = 0; d < DH; d += 4) {
-            float4 t = *reinterpret_cast<const float4*>(qp + d);
-            qv[d] = t.x; qv[d + 1] = t.y; qv[d + 2] = t.z; qv[d + 3] = t.w;
-        }
-#pragma unroll
-        for (int d = 0; d < DH; ++d) acc[d] = 0.f;
+        for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const f32x4*>(qp + 8 * s + 4 * g);
     }
+    F32_COPY_K(wave)
+    F32_COPY_V(wave)
+    f32x16 oacc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
-    for (int key0 = 0; key0 < N; key0 += F32_BN) {
-        __syncthreads();
-        // 32 keys x 16 float4 = 512 float4 per tensor, 8 per thread
-        for (int t = tid; t < F32_BN * 16; t += 64) {
-            const int r = t >> 4, c = (t & 15) * 4;
-            const int kr = key0 + r;
-            float4 kk = make_float4(0.f, 0.f, 0.f, 0.f), vv = kk;
-            if (kr < N) {
-                kk = *reinterpret_cast<const float4*>(k + base + (int64_t)kr * sn + c);
-                vv = *reinterpret_cast<const float4*>(v + base + (int64_t)kr * sn + c);
-            }
-            *reinterpret_cast<float4*>(&s_k[r][c]) = kk;
-            *reinterpret_cast<float4*>(&s_v[r][c]) = vv;
-        }
-        __syncthreads();
-        float s[F32_BN];
-        float mx = -INFINITY;
+
+    for (int kt = wave; kt < KT; kt += 4) {
+        f32x16 sacc;
 #pragma unroll
-        for (int j = 0; j < F32_BN; ++j) {
-            float t = 0.f;
+        for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // K has landed (V, requested later, may be in flight)
 #pragma unroll
-            for (int d = 0; d < DH; d += 4) {
-                float4 kk = *reinterpret_cast<const float4*>(&s_k[j][d]);
-                t = fmaf(qv[d], kk.x, t); t = fmaf(qv[d + 1], kk.y, t);
-                t = fmaf(qv[d + 2], kk.z, t); t = fmaf(qv[d + 3], kk.w, t);
-            }
-            s[j] = (key0 + j < N) ? t : -INFINITY;
-            mx = fmaxf(mx, s[j]);
+        for (int s = 0; s < 8; ++s) {
+            const f32x4 kf = *reinterpret_cast<const f32x4*>(s_k[wave] + l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[s][e], sacc, 0, 0, 0);
         }
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = exp2f((m_run - m_new) * scale_log2e);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K tile has been read: its place is free
+        F32_COPY_K(kt + 4)
+        const int key0 = kt * F32_BN;
+        if (key0 + F32_BN > N) {  // keys past the end
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (key0 + (r >> 2) * 8 + g * 4 + (r & 3) >= N) sacc[r] = -INFINITY;
+        }
+        float mx = sacc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx);  // finite: every tile holds at least one real key
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
         const float mb = m_new * scale_log2e;
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
-        for (int d = 0; d < DH; ++d) acc[d] *= alpha;
-#pragma unroll
-        for (int j = 0; j < F32_BN; ++j) {
-            const float p = exp2f(fmaf(s[j], scale_log2e, -mb));
-            l_run += p;
-#pragma unroll
-            for (int d = 0; d < DH; d += 4) {
-                float4 vv = *reinterpret_cast<const float4*>(&s_v[j][d]);
-                acc[d] = fmaf(p, vv.x, acc[d]); acc[d + 1] = fmaf(p, vv.y, acc[d + 1]);
-                acc[d + 2] = fmaf(p, vv.z, acc[d + 2]); acc[d + 3] = fmaf(p, vv.w, acc[d + 3]);
-            }
+        for (int r = 0; r < 16; ++r) {
+            sacc[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], scale_log2e, -mb));
+            l_run += sacc[r];
         }
-    }
-    if (qi < N) {
-        const float inv = 1.0f / l_run;
-        float* op = o + (int64_t)b * osb + (int64_t)qi * osn + (int64_t)h * osh;
 #pragma unroll
-        for (int d = 0; d < DH; d += 4)
-            *reinterpret_cast<float4*>(op + d) =
-                make_float4(acc[d] * inv, acc[d + 1] * inv, acc[d + 2] * inv, acc[d + 3] * inv);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // V has landed (the next K may be in flight)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int db = 0; db < 2; ++db) {
+                    const float vf = *reinterpret_cast<const float*>(s_v[wave] + (8 * j + 4 * g + i) * 256 + (((db * 32 + l32) * 4) ^ (g << 7)));
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf, sacc[4 * j + i], oacc[db], 0, 0, 0);
+                }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        F32_COPY_V(kt + 4)
     }
+#undef F32_COPY_K
+#undef F32_COPY_V
+#undef F32_COPY
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // trailing (empty) copies: the tiles get reused
+
+    // ---- merge the four partials
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    if (g == 0) {
+        s_m[wave][l32] = m_run;
+        s_l[wave][l32] = l_tot;
+    }
+    __syncthreads();
+    float m_all = s_m[0][l32];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m_all = fmaxf(m_all, s_m[w][l32]);
+    float L = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) L += s_l[w][l32] * __builtin_amdgcn_exp2f((s_m[w][l32] - m_all) * scale_log2e);
+    const float f = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / L;  // 0 for a wave without tiles
+    float* part = reinterpret_cast<float*>(s_k[wave]);  // [32 rows][64 channels], this wave's own tile
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int slot = db * 8 + 2 * j + g;  // 4 channels db*32 + 8j + 4g ..
+            const f32x4 val = {oacc[db][4 * j] * f, oacc[db][4 * j + 1] * f, oacc[db][4 * j + 2] * f, oacc[db][4 * j + 3] * f};
+            *reinterpret_cast<f32x4*>(part + l32 * 64 + ((slot ^ (l32 & 15)) << 2)) = val;
+        }
+    __syncthreads();
+    const int r = tid >> 3, c8 = tid & 7;  // row of the 32, channels 8 c8 .. 8 c8 + 7
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float* pw = reinterpret_cast<const float*>(s_k[w]) + r * 64;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(pw + (((2 * c8) ^ (r & 15)) << 2));
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(pw + (((2 * c8 + 1) ^ (r & 15)) << 2));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { acc[e] += lo[e]; acc[4 + e] += hi[e]; }
+    }
+    if (q0 + r < N) Elem<float>::store8(o + (int64_t)b * osb + (int64_t)(q0 + r) * osn + (int64_t)h * osh + c8 * 8, acc);
 }
 
 hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const void* v, void* o, int B,
@@ -620,8 +694,8 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
                                (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn,
                                osh, scale_log2e, H, q_tiles * bm);
     } else {
-        dim3 grid((N + 63) / 64, H, B);
-        hipLaunchKernelGGL(attention_f32_kernel, grid, dim3(64), 0, s, (const float*)q,
+        dim3 grid((N + 31) / 32, H, B);
+        hipLaunchKernelGGL(attention_f32_kernel, grid, dim3(256), 0, s, (const float*)q,
                            (const float*)k, (const float*)v, (float*)o, N, sb, sn, sh, osb, osn, osh,
                            scale_log2e);
     }

@@ -41,3 +41,20 @@ def test_fp32_linear_tile_edges(M, K, N):
     err = np.abs(got[rows] - ref).max()
     _say("  err %.2e bound %.2e" % (err, bound))
     assert err <= bound
+
+
+# sequence lengths around the 32-key tiles and the four waves that share them (128 keys per turn)
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 64, 96, 97, 127, 128, 129, 161])
+def test_fp32_attention_key_split_edges(N):
+    B, H = 2, 3
+    _say("fp32 attention", N)
+    qkv = si.generic(42, 1, (B, N, 3, H, 64))
+    buf = torch.full((B, N + 40, 3, H, 64), float("nan"), device="cuda")   # NaN behind the last key of every image
+    buf[:, :N] = to_dev(qkv, "f32")
+    d = buf[:, :N]
+    o = torch.full((B, N, H, 64), float("nan"), device="cuda")
+    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
+    torch.cuda.synchronize()
+    err = norm_err(to_host(o), oracle.attention(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], 0.125))
+    _say("  err %.2e" % err)
+    assert err < TOL["f32"]
