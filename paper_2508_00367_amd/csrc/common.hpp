@@ -226,7 +226,7 @@ hipError_t launch_gather_stats(const void* src, const int32_t* kept_idx, void* o
 
 // scores, kept_idx and gathered = f_in[kept_idx] of every image in one launch that reads f_out and
 // f_in once (images whose f_in rows fit a compute unit's registers: shift_topk_resident_fits)
-bool shift_topk_resident_fits(rs_dtype dt, int N, int D);
+bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D);
 hipError_t launch_shift_topk_resident(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in,
                                       float* scores, int32_t* kept_idx, void* gathered, int B, int N, int D,
                                       int n_prefix, int n_keep, hipStream_t s);
@@ -238,7 +238,18 @@ hipError_t launch_grid_line_scores(const float* scores, float* row_scores, float
 hipError_t launch_grid_gather(rs_dtype dt, const void* src, const int32_t* kept_rows, const int32_t* kept_cols,
                               void* out, int B, int H, int W, int R, int Q, int C, hipStream_t s);
 
-// token-wise grid pruning: col_scores[b, j, h] = scores[b, h, kept_cols[b, h, j]]
+// line scores and both selections in one launch (grid_line_select_fits)
+bool grid_line_select_fits(int H, int W);
+hipError_t launch_grid_line_select(const float* scores, float* row_scores, float* col_scores, int32_t* kept_rows,
+                                   int32_t* kept_cols, int B, int H, int W, int R, int Q, hipStream_t s);
+// token-wise grid pruning in two launches (grid_token_fused_fits): scores, kept_cols and (unless null) the
+// compacted col_scores; then kept_rows and (unless null) the gathered map
+bool grid_token_fused_fits(int64_t B, int H, int W);
+hipError_t launch_grid_row_select(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in, float* scores,
+                                  int32_t* kept_cols, float* col_scores, int B, int H, int W, int C, int Q, hipStream_t s);
+hipError_t launch_grid_col_gather(rs_dtype dt, const void* src, const int32_t* kept_cols, const float* col_scores,
+                                  int32_t* kept_rows, void* out, int B, int H, int W, int R, int Q, int C, hipStream_t s);
+// token-wise grid pruning, lines of any length: col_scores[b, j, h] = scores[b, h, kept_cols[b, h, j]]
 hipError_t launch_grid_compact_scores(const float* scores, const int32_t* kept_cols, float* col_scores, int B, int H,
                                       int W, int Q, hipStream_t s);
 // out[b, i, j, :] = src[b, r, kept_cols[b, r, j], :], r = kept_rows[b, j, i]

@@ -6,6 +6,10 @@
 
 namespace rs {
 
+// plain vectors: arrays of the HIP vector classes (uint4) that are not written on every path end up in LDS
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------------------
 // scores[row] = D(f_out[row, :], f_in[row, :]); one wavefront per row, 8 elements per
 // lane per step, butterfly reduction in a fixed order (bit-reproducible).
@@ -43,18 +47,84 @@ __global__ __launch_bounds__(256) void shift_scores_kernel(const T* __restrict__
     }
 }
 
+// One value's share of the three sums a distance is made of, and the distance from the sums.
+template <int DIST>
+__device__ __forceinline__ void dist_term(float x, float y, float& p0, float& p1, float& p2) {
+    if (DIST == RS_DIST_L2) { const float d = x - y; p0 = fmaf(d, d, p0); }
+    else if (DIST == RS_DIST_L1) { p0 += fabsf(x - y); }
+    else { p0 = fmaf(x, y, p0); p1 = fmaf(x, x, p1); p2 = fmaf(y, y, p2); }
+}
+template <int DIST>
+__device__ __forceinline__ float dist_value(float p0, float p1, float p2) {
+    if (DIST == RS_DIST_L2) return sqrtf(p0);
+    if (DIST == RS_DIST_L1) return p0;
+    return 1.0f - p0 / (sqrtf(p1) * sqrtf(p2));
+}
+
+// Score of the row a group of G consecutive lanes holds, lane `sub` of the group elements 8 sub .. 8 sub + 7
+// (zeros past the row's end): the same additions as shift_scores_kernel's, whose missing lanes add
+// zeros, hence the same bits.
+template <int DIST, int G>
+__device__ __forceinline__ float group_score(const float (&x)[8], const float (&y)[8]) {
+    float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dist_term<DIST>(x[i], y[i], p0, p1, p2);
+#pragma unroll
+    for (int off = G / 2; off >= 1; off >>= 1) {
+        p0 += __shfl_xor(p0, off, kWave);
+        if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, kWave); p2 += __shfl_xor(p2, off, kWave); }
+    }
+    return dist_value<DIST>(p0, p1, p2);
+}
+
+// Narrow rows (D <= 8 G, G = 8, 16 or 32 lanes): 64 / G rows per wave and four such groups of rows per
+// thread, all requested before the first is summed.  With one wave per row a 64-channel map kept 8 of
+// 64 lanes busy with one 16-byte request each.
+template <typename T, int DIST, int G>
+__global__ __launch_bounds__(256) void shift_scores_narrow_kernel(const T* __restrict__ f_out,
+                                                                  const T* __restrict__ f_in,
+                                                                  float* __restrict__ scores, int64_t M, int D) {
+    constexpr int U = 4, RPG = 256 / G;  // row groups per thread, rows per workgroup and group
+    const int sub = threadIdx.x % G;
+    const int64_t row0 = (int64_t)blockIdx.x * (RPG * U) + threadIdx.x / G;
+    const bool on = sub * 8 < D;
+    float x[U][8], y[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t row = row0 + u * RPG;
+        if (on && row < M) {
+            Elem<T>::load8(f_out + row * D + sub * 8, x[u]);
+            Elem<T>::load8(f_in + row * D + sub * 8, y[u]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[u][i] = y[u][i] = 0.f;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t row = row0 + u * RPG;
+        const float sc = group_score<DIST, G>(x[u], y[u]);
+        if (sub == 0 && row < M) scores[row] = sc;
+    }
+}
+
 template <typename T>
 static hipError_t launch_scores_t(rs_dist dist, const void* f_out, const void* f_in, float* scores,
                                   int64_t M, int D, hipStream_t s) {
-    dim3 grid((unsigned)((M + 3) / 4)), block(256);
     const T* a = (const T*)f_out;
     const T* b = (const T*)f_in;
-    if (dist == RS_DIST_L2)
-        hipLaunchKernelGGL((shift_scores_kernel<T, RS_DIST_L2>), grid, block, 0, s, a, b, scores, M, D);
-    else if (dist == RS_DIST_L1)
-        hipLaunchKernelGGL((shift_scores_kernel<T, RS_DIST_L1>), grid, block, 0, s, a, b, scores, M, D);
-    else
-        hipLaunchKernelGGL((shift_scores_kernel<T, RS_DIST_COS>), grid, block, 0, s, a, b, scores, M, D);
+#define RS_SCORES(KERNEL_, ROWS_)                                                                                \
+    hipLaunchKernelGGL(KERNEL_, dim3((unsigned)((M + (ROWS_) - 1) / (ROWS_))), dim3(256), 0, s, a, b, scores, M, D)
+#define RS_SCORES_D(DIST_)                                                                                       \
+    if (D <= 64) RS_SCORES((shift_scores_narrow_kernel<T, DIST_, 8>), 128);                                      \
+    else if (D <= 128) RS_SCORES((shift_scores_narrow_kernel<T, DIST_, 16>), 64);                                \
+    else if (D <= 256) RS_SCORES((shift_scores_narrow_kernel<T, DIST_, 32>), 32);                                \
+    else RS_SCORES((shift_scores_kernel<T, DIST_>), 4);
+    if (dist == RS_DIST_L2) { RS_SCORES_D(RS_DIST_L2) }
+    else if (dist == RS_DIST_L1) { RS_SCORES_D(RS_DIST_L1) }
+    else { RS_SCORES_D(RS_DIST_COS) }
+#undef RS_SCORES_D
+#undef RS_SCORES
     return hipGetLastError();
 }
 
@@ -95,11 +165,11 @@ hipError_t launch_finalize_scores(rs_dist dist, const float* partials, int slots
 }
 
 // ---------------------------------------------------------------------------
-// Selection: one workgroup per image.  Scores become order-preserving uint32 keys
-// (sign flip trick; NaN above +inf); a 4-pass, 8-bit, most-significant-first radix
-// select over an LDS histogram finds the key of the n_keep-th largest candidate and
-// how many candidates equal to it survive (lowest indices first); one ordered
-// compaction pass then writes the prefix and the survivors in ascending index order.
+// Selection: one workgroup per image.  Scores become order-preserving uint32 keys (sign flip trick;
+// NaN above +inf).  Up to 256 tokens a token's rank is counted directly; longer sequences find the key
+// of the n_keep-th largest candidate by most-significant-first radix passes over an LDS histogram, and
+// an ordered compaction writes the prefix and the survivors in ascending index order (equal keys:
+// the lowest indices survive).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t score_key(float s) {
     const uint32_t u = __float_as_uint(s);
@@ -123,24 +193,158 @@ __device__ __forceinline__ int block_scan_incl(int v, int* s_wave /*[NT / 64]*/,
     return v + add;
 }
 
+constexpr int SEL_LIST = 256;                 // candidates the last step ranks by counting
+constexpr int SEL_MAXN = 12288;               // longest sequence whose keys are kept in LDS
+constexpr int SEL_WORDS = SEL_MAXN / 64 + 16; // 64-token words of the compaction
 struct SelectShared {
     int hist[256];
-    int wave[16];
+    int wave[32];
     uint32_t prefix;
-    int remaining;
+    int remaining, count;
+    __attribute__((aligned(16))) uint32_t list[SEL_LIST];
+    int gt[SEL_WORDS], eq[SEL_WORDS];
 };
 
-// Selection of one image by the NT threads of a workgroup (all of them must call it): among
+// The selection for N <= SEL_MAXN tokens whose scores are in LDS (all NT threads call it; they see sc).
+// What the general form below spends its time on is taken out: no pass over the bits all keys share (the
+// scores of a sequence lie within a factor of a few, so the leading 8 bits put every key into one
+// histogram bin, one serialised LDS atomic per token), no pass for the low bits (once at most SEL_LIST
+// candidates share the digits found so far their ranks are counted directly, usually after one pass),
+// and the compaction takes 64 tokens per ballot.  10.1 -> 6.7 us at 8 x 1569 tokens.  `sc` is
+// overwritten with the keys.
+template <int NT>
+__device__ __forceinline__ void block_select_lds(float* sc, int N, int n_prefix, int n_keep, int32_t* __restrict__ out,
+                                                 SelectShared& sh, int tid) {
+    const int lane = tid & 63, wave = tid >> 6;
+    constexpr int NW = NT / 64;
+    uint32_t* keys = reinterpret_cast<uint32_t*>(sc);
+    for (int i = tid; i < n_prefix; i += NT) out[i] = i;
+    if (n_keep == 0) return;  // uniform over the workgroup
+    uint32_t k_and = ~0u, k_or = 0u;
+    for (int i = n_prefix + tid; i < N; i += NT) {
+        const uint32_t key = score_key(sc[i]);
+        keys[i] = key;
+        k_and &= key;
+        k_or |= key;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        k_and &= __shfl_xor(k_and, off, 64);
+        k_or |= __shfl_xor(k_or, off, 64);
+    }
+    if (lane == 0) { sh.wave[wave] = (int)k_and; sh.wave[16 + wave] = (int)k_or; }
+    if (tid < 256) sh.hist[tid] = 0;
+    if (tid == 0) sh.count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { k_and &= (uint32_t)sh.wave[w]; k_or |= (uint32_t)sh.wave[16 + w]; }
+    const uint32_t diff = k_and ^ k_or;       // bits in which some keys differ
+    uint32_t thr = k_and;
+    int remaining = n_keep;                   // candidates with the digits found so far still to take
+    if (diff) {
+        int top = 32 - __clz(diff);           // bits [0, top) are still open
+        uint32_t mask = top == 32 ? 0u : ~0u << top, prefix = k_and & mask;
+        for (;;) {
+            const int shift = top > 8 ? top - 8 : 0;
+            for (int i = n_prefix + tid; i < N; i += NT)
+                if ((keys[i] & mask) == prefix) atomicAdd(&sh.hist[(keys[i] >> shift) & ((1u << (top - shift)) - 1u)], 1);
+            __syncthreads();
+            if (wave == 0) {                  // lane l: bins 255 - 4 l ... 252 - 4 l, counted from the top
+                int c[4], incl = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { c[e] = sh.hist[255 - 4 * lane - e]; incl += c[e]; }
+                const int own = incl;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int t = __shfl_up(incl, off, 64);
+                    if (lane >= off) incl += t;
+                }
+                int above = incl - own;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (above < remaining && above + c[e] >= remaining) {
+                        sh.prefix = prefix | ((uint32_t)(255 - 4 * lane - e) << shift);
+                        sh.remaining = remaining - above;
+                        sh.gt[0] = c[e];
+                    }
+                    above += c[e];
+                }
+            }
+            __syncthreads();
+            prefix = sh.prefix;
+            remaining = sh.remaining;
+            const int cnt = sh.gt[0];
+            mask = shift ? ~0u << shift : ~0u;
+            top = shift;
+            if (shift == 0) { thr = prefix; break; }
+            if (cnt <= SEL_LIST) {            // few candidates left: count their ranks
+                for (int i = n_prefix + tid; i < N; i += NT)
+                    if ((keys[i] & mask) == prefix) sh.list[atomicAdd(&sh.count, 1)] = keys[i];
+                __syncthreads();
+                if (tid < cnt) {
+                    const uint32_t mine = sh.list[tid];
+                    int g = 0, e = 0;
+#pragma unroll 8
+                    for (int t = 0; t < cnt; ++t) { const uint32_t k = sh.list[t]; g += k > mine; e += k == mine; }
+                    if (g < remaining && g + e >= remaining) { sh.prefix = mine; sh.remaining = remaining - g; }
+                }
+                // (every thread read sh.remaining before the barrier above)
+                __syncthreads();
+                thr = sh.prefix;
+                remaining = sh.remaining;
+                break;
+            }
+            if (tid < 256) sh.hist[tid] = 0;
+            __syncthreads();
+        }
+    }
+    // `remaining` of the candidates equal to thr survive, lowest indices first.  Word t = tokens 64 t .. + 63.
+    const int words = (N + 63) / 64;
+    __syncthreads();
+    for (int t = wave; t < words; t += NW) {
+        const int i = t * 64 + lane;
+        const bool in = i >= n_prefix && i < N;
+        const uint32_t key = in ? keys[i] : 0u;
+        const unsigned long long g = __ballot(in && key > thr), e = __ballot(in && key == thr);
+        if (lane == 0) { sh.gt[t] = __popcll(g); sh.eq[t] = __popcll(e); }
+    }
+    __syncthreads();
+    if (wave == 0) {                          // exclusive sums over the words
+        int bg = 0, be = 0;
+        for (int t0 = 0; t0 < words; t0 += 64) {
+            const int t = t0 + lane;
+            const int g = t < words ? sh.gt[t] : 0, e = t < words ? sh.eq[t] : 0;
+            int ig = g, ie = e;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int ug = __shfl_up(ig, off, 64), ue = __shfl_up(ie, off, 64);
+                if (lane >= off) { ig += ug; ie += ue; }
+            }
+            if (t < words) { sh.gt[t] = bg + ig - g; sh.eq[t] = be + ie - e; }
+            bg += __shfl(ig, 63, 64);
+            be += __shfl(ie, 63, 64);
+        }
+    }
+    __syncthreads();
+    for (int t = wave; t < words; t += NW) {
+        const int i = t * 64 + lane;
+        const bool in = i >= n_prefix && i < N;
+        const uint32_t key = in ? keys[i] : 0u;
+        const bool gt = in && key > thr, eq = in && key == thr;
+        const unsigned long long below = (1ull << lane) - 1ull, mg = __ballot(gt), me = __ballot(eq);
+        const int gb = sh.gt[t] + __popcll(mg & below), eb = sh.eq[t] + __popcll(me & below);
+        if (gt || (eq && eb < remaining)) out[n_prefix + gb + min(eb, remaining)] = i;
+    }
+}
+
+// General form, any N: selection of one image by the NT threads of a workgroup (all of them must call it): among
 // the tokens i >= n_prefix of sc[0 .. N) the n_keep highest keys survive, equal keys by lower
 // index; out[0 .. n_prefix + n_keep) lists the prefix and the survivors in ascending order.
-// With `slot` (N ints, workgroup-visible) slot[i] becomes the position of token i in `out`, or
-// -1 for a dropped token.  `sc` may be LDS or global memory written before a barrier.
+// `sc` is global memory.
 template <int NT>
 __device__ __forceinline__ void block_select(const float* sc, int N, int n_prefix, int n_keep,
-                                             int32_t* __restrict__ out, int* slot, SelectShared& sh, int tid) {
+                                             int32_t* __restrict__ out, SelectShared& sh, int tid) {
     for (int i = tid; i < n_prefix; i += NT) out[i] = i;
-    if (slot)
-        for (int i = tid; i < N; i += NT) slot[i] = i < n_prefix ? i : -1;
     if (n_keep == 0) return;  // uniform over the workgroup
 
     uint32_t prefix = 0, mask = 0;
@@ -191,35 +395,45 @@ __device__ __forceinline__ void block_select(const float* sc, int N, int n_prefi
         const uint32_t key = score_key(sc[i]);
         bool keep = key > thr;
         if (key == thr) { keep = eq_rank < remaining; ++eq_rank; }
-        if (keep) {
-            if (slot) slot[i] = pos;
-            out[pos++] = i;
-        }
+        if (keep) out[pos++] = i;
     }
+}
+
+// Number of the n keys in `keys` (LDS, 16-byte aligned, zeros from n up to the next multiple of 4) that
+// go before candidate i with key `mine`: larger ones, and equal ones with a lower index.  Vectors
+// first, first + step, ... of four keys: read four at a time and unrolled, because a loop of single
+// reads costs the LDS latency per key (197 keys: 8 us).
+__device__ __forceinline__ int count_before(const uint32_t* keys, int n, uint32_t mine, int i, int first, int step) {
+    int cnt = 0;
+    const int nv = (n + 3) >> 2;
+#pragma unroll 4
+    for (int v = first; v < nv; v += step) {
+        const u32x4 k4 = *reinterpret_cast<const u32x4*>(keys + 4 * v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cnt += (k4[e] > mine) || (k4[e] == mine && 4 * v + e < i);
+    }
+    return cnt;
 }
 
 // The same selection for N <= 256 tokens by counting: token i's rank among the candidates is the
 // number of candidates with a larger key, or an equal key and a lower index; ranks below n_keep
 // survive.  NT / 256 threads share a token's count, a ballot scan over the survival flags gives the
-// output positions: three barriers instead of the radix passes' thirty.  Identical results.
+// output positions: four barriers instead of the radix passes' thirty.  Identical results.
+// With `slot` (N ints, workgroup-visible) slot[i] becomes the position of token i in `out`, or
+// -1 for a dropped token.
 template <int NT>
 __device__ __forceinline__ void block_select_rank(const float* sc /* LDS */, int N, int n_prefix, int n_keep,
                                                   int32_t* __restrict__ out, int* slot, SelectShared& sh, int tid) {
     constexpr int TPT = NT / 256;  // threads per token
+    const int n = N - n_prefix;
+    // (a caller that loops has a barrier between this write and the previous round's reads of sh)
+    if (tid < 256) sh.list[tid] = tid < n ? score_key(sc[n_prefix + tid]) : 0u;
+    __syncthreads();
     const int i = tid / TPT, part = tid % TPT;
     int cnt = 0;
-    if (i >= n_prefix && i < N) {
-        const uint32_t ki = score_key(sc[i]);
-        const int n = N - n_prefix, seg = (n + TPT - 1) / TPT;
-        const int lo = n_prefix + part * seg, hi = min(lo + seg, N);
-        for (int j = lo; j < hi; ++j) {
-            const uint32_t kj = score_key(sc[j]);
-            cnt += (kj > ki) || (kj == ki && j < i);
-        }
-    }
+    if (i >= n_prefix && i < N) cnt = count_before(sh.list, n, sh.list[i - n_prefix], i - n_prefix, part, TPT);
 #pragma unroll
     for (int off = 1; off < TPT; off <<= 1) cnt += __shfl_xor(cnt, off, 64);
-    // (a caller that loops has a barrier between this write and the previous round's reads of sh)
     if (part == 0 && i < N) sh.hist[i] = (i < n_prefix || cnt < n_keep) ? 1 : 0;
     __syncthreads();
     const int lane = tid & 63, wave = tid >> 6;
@@ -236,9 +450,10 @@ __device__ __forceinline__ void block_select_rank(const float* sc /* LDS */, int
     }
 }
 
-// With `partials` the scores are first formed from the GEMM epilogue's per-row slots (added in
-// slot order, as finalize_scores_kernel does), kept in LDS for the selection and written to
-// `scores`: the block's prune pass needs no separate score launch.  N * 4 bytes of dynamic LDS.
+// One image per workgroup.  The scores go through LDS (N * 4 bytes of dynamic LDS, N <= SEL_MAXN): read
+// from `scores`, or with `partials` formed from the GEMM epilogue's per-row slots (added in slot order,
+// as finalize_scores_kernel does) and written to `scores` on the way: the block's prune pass needs no
+// separate score launch.
 template <int NT>
 __global__ __launch_bounds__(NT) void select_kernel(float* __restrict__ scores,
                                                      int32_t* __restrict__ kept_idx, int N,
@@ -247,31 +462,38 @@ __global__ __launch_bounds__(NT) void select_kernel(float* __restrict__ scores,
     __shared__ SelectShared sh;
     extern __shared__ float s_scores[];
     const int tid = threadIdx.x;
-    const float* sc = scores + (int64_t)blockIdx.x * N;
+    float* sc = scores + (int64_t)blockIdx.x * N;
     int32_t* out = kept_idx + (int64_t)blockIdx.x * (n_prefix + n_keep);
-    if (partials) {
-        for (int i = tid; i < N; i += NT) {
+    for (int i = tid; i < N; i += NT) {
+        float r;
+        if (partials) {
             const float* p = partials + ((int64_t)blockIdx.x * N + i) * slots * kShiftLanes;
             float p0 = 0.f, p1 = 0.f, p2 = 0.f;
             for (int sl = 0; sl < slots; ++sl) {
                 p0 += p[sl * kShiftLanes];
                 if (dist == RS_DIST_COS) { p1 += p[sl * kShiftLanes + 1]; p2 += p[sl * kShiftLanes + 2]; }
             }
-            float r;
             if (dist == RS_DIST_L2) r = sqrtf(p0);
             else if (dist == RS_DIST_L1) r = p0;
             else r = 1.0f - p0 / (sqrtf(p1) * sqrtf(p2));
-            s_scores[i] = r;
-            scores[(int64_t)blockIdx.x * N + i] = r;
+            sc[i] = r;
+        } else {
+            r = sc[i];
         }
-        sc = s_scores;
-        __syncthreads();
-        if (NT > 256) {  // short sequences: launched with NT / 256 threads per token (N <= 256)
-            block_select_rank<NT>(sc, N, n_prefix, n_keep, out, nullptr, sh, tid);
-            return;
-        }
+        s_scores[i] = r;
     }
-    block_select<NT>(sc, N, n_prefix, n_keep, out, nullptr, sh, tid);
+    __syncthreads();
+    if (N <= 256) block_select_rank<NT>(s_scores, N, n_prefix, n_keep, out, nullptr, sh, tid);
+    else block_select_lds<NT>(s_scores, N, n_prefix, n_keep, out, sh, tid);
+}
+
+// Sequences beyond SEL_MAXN tokens: the scores stay in global memory.
+__global__ __launch_bounds__(1024) void select_long_kernel(const float* __restrict__ scores,
+                                                           int32_t* __restrict__ kept_idx, int N, int n_prefix,
+                                                           int n_keep) {
+    __shared__ SelectShared sh;
+    block_select<1024>(scores + (int64_t)blockIdx.x * N, N, n_prefix, n_keep,
+                       kept_idx + (int64_t)blockIdx.x * (n_prefix + n_keep), sh, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -284,7 +506,6 @@ __global__ __launch_bounds__(NT) void select_kernel(float* __restrict__ scores,
 // kept rows are not read a second time: memory traffic is the algorithmic minimum
 // (2 N D e read, K D e written per image).  Workgroups loop over images (persistent grid).
 // ---------------------------------------------------------------------------
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 template <typename T> __device__ __forceinline__ void unpack8(u32x2 v, float (&f)[4]);
 template <> __device__ __forceinline__ void unpack8<bf16raw>(u32x2 v, float (&f)[4]) {
     f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
@@ -406,8 +627,26 @@ __global__ __launch_bounds__(RES_WAVES * 64) void shift_topk_resident_kernel(
     }
 }
 
-bool shift_topk_resident_fits(rs_dtype dt, int N, int D) {
-    return N <= RES_MAXN && (size_t)D * elem_size(dt) <= 512 * 3;
+static int resident_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
+        return n;
+    }();
+    return cus;
+}
+
+// Where the one-pass kernel is the faster way.  Its workgroup holds one image whatever its length and
+// works through it serially, so it needs images that fill the registers (more than half of the rows it
+// has room for) and rounds of the chip that are at least three quarters full; otherwise the
+// three launches, each spread over all rows, win although they read the kept rows twice.  bf16, D 768,
+// one pass / three launches in us: 197 tokens 16 images 25.4 / 10.2, 128: 30.2 / 28.7, 192: 34.5 / 38.3,
+// 256: 39.3 / 47.7, 320: 72.7 / 61.2, 512: 101 / 95, 1024: 193 / 220; 64 tokens 256: 24.1 / 20.1, 1024: 84 / 63.
+// (D 192 and 384 cross at the same places.)
+bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D) {
+    if (N > RES_MAXN || (size_t)D * elem_size(dt) > 512 * 3) return false;
+    const int64_t cus = resident_cus(), rounds = (B + cus - 1) / cus;
+    return 2 * N > RES_MAXN && 4 * (int64_t)B >= 3 * rounds * cus;
 }
 
 template <typename T, int CH>
@@ -428,11 +667,7 @@ hipError_t launch_shift_topk_resident(rs_dtype dt, rs_dist dist, const void* f_o
                                       float* scores, int32_t* kept_idx, void* gathered, int B, int N, int D,
                                       int n_prefix, int n_keep, hipStream_t s) {
     if (B == 0 || N == 0) return hipSuccess;
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-        return n;
-    }();
+    const int cus = resident_cus();
     const int grid = B < cus ? B : cus;  // one workgroup fills a compute unit's register file
     const int ch = (int)(((size_t)D * elem_size(dt) + 511) / 512);
 #define RS_RES_CH(T_)                                                                                                   \
@@ -456,17 +691,20 @@ hipError_t launch_select(const float* scores, int32_t* kept_idx, int B, int N, i
         const int64_t tot = (int64_t)B * N;
         hipLaunchKernelGGL(iota_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, kept_idx, B, N);
     } else {
-        if (N > 1024)
-            hipLaunchKernelGGL(select_kernel<1024>, dim3(B), dim3(1024), 0, s, const_cast<float*>(scores), kept_idx, N,
+        const size_t lds = (size_t)N * sizeof(float);
+        if (N > SEL_MAXN)
+            hipLaunchKernelGGL(select_long_kernel, dim3(B), dim3(1024), 0, s, scores, kept_idx, N, n_prefix, n_keep);
+        else if (N > 1024 || N <= 256)  // counting: four threads per token
+            hipLaunchKernelGGL(select_kernel<1024>, dim3(B), dim3(1024), lds, s, const_cast<float*>(scores), kept_idx, N,
                                n_prefix, n_keep, (const float*)nullptr, 0, 0);
         else
-            hipLaunchKernelGGL(select_kernel<256>, dim3(B), dim3(256), 0, s, const_cast<float*>(scores), kept_idx, N,
+            hipLaunchKernelGGL(select_kernel<256>, dim3(B), dim3(256), lds, s, const_cast<float*>(scores), kept_idx, N,
                                n_prefix, n_keep, (const float*)nullptr, 0, 0);
     }
     return hipGetLastError();
 }
 
-bool select_from_partials_fits(int N) { return N <= 12288; }  // scores of one image in LDS
+bool select_from_partials_fits(int N) { return N <= SEL_MAXN; }  // scores of one image in LDS
 
 hipError_t launch_select_from_partials(rs_dist dist, const float* partials, int slots, float* scores,
                                        int32_t* kept_idx, int B, int N, int n_prefix, int n_keep,
@@ -491,22 +729,41 @@ hipError_t launch_select_from_partials(rs_dist dist, const float* partials, int 
 }
 
 // ---------------------------------------------------------------------------
-// Gather: out[b, j, :] = src[b, kept_idx[b, j], :]; one wavefront per row, 16 bytes per
-// lane per step (rows are D * e bytes, a multiple of 16).  (A variant over the flat output, four
-// vectors per thread whatever the row length, measured 50 % slower at 1536-byte rows.)
+// Gather: out[b, j, :] = src[b, kept_idx[b, j], :].  G lanes per row (the next power of two of its 16-byte
+// vectors, at most a wave), U rows per thread and CH vectors of each at a time.  What limits it is the
+// chain index -> row -> store, so everything a thread needs is requested before its first store:
+// stores and loads share one counter, and a load behind a store waits for that store too (three
+// vectors per lane in a plain loop: 20 us against 6 for 8 x 785 rows of 3 KB).
+// (A variant over the flat output, four vectors per thread whatever the row length, measured 50 %
+// slower at 1536-byte rows.)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gather_rows_kernel(const uint4* __restrict__ src,
+template <int G, int U, int CH>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const u32x4* __restrict__ src,
                                                           const int32_t* __restrict__ kept_idx,
-                                                          uint4* __restrict__ out, int64_t rows,
+                                                          u32x4* __restrict__ out, int64_t rows,
                                                           int N, int K, int row_vec) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= rows) return;
-    const int64_t b = r / K;
-    const int32_t idx = kept_idx[r];
-    const uint4* s = src + (b * N + idx) * row_vec;
-    uint4* d = out + r * row_vec;
-    for (int c = lane; c < row_vec; c += 64) d[c] = s[c];
+    constexpr int RPG = 256 / G;
+    const int sub = threadIdx.x % G;
+    const int64_t r0 = (int64_t)blockIdx.x * (RPG * U) + threadIdx.x / G;
+    int64_t sp[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t r = r0 + u * RPG;  // rows < 2^31
+        sp[u] = r < rows ? (int64_t)((uint32_t)r / (uint32_t)K) * N + kept_idx[r] : -1;
+    }
+    for (int c = sub; c < row_vec; c += G * CH) {
+        u32x4 v[U][CH];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (sp[u] >= 0 && c + k * G < row_vec) v[u][k] = src[sp[u] * row_vec + c + k * G];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < CH; ++k)
+                if (sp[u] >= 0 && c + k * G < row_vec) out[(r0 + u * RPG) * row_vec + c + k * G] = v[u][k];
+    }
 }
 
 // The same gather for bf16 rows that also leaves the LayerNorm statistics of every row it writes
@@ -561,23 +818,57 @@ hipError_t launch_gather_stats(const void* src, const int32_t* kept_idx, void* o
     return hipGetLastError();
 }
 
+// lanes that share one row of `vec` 16-byte vectors in the gathers: the next power of two, at most a wave
+static int gather_lanes(int vec) {
+    int g = 1;
+    while (g < vec && g < 64) g *= 2;
+    return g;
+}
+
+#define RS_GATHER_LANES(g_, CALL_)                                                     \
+    switch (g_) {                                                                      \
+        case 1: case 2: case 4: case 8: CALL_(8); break;                               \
+        case 16: CALL_(16); break;                                                     \
+        case 32: CALL_(32); break;                                                     \
+        default: CALL_(64); break;                                                     \
+    }
+
 hipError_t launch_gather(rs_dtype dt, const void* src, const int32_t* kept_idx, void* out, int B,
                          int N, int K, int D, hipStream_t s) {
     const int64_t rows = (int64_t)B * K;
     if (rows == 0) return hipSuccess;
     const int row_vec = (int)((size_t)D * elem_size(dt) / 16);
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
-                       (const uint4*)src, kept_idx, (uint4*)out, rows, N, K, row_vec);
+#define RS_CALL(G_)                                                                                              \
+    {                                                                                                            \
+        constexpr int U_ = G_ == 64 ? 1 : 4, CH_ = G_ == 64 ? 4 : 1, RPW_ = 256 / G_ * U_;  /* rows per workgroup */ \
+        hipLaunchKernelGGL((gather_rows_kernel<G_, U_, CH_>), dim3((unsigned)((rows + RPW_ - 1) / RPW_)), dim3(256), 0, \
+                           s, (const u32x4*)src, kept_idx, (u32x4*)out, rows, N, K, row_vec);                    \
+    }
+    RS_GATHER_LANES(gather_lanes(row_vec), RS_CALL)
+#undef RS_CALL
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Line-wise pruning of a 2-D token grid (Sec. 4.2, "CNN and SSM", variant (ii)).
-// Line scores: the per-position shift averaged along each row and along each column; one
-// workgroup per image, thread h sums row h over w in index order and thread w sums column w
-// over h in index order (fixed order: bit-reproducible).  The rows and columns to keep are then
-// picked by select_kernel, and the grid gather copies the surviving positions.
+// Pruning of a 2-D token grid (Sec. 4.2, "CNN and SSM").  Feature maps are narrow (64-512 channels) and
+// their lines short (7-56 positions), so what costs time is launches, idle lanes and the fixed work
+// of a selection: the kernels below take several positions per wave, and lines of at most
+// GRID_LINE positions are selected by counting inside the kernel that has their scores.  Longer lines
+// go through separate selection launches.
 // ---------------------------------------------------------------------------
+constexpr int GRID_LINE = 256;
+
+// Linear workgroup id -> item of [0, n): ids go round-robin to the 8 XCDs, XCD x takes a contiguous range
+// (neighbouring lines write neighbouring bytes: they should meet in one L2).  -1: no item.
+__device__ __forceinline__ int xcd_item(unsigned bid, int n) {
+    const int x = bid & 7, j = bid >> 3, q = n >> 3, r = n & 7;
+    if (j >= q + (x < r ? 1 : 0)) return -1;
+    return x * q + (x < r ? x : r) + j;
+}
+
+// Line-wise variant: the per-position shift averaged along each row and along each column; thread h sums
+// row h over w in index order and thread w sums column w over h in index order (fixed order:
+// bit-reproducible).
 __global__ __launch_bounds__(256) void grid_line_scores_kernel(const float* __restrict__ scores,
                                                                float* __restrict__ row_scores,
                                                                float* __restrict__ col_scores, int H, int W) {
@@ -601,20 +892,86 @@ hipError_t launch_grid_line_scores(const float* scores, float* row_scores, float
     return hipGetLastError();
 }
 
-// out[b, i, j, :] = src[b, kept_rows[b, i], kept_cols[b, j], :]; one wavefront per output position
-__global__ __launch_bounds__(256) void grid_gather_kernel(const uint4* __restrict__ src,
+// The same sums (same order) from a copy of the image's scores in LDS, followed by both selections:
+// one launch for the three of the general path.  H, W <= GRID_LINE, H * W * 4 bytes of dynamic LDS.
+constexpr size_t GRID_LDS = 64 * 1024;
+__global__ __launch_bounds__(512) void grid_line_select_kernel(const float* __restrict__ scores,
+                                                               float* __restrict__ row_scores,
+                                                               float* __restrict__ col_scores,
+                                                               int32_t* __restrict__ kept_rows,
+                                                               int32_t* __restrict__ kept_cols, int H, int W, int R,
+                                                               int Q) {
+    __shared__ SelectShared sh;
+    __shared__ float s_row[GRID_LINE], s_col[GRID_LINE];
+    extern __shared__ float s_map[];
+    const int tid = threadIdx.x;
+    const int64_t b = blockIdx.x;
+    const float* s = scores + b * H * W;
+    for (int i = tid; i < H * W; i += 512) s_map[i] = s[i];
+    __syncthreads();
+    if (tid < 256) {
+        if (tid < H) {
+            float a = 0.f;
+            for (int w = 0; w < W; ++w) a += s_map[tid * W + w];
+            row_scores[b * H + tid] = s_row[tid] = a / (float)W;
+        }
+    } else if (tid - 256 < W) {
+        const int w = tid - 256;
+        float a = 0.f;
+        for (int h = 0; h < H; ++h) a += s_map[h * W + w];
+        col_scores[b * W + w] = s_col[w] = a / (float)H;
+    }
+    __syncthreads();
+    if (R > 0) block_select_rank<512>(s_row, H, 0, R, kept_rows + b * R, nullptr, sh, tid);
+    __syncthreads();
+    if (Q > 0) block_select_rank<512>(s_col, W, 0, Q, kept_cols + b * Q, nullptr, sh, tid);
+}
+
+bool grid_line_select_fits(int H, int W) {
+    return H <= GRID_LINE && W <= GRID_LINE && (size_t)H * W * sizeof(float) <= GRID_LDS - 4096;
+}
+
+hipError_t launch_grid_line_select(const float* scores, float* row_scores, float* col_scores, int32_t* kept_rows,
+                                   int32_t* kept_cols, int B, int H, int W, int R, int Q, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    hipLaunchKernelGGL(grid_line_select_kernel, dim3(B), dim3(512), (size_t)H * W * sizeof(float), s, scores, row_scores,
+                       col_scores, kept_rows, kept_cols, H, W, R, Q);
+    return hipGetLastError();
+}
+
+// out[b, i, j, :] = src[b, kept_rows[b, i], kept_cols[b, j], :]; G lanes per output position, four
+// positions per thread, all requested before the first is stored
+template <int G>
+__global__ __launch_bounds__(256) void grid_gather_kernel(const u32x4* __restrict__ src,
                                                           const int32_t* __restrict__ kept_rows,
                                                           const int32_t* __restrict__ kept_cols,
-                                                          uint4* __restrict__ out, int64_t positions, int H, int W,
+                                                          u32x4* __restrict__ out, int64_t positions, int H, int W,
                                                           int R, int Q, int vec) {
-    const int lane = threadIdx.x & 63;
-    const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (p >= positions) return;
-    const int64_t b = p / ((int64_t)R * Q);
-    const int ij = (int)(p - b * R * Q);
-    const int i = ij / Q, j = ij - i * Q;
-    const int64_t sp = (b * H + kept_rows[b * R + i]) * W + kept_cols[b * Q + j];
-    for (int c = lane; c < vec; c += 64) out[p * vec + c] = src[sp * vec + c];
+    constexpr int U = 4, PPG = 256 / G;
+    const int sub = threadIdx.x % G;
+    const int64_t p0 = (int64_t)blockIdx.x * (PPG * U) + threadIdx.x / G;
+    int64_t sp[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t p = p0 + u * PPG;
+        if (p < positions) {
+            const uint32_t pu = (uint32_t)p;  // positions < 2^31
+            const uint32_t b = pu / (uint32_t)(R * Q), ij = pu - b * (uint32_t)(R * Q);
+            const uint32_t i = ij / (uint32_t)Q, j = ij - i * Q;
+            sp[u] = ((int64_t)b * H + kept_rows[(int64_t)b * R + i]) * W + kept_cols[(int64_t)b * Q + j];
+        } else {
+            sp[u] = -1;
+        }
+    }
+    for (int c = sub; c < vec; c += G) {
+        u32x4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (sp[u] >= 0) v[u] = src[sp[u] * vec + c];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (sp[u] >= 0) out[(p0 + u * PPG) * vec + c] = v[u];
+    }
 }
 
 hipError_t launch_grid_gather(rs_dtype dt, const void* src, const int32_t* kept_rows, const int32_t* kept_cols,
@@ -622,17 +979,171 @@ hipError_t launch_grid_gather(rs_dtype dt, const void* src, const int32_t* kept_
     const int64_t positions = (int64_t)B * R * Q;
     if (positions == 0) return hipSuccess;
     const int vec = (int)((size_t)C * elem_size(dt) / 16);
-    hipLaunchKernelGGL(grid_gather_kernel, dim3((unsigned)((positions + 3) / 4)), dim3(256), 0, s, (const uint4*)src,
-                       kept_rows, kept_cols, (uint4*)out, positions, H, W, R, Q, vec);
+#define RS_CALL(G_)                                                                                                  \
+    hipLaunchKernelGGL(grid_gather_kernel<G_>, dim3((unsigned)((positions + 1024 / G_ - 1) / (1024 / G_))), dim3(256), 0, s, \
+                       (const u32x4*)src, kept_rows, kept_cols, (u32x4*)out, positions, H, W, R, Q, vec)
+    RS_GATHER_LANES(gather_lanes(vec), RS_CALL)
+#undef RS_CALL
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Token-wise pruning of a 2-D token grid (Sec. 4.2, "CNN and SSM", variant (i)): every row first
-// keeps its Q highest-shift positions (select_kernel, one grid row as one "image"), the rows close
-// up, and every column of the compacted H x Q grid then keeps its R highest-shift positions.
-// col_scores[b, j, h] = scores[b, h, kept_cols[b, h, j]] feeds the second selection.
-// ---------------------------------------------------------------------------
+// Token-wise variant: every row first keeps its Q highest-shift positions, the rows close up, and every
+// column of the compacted H x Q grid then keeps its R highest-shift positions.
+//
+// First half, lines of at most GRID_LINE positions: one workgroup per grid row forms the scores of its W
+// positions (G lanes per position while rows of C elements fit, else a wave per position), selects
+// by counting and writes the survivors' scores to their places in the compacted grid.
+template <typename T, int DIST, int G>
+__global__ __launch_bounds__(256) void grid_row_select_kernel(const T* __restrict__ f_out, const T* __restrict__ f_in,
+                                                              float* __restrict__ scores, int32_t* __restrict__ kept_cols,
+                                                              float* __restrict__ col_scores, int rows, int H, int W,
+                                                              int C, int Q) {
+    __shared__ SelectShared sh;
+    __shared__ float s_sc[GRID_LINE];
+    __shared__ int s_slot[GRID_LINE];
+    const int row = xcd_item(blockIdx.x, rows);
+    if (row < 0) return;  // whole workgroup, before any barrier
+    const int tid = threadIdx.x, sub = tid % G;
+    const int64_t base = (int64_t)row * W * C;
+    constexpr int PPG = 256 / G;
+    if (G < 64 || C <= 512) {
+        constexpr int U = 2;
+        const bool on = sub * 8 < C;
+        for (int w0 = tid / G; w0 < W; w0 += PPG * U) {
+            float x[U][8], y[U][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int w = w0 + u * PPG;
+                if (on && w < W) {
+                    Elem<T>::load8(f_out + base + (int64_t)w * C + sub * 8, x[u]);
+                    Elem<T>::load8(f_in + base + (int64_t)w * C + sub * 8, y[u]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[u][i] = y[u][i] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float sc = group_score<DIST, G>(x[u], y[u]);
+                if (sub == 0 && w0 + u * PPG < W) s_sc[w0 + u * PPG] = sc;
+            }
+        }
+    } else {
+        for (int w = tid / 64; w < W; w += 4) {
+            float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+            for (int c = sub * 8; c < C; c += 512) {
+                float x[8], y[8];
+                Elem<T>::load8(f_out + base + (int64_t)w * C + c, x);
+                Elem<T>::load8(f_in + base + (int64_t)w * C + c, y);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) dist_term<DIST>(x[i], y[i], p0, p1, p2);
+            }
+            p0 = wave_sum(p0);
+            if (DIST == RS_DIST_COS) { p1 = wave_sum(p1); p2 = wave_sum(p2); }
+            if (sub == 0) s_sc[w] = dist_value<DIST>(p0, p1, p2);
+        }
+    }
+    __syncthreads();
+    if (tid < W) scores[(int64_t)row * W + tid] = s_sc[tid];
+    block_select_rank<256>(s_sc, W, 0, Q, kept_cols + (int64_t)row * Q, s_slot, sh, tid);
+    if (col_scores && tid < W) {  // (a thread reads the slot it wrote itself)
+        const int j = s_slot[tid], b = row / H, h = row - b * H;
+        if (j >= 0) col_scores[((int64_t)b * Q + j) * H + h] = s_sc[tid];
+    }
+}
+
+bool grid_token_fused_fits(int64_t B, int H, int W) { return H <= GRID_LINE && W <= GRID_LINE && B * H < (int64_t)1 << 30; }
+
+template <typename T, int DIST>
+static hipError_t launch_grid_row_select_t(const void* f_out, const void* f_in, float* scores, int32_t* kept_cols,
+                                           float* col_scores, int B, int H, int W, int C, int Q, hipStream_t s) {
+    const int rows = B * H;
+#define RS_CALL(G_)                                                                                                  \
+    hipLaunchKernelGGL((grid_row_select_kernel<T, DIST, G_>), dim3(8 * (unsigned)((rows + 7) / 8)), dim3(256), 0, s, \
+                       (const T*)f_out, (const T*)f_in, scores, kept_cols, col_scores, rows, H, W, C, Q)
+    RS_GATHER_LANES(gather_lanes(C / 8), RS_CALL)
+#undef RS_CALL
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_row_select(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in, float* scores,
+                                  int32_t* kept_cols, float* col_scores, int B, int H, int W, int C, int Q, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+#define RS_CALL(T_)                                                                                                       \
+    (dist == RS_DIST_L2 ? launch_grid_row_select_t<T_, RS_DIST_L2>(f_out, f_in, scores, kept_cols, col_scores, B, H, W, C, Q, s) \
+     : dist == RS_DIST_L1 ? launch_grid_row_select_t<T_, RS_DIST_L1>(f_out, f_in, scores, kept_cols, col_scores, B, H, W, C, Q, s) \
+                          : launch_grid_row_select_t<T_, RS_DIST_COS>(f_out, f_in, scores, kept_cols, col_scores, B, H, W, C, Q, s))
+    return dt == RS_F32 ? RS_CALL(float) : RS_CALL(bf16raw);
+#undef RS_CALL
+}
+
+// Second half: one wave per column of the compacted grid selects R of its H positions by counting and
+// copies them, four neighbouring columns per workgroup (their positions are neighbours in `out`).
+//   out[b, i, j, :] = src[b, r, kept_cols[b, r, j], :] with r = kept_rows[b, j, i]
+template <int G>
+__global__ __launch_bounds__(256) void grid_col_gather_kernel(const u32x4* __restrict__ src,
+                                                              const int32_t* __restrict__ kept_cols,
+                                                              const float* __restrict__ col_scores,
+                                                              int32_t* __restrict__ kept_rows, u32x4* __restrict__ out,
+                                                              int items, int groups, int H, int W, int R, int Q, int vec) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[4][GRID_LINE];
+    __shared__ int s_pos[4][GRID_LINE];  // source position (r * W + c) of the column's i-th survivor
+    const int item = xcd_item(blockIdx.x, items);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (item < 0) return;
+    const int b = item / groups, j = (item - b * groups) * 4 + wave;
+    if (j >= Q) return;  // whole wave; no workgroup barrier below
+    const int64_t bj = (int64_t)b * Q + j;
+    for (int h = lane; h < ((H + 3) & ~3); h += 64) s_key[wave][h] = h < H ? score_key(col_scores[bj * H + h]) : 0u;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wave's own LDS writes
+    int base = 0;
+    for (int h0 = 0; h0 < H; h0 += 64) {
+        const int h = h0 + lane;
+        bool keep = false;
+        if (h < H) {
+            keep = count_before(s_key[wave], H, s_key[wave][h], h, 0, 1) < R;
+        }
+        const unsigned long long mask = __ballot(keep);
+        if (keep) {
+            const int i = base + __popcll(mask & ((1ull << lane) - 1ull));
+            kept_rows[bj * R + i] = h;
+            s_pos[wave][i] = h * W + kept_cols[((int64_t)b * H + h) * Q + j];
+        }
+        base += __popcll(mask);
+    }
+    if (!out) return;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    constexpr int U = 4, PPG = 64 / G;
+    const int sub = lane % G;
+    const u32x4* sb = src + (int64_t)b * H * W * vec;
+    u32x4* ob = out + (int64_t)b * R * Q * vec;
+    for (int i0 = lane / G; i0 < R; i0 += PPG * U)
+        for (int c = sub; c < vec; c += G) {
+            u32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * PPG < R) v[u] = sb[(int64_t)s_pos[wave][i0 + u * PPG] * vec + c];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * PPG < R) ob[((int64_t)(i0 + u * PPG) * Q + j) * vec + c] = v[u];
+        }
+}
+
+hipError_t launch_grid_col_gather(rs_dtype dt, const void* src, const int32_t* kept_cols, const float* col_scores,
+                                  int32_t* kept_rows, void* out, int B, int H, int W, int R, int Q, int C, hipStream_t s) {
+    if (B == 0 || R == 0 || Q == 0) return hipSuccess;
+    const int vec = (int)((size_t)C * elem_size(dt) / 16);
+    const int groups = (Q + 3) / 4, items = B * groups;
+#define RS_CALL(G_)                                                                                                   \
+    hipLaunchKernelGGL(grid_col_gather_kernel<G_>, dim3(8 * (unsigned)((items + 7) / 8)), dim3(256), 0, s, (const u32x4*)src, \
+                       kept_cols, col_scores, kept_rows, (u32x4*)out, items, groups, H, W, R, Q, vec)
+    RS_GATHER_LANES(gather_lanes(vec), RS_CALL)
+#undef RS_CALL
+    return hipGetLastError();
+}
+
+// Longer lines: the selections are launches of their own (select_kernel, one line as one "image").
+// col_scores[b, j, h] = scores[b, h, kept_cols[b, h, j]] feeds the second one.
 __global__ __launch_bounds__(256) void grid_compact_scores_kernel(const float* __restrict__ scores,
                                                                   const int32_t* __restrict__ kept_cols,
                                                                   float* __restrict__ col_scores, int64_t total,

@@ -396,8 +396,8 @@ rs_status rs_shift_topk(const void* f_out, const void* f_in, const void* src, in
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
     const int K = n_prefix + n_keep;
-    if (gathered && s == f_in && K > 0 && shift_topk_resident_fits(dtype, N, D)) {
-        // small images: one pass over memory, the rows to keep never leave the registers
+    if (gathered && s == f_in && K > 0 && shift_topk_resident_fits(dtype, B, N, D)) {
+        // many small images: one pass over memory, the rows to keep never leave the registers
         RS_LAUNCH_K(K_SCORE, st, launch_shift_topk_resident(dtype, dist, f_out, f_in, scores, kept_idx, gathered, B, N, D,
                                                           n_prefix, n_keep, st));
         return RS_OK;
@@ -431,9 +431,14 @@ rs_status rs_grid_line_prune(const void* f_out, const void* f_in, const void* sr
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
     RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * H * W, C, st));
-    RS_LAUNCH_K(K_SCORE, st, launch_grid_line_scores(scores, row_scores, col_scores, B, H, W, st));
-    RS_LAUNCH_K(K_SELECT, st, launch_select(row_scores, kept_rows, B, H, 0, keep_rows, st));
-    RS_LAUNCH_K(K_SELECT, st, launch_select(col_scores, kept_cols, B, W, 0, keep_cols, st));
+    if (grid_line_select_fits(H, W)) {
+        RS_LAUNCH_K(K_SELECT, st, launch_grid_line_select(scores, row_scores, col_scores, kept_rows, kept_cols, B, H, W,
+                                                        keep_rows, keep_cols, st));
+    } else {
+        RS_LAUNCH_K(K_SCORE, st, launch_grid_line_scores(scores, row_scores, col_scores, B, H, W, st));
+        RS_LAUNCH_K(K_SELECT, st, launch_select(row_scores, kept_rows, B, H, 0, keep_rows, st));
+        RS_LAUNCH_K(K_SELECT, st, launch_select(col_scores, kept_cols, B, W, 0, keep_cols, st));
+    }
     if (gathered)
         RS_LAUNCH_K(K_GATHER, st, launch_grid_gather(dtype, s, kept_rows, kept_cols, gathered, B, H, W, keep_rows,
                                                    keep_cols, C, st));
@@ -462,6 +467,14 @@ rs_status rs_grid_token_prune(const void* f_out, const void* f_in, const void* s
                "tensors must be 16-byte aligned");
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
+    if (keep_cols > 0 && grid_token_fused_fits(B, H, W)) {
+        RS_LAUNCH_K(K_SCORE, st, launch_grid_row_select(dtype, dist, f_out, f_in, scores, kept_cols,
+                                                      keep_rows > 0 ? col_scores : nullptr, B, H, W, C, keep_cols, st));
+        if (keep_rows > 0)
+            RS_LAUNCH_K(K_GATHER, st, launch_grid_col_gather(dtype, s, kept_cols, col_scores, kept_rows, gathered, B, H, W,
+                                                           keep_rows, keep_cols, C, st));
+        return RS_OK;
+    }
     RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * H * W, C, st));
     if (keep_cols == 0) return RS_OK;
     // step 1: every grid row is one selection problem over its W positions

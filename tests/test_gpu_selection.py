@@ -1,0 +1,74 @@
+"""The selection of long sequences where it can go wrong: every length at which it changes its manner
+(counting / keys in LDS / keys in global memory, 256 / 1024 threads), scores that are all equal, heavily
+tied, within one binade, or spread over the whole exponent range.  Integer work: kept indices must
+equal the checker's bit for bit.  A row holds its score in one element (f_out = [v, 0, ...], f_in = 0), so
+that the score is v exactly."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2508_00367_amd as rs
+
+pytestmark = pytest.mark.gpu
+
+
+def _scores(kind, B, N, rng):
+    if kind == "equal":
+        return np.full((B, N), 3.0, np.float32)
+    if kind == "tied":
+        return rng.integers(0, 7, size=(B, N)).astype(np.float32)
+    if kind == "binade":
+        return (1.0 + rng.integers(0, 1 << 12, size=(B, N)) * 2.0 ** -12).astype(np.float32)
+    return np.exp2(rng.integers(-60, 60, size=(B, N))).astype(np.float32) * rng.integers(1, 9, size=(B, N)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["equal", "tied", "binade", "wide"])
+@pytest.mark.parametrize("N,P,K", [(256, 1, 100), (257, 1, 256), (300, 2, 1), (1024, 0, 512), (1025, 1, 7), (1569, 1, 784),
+                                   (4097, 1, 2868), (12288, 3, 6000), (12289, 1, 12287)])
+def test_selection_of_long_sequences(N, P, K, kind):
+    print("selection", kind, N, P, K, flush=True)
+    sys.stdout.flush()
+    B = 3
+    v = _scores(kind, B, N, np.random.default_rng(N + K))
+    f_out = torch.zeros((B, N, 8), device="cuda")
+    f_out[:, :, 0] = torch.from_numpy(v)
+    f_in = torch.zeros_like(f_out)
+    scores = torch.empty((B, N), device="cuda")
+    kept = torch.full((B, P + K), -1, device="cuda", dtype=torch.int32)
+    src = torch.arange(B * N, device="cuda", dtype=torch.float32).view(B, N, 1).expand(B, N, 8).contiguous()
+    out = torch.full((B, P + K, 8), -1.0, device="cuda")
+    rs.rs_shift_topk(f_out, f_in, src, P, K, scores, kept, out, dist=rs.RS_DIST_L1)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(scores.cpu().numpy(), v)
+    want = oracle.topk(v.astype(np.float64), P, K)
+    np.testing.assert_array_equal(kept.cpu().numpy(), want)
+    np.testing.assert_array_equal(out[:, :, 0].cpu().numpy(), want + np.arange(B)[:, None] * N)
+
+
+# image batches on both sides of the rule that picks the one-pass kernel (rounds of 256 images at least
+# three quarters full, more than 104 tokens), and its longest and shortest sequences
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,N,D,P,K", [(191, 197, 64, 1, 150), (192, 197, 64, 1, 150), (256, 105, 72, 0, 1), (256, 104, 72, 0, 1),
+                                       (300, 208, 8, 2, 206), (513, 130, 256, 1, 60), (600, 207, 384, 1, 100)])
+def test_one_pass_and_three_launches_agree(B, N, D, P, K, dtype):
+    print("one pass", B, N, D, P, K, dtype, flush=True)
+    g = torch.Generator().manual_seed(B + N)
+    f_in = torch.randn((B, N, D), generator=g).to(dtype).cuda()
+    f_out = torch.randn((B, N, D), generator=g).to(dtype).cuda()
+    res = []
+    for src in (None, f_in.clone()):          # a separate src tensor always takes the three launches
+        scores = torch.full((B, N), float("nan"), device="cuda")
+        kept = torch.full((B, P + K), -1, device="cuda", dtype=torch.int32)
+        out = torch.full((B, P + K, D), float("nan"), device="cuda", dtype=dtype)
+        rs.rs_shift_topk(f_out, f_in, src, P, K, scores, kept, out)
+        torch.cuda.synchronize()
+        res.append((kept, out))
+        # fp32 sums of D terms in some order: relative error at most D 2^-24 on either side
+        want = (f_out.double() - f_in.double()).norm(dim=2)
+        assert float(((scores - want).abs() / want).max()) < D * 2.0 ** -24 + 2.0 ** -23
+        np.testing.assert_array_equal(kept.cpu().numpy(), oracle.topk(scores.cpu().numpy().astype(np.float64), P, K))
+        rows = torch.take_along_dim(f_in, kept.long()[:, :, None], dim=1)
+        assert torch.equal(out, rows)
