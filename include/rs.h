@@ -113,8 +113,8 @@ RS_API int32_t rs_version(void);
 RS_API const char *rs_build_info(void);
 
 /* Tuning aid (process-wide, not part of the method): which tile variant the bf16 matrix kernels
- * use.  0 = chosen by shape (the default), 1 = 256 x 256 persistent workgroups, 2 = 256 x 128 and
- * 3 = 128 x 128 tiles with two workgroups per compute unit.  Every variant gives the same bits;
+ * use.  0 = chosen by shape (the default), 1 = 256 x 256 persistent workgroups, 2 = 256 x 128 tiles, 3 =
+ * 128 x 128 and 4 = 128 x 256 tiles with two workgroups per compute unit.  Every variant gives the same bits;
  * only the speed differs.  The environment variable RS_GEMM_FORCE sets the initial value. */
 RS_API rs_status rs_tune_gemm_variant(int32_t variant);
 

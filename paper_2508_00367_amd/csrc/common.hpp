@@ -14,6 +14,9 @@ typedef uint16_t bf16raw;  // bf16 storage: upper half of an fp32
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// plain vectors: arrays of the HIP vector classes (uint4) that are not written on every path end up in LDS
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ---- bf16 <-> fp32 -------------------------------------------------------
 __device__ __forceinline__ float bf2f(bf16raw b) { return __uint_as_float(((uint32_t)b) << 16); }
@@ -152,7 +155,7 @@ constexpr int kGemmMaxN = 1 << 20;
 // Tile configurations the bf16 GEMM was built with (measurements carried from one run to another
 // are only valid for the same string).
 const char* gemm_build_info();
-// bf16 tile variant switch (0 = by shape, 1 = 256 x 256 persistent, 2 = 256 x 128 ring, 3 = 128 x 128 ring)
+// bf16 tile variant switch (0 = by shape, 1 = 256 x 256 persistent, 2 = 256 x 128, 3 = 128 x 128 ring, 4 = 128 x 256 ring)
 int gemm_variant();
 void set_gemm_variant(int v);
 

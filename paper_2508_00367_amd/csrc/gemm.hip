@@ -581,74 +581,92 @@ struct EpiRegions {
     unsigned char* r[TM];  // one 4 KB LDS region per 32-row group of this wave
 };
 
-template <int TM, int EPI, int DIST>
-__device__ __forceinline__ void gemm_epilogue_acc_layout(
-    f32x16 (&acc)[2][TM], const EpiRegions<TM>& reg,
-    const bf16raw* __restrict__ bias, const bf16raw* __restrict__ res, bf16raw* __restrict__ out,
-    float* __restrict__ partials, const bf16raw* __restrict__ ref, int post, const GemmLnFold& ln,
-    int M, int N, int slots, int m_base /* first row of the wave tile */, int n_base /* first feature */,
-    int lane) {
-    constexpr bool LN = EPI == EPI_LN_BIAS || EPI == EPI_LN_BIAS_GELU;
-    constexpr bool GELU = EPI == EPI_BIAS_GELU || EPI == EPI_LN_BIAS_GELU;
-    constexpr bool RES = EPI == EPI_BIAS_RES || EPI == EPI_BIAS_RES_SHIFT;
-    constexpr bool SHIFT = EPI == EPI_BIAS_RES_SHIFT;
-    if (n_base >= N) return;  // a wave's 64 features are all inside N or all outside (N % 64 == 0)
-    const int l32 = lane & 31, g = lane >> 5;
-    const int rows_valid = min(max(M - m_base, 0), 32 * TM);
-    if (rows_valid == 0) return;
+constexpr bool epi_ln(int epi) { return epi == EPI_LN_BIAS || epi == EPI_LN_BIAS_GELU; }
+constexpr bool epi_res(int epi) { return epi == EPI_BIAS_RES || epi == EPI_BIAS_RES_SHIFT; }
 
-    // residual rows: per group 4 copies of 8 rows x 128 bytes (lane l: row l / 8, slot l % 8 holds
-    // chunk (l % 8) ^ swz(row)); rows past M read as zeros through the resource
-    if (RES) {
-        const __amdgpu_buffer_rsrc_t rs_res =
-            make_rsrc(res + (int64_t)m_base * N + n_base, ((int64_t)(rows_valid - 1) * N + 64) * 2);
+// What the epilogue of one wave reads besides the accumulators: the per-column vectors of the lane's 32
+// features and the LayerNorm statistics of its TM rows.  The bias stays as it is in memory until it is
+// used, and nothing here depends on a loaded value: all the loads are in flight together.
+template <int TM, int EPI>
+struct EpiVecs {
+    static constexpr bool LN = epi_ln(EPI);
+    f32x4 bv[LN ? 2 : 1][4], cs[LN ? 2 : 1][4];
+    u32x2 raw[LN ? 1 : 2][4];
+    float2 stats[LN ? TM : 1];
+    __device__ __forceinline__ void load(const bf16raw* __restrict__ bias, const GemmLnFold& ln, int M, int N, int m_base,
+                                         int n_base, int lane) {
+        const int l32 = lane & 31, g = lane >> 5;
+        n_base = n_base < N ? n_base : 0;  // a wave's 64 features are all inside N or all outside (N % 64 == 0)
+        if constexpr (LN) {
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int r = p * 8 + (lane >> 3);
-            const int voff = (r * N + (((lane & 7) ^ epi_swz(r)) << 3)) * 2;
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < TM; ++j) dma16(rs_res, reg.r[j] + p * 1024, voff, j * 32 * N * 2);
-        }
-    }
-
-    // per-column vectors of this lane's 32 features
-    float bv[2][4][4], cs[LN ? 2 : 1][4][4];
+                for (int q = 0; q < 4; ++q) {
+                    const int n = n_base + i * 32 + q * 8 + g * 4;
+                    bv[i][q] = *reinterpret_cast<const f32x4*>(ln.bias + n);
+                    cs[i][q] = *reinterpret_cast<const f32x4*>(ln.colsum + n);
+                }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < TM; ++j)  // rows past M are computed on a copy and never stored
+                stats[j] = reinterpret_cast<const float2*>(ln.stats)[min(m_base + j * 32 + l32, M - 1)];
+        } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int n = n_base + i * 32 + q * 8 + g * 4;
-            if (LN) {
-                const f32x4 b4 = *reinterpret_cast<const f32x4*>(ln.bias + n);
-                const f32x4 c4 = *reinterpret_cast<const f32x4*>(ln.colsum + n);
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { bv[i][q][e] = b4[e]; cs[LN ? i : 0][q][e] = c4[e]; }
-            } else if (bias) {
-                const uint2 b2 = *reinterpret_cast<const uint2*>(bias + n);
-                bv[i][q][0] = __uint_as_float(b2.x << 16); bv[i][q][1] = __uint_as_float(b2.x & 0xffff0000u);
-                bv[i][q][2] = __uint_as_float(b2.y << 16); bv[i][q][3] = __uint_as_float(b2.y & 0xffff0000u);
-            } else {
+                for (int q = 0; q < 4; ++q) raw[i][q] = u32x2{0u, 0u};
+            if (bias) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) bv[i][q][e] = 0.f;
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        raw[i][q] = *reinterpret_cast<const u32x2*>(bias + n_base + i * 32 + q * 8 + g * 4);
             }
         }
-    // per-row LayerNorm statistics of this lane's TM rows
-    float2 stats[LN ? TM : 1];
-    if (LN) {
-#pragma unroll
-        for (int j = 0; j < TM; ++j) {
-            const int m = m_base + j * 32 + l32;
-            stats[LN ? j : 0] = m < M ? reinterpret_cast<const float2*>(ln.stats)[m] : make_float2(0.f, 0.f);
-        }
     }
-    if (RES) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
+    __device__ __forceinline__ float bias_at(int i, int q, int e) const {
+        if constexpr (LN) return bv[i][q][e];
+        else return __uint_as_float((e & 1) ? (raw[i][q][e >> 1] & 0xffff0000u) : (raw[i][q][e >> 1] << 16));
+    }
+};
+
+// Requests the residual rows of a wave tile: per 32-row group 4 copies of 8 rows x 128 bytes (lane l:
+// row l / 8, slot l % 8 holds chunk (l % 8) ^ swz(row)); rows past M, and every row when the wave's features
+// lie past N, read as zeros through the resource.
+template <int TM>
+__device__ __forceinline__ void epi_request_residual(const EpiRegions<TM>& reg, const bf16raw* __restrict__ res, int M, int N,
+                                                     int m_base, int n_base, int lane) {
+    const int rows_valid = n_base < N ? min(max(M - m_base, 0), 32 * TM) : 0;
+    const __amdgpu_buffer_rsrc_t rs_res =
+        make_rsrc(rows_valid > 0 ? res + (int64_t)m_base * N + n_base : res, rows_valid > 0 ? ((int64_t)(rows_valid - 1) * N + 64) * 2 : 0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int r = p * 8 + (lane >> 3);
+        const int voff = (r * N + (((lane & 7) ^ epi_swz(r)) << 3)) * 2;
+#pragma unroll
+        for (int j = 0; j < TM; ++j) dma16(rs_res, reg.r[j] + p * 1024, voff, j * 32 * N * 2);
+    }
+}
+
+// The arithmetic and the stores.  The residual rows have landed in the regions.
+template <int TM, int EPI, int DIST>
+__device__ __forceinline__ void gemm_epilogue_acc_layout(
+    f32x16 (&acc)[2][TM], const EpiRegions<TM>& reg, const EpiVecs<TM, EPI>& vec, bf16raw* __restrict__ out,
+    float* __restrict__ partials, const bf16raw* __restrict__ ref, int post,
+    int M, int N, int slots, int m_base /* first row of the wave tile */, int n_base /* first feature */,
+    int lane) {
+    constexpr bool LN = epi_ln(EPI);
+    constexpr bool GELU = EPI == EPI_BIAS_GELU || EPI == EPI_LN_BIAS_GELU;
+    constexpr bool RES = epi_res(EPI);
+    constexpr bool SHIFT = EPI == EPI_BIAS_RES_SHIFT;
+    if (n_base >= N || m_base >= M) return;
+    const int l32 = lane & 31, g = lane >> 5;
 
     const int sw = epi_swz(l32);
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
         const int m = m_base + j * 32 + l32;
         const bool m_ok = m < M;
-        const float2 st = stats[LN ? j : 0];
+        const float2 st = vec.stats[LN ? j : 0];
         unsigned char* buf = reg.r[j];
         // Shift sums of the row's 64 features: per chunk of 8 features a running sum in feature order
         // (half-wave g = 0 holds the first four terms and hands its sum to g = 1, which goes on with
@@ -663,7 +681,7 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float a_ = acc[i][j][4 * q + e];
-                    v[e] = LN ? fmaf(st.y, fmaf(-st.x, cs[LN ? i : 0][q][e], a_), bv[i][q][e]) : a_ + bv[i][q][e];
+                    v[e] = LN ? fmaf(st.y, fmaf(-st.x, vec.cs[LN ? i : 0][q][e], a_), vec.bias_at(i, q, e)) : a_ + vec.bias_at(i, q, e);
                     if (GELU) v[e] = gelu_sp(v[e]);
                 }
                 if (RES) {
@@ -891,8 +909,226 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
             reg.r[j] = (gi / PER == 0 ? st0 : gi / PER == 1 ? st1 : st2) + (gi % PER) * 4096;
         }
     }
-    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, bias, res, out, partials, ref, post, ln, M, N, slots,
-                                            m0 + wm * WM, n0 + wn * WN, lane);
+    const int m_base = m0 + wm * WM, n_base = n0 + wn * WN;
+    EpiVecs<TM, EPI> vec;
+    if (epi_res(EPI)) epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
+    vec.load(bias, ln, M, N, m_base, n_base, lane);
+    if (epi_res(EPI)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, m_base, n_base, lane);
+}
+
+// ---------------------------------------------------------------------------
+// Slim kernel, for grids that leave the chip empty with larger tiles: workgroup tile (32 TM WGM) x (64 WGN),
+// wave tile (32 TM) x 64, K slices of 64 in a ring of NST stages (copies run NST - 1 slices ahead), one tile
+// per workgroup.  What bounds such a problem is how fast one CU can stream its operands (a latency per
+// slice times the slices, 45 GB/s with a shallow ring), so the tile is small (more CUs stream, each
+// fewer bytes), the ring deep, and everything the epilogue needs -- residual rows, bias, LayerNorm
+// statistics -- is requested before the first slice instead of after the last.
+// Same MFMA, same order of the sums as the other kernels: the same bits.
+// ---------------------------------------------------------------------------
+template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
+    const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
+    const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
+    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
+    int tiles_n, int slots, int gm) {
+    constexpr int NW = WGM * WGN, TN = 2, WM = 32 * TM, WN = 64, BM = WM * WGM, BN = WN * WGN;
+    constexpr int RB = 128, RPI = 8;                       // LDS row bytes, rows per wave copy
+    constexpr int A_LOADS = BM / RPI / NW, W_LOADS = BN / RPI / NW, LPW = A_LOADS + W_LOADS;
+    constexpr int STAGE = (BM + BN) * RB;
+    constexpr bool RES = epi_res(EPI);
+    static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split evenly over the wave copies");
+    static_assert(NST >= 2 && NST <= 4, "ring of two to four stages");
+    static_assert(LPW * (NST - 1) <= 63, "copies in flight must fit the counter");
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st2[NST >= 3 ? STAGE : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char st3[NST == 4 ? STAGE : 16];
+    // residual rows requested up front when there is room for them next to the ring
+    constexpr bool PRE_RES = RES && NST * STAGE + NW * TM * 4096 <= 160 * 1024;
+    constexpr bool PRE_VEC = NW <= 4;  // two waves per SIMD: no registers for the epilogue's vectors during the loop
+    __shared__ __attribute__((aligned(1024))) unsigned char s_epi[PRE_RES ? NW * TM * 4096 : 16];
+
+    const int nblk = tiles_m * tiles_n;
+    const int xcd = blockIdx.x & 7;
+    const int xq = nblk >> 3, xr = nblk & 7;
+    const int x_cnt = xq + (xcd < xr ? 1 : 0), x_start = xcd * xq + (xcd < xr ? xcd : xr);
+    const int seq = blockIdx.x >> 3;
+    if (seq >= x_cnt) return;  // whole workgroup, before any barrier
+    int m0, n0;
+    {
+        const int bid = x_start + seq;
+        const int per_group = gm * tiles_n;
+        const int grp = bid / per_group, rem = bid - grp * per_group;
+        const int first_m = grp * gm;
+        const int gsz = min(tiles_m - first_m, gm);
+        const int tn = rem / gsz;
+        n0 = tn * BN;
+        m0 = (first_m + rem - tn * gsz) * BM;
+    }
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WGM, wn = wave / WGM;
+    const int l32 = lane & 31, g = lane >> 5;
+    const int m_base = m0 + wm * WM, n_base = n0 + wn * WN;
+
+    // LDS layout as in gemm_bf16_kernel: chunk c of row r in slot c ^ (r & 7) ^ ((r >> 3) & 1).  Wave copy i of
+    // wave w fills rows (NW i + w) 8 .. + 7; with an odd number of waves the parity of row >> 3 depends on i.
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 2);
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * K, (int64_t)min(N - n0, BN) * K * 2);
+    const int ld_r = lane >> 3, ld_p = lane & 7;
+    const int voff0 = ((wave * RPI + ld_r) * K + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
+    const int voff1 = NW == 1 ? (ld_r * K + ((ld_p ^ ld_r ^ 1) << 3)) * 2 : voff0;
+    const int pass_bytes = NW * RPI * K * 2;
+    const int S = K / 64;
+    const int a_row0 = wm * WM + l32, w_row0 = wn * WN + l32;
+    const int sw = (l32 & 7) ^ ((l32 >> 3) & 1);
+
+#define RS_SLIM_DMA(stage_, t_)                                                                           \
+    {                                                                                                     \
+        const bool real_ = (t_) < S;                                                                      \
+        const int kb_ = (t_) * RB;                                                                        \
+        _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i)                                               \
+            dma16(rs_a, (stage_) + (i * NW + wave) * 1024, (i & 1) ? voff1 : voff0, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i)                                               \
+            dma16(rs_w, (stage_) + BM * RB + (i * NW + wave) * 1024, (i & 1) ? voff1 : voff0, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+    }
+#define RS_SLIM_FRAGS(f_, stage_, kk_)                                                                    \
+    {                                                                                                     \
+        const int co_ = ((((kk_) * 2 + g) ^ sw) << 4);                                                    \
+        _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
+            (f_).w[i] = *reinterpret_cast<const bf16x8*>((stage_) + (BM + w_row0 + i * 32) * RB + co_);   \
+        _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
+            (f_).a[j] = *reinterpret_cast<const bf16x8*>((stage_) + (a_row0 + j * 32) * RB + co_);        \
+    }
+#define RS_SLIM_MFMA(f_)                                                                                  \
+    {                                                                                                     \
+        _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
+            _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16((f_).w[i], (f_).a[j], acc[i][j], 0, 0, 0); \
+    }
+#define RS_SLIM_WAIT(n_)                                                                                  \
+    {                                                                                                     \
+        __builtin_amdgcn_s_waitcnt(((n_) & 15) | (((n_) >> 4) << 14) | 0x0070);                           \
+        if (NW > 1) __builtin_amdgcn_s_barrier();                                                         \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); /* LDS reads stay below the barrier */     \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+    }
+// Slice t from registers (fc_) while the fragments of slice t + 1 are read from nxt_ into fn_: the wave waits
+// for slice t + 1 and for its own reads of slice t, meets the barrier (every wave has slice t in registers:
+// cur_ is free), requests slice t + NST into cur_ and starts the reads of slice t + 1, which pass under the
+// matrix work.
+#define RS_SLIM_SLICE(cur_, nxt_, fc_, fn_, t_)                                                           \
+    {                                                                                                     \
+        RS_SLIM_WAIT((NST - 2) * LPW)                                                                     \
+        RS_SLIM_DMA(cur_, (t_) + NST)                                                                     \
+        _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) RS_SLIM_FRAGS(fn_[kk], nxt_, kk)                 \
+        _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) RS_SLIM_MFMA(fc_[kk])                            \
+        _Pragma("unroll") for (int s_ = 0; s_ < 4 * TN * TM; ++s_) {                                      \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                            \
+            __builtin_amdgcn_sched_group_barrier(0x020, (LPW + 4 * TN * TM - 2) / (4 * TN * TM - 1), 0);  \
+            __builtin_amdgcn_sched_group_barrier(0x100, (4 * (TN + TM) + 4 * TN * TM - 2) / (4 * TN * TM - 1), 0); \
+        }                                                                                                 \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+    }
+
+#define RS_SLIM_ALL_FRAGS(f_, stage_) { _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) RS_SLIM_FRAGS(f_[kk], stage_, kk) }
+#define RS_SLIM_ALL_MFMA(f_) { _Pragma("unroll") for (int kk = 0; kk < 4; ++kk) RS_SLIM_MFMA(f_[kk]) }
+
+    EpiRegions<TM> reg;
+    if constexpr (PRE_RES) {
+#pragma unroll
+        for (int j = 0; j < TM; ++j) reg.r[j] = s_epi + (wave * TM + j) * 4096;
+        epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
+    } else {
+        static_assert(NW * TM * 4096 <= 2 * STAGE, "epilogue regions in the first two stages");
+#pragma unroll
+        for (int j = 0; j < TM; ++j) {
+            const int at = (wave * TM + j) * 4096;  // STAGE is a multiple of 4096
+            reg.r[j] = at < STAGE ? st0 + at : st1 + (at - STAGE);
+        }
+    }
+    EpiVecs<TM, EPI> vec;
+    if constexpr (PRE_VEC) vec.load(bias, ln, M, N, m_base, n_base, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    RS_SLIM_DMA(st0, 0)
+    RS_SLIM_DMA(st1, 1)
+    if constexpr (NST >= 3) RS_SLIM_DMA(st2, 2)
+    if constexpr (NST == 4) RS_SLIM_DMA(st3, 3)
+
+    f32x16 acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    Frags<TN, TM> f0[4], f1[4];
+    RS_SLIM_WAIT((NST - 1) * LPW)  // slice 0 has landed
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) RS_SLIM_FRAGS(f0[kk], st0, kk)
+    // Whole trips of the ring, then the slices that are left (fewer than a trip; all of them have been
+    // requested by then).  No way out inside a trip: every exit would keep its own copy of the accumulators,
+    // and the compiler would lose track of which copies a stage's reads wait for.
+    constexpr int TRIP = NST == 3 ? 6 : NST;
+    const int full = S / TRIP * TRIP;
+    if constexpr (NST == 3) {
+        for (int t = 0; t < full; t += 6) {
+            RS_SLIM_SLICE(st0, st1, f0, f1, t)
+            RS_SLIM_SLICE(st1, st2, f1, f0, t + 1)
+            RS_SLIM_SLICE(st2, st0, f0, f1, t + 2)
+            RS_SLIM_SLICE(st0, st1, f1, f0, t + 3)
+            RS_SLIM_SLICE(st1, st2, f0, f1, t + 4)
+            RS_SLIM_SLICE(st2, st0, f1, f0, t + 5)
+        }
+        const int left = S - full;
+        if (left > 0) {
+            RS_SLIM_SLICE(st0, st1, f0, f1, full)
+            if (left > 1) RS_SLIM_SLICE(st1, st2, f1, f0, full + 1)
+            if (left > 2) RS_SLIM_SLICE(st2, st0, f0, f1, full + 2)
+            if (left > 3) RS_SLIM_SLICE(st0, st1, f1, f0, full + 3)
+            if (left > 4) RS_SLIM_SLICE(st1, st2, f0, f1, full + 4)
+        }
+    } else if constexpr (NST == 4) {
+        for (int t = 0; t < full; t += 4) {
+            RS_SLIM_SLICE(st0, st1, f0, f1, t)
+            RS_SLIM_SLICE(st1, st2, f1, f0, t + 1)
+            RS_SLIM_SLICE(st2, st3, f0, f1, t + 2)
+            RS_SLIM_SLICE(st3, st0, f1, f0, t + 3)
+        }
+        const int left = S - full;
+        if (left > 0) {
+            RS_SLIM_WAIT(0)
+            if (left > 1) RS_SLIM_ALL_FRAGS(f1, st1)
+            RS_SLIM_ALL_MFMA(f0)
+            if (left > 1) {
+                if (left > 2) RS_SLIM_ALL_FRAGS(f0, st2)
+                RS_SLIM_ALL_MFMA(f1)
+                if (left > 2) RS_SLIM_ALL_MFMA(f0)
+            }
+        }
+    } else {
+        for (int t = 0; t < full; t += 2) {
+            RS_SLIM_SLICE(st0, st1, f0, f1, t)
+            RS_SLIM_SLICE(st1, st0, f1, f0, t + 1)
+        }
+        if (S > full) RS_SLIM_ALL_MFMA(f0)
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xC07F);  // trailing (empty) copies and reads: the stages get reused
+    if (!PRE_RES && NW > 1) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if constexpr (RES && !PRE_RES) epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
+    if constexpr (!PRE_VEC) vec.load(bias, ln, M, N, m_base, n_base, lane);
+    if constexpr (RES && !PRE_RES) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+#undef RS_SLIM_DMA
+#undef RS_SLIM_FRAGS
+#undef RS_SLIM_MFMA
+#undef RS_SLIM_WAIT
+#undef RS_SLIM_ALL_FRAGS
+#undef RS_SLIM_ALL_MFMA
+#undef RS_SLIM_SLICE
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, m_base, n_base, lane);
 }
 
 // Tile configuration of the bf16 GEMM: BM, BN, BK, NSTAGE, waves along tokens, waves along features.
@@ -918,7 +1154,7 @@ static int device_cus() {
 }
 
 // Which bf16 tile variant runs: 0 = chosen by shape (below), 1 = 256 x 256 persistent kernel,
-// 2 = 256 x 128 ring kernel, 3 = 128 x 128 ring kernel.  Every variant gives the same bits; the
+// 2 = 256 x 128 slim kernel, 3 = 128 x 128 and 4 = 128 x 256 ring kernel.  Every variant gives the same bits; the
 // switch exists for tuning and for the test that checks exactly that.  Initial value from the
 // environment variable RS_GEMM_FORCE.
 static std::atomic<int> g_gemm_variant{-1};
@@ -969,6 +1205,16 @@ static void launch_ring(const GemmArgs& g, hipStream_t s) {
                        tiles_n, (g.N + 63) / 64, RS_GEMM_GM, GemmBatch{0, 0, 0});
 }
 
+template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
+static void launch_slim(const GemmArgs& g, hipStream_t s) {
+    constexpr int BM = 32 * TM * WGM, BN = 64 * WGN;
+    const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (g.N + BN - 1) / BN;
+    const int nblk = tiles_m * tiles_n;
+    hipLaunchKernelGGL((gemm_bf16_slim_kernel<WGM, WGN, TM, NST, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(WGM * WGN * 64), 0, s,
+                       g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m,
+                       tiles_n, (g.N + 63) / 64, RS_GEMM_GM);
+}
+
 // The ring kernel with the tile width that suits the grid.  128 x 128 tiles unless they would leave
 // some CUs two workgroups and others one (more than one workgroup per CU, at most two): then the
 // 128 x 256 tiles, half as many, give every CU one workgroup of the same length (fc2 at 6280 rows:
@@ -1010,31 +1256,40 @@ static void launch_persistent(const GemmArgs& g, hipStream_t s) {
                            g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, RS_GEMM_GM);
 }
 
-// Choice by shape.  The persistent 256 x 256 kernel has the best matrix-core rate while most CUs
-// have a tile, but its last round costs a whole round however few tiles it holds, and well below
-// one round it leaves CUs empty; the ring kernels (two smaller workgroups per CU, tiles handed out
-// as slots free up, epilogues under the other workgroup's matrix work) keep the chip busy on
-// small and ragged problems at a lower peak rate.  Measured crossovers on MI355X: the ring kernels
-// win up to half a round of 256 x 256 tiles, and up to a round and a half when K is short
-// (K <= 512: a tile is mostly epilogue).  Beyond that: the rows that make up whole rounds go to the
-// persistent kernel and the rows behind them to a ring kernel in a second launch -- when a round
-// is long (K at least RS_GEMM_TAIL_MINK: a second launch costs a few microseconds) and the last
-// one is at most RS_GEMM_TAIL_FRAC full.
-#ifndef RS_GEMM_TAIL_FRAC
-#define RS_GEMM_TAIL_FRAC 0.5
-#endif
-#ifndef RS_GEMM_TAIL_MINK
-#define RS_GEMM_TAIL_MINK 2048
-#endif
-// (tuning aids: the environment variables of the same names override the two thresholds)
-static double gemm_tail_frac() {
-    static const double v = [] { const char* e = getenv("RS_GEMM_TAIL_FRAC"); return e ? atof(e) : (double)RS_GEMM_TAIL_FRAC; }();
-    return v;
+// Choice by shape: the smallest tile of 64 x 64, 128 x 64, 128 x 128, 256 x 128 (slim kernels) and 256 x 256
+// (persistent kernel) that gives every CU at most one workgroup.  A workgroup streams its operands at
+// the pace of one CU whatever else runs, so a smaller tile is faster as long as it does not put two
+// workgroups on some CUs; at 48 slices of K the steps are 12 / 20 / 24 / 34 / 59 us per launch (768 x 3072).
+// Chains of the four layers of a block, sizes on both sides of the steps (us per layer against the
+// next smaller / larger tile): 768 x 3072 at 1182 rows (228 tiles of 64 x 64) -22.5 / -16.0 against the 128 x 128
+// ring kernel, at 1576 rows (300) -12.0 / -15.2; at 3152 rows (150 of 128 x 128) -11.1 / -0.3; at 8471
+// rows (204 of 256 x 128) -4.5 / -24.7; 384 x 1152 at 12608 rows (250 of 256 x 256) 18.9 us persistent, 24 ring.
+// Beyond one round:
+//  - K <= 384: a tile is mostly epilogue; the ring kernels (two workgroups per CU, one's epilogue under the
+//    other's K loop): 1536 x 384 at 25216 rows -5 us of 62 against the persistent kernel.
+//  - K < 2048 and up to 1.45 rounds of 256 x 256 tiles: the 256 x 128 tiles, whose last round costs half as much
+//    (768 x 768 at 25216 rows -7 us of 53, 2304 x 768 at 10047 rows -4 of 50; at 1.59 rounds +5).
+//  - otherwise the persistent kernel; with K >= 2048 and a last round at most half full the rows that make up
+//    whole rounds go to it and the rows behind them to the tile that suits them, in a second launch
+//    (a round is long there: 768 x 3072 at 50432 rows -19 us of 260).
+template <int EPI, int DIST>
+static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
+    const int64_t cus = device_cus();
+    auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+    if (tiles(64, 64) <= cus) return launch_slim<2, 1, 1, 4, EPI, DIST>(g, s);
+    if (tiles(128, 64) <= cus) return launch_slim<4, 1, 1, 4, EPI, DIST>(g, s);
+    if (tiles(128, 128) <= cus) return launch_slim<2, 2, 2, 3, EPI, DIST>(g, s);
+    if (tiles(256, 128) <= cus) return launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
+    const int64_t t = tiles(256, 256), rounds = t / cus, rem = t - rounds * cus;
+    if (rounds == 0 || rem == 0) return launch_persistent<EPI, DIST>(g, s);
+    if (g.K <= 384) return launch_ring_auto<EPI, DIST>(g, s);
+    if (g.K < 2048 && 100 * t <= 145 * cus) return launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
+    if (g.K < 2048 || 2 * rem > cus) return launch_persistent<EPI, DIST>(g, s);
+    const int64_t m1 = rounds * cus / ((g.N + 255) / 256) * 256;  // row panels that fill whole rounds
+    launch_persistent<EPI, DIST>(g.rows(0, m1), s);
+    launch_by_shape<EPI, DIST>(g.rows(m1, g.M), s);
 }
-static int gemm_tail_mink() {
-    static const int v = [] { const char* e = getenv("RS_GEMM_TAIL_MINK"); return e ? atoi(e) : (int)RS_GEMM_TAIL_MINK; }();
-    return v;
-}
+
 template <int EPI, int DIST>
 static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, const void* res,
                               void* out, float* partials, const void* ref, bool post, GemmLnFold ln,
@@ -1043,23 +1298,10 @@ static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, c
                      (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K};
     const int variant = gemm_variant();
     if (variant == 1) launch_persistent<EPI, DIST>(g, s);
-    else if (variant == 2) launch_ring<256, 128, EPI, DIST>(g, s);
+    else if (variant == 2) launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
     else if (variant == 3) launch_ring<128, 128, EPI, DIST>(g, s);
     else if (variant == 4) launch_ring<128, 256, EPI, DIST>(g, s);
-    else {
-        const int cus = device_cus();
-        const int64_t tiles_n = (N + 255) / 256, panels = (M + 255) / 256;
-        const int64_t tiles = panels * tiles_n, rounds = tiles / cus, rem = tiles - rounds * cus;
-        const bool small = 2 * tiles <= cus || (K <= 512 && 2 * tiles <= 3 * cus);
-        if (small) launch_ring_auto<EPI, DIST>(g, s);
-        else if (rounds == 0) launch_persistent<EPI, DIST>(g, s);
-        else if (rem == 0 || K < gemm_tail_mink() || (double)rem > gemm_tail_frac() * cus) launch_persistent<EPI, DIST>(g, s);
-        else {
-            const int64_t m1 = (rounds * cus / tiles_n) * 256;  // row panels that fill whole rounds
-            launch_persistent<EPI, DIST>(g.rows(0, m1), s);
-            launch_ring_auto<EPI, DIST>(g.rows(m1, M), s);
-        }
-    }
+    else launch_by_shape<EPI, DIST>(g, s);
     return hipGetLastError();
 }
 
@@ -1067,9 +1309,9 @@ static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, c
 #define RS_STR(...) RS_STR2(__VA_ARGS__)
 const char* gemm_build_info() {
     return "bf16 gemm: persistent tiles (BM,BN,BK,stages,waves m,waves n) " RS_STR(RS_GEMM_CFG)
-           ", three activation stages when K >= 2048"
-           "; ring tiles 128x256x32 and 128x128x32, 3 stages, 4 waves, 2 workgroups per CU, up to 0.5 rounds (1.5 if K <= 512)"
-           "; rows behind whole rounds go to a ring kernel when K >= " RS_STR(RS_GEMM_TAIL_MINK) " and the last round is under " RS_STR(RS_GEMM_TAIL_FRAC) " full";
+           ", three activation stages when K >= 2048; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU"
+           " (256x128 up to 1.45 rounds of 256x256 when K < 2048); ring tiles 128x128x32 and 128x256x32 beyond one round when K <= 384"
+           "; rows behind whole rounds apart when K >= 2048 and the last round is at most 0.5 full";
 }
 
 // `count` independent products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T (bf16, no bias), problem p at

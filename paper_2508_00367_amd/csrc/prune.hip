@@ -6,10 +6,6 @@
 
 namespace rs {
 
-// plain vectors: arrays of the HIP vector classes (uint4) that are not written on every path end up in LDS
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
 // ---------------------------------------------------------------------------
 // scores[row] = D(f_out[row, :], f_in[row, :]); one wavefront per row, 8 elements per
 // lane per step, butterfly reduction in a fixed order (bit-reproducible).
