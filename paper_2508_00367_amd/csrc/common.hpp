@@ -161,10 +161,11 @@ void set_gemm_variant(int v);
 
 // Number of per-row partial slots the SHIFT epilogue writes for an output width N.
 int gemm_shift_slots(rs_dtype dt, int N);
-constexpr int kShiftLanes = 3;  // floats per slot (L2/L1 use the first, cosine all three)
+constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine all three)
 
 // out[M, N] = epilogue(a[M, K] @ W).  bf16: `w` is the packed [N, K] matrix; fp32: `w` is the
-// caller's [K, N] matrix.  partials: float [M, slots, kShiftLanes] for EPI_BIAS_RES_SHIFT.
+// caller's [K, N] matrix.  partials: float [kShiftLanes][slots][M] for EPI_BIAS_RES_SHIFT
+// (rows innermost: the epilogues store and the selection reads whole lines).
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials,
                        const void* ref, bool post, int64_t M, int N, int K, hipStream_t s);
@@ -209,6 +210,12 @@ hipError_t launch_shift_scores(rs_dtype dt, rs_dist dist, const void* f_out, con
 // scores[M] from the GEMM epilogue's partial slots
 hipError_t launch_finalize_scores(rs_dist dist, const float* partials, int slots, float* scores,
                                   int64_t M, hipStream_t s);
+// Scores, selection and gather of short images (select_gather_fits) in one launch; stats as in
+// launch_gather_stats, or null.
+bool select_gather_fits(rs_dtype dt, int N, int D);
+hipError_t launch_select_gather(rs_dtype dt, rs_dist dist, const float* partials, int slots, float* scores,
+                                int32_t* kept_idx, const void* src, void* out, float* stats, int B, int N, int n_prefix,
+                                int n_keep, int D, float eps, hipStream_t s);
 // per image: the n_keep highest scores among tokens >= n_prefix, ascending kept_idx[B, K]
 // the two steps above in one launch (a real selection only: n_keep < N - n_prefix, n_keep > 0;
 // N must pass select_from_partials_fits)

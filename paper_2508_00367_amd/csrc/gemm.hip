@@ -102,7 +102,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
     const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
-    int tiles_n, int slots, int gm) {
+    int tiles_n, int slots, int64_t ldp, int gm) {
     constexpr int NW = WGM * WGN;               // waves: WGM along tokens x WGN along features
     constexpr int WM = BM / WGM, WN = BN / WGN; // wave tile
     constexpr int TM = WM / 32, TN = WN / 32;   // MFMA tiles per wave
@@ -533,9 +533,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
                     }
                     const int slot = (n0_cur + wn * WN) / WN;
                     if ((lane % LPR) == 0 && m < M && slot < slots) {
-                        float* dst = partials + ((int64_t)m * slots + slot) * kShiftLanes;
+                        float* dst = partials + slot * ldp + m;
                         dst[0] = p0;
-                        if (DIST == RS_DIST_COS) { dst[1] = p1; dst[2] = p2; }
+                        if (DIST == RS_DIST_COS) { dst[slots * ldp] = p1; dst[2 * slots * ldp] = p2; }
                     }
                 }
             }
@@ -652,7 +652,7 @@ template <int TM, int EPI, int DIST>
 __device__ __forceinline__ void gemm_epilogue_acc_layout(
     f32x16 (&acc)[2][TM], const EpiRegions<TM>& reg, const EpiVecs<TM, EPI>& vec, bf16raw* __restrict__ out,
     float* __restrict__ partials, const bf16raw* __restrict__ ref, int post,
-    int M, int N, int slots, int m_base /* first row of the wave tile */, int n_base /* first feature */,
+    int M, int N, int slots, int64_t ldp, int m_base /* first row of the wave tile */, int n_base /* first feature */,
     int lane) {
     constexpr bool LN = epi_ln(EPI);
     constexpr bool GELU = EPI == EPI_BIAS_GELU || EPI == EPI_LN_BIAS_GELU;
@@ -723,12 +723,12 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
             }
         if (SHIFT) {
             if (g == 1 && m_ok) {  // the half-wave that holds the complete chunk sums
-                float* dst = partials + ((int64_t)m * slots + (n_base >> 6)) * kShiftLanes;
+                float* dst = partials + (n_base >> 6) * ldp + m;
                 dst[0] = ((pc0[0] + pc0[4]) + (pc0[2] + pc0[6])) + ((pc0[1] + pc0[5]) + (pc0[3] + pc0[7]));
                 if (DIST == RS_DIST_COS) {
                     constexpr int C = DIST == RS_DIST_COS ? 1 : 0;
-                    dst[1] = ((pc1[0] + pc1[4 * C]) + (pc1[2 * C] + pc1[6 * C])) + ((pc1[1 * C] + pc1[5 * C]) + (pc1[3 * C] + pc1[7 * C]));
-                    dst[2] = ((pc2[0] + pc2[4 * C]) + (pc2[2 * C] + pc2[6 * C])) + ((pc2[1 * C] + pc2[5 * C]) + (pc2[3 * C] + pc2[7 * C]));
+                    dst[slots * ldp] = ((pc1[0] + pc1[4 * C]) + (pc1[2 * C] + pc1[6 * C])) + ((pc1[1 * C] + pc1[5 * C]) + (pc1[3 * C] + pc1[7 * C]));
+                    dst[2 * slots * ldp] = ((pc2[0] + pc2[4 * C]) + (pc2[2 * C] + pc2[6 * C])) + ((pc2[1 * C] + pc2[5 * C]) + (pc2[3 * C] + pc2[7 * C]));
                 }
             }
         }
@@ -762,7 +762,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
     const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
-    int tiles_n, int slots, int gm, GemmBatch batch) {
+    int tiles_n, int slots, int64_t ldp, int gm, GemmBatch batch) {
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
@@ -914,7 +914,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     if (epi_res(EPI)) epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
     vec.load(bias, ln, M, N, m_base, n_base, lane);
     if (epi_res(EPI)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
-    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, m_base, n_base, lane);
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, ldp, m_base, n_base, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -931,7 +931,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
     const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
-    int tiles_n, int slots, int gm) {
+    int tiles_n, int slots, int64_t ldp, int gm) {
     constexpr int NW = WGM * WGN, TN = 2, WM = 32 * TM, WN = 64, BM = WM * WGM, BN = WN * WGN;
     constexpr int RB = 128, RPI = 8;                       // LDS row bytes, rows per wave copy
     constexpr int A_LOADS = BM / RPI / NW, W_LOADS = BN / RPI / NW, LPW = A_LOADS + W_LOADS;
@@ -1128,7 +1128,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
 #undef RS_SLIM_ALL_FRAGS
 #undef RS_SLIM_ALL_MFMA
 #undef RS_SLIM_SLICE
-    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, m_base, n_base, lane);
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, ldp, m_base, n_base, lane);
 }
 
 // Tile configuration of the bf16 GEMM: BM, BN, BK, NSTAGE, waves along tokens, waves along features.
@@ -1180,15 +1180,15 @@ struct GemmArgs {
     GemmLnFold ln;
     int64_t M;
     int N, K;
+    int64_t ldp;  // floats between the slots of the shift sums: the rows of the whole problem
     // the same problem restricted to rows [r0, r1)
     GemmArgs rows(int64_t r0, int64_t r1) const {
         GemmArgs g = *this;
-        const int slots = (N + 63) / 64;
         g.a = a + r0 * K;
         g.res = res ? res + r0 * N : nullptr;
         g.ref = ref ? ref + r0 * N : nullptr;
         g.out = out + r0 * N;
-        g.partials = partials ? partials + r0 * slots * kShiftLanes : nullptr;
+        g.partials = partials ? partials + r0 : nullptr;
         g.ln.stats = ln.stats ? ln.stats + r0 * 2 : nullptr;
         g.M = r1 - r0;
         return g;
@@ -1202,7 +1202,7 @@ static void launch_ring(const GemmArgs& g, hipStream_t s) {
     constexpr int WGN = BN / 64, WGM = 4 / WGN;  // four waves, each 64 features wide
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(256), 0, s,
                        g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m,
-                       tiles_n, (g.N + 63) / 64, RS_GEMM_GM, GemmBatch{0, 0, 0});
+                       tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM, GemmBatch{0, 0, 0});
 }
 
 template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
@@ -1212,7 +1212,7 @@ static void launch_slim(const GemmArgs& g, hipStream_t s) {
     const int nblk = tiles_m * tiles_n;
     hipLaunchKernelGGL((gemm_bf16_slim_kernel<WGM, WGN, TM, NST, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(WGM * WGN * 64), 0, s,
                        g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m,
-                       tiles_n, (g.N + 63) / 64, RS_GEMM_GM);
+                       tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
 // The ring kernel with the tile width that suits the grid.  128 x 128 tiles unless they would leave
@@ -1249,11 +1249,11 @@ static void launch_persistent(const GemmArgs& g, hipStream_t s) {
     if (gemm_deep_stages(g.K))
         hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 3, C::WGM, C::WGN, EPI, DIST>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
-                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, RS_GEMM_GM);
+                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
     else
         hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 2, C::WGM, C::WGN, EPI, DIST>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
-                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, RS_GEMM_GM);
+                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
 // Choice by shape: the smallest tile of 64 x 64, 128 x 64, 128 x 128, 256 x 128 (slim kernels) and 256 x 256
@@ -1295,7 +1295,7 @@ static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, c
                               void* out, float* partials, const void* ref, bool post, GemmLnFold ln,
                               int64_t M, int N, int K, hipStream_t s) {
     const GemmArgs g{(const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)bias, (const bf16raw*)res,
-                     (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K};
+                     (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K, M};
     const int variant = gemm_variant();
     if (variant == 1) launch_persistent<EPI, DIST>(g, s);
     else if (variant == 2) launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
@@ -1325,14 +1325,14 @@ hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int cou
         hipLaunchKernelGGL((gemm_bf16_ring_kernel<256, 64, 4, 1, EPI_BIAS, 0>), dim3(8 * ((tiles_m + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
                            (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, tiles_m, 1,
-                           1, RS_GEMM_GM, gb);
+                           1, (int64_t)0, RS_GEMM_GM, gb);
     } else {
         const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
         const int nblk = tiles_m * tiles_n;
         hipLaunchKernelGGL((gemm_bf16_ring_kernel<128, 128, 2, 2, EPI_BIAS, 0>), dim3(8 * ((nblk + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
                            (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, tiles_m,
-                           tiles_n, (N + 63) / 64, RS_GEMM_GM, gb);
+                           tiles_n, (N + 63) / 64, (int64_t)0, RS_GEMM_GM, gb);
     }
     return hipGetLastError();
 }

@@ -221,9 +221,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
                 if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
             }
             if (tx == 0 && m_ok) {
-                float* dst = partials + ((int64_t)m * slots + tn) * kShiftLanes;
+                float* dst = partials + (int64_t)tn * M + m;
                 dst[0] = p0;
-                if (DIST == RS_DIST_COS) { dst[1] = p1; dst[2] = p2; }
+                if (DIST == RS_DIST_COS) { dst[(int64_t)slots * M] = p1; dst[(int64_t)2 * slots * M] = p2; }
             }
         }
     }

@@ -2,6 +2,8 @@
 // (Eq. (4) of Sec. 3.2; "Distance metrics", Sec. 3.3; pruning of the lowest-score
 // tokens, Secs. 3.1 and 3.2).  All of it is HBM-bound: the score pass streams F(x)
 // and x once, the selection works on N floats per image, the gather copies K rows.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace rs {
@@ -132,24 +134,27 @@ hipError_t launch_shift_scores(rs_dtype dt, rs_dist dist, const void* f_out, con
 }
 
 // ---------------------------------------------------------------------------
-// scores from the fc2 epilogue's per-row partial slots, summed in slot order.
+// scores from the GEMM epilogue's per-row partial slots ([kShiftLanes][slots][M]), summed in slot order.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ float score_from_partials(const float* __restrict__ partials, int slots, int64_t M, int64_t row,
+                                                     int dist) {
+    const float* p = partials + row;
+    float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < slots; ++s) p0 += p[s * M];
+    if (dist == RS_DIST_COS) {
+#pragma unroll 4
+        for (int s = 0; s < slots; ++s) { p1 += p[(slots + s) * M]; p2 += p[(2 * slots + s) * M]; }
+        return dist_value<RS_DIST_COS>(p0, p1, p2);
+    }
+    return dist == RS_DIST_L2 ? dist_value<RS_DIST_L2>(p0, p1, p2) : p0;
+}
+
 __global__ __launch_bounds__(256) void finalize_scores_kernel(const float* __restrict__ partials,
                                                               int slots, int dist,
                                                               float* __restrict__ scores, int64_t M) {
     const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (row >= M) return;
-    const float* p = partials + row * slots * kShiftLanes;
-    float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-    for (int s = 0; s < slots; ++s) {
-        p0 += p[s * kShiftLanes];
-        if (dist == RS_DIST_COS) { p1 += p[s * kShiftLanes + 1]; p2 += p[s * kShiftLanes + 2]; }
-    }
-    float r;
-    if (dist == RS_DIST_L2) r = sqrtf(p0);
-    else if (dist == RS_DIST_L1) r = p0;
-    else r = 1.0f - p0 / (sqrtf(p1) * sqrtf(p2));
-    scores[row] = r;
+    if (row < M) scores[row] = score_from_partials(partials, slots, M, row, dist);
 }
 
 hipError_t launch_finalize_scores(rs_dist dist, const float* partials, int slots, float* scores,
@@ -395,58 +400,52 @@ __device__ __forceinline__ void block_select(const float* sc, int N, int n_prefi
     }
 }
 
-// Number of the n keys in `keys` (LDS, 16-byte aligned, zeros from n up to the next multiple of 4) that
-// go before candidate i with key `mine`: larger ones, and equal ones with a lower index.  Vectors
-// first, first + step, ... of four keys: read four at a time and unrolled, because a loop of single
-// reads costs the LDS latency per key (197 keys: 8 us).
-__device__ __forceinline__ int count_before(const uint32_t* keys, int n, uint32_t mine, int i, int first, int step) {
-    int cnt = 0;
-    const int nv = (n + 3) >> 2;
-#pragma unroll 4
-    for (int v = first; v < nv; v += step) {
-        const u32x4 k4 = *reinterpret_cast<const u32x4*>(keys + 4 * v);
+// The same selection for at most 64 R tokens by ONE wave, in registers: lane l holds the keys of tokens
+// l, l + 64, ...; on return pos[r] is the place of token 64 r + l in the ascending list of survivors
+// (prefix included) or -1.  The key of the n_keep-th largest candidate is found bit by bit, counting with
+// ballots how many keys reach a trial value (about 20 trials: it ends as soon as exactly n_keep do); no
+// LDS, no barrier.  (Counting every token's rank against all others took N^2 comparisons per image, in
+// every workgroup that shares an image: 5 us of the block's prune pass at 64 x 197 tokens.)
+template <int R>
+__device__ __forceinline__ void wave_select(const uint32_t (&key)[R], int N, int n_prefix, int n_keep, int lane, int (&pos)[R]) {
+    bool valid[R];
+    uint32_t k[R];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) cnt += (k4[e] > mine) || (k4[e] == mine && 4 * v + e < i);
+    for (int r = 0; r < R; ++r) {
+        const int i = r * 64 + lane;
+        valid[r] = i >= n_prefix && i < N;
+        k[r] = valid[r] ? key[r] : 0u;  // below every trial value
     }
-    return cnt;
-}
-
-// The same selection for N <= 256 tokens by counting: token i's rank among the candidates is the
-// number of candidates with a larger key, or an equal key and a lower index; ranks below n_keep
-// survive.  NT / 256 threads share a token's count, a ballot scan over the survival flags gives the
-// output positions: four barriers instead of the radix passes' thirty.  Identical results.
-// With `slot` (N ints, workgroup-visible) slot[i] becomes the position of token i in `out`, or
-// -1 for a dropped token.
-template <int NT>
-__device__ __forceinline__ void block_select_rank(const float* sc /* LDS */, int N, int n_prefix, int n_keep,
-                                                  int32_t* __restrict__ out, int* slot, SelectShared& sh, int tid) {
-    constexpr int TPT = NT / 256;  // threads per token
-    const int n = N - n_prefix;
-    // (a caller that loops has a barrier between this write and the previous round's reads of sh)
-    if (tid < 256) sh.list[tid] = tid < n ? score_key(sc[n_prefix + tid]) : 0u;
-    __syncthreads();
-    const int i = tid / TPT, part = tid % TPT;
-    int cnt = 0;
-    if (i >= n_prefix && i < N) cnt = count_before(sh.list, n, sh.list[i - n_prefix], i - n_prefix, part, TPT);
+    uint32_t thr = 0u;         // kept: keys above thr, and `ties` of those equal to it, lowest indices first
+    bool exact = false;
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t c = thr | (1u << bit);
+        int cnt = 0;
 #pragma unroll
-    for (int off = 1; off < TPT; off <<= 1) cnt += __shfl_xor(cnt, off, 64);
-    if (part == 0 && i < N) sh.hist[i] = (i < n_prefix || cnt < n_keep) ? 1 : 0;
-    __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6;
-    const int f = (tid < N) ? sh.hist[tid] : 0;        // thread t now stands for token t
-    const unsigned long long mask = __ballot(f);
-    const int before = __popcll(mask & ((1ull << lane) - 1ull));
-    if (wave < 4 && lane == 0) sh.wave[wave] = __popcll(mask);
-    __syncthreads();
-    if (tid < N) {
-        int pos = before;
-        for (int w = 0; w < wave; ++w) pos += sh.wave[w];
-        if (f) out[pos] = tid;
-        if (slot) slot[tid] = f ? pos : -1;
+        for (int r = 0; r < R; ++r) cnt += __popcll(__ballot(k[r] >= c));
+        if (cnt >= n_keep) thr = c;
+        if (cnt == n_keep) { exact = true; break; }
+    }
+    if (exact) thr -= 1u;      // exactly the keys that reach thr (>= 1) survive
+    int above = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) above += __popcll(__ballot(valid[r] && k[r] > thr));
+    const int ties = n_keep - above;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int base = 0, eq_base = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned long long me = __ballot(valid[r] && k[r] == thr);
+        const bool tie = valid[r] && k[r] == thr && eq_base + __popcll(me & below) < ties;
+        const bool keep = r * 64 + lane < n_prefix || (valid[r] && k[r] > thr) || tie;
+        const unsigned long long mk = __ballot(keep);
+        pos[r] = keep ? base + __popcll(mk & below) : -1;
+        base += __popcll(mk);
+        eq_base += __popcll(me);
     }
 }
 
-// One image per workgroup.  The scores go through LDS (N * 4 bytes of dynamic LDS, N <= SEL_MAXN): read
+// Longer sequences, one image per workgroup.  The scores go through LDS (N * 4 bytes of dynamic LDS, N <= SEL_MAXN): read
 // from `scores`, or with `partials` formed from the GEMM epilogue's per-row slots (added in slot order,
 // as finalize_scores_kernel does) and written to `scores` on the way: the block's prune pass needs no
 // separate score launch.
@@ -463,15 +462,7 @@ __global__ __launch_bounds__(NT) void select_kernel(float* __restrict__ scores,
     for (int i = tid; i < N; i += NT) {
         float r;
         if (partials) {
-            const float* p = partials + ((int64_t)blockIdx.x * N + i) * slots * kShiftLanes;
-            float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-            for (int sl = 0; sl < slots; ++sl) {
-                p0 += p[sl * kShiftLanes];
-                if (dist == RS_DIST_COS) { p1 += p[sl * kShiftLanes + 1]; p2 += p[sl * kShiftLanes + 2]; }
-            }
-            if (dist == RS_DIST_L2) r = sqrtf(p0);
-            else if (dist == RS_DIST_L1) r = p0;
-            else r = 1.0f - p0 / (sqrtf(p1) * sqrtf(p2));
+            r = score_from_partials(partials, slots, (int64_t)gridDim.x * N, (int64_t)blockIdx.x * N + i, dist);
             sc[i] = r;
         } else {
             r = sc[i];
@@ -479,8 +470,24 @@ __global__ __launch_bounds__(NT) void select_kernel(float* __restrict__ scores,
         s_scores[i] = r;
     }
     __syncthreads();
-    if (N <= 256) block_select_rank<NT>(s_scores, N, n_prefix, n_keep, out, nullptr, sh, tid);
-    else block_select_lds<NT>(s_scores, N, n_prefix, n_keep, out, sh, tid);
+    block_select_lds<NT>(s_scores, N, n_prefix, n_keep, out, sh, tid);
+}
+
+// Sequences of at most 256 tokens: one wave per image.
+__global__ __launch_bounds__(256) void select_short_kernel(const float* __restrict__ scores,
+                                                           int32_t* __restrict__ kept_idx, int B, int N, int n_prefix,
+                                                           int n_keep) {
+    const int lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (b >= B) return;
+    uint32_t key[4];
+    int pos[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < N ? score_key(scores[b * N + r * 64 + lane]) : 0u;
+    wave_select<4>(key, N, n_prefix, n_keep, lane, pos);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (pos[r] >= 0) kept_idx[b * (n_prefix + n_keep) + pos[r]] = r * 64 + lane;
 }
 
 // Sequences beyond SEL_MAXN tokens: the scores stay in global memory.
@@ -525,10 +532,9 @@ template <typename T, int DIST, int CH, int NR>
 __global__ __launch_bounds__(RES_WAVES * 64) void shift_topk_resident_kernel(
     const T* __restrict__ f_out, const T* __restrict__ f_in, float* __restrict__ scores,
     int32_t* __restrict__ kept_idx, T* __restrict__ gathered, int B, int N, int D, int n_prefix, int n_keep) {
-    constexpr int NT = RES_WAVES * 64;
-    __shared__ SelectShared sh;
-    __shared__ float s_scores[NR * RES_WAVES];
-    __shared__ int s_slot[NR * RES_WAVES];
+    static_assert(RES_WAVES == 16 && RES_MAXN <= 256, "the selection below: row wave + 16 k is token 64 (k / 4) + wave + 16 (k % 4)");
+    __shared__ float s_scores[2][256];
+    int par = 0;  // scores of two images alternate, so that one barrier per image is enough
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: row addresses stay scalar
     const int row_u = D * (int)sizeof(T) / 8;  // 8-byte units per row
@@ -591,17 +597,25 @@ __global__ __launch_bounds__(RES_WAVES * 64) void shift_topk_resident_kernel(
                     if (DIST == RS_DIST_L2) sc = sqrtf(p0);
                     else if (DIST == RS_DIST_L1) sc = p0;
                     else sc = 1.0f - p0 / (sqrtf(p1) * sqrtf(p2));
-                    s_scores[i] = sc;
+                    s_scores[par][i] = sc;
                     scores[(int64_t)b * N + i] = sc;
                 }
             }
             __builtin_amdgcn_sched_barrier(0);  // the next group's loads stay behind this group's sums
         }
         __syncthreads();
-        block_select_rank<NT>(s_scores, N, n_prefix, n_keep, kept_idx + (int64_t)b * K, s_slot, sh, tid);
-        __syncthreads();
-        // (no barrier at the end of the loop: s_scores is next written before the barrier above, which
-        // no wave passes before all have left the selection; s_slot and sh are next written two barriers on)
+        // every wave selects for itself (registers only) and needs nothing from the others
+        uint32_t key[4];
+        int pos[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < N ? score_key(s_scores[par][r * 64 + lane]) : 0u;
+        wave_select<4>(key, N, n_prefix, n_keep, lane, pos);
+        if (wave == 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (pos[r] >= 0) kept_idx[(int64_t)b * K + pos[r]] = r * 64 + lane;
+        }
+        par ^= 1;
         const __amdgpu_buffer_rsrc_t r_out = __builtin_amdgcn_make_buffer_rsrc(
             gathered + (int64_t)b * K * D, 0, K * row_bytes, 0x00020000);
         const int b_next = b + gridDim.x;
@@ -610,11 +624,11 @@ __global__ __launch_bounds__(RES_WAVES * 64) void shift_topk_resident_kernel(
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             const int i = wave + RES_WAVES * k;
-            const int j = i < N ? s_slot[i] : -1;  // wave-uniform
+            const int j = __builtin_amdgcn_readlane(pos[k >> 2], wave + 16 * (k & 3));  // place of row i, or -1
             if (j >= 0) {
 #pragma unroll
                 for (int c = 0; c < CH; ++c)
-                    __builtin_amdgcn_raw_buffer_store_b64(keep[k][c], r_out, voff[c], __builtin_amdgcn_readfirstlane(j) * row_bytes, 0);
+                    __builtin_amdgcn_raw_buffer_store_b64(keep[k][c], r_out, voff[c], j * row_bytes, 0);
             }
 #pragma unroll
             for (int c = 0; c < CH; ++c)
@@ -688,9 +702,11 @@ hipError_t launch_select(const float* scores, int32_t* kept_idx, int B, int N, i
         hipLaunchKernelGGL(iota_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, kept_idx, B, N);
     } else {
         const size_t lds = (size_t)N * sizeof(float);
-        if (N > SEL_MAXN)
+        if (N <= 256)
+            hipLaunchKernelGGL(select_short_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, scores, kept_idx, B, N, n_prefix, n_keep);
+        else if (N > SEL_MAXN)
             hipLaunchKernelGGL(select_long_kernel, dim3(B), dim3(1024), 0, s, scores, kept_idx, N, n_prefix, n_keep);
-        else if (N > 1024 || N <= 256)  // counting: four threads per token
+        else if (N > 1024)
             hipLaunchKernelGGL(select_kernel<1024>, dim3(B), dim3(1024), lds, s, const_cast<float*>(scores), kept_idx, N,
                                n_prefix, n_keep, (const float*)nullptr, 0, 0);
         else
@@ -706,10 +722,7 @@ hipError_t launch_select_from_partials(rs_dist dist, const float* partials, int 
                                        int32_t* kept_idx, int B, int N, int n_prefix, int n_keep,
                                        hipStream_t s) {
     if (B == 0) return hipSuccess;
-    if (N <= 256) {
-        hipLaunchKernelGGL(select_kernel<1024>, dim3(B), dim3(1024), (size_t)N * sizeof(float), s, scores, kept_idx, N,
-                           n_prefix, n_keep, partials, slots, (int)dist);
-    } else if (B < 64) {
+    if (N <= 256 || B < 64) {
         // a few long sequences (video clips): one workgroup per image would walk its image's slots
         // alone, one cache line per thread and slot, and spend more time there than selecting.
         // The scores are formed by a grid over all rows instead (the same additions in the same
@@ -814,6 +827,103 @@ hipError_t launch_gather_stats(const void* src, const int32_t* kept_idx, void* o
     return hipGetLastError();
 }
 
+// Scores, selection and gather of one short image (N <= 256) in one launch: `parts` workgroups per image,
+// each of which forms the image's scores from the partial sums and selects (a microsecond; the sums
+// are a few KB per image) and then copies its share of the surviving rows, STATS: with their LayerNorm
+// statistics as in gather_rows_stats_kernel.  Against a selection and a gather of their own it saves
+// a launch of every pruning block (vit_s16, eleven of them: 1020 -> 944 us per forward together with the
+// selection by one wave); one workgroup per image would leave the chip idle and copy with too few
+// requests in flight.  MAXC: 16-byte vectors per lane and row.
+constexpr int SG_WAVES = 8;
+template <bool STATS, int MAXC>
+__global__ __launch_bounds__(SG_WAVES * 64) void select_gather_kernel(
+    const float* __restrict__ partials, int slots, int dist, float* __restrict__ scores,
+    int32_t* __restrict__ kept_idx, const u32x4* __restrict__ src, u32x4* __restrict__ out,
+    float2* __restrict__ stats, int N, int n_prefix, int n_keep, int row_vec, int D, float eps) {
+    __shared__ float s_scores[256];
+    __shared__ int32_t s_idx[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t b = blockIdx.y;
+    const int K = n_prefix + n_keep;
+    if (tid < N) {
+        const float r = score_from_partials(partials, slots, (int64_t)gridDim.y * N, b * N + tid, dist);
+        s_scores[tid] = r;
+        if (blockIdx.x == 0) scores[b * N + tid] = r;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t key[4];
+        int pos[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < N ? score_key(s_scores[r * 64 + lane]) : 0u;
+        wave_select<4>(key, N, n_prefix, n_keep, lane, pos);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (pos[r] >= 0) {
+                s_idx[pos[r]] = r * 64 + lane;
+                if (blockIdx.x == 0) kept_idx[b * K + pos[r]] = r * 64 + lane;
+            }
+    }
+    __syncthreads();
+    const int per = (K + gridDim.x - 1) / gridDim.x;
+    const int j1 = min((int)(blockIdx.x + 1) * per, K);
+    constexpr int U = 2;  // rows in flight per wave
+    for (int j0 = blockIdx.x * per + wave; j0 < j1; j0 += SG_WAVES * U) {
+        u32x4 v[U][MAXC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * SG_WAVES;
+            const u32x4* s = src + (b * N + s_idx[min(j, K - 1)]) * row_vec;
+#pragma unroll
+            for (int c = 0; c < MAXC; ++c)
+                v[u][c] = j < j1 && lane + c * 64 < row_vec ? s[lane + c * 64] : u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * SG_WAVES;
+            if (j >= j1) break;  // wave-uniform
+            u32x4* d = out + (b * K + j) * row_vec;
+#pragma unroll
+            for (int c = 0; c < MAXC; ++c)
+                if (lane + c * 64 < row_vec) d[lane + c * 64] = v[u][c];
+            if constexpr (STATS) {
+                float f[MAXC][8];
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        f[c][2 * i] = __uint_as_float(v[u][c][i] << 16);
+                        f[c][2 * i + 1] = __uint_as_float(v[u][c][i] & 0xffff0000u);
+                    }
+                const float2 st = wave_row_stats<MAXC>(f, row_vec, lane, D, eps);
+                if (lane == 0) stats[b * K + j] = st;
+            }
+        }
+    }
+}
+
+bool select_gather_fits(rs_dtype dt, int N, int D) { return N <= 256 && (size_t)D * elem_size(dt) <= 4 * 1024; }
+
+hipError_t launch_select_gather(rs_dtype dt, rs_dist dist, const float* partials, int slots, float* scores,
+                                int32_t* kept_idx, const void* src, void* out, float* stats, int B, int N, int n_prefix,
+                                int n_keep, int D, float eps, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    const int K = n_prefix + n_keep, row_vec = (int)((size_t)D * elem_size(dt) / 16);
+    // about two workgroups per CU over all images (256 .. 2048 in all measured within 1 %), at least one row per wave
+    int parts = (512 + B - 1) / B;
+    parts = parts < (K + SG_WAVES - 1) / SG_WAVES ? parts : (K + SG_WAVES - 1) / SG_WAVES;
+    const bool st = stats && dt == RS_BF16;
+#define RS_SG(ST_, C_)                                                                                                   \
+    hipLaunchKernelGGL((select_gather_kernel<ST_, C_>), dim3(parts, B), dim3(SG_WAVES * 64), 0, s, partials, slots, (int)dist, \
+                       scores, kept_idx, (const u32x4*)src, (u32x4*)out, reinterpret_cast<float2*>(stats), N, n_prefix,      \
+                       n_keep, row_vec, D, eps)
+    if (row_vec <= 64) { if (st) RS_SG(true, 1); else RS_SG(false, 1); }
+    else if (row_vec <= 128) { if (st) RS_SG(true, 2); else RS_SG(false, 2); }
+    else { if (st) RS_SG(true, 4); else RS_SG(false, 4); }
+#undef RS_SG
+    return hipGetLastError();
+}
+
 // lanes that share one row of `vec` 16-byte vectors in the gathers: the next power of two, at most a wave
 static int gather_lanes(int vec) {
     int g = 1;
@@ -897,7 +1007,6 @@ __global__ __launch_bounds__(512) void grid_line_select_kernel(const float* __re
                                                                int32_t* __restrict__ kept_rows,
                                                                int32_t* __restrict__ kept_cols, int H, int W, int R,
                                                                int Q) {
-    __shared__ SelectShared sh;
     __shared__ float s_row[GRID_LINE], s_col[GRID_LINE];
     extern __shared__ float s_map[];
     const int tid = threadIdx.x;
@@ -918,9 +1027,21 @@ __global__ __launch_bounds__(512) void grid_line_select_kernel(const float* __re
         col_scores[b * W + w] = s_col[w] = a / (float)H;
     }
     __syncthreads();
-    if (R > 0) block_select_rank<512>(s_row, H, 0, R, kept_rows + b * R, nullptr, sh, tid);
-    __syncthreads();
-    if (Q > 0) block_select_rank<512>(s_col, W, 0, Q, kept_cols + b * Q, nullptr, sh, tid);
+    const int wave = tid >> 6, lane = tid & 63;
+    if (wave > 1) return;
+    // wave 0: rows, wave 1: columns
+    const float* sc = wave == 0 ? s_row : s_col;
+    const int n = wave == 0 ? H : W, n_keep = wave == 0 ? R : Q;
+    int32_t* out = wave == 0 ? kept_rows + b * R : kept_cols + b * Q;
+    if (n_keep == 0) return;
+    uint32_t key[4];
+    int pos[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < n ? score_key(sc[r * 64 + lane]) : 0u;
+    wave_select<4>(key, n, 0, n_keep, lane, pos);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (pos[r] >= 0) out[pos[r]] = r * 64 + lane;
 }
 
 bool grid_line_select_fits(int H, int W) {
@@ -994,9 +1115,7 @@ __global__ __launch_bounds__(256) void grid_row_select_kernel(const T* __restric
                                                               float* __restrict__ scores, int32_t* __restrict__ kept_cols,
                                                               float* __restrict__ col_scores, int rows, int H, int W,
                                                               int C, int Q) {
-    __shared__ SelectShared sh;
     __shared__ float s_sc[GRID_LINE];
-    __shared__ int s_slot[GRID_LINE];
     const int row = xcd_item(blockIdx.x, rows);
     if (row < 0) return;  // whole workgroup, before any barrier
     const int tid = threadIdx.x, sub = tid % G;
@@ -1040,12 +1159,27 @@ __global__ __launch_bounds__(256) void grid_row_select_kernel(const T* __restric
         }
     }
     __syncthreads();
-    if (tid < W) scores[(int64_t)row * W + tid] = s_sc[tid];
-    block_select_rank<256>(s_sc, W, 0, Q, kept_cols + (int64_t)row * Q, s_slot, sh, tid);
-    if (col_scores && tid < W) {  // (a thread reads the slot it wrote itself)
-        const int j = s_slot[tid], b = row / H, h = row - b * H;
-        if (j >= 0) col_scores[((int64_t)b * Q + j) * H + h] = s_sc[tid];
+    if (tid >= 64) {  // waves 1 .. 3 write the scores while wave 0 selects
+        for (int w = tid - 64; w < W; w += 192) scores[(int64_t)row * W + w] = s_sc[w];
+        return;
     }
+    const int b = row / H, h = row - b * H;
+    auto select = [&](auto regs) {
+        constexpr int R = decltype(regs)::value;
+        uint32_t key[R];
+        int pos[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) key[r] = r * 64 + tid < W ? score_key(s_sc[r * 64 + tid]) : 0u;
+        wave_select<R>(key, W, 0, Q, tid, pos);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (pos[r] >= 0) {
+                kept_cols[(int64_t)row * Q + pos[r]] = r * 64 + tid;
+                if (col_scores) col_scores[((int64_t)b * Q + pos[r]) * H + h] = s_sc[r * 64 + tid];
+            }
+    };
+    if (W <= 64) select(std::integral_constant<int, 1>{});
+    else select(std::integral_constant<int, 4>{});
 }
 
 bool grid_token_fused_fits(int64_t B, int H, int W) { return H <= GRID_LINE && W <= GRID_LINE && B * H < (int64_t)1 << 30; }
@@ -1082,7 +1216,6 @@ __global__ __launch_bounds__(256) void grid_col_gather_kernel(const u32x4* __res
                                                               const float* __restrict__ col_scores,
                                                               int32_t* __restrict__ kept_rows, u32x4* __restrict__ out,
                                                               int items, int groups, int H, int W, int R, int Q, int vec) {
-    __shared__ __attribute__((aligned(16))) uint32_t s_key[4][GRID_LINE];
     __shared__ int s_pos[4][GRID_LINE];  // source position (r * W + c) of the column's i-th survivor
     const int item = xcd_item(blockIdx.x, items);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1090,23 +1223,24 @@ __global__ __launch_bounds__(256) void grid_col_gather_kernel(const u32x4* __res
     const int b = item / groups, j = (item - b * groups) * 4 + wave;
     if (j >= Q) return;  // whole wave; no workgroup barrier below
     const int64_t bj = (int64_t)b * Q + j;
-    for (int h = lane; h < ((H + 3) & ~3); h += 64) s_key[wave][h] = h < H ? score_key(col_scores[bj * H + h]) : 0u;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wave's own LDS writes
-    int base = 0;
-    for (int h0 = 0; h0 < H; h0 += 64) {
-        const int h = h0 + lane;
-        bool keep = false;
-        if (h < H) {
-            keep = count_before(s_key[wave], H, s_key[wave][h], h, 0, 1) < R;
+    auto select = [&](auto regs) {
+        constexpr int RG = decltype(regs)::value;
+        uint32_t key[RG];
+        int pos[RG];
+#pragma unroll
+        for (int r = 0; r < RG; ++r) key[r] = r * 64 + lane < H ? score_key(col_scores[bj * H + r * 64 + lane]) : 0u;
+        wave_select<RG>(key, H, 0, R, lane, pos);
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const int h = r * 64 + lane;
+            if (pos[r] >= 0) {
+                kept_rows[bj * R + pos[r]] = h;
+                s_pos[wave][pos[r]] = h * W + kept_cols[((int64_t)b * H + h) * Q + j];
+            }
         }
-        const unsigned long long mask = __ballot(keep);
-        if (keep) {
-            const int i = base + __popcll(mask & ((1ull << lane) - 1ull));
-            kept_rows[bj * R + i] = h;
-            s_pos[wave][i] = h * W + kept_cols[((int64_t)b * H + h) * Q + j];
-        }
-        base += __popcll(mask);
-    }
+    };
+    if (H <= 64) select(std::integral_constant<int, 1>{});
+    else select(std::integral_constant<int, 4>{});
     if (!out) return;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     constexpr int U = 4, PPG = 64 / G;

@@ -727,6 +727,13 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
         }
         return RS_OK;
     };
+    if (prune && c.n_keep > 0 && select_gather_fits(dt, c.N, D)) {
+        // short images: scores, selection, gather and the statistics of the gathered rows in one launch
+        RS_LAUNCH_K(K_GATHER, s, launch_select_gather(dt, c.dist, partials, L.slots, sc, kept_idx, xhat, y, y_stats, c.B, c.N,
+                                                    c.n_prefix, c.n_keep, D, c.ln_eps, s));
+        if (y_stats && dt != RS_BF16) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, y, y_stats, (int64_t)c.B * K, D, c.ln_eps, s));
+        return RS_OK;
+    }
     if (prune && c.n_keep > 0 && select_from_partials_fits(c.N)) {
         // scores straight from the epilogue's partial sums inside the selection kernel
         RS_LAUNCH_K(K_SELECT, s, launch_select_from_partials(c.dist, partials, L.slots, sc, kept_idx, c.B, c.N, c.n_prefix,

@@ -40,7 +40,8 @@ class EncoderStack:
             self._keep_alive.append((w, packed))
             self.weights.append(rs.make_weights(w, packed))
         self.gemm_variant = 0            # tile-variant switch of the bf16 GEMMs (0 = chosen by shape)
-        self.chain = True                # hand row statistics from block to block (same results either way)
+        # hand row statistics from block to block (same results either way; the fp32 blocks make no use of them)
+        self.chain = self.dtype == torch.bfloat16
         self.set_streams(streams)
 
     def tune(self, candidates=((1, 0), (2, 0), (2, 1)), steps: int = 8, rounds: int = 2):

@@ -72,3 +72,36 @@ def test_one_pass_and_three_launches_agree(B, N, D, P, K, dtype):
         np.testing.assert_array_equal(kept.cpu().numpy(), oracle.topk(scores.cpu().numpy().astype(np.float64), P, K))
         rows = torch.take_along_dim(f_in, kept.long()[:, :, None], dim=1)
         assert torch.equal(out, rows)
+
+
+# the block's prune step in one launch (at most 256 tokens, rows of at most 4 KB) and just past it: sequence
+# lengths around the 64-token registers of the selecting wave, one survivor, all but one, no prefix, many
+# images, rows of one to four vectors per lane
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,N,D,P,K", [(1, 256, 64, 0, 1), (3, 255, 128, 2, 252), (600, 20, 64, 1, 7), (2, 64, 576, 1, 62),
+                                       (2, 65, 1024, 1, 30), (2, 129, 1088, 0, 128), (1, 257, 64, 1, 100)])
+def test_block_prune_step(B, N, D, P, K, dtype):
+    """A pruning block against the same block that keeps every token (its y is the unpruned output): the same
+    scores, the kept set exact on them, the kept rows and their LayerNorm statistics copied bit for bit."""
+    print("block prune step", B, N, D, P, K, dtype, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N * D + K)
+    rnd = lambda *s, std=0.05: (torch.randn(s, device="cuda", generator=g) * std).to(dtype)
+    w = dict(w_qkv=rnd(D, 3 * D), w_proj=rnd(D, D), w_fc1=rnd(D, 64), w_fc2=rnd(64, D))
+    x = rnd(B, N, D, std=1.0)
+    res = []
+    for n_keep in (K, N - P):
+        cfg = rs.make_cfg(B, N, D, D // 64, 64, P, n_keep, dtype)
+        ws = torch.empty(rs.rs_block_workspace_size(cfg), dtype=torch.uint8, device="cuda")
+        y = torch.full((B, P + n_keep, D), float("nan"), device="cuda", dtype=dtype)
+        stats = torch.full((B, P + n_keep, 2), float("nan"), device="cuda")
+        kept = torch.full((B, P + n_keep), -1, device="cuda", dtype=torch.int32)
+        scores = torch.full((B, N), float("nan"), device="cuda")
+        rs.rs_block_fwd_chained(cfg, rs.make_weights(w), x, None, y, stats, kept, scores, ws)
+        torch.cuda.synchronize()
+        res.append((y, stats, kept, scores))
+    (y, stats, kept, scores), (y_all, stats_all, _, scores_all) = res
+    assert torch.equal(scores, scores_all)
+    np.testing.assert_array_equal(kept.cpu().numpy(), oracle.topk(scores.cpu().numpy().astype(np.float64), P, K))
+    idx = kept.long()[:, :, None]
+    assert torch.equal(y, torch.take_along_dim(y_all, idx, dim=1))
+    assert torch.equal(stats, torch.take_along_dim(stats_all, idx, dim=1))
