@@ -163,18 +163,27 @@ void set_gemm_variant(int v);
 int gemm_shift_slots(rs_dtype dt, int N);
 constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine all three)
 
+// Row pitch (elements) of the MLP's hidden activations and of the packed W_fc2 behind them: the rows of an operand
+// tile are requested together, and when the pitch is a multiple of 512 bytes they meet in a few of the
+// L2's channels.  One extra line per row spreads them: 768 x 3072 at 50432 rows 252 -> 243 us, at 3152 rows
+// 26.5 -> 23.7, 384 x 1536 at 12608 rows 24.8 -> 23.0 (128, 192 or 256 extra elements: the same; 32 or less
+// split lines and cost 5-30 %).  vit_s16 -1.1 %, video_vit_b16 -1.8 % per forward, vit_b16 -0.4 %.  (The attention
+// output and W_proj, padded the same way: no change.)
+inline int padded_ld(int K) { return K % 256 == 0 ? K + 64 : K; }
+
 // out[M, N] = epilogue(a[M, K] @ W).  bf16: `w` is the packed [N, K] matrix; fp32: `w` is the
 // caller's [K, N] matrix.  partials: float [kShiftLanes][slots][M] for EPI_BIAS_RES_SHIFT
-// (rows innermost: the epilogues store and the selection reads whole lines).
+// (rows innermost: the epilogues store and the selection reads whole lines).  ld: elements between the rows
+// of a and of the packed w (bf16; 0 = K), ldo: of out (0 = N).
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials,
-                       const void* ref, bool post, int64_t M, int N, int K, hipStream_t s);
+                       const void* ref, bool post, int64_t M, int N, int K, hipStream_t s, int ld = 0, int ldo = 0);
 hipError_t launch_gemm_f32(GemmEpilogue epi, rs_dist dist, const void* a, const void* w, const void* bias,
                            const void* res, void* out, float* partials, const void* ref, bool post, int64_t M, int N,
                            int K, hipStream_t s);
 // bf16 GEMM behind a LayerNorm (EPI_LN_BIAS / EPI_LN_BIAS_GELU).
 hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded, GemmLnFold ln, void* out,
-                          int64_t M, int N, int K, hipStream_t s);
+                          int64_t M, int N, int K, hipStream_t s, int ld = 0, int ldo = 0);
 
 // `count` independent bf16 products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T, problem p at element offset
 // p * stride from each base pointer (K % 32 == 0, N % 64 == 0; rows of wt_p past N must exist as zeros)
@@ -194,7 +203,7 @@ hipError_t launch_attn_unpack(const void* oh, void* o, int B, int H, int N, int6
 
 // bf16 [K, N] row-major -> [N, K] row-major; with `gamma` ([K] bf16) row k is scaled by gamma[k]
 // (product rounded to bf16).
-hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s);
+hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld = 0);
 // colsum[n] = sum_k bf16(gamma[k] * w[k][n]),  bias_out[n] = sum_k beta[k] * w[k][n] + bias[n]
 // (w [K, N] bf16; gamma, beta, bias bf16 or null = 1, 0, 0; outputs fp32).
 hipError_t launch_pack_ln_fold(const void* w, const void* gamma, const void* beta, const void* bias,

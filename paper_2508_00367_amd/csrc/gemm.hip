@@ -101,7 +101,7 @@ template <int BM, int BN, int BK, int NSTAGE, int WGM, int WGN, int EPI, int DIS
 __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
-    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
+    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int ld, int ldo, int tiles_m,
     int tiles_n, int slots, int64_t ldp, int gm) {
     constexpr int NW = WGM * WGN;               // waves: WGM along tokens x WGN along features
     constexpr int WM = BM / WGM, WN = BN / WGN; // wave tile
@@ -187,13 +187,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     //    64-byte rows (BK 32): f(r) = (r >> 2) & 3         (r & 3 picks the quarter line)
     // global -> LDS: wave copy i of wave w fills rows (NW*i + w)*RPI .. +RPI-1 (lane l: row l / SPR,
     // slot l % SPR), so the lane fetches chunk (l % SPR) ^ f(row).
-    __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 2);
-    __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * K, (int64_t)min(N - n0, BN) * K * 2);
+    __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
+    __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
     const int ld_r = lane / SPR, ld_p = lane % SPR;
     // lane byte offset inside a wave copy (NW is even, so row >> 3 = NW*i + w has the parity of w)
-    const int voff = SPR == 8 ? ((wave * RPI + ld_r) * K + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2
-                              : ((wave * RPI + ld_r) * K + ((ld_p ^ ((ld_r >> 2) & 3)) << 3)) * 2;
-    const int pass_bytes = NW * RPI * K * 2;
+    const int voff = SPR == 8 ? ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2
+                              : ((wave * RPI + ld_r) * ld + ((ld_p ^ ((ld_r >> 2) & 3)) << 3)) * 2;
+    const int pass_bytes = NW * RPI * ld * 2;
 
     const int S = K / BK;                                   // real slices
     constexpr int PERIOD = DEEP ? 6 : 2;                    // slices per trip of the unrolled ring
@@ -395,8 +395,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     const bool more = seq < x_cnt;
     if (more) {
         RS_GEMM_DECODE(seq, m0, n0)
-        rs_a = make_rsrc(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 2);
-        rs_w = make_rsrc(wt + (int64_t)n0 * K, (int64_t)min(N - n0, BN) * K * 2);
+        rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
+        rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
     }
 
     // ---- epilogue, staged through LDS so that global traffic is row-contiguous.
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] += rr[e];
                 }
-                if (ok) Elem<bf16raw>::store8(out + (int64_t)m * N + n, v);
+                if (ok) Elem<bf16raw>::store8(out + (int64_t)m * ldo + n, v);
                 if (EPI == EPI_BIAS_RES_SHIFT) {
                     // sum over the LPR lanes that share the row (fixed butterfly order)
 #pragma unroll
@@ -652,7 +652,7 @@ template <int TM, int EPI, int DIST>
 __device__ __forceinline__ void gemm_epilogue_acc_layout(
     f32x16 (&acc)[2][TM], const EpiRegions<TM>& reg, const EpiVecs<TM, EPI>& vec, bf16raw* __restrict__ out,
     float* __restrict__ partials, const bf16raw* __restrict__ ref, int post,
-    int M, int N, int slots, int64_t ldp, int m_base /* first row of the wave tile */, int n_base /* first feature */,
+    int M, int N, int ldo, int slots, int64_t ldp, int m_base /* first row of the wave tile */, int n_base /* first feature */,
     int lane) {
     constexpr bool LN = epi_ln(EPI);
     constexpr bool GELU = EPI == EPI_BIAS_GELU || EPI == EPI_LN_BIAS_GELU;
@@ -738,7 +738,7 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
             const int r = p * 8 + (lane >> 3), cc = lane & 7;
             const uint4 o4 = *reinterpret_cast<const uint4*>(buf + r * 128 + ((cc ^ epi_swz(r)) << 4));
             const int mo = m_base + j * 32 + r;
-            if (mo < M) *reinterpret_cast<uint4*>(out + (int64_t)mo * N + n_base + cc * 8) = o4;
+            if (mo < M) *reinterpret_cast<uint4*>(out + (int64_t)mo * ldo + n_base + cc * 8) = o4;
         }
     }
 }
@@ -761,7 +761,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, int DIST>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
-    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
+    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int ld, int ldo, int tiles_m,
     int tiles_n, int slots, int64_t ldp, int gm, GemmBatch batch) {
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -808,11 +808,11 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     // global -> LDS: wave copy i of wave w fills rows (NW i + w) 16 .. + 15 (lane l: row l / 4, slot
     // l % 4 holds chunk (l % 4) ^ f(row), f(r) = (r >> 2) & 3: the 16 rows an operand read touches
     // fall into 16 different 16-byte bank groups)
-    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 2);
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * K, (int64_t)min(N - n0, BN) * K * 2);
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
     const int ld_r = lane >> 2, ld_p = lane & 3;
-    const int voff = ((wave * RPI + ld_r) * K + ((ld_p ^ ((ld_r >> 2) & 3)) << 3)) * 2;
-    const int pass_bytes = NW * RPI * K * 2;
+    const int voff = ((wave * RPI + ld_r) * ld + ((ld_p ^ ((ld_r >> 2) & 3)) << 3)) * 2;
+    const int pass_bytes = NW * RPI * ld * 2;
     const int S = K / BK;
     const int S_pad = (S + 2) / 3 * 3;
     const int a_row0 = wm * WM + l32, w_row0 = wn * WN + l32;
@@ -914,7 +914,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     if (epi_res(EPI)) epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
     vec.load(bias, ln, M, N, m_base, n_base, lane);
     if (epi_res(EPI)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
-    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, ldp, m_base, n_base, lane);
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, ldo, slots, ldp, m_base, n_base, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -930,7 +930,7 @@ template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
-    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int tiles_m,
+    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int ld, int ldo, int tiles_m,
     int tiles_n, int slots, int64_t ldp, int gm) {
     constexpr int NW = WGM * WGN, TN = 2, WM = 32 * TM, WN = 64, BM = WM * WGM, BN = WN * WGN;
     constexpr int RB = 128, RPI = 8;                       // LDS row bytes, rows per wave copy
@@ -975,12 +975,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
 
     // LDS layout as in gemm_bf16_kernel: chunk c of row r in slot c ^ (r & 7) ^ ((r >> 3) & 1).  Wave copy i of
     // wave w fills rows (NW i + w) 8 .. + 7; with an odd number of waves the parity of row >> 3 depends on i.
-    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 2);
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * K, (int64_t)min(N - n0, BN) * K * 2);
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
     const int ld_r = lane >> 3, ld_p = lane & 7;
-    const int voff0 = ((wave * RPI + ld_r) * K + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
-    const int voff1 = NW == 1 ? (ld_r * K + ((ld_p ^ ld_r ^ 1) << 3)) * 2 : voff0;
-    const int pass_bytes = NW * RPI * K * 2;
+    const int voff0 = ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
+    const int voff1 = NW == 1 ? (ld_r * ld + ((ld_p ^ ld_r ^ 1) << 3)) * 2 : voff0;
+    const int pass_bytes = NW * RPI * ld * 2;
     const int S = K / 64;
     const int a_row0 = wm * WM + l32, w_row0 = wn * WN + l32;
     const int sw = (l32 & 7) ^ ((l32 >> 3) & 1);
@@ -1128,7 +1128,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
 #undef RS_SLIM_ALL_FRAGS
 #undef RS_SLIM_ALL_MFMA
 #undef RS_SLIM_SLICE
-    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, slots, ldp, m_base, n_base, lane);
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, ldo, slots, ldp, m_base, n_base, lane);
 }
 
 // Tile configuration of the bf16 GEMM: BM, BN, BK, NSTAGE, waves along tokens, waves along features.
@@ -1180,14 +1180,15 @@ struct GemmArgs {
     GemmLnFold ln;
     int64_t M;
     int N, K;
+    int ld, ldo;  // elements between the rows of a and wt, and of out (res and ref: N)
     int64_t ldp;  // floats between the slots of the shift sums: the rows of the whole problem
     // the same problem restricted to rows [r0, r1)
     GemmArgs rows(int64_t r0, int64_t r1) const {
         GemmArgs g = *this;
-        g.a = a + r0 * K;
+        g.a = a + r0 * ld;
         g.res = res ? res + r0 * N : nullptr;
         g.ref = ref ? ref + r0 * N : nullptr;
-        g.out = out + r0 * N;
+        g.out = out + r0 * ldo;
         g.partials = partials ? partials + r0 : nullptr;
         g.ln.stats = ln.stats ? ln.stats + r0 * 2 : nullptr;
         g.M = r1 - r0;
@@ -1201,7 +1202,7 @@ static void launch_ring(const GemmArgs& g, hipStream_t s) {
     const int nblk = tiles_m * tiles_n;
     constexpr int WGN = BN / 64, WGM = 4 / WGN;  // four waves, each 64 features wide
     hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(256), 0, s,
-                       g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m,
+                       g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m,
                        tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM, GemmBatch{0, 0, 0});
 }
 
@@ -1211,7 +1212,7 @@ static void launch_slim(const GemmArgs& g, hipStream_t s) {
     const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (g.N + BN - 1) / BN;
     const int nblk = tiles_m * tiles_n;
     hipLaunchKernelGGL((gemm_bf16_slim_kernel<WGM, WGN, TM, NST, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(WGM * WGN * 64), 0, s,
-                       g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m,
+                       g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m,
                        tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
@@ -1249,11 +1250,11 @@ static void launch_persistent(const GemmArgs& g, hipStream_t s) {
     if (gemm_deep_stages(g.K))
         hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 3, C::WGM, C::WGN, EPI, DIST>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
-                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
+                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
     else
         hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 2, C::WGM, C::WGN, EPI, DIST>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
-                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
+                           g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
 // Choice by shape: the smallest tile of 64 x 64, 128 x 64, 128 x 128, 256 x 128 (slim kernels) and 256 x 256
@@ -1293,9 +1294,9 @@ static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
 template <int EPI, int DIST>
 static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, const void* res,
                               void* out, float* partials, const void* ref, bool post, GemmLnFold ln,
-                              int64_t M, int N, int K, hipStream_t s) {
+                              int64_t M, int N, int K, int ld, int ldo, hipStream_t s) {
     const GemmArgs g{(const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)bias, (const bf16raw*)res,
-                     (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K, M};
+                     (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K, ld, ldo, M};
     const int variant = gemm_variant();
     if (variant == 1) launch_persistent<EPI, DIST>(g, s);
     else if (variant == 2) launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
@@ -1324,14 +1325,14 @@ hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int cou
         const int tiles_m = (M + 255) / 256;
         hipLaunchKernelGGL((gemm_bf16_ring_kernel<256, 64, 4, 1, EPI_BIAS, 0>), dim3(8 * ((tiles_m + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
-                           (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, tiles_m, 1,
+                           (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, K, N, tiles_m, 1,
                            1, (int64_t)0, RS_GEMM_GM, gb);
     } else {
         const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
         const int nblk = tiles_m * tiles_n;
         hipLaunchKernelGGL((gemm_bf16_ring_kernel<128, 128, 2, 2, EPI_BIAS, 0>), dim3(8 * ((nblk + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
-                           (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, tiles_m,
+                           (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, K, N, tiles_m,
                            tiles_n, (N + 63) / 64, (int64_t)0, RS_GEMM_GM, gb);
     }
     return hipGetLastError();
@@ -1344,30 +1345,34 @@ int gemm_shift_slots(rs_dtype dt, int N) {
 
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials, const void* ref,
-                       bool post, int64_t M, int N, int K, hipStream_t s) {
+                       bool post, int64_t M, int N, int K, hipStream_t s, int ld, int ldo) {
     if (M == 0) return hipSuccess;
     if (dt == RS_F32) return launch_gemm_f32(epi, dist, a, w, bias, res, out, partials, ref, post, M, N, K, s);
     const GemmLnFold ln{};
+    ld = ld ? ld : K;
+    ldo = ldo ? ldo : N;
     switch (epi) {
-        case EPI_BIAS: return launch_bf16<EPI_BIAS, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
-        case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
-        case EPI_BIAS_RES: return launch_bf16<EPI_BIAS_RES, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+        case EPI_BIAS: return launch_bf16<EPI_BIAS, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
+        case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
+        case EPI_BIAS_RES: return launch_bf16<EPI_BIAS_RES, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
         case EPI_BIAS_RES_SHIFT:
-            if (dist == RS_DIST_L2) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L2>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
-            if (dist == RS_DIST_L1) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L1>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
-            return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_COS>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, s);
+            if (dist == RS_DIST_L2) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L2>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
+            if (dist == RS_DIST_L1) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L1>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
+            return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_COS>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
         default: break;  // the LayerNorm-folded epilogues go through launch_gemm_ln
     }
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded, GemmLnFold ln, void* out,
-                          int64_t M, int N, int K, hipStream_t s) {
+                          int64_t M, int N, int K, hipStream_t s, int ld, int ldo) {
     if (M == 0) return hipSuccess;
+    ld = ld ? ld : K;
+    ldo = ldo ? ldo : N;
     if (epi == EPI_LN_BIAS)
-        return launch_bf16<EPI_LN_BIAS, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, s);
+        return launch_bf16<EPI_LN_BIAS, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
     if (epi == EPI_LN_BIAS_GELU)
-        return launch_bf16<EPI_LN_BIAS_GELU, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, s);
+        return launch_bf16<EPI_LN_BIAS_GELU, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
     return hipErrorInvalidValue;
 }
 
@@ -1382,7 +1387,7 @@ __device__ __forceinline__ bf16raw fold_gamma(bf16raw w, const bf16raw* gamma, i
 
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16raw* __restrict__ w,
                                                              const bf16raw* __restrict__ gamma,
-                                                             bf16raw* __restrict__ wt, int K, int N) {
+                                                             bf16raw* __restrict__ wt, int K, int N, int ld) {
     __shared__ bf16raw tile[64][66];
     const int k0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -1393,14 +1398,14 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16raw* __re
     __syncthreads();
     for (int r = ty; r < 64; r += 4) {
         const int n = n0 + r, k = k0 + tx;
-        if (n < N && k < K) wt[(int64_t)n * K + k] = tile[tx][r];
+        if (n < N && k < K) wt[(int64_t)n * ld + k] = tile[tx][r];
     }
 }
 
-hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s) {
+hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld) {
     dim3 grid((N + 63) / 64, (K + 63) / 64);
     hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, (const bf16raw*)w, (const bf16raw*)gamma,
-                       (bf16raw*)wt, K, N);
+                       (bf16raw*)wt, K, N, ld ? ld : K);
     return hipGetLastError();
 }
 

@@ -108,7 +108,7 @@ struct BlockLayout {
 };
 
 // Packed bf16 weights: the four matrices as [out, in] (LayerNorm scales folded into W_qkv and
-// W_fc1), then the fp32 column vectors of the two folded LayerNorms.
+// W_fc1; W_fc2 with the row pitch of its activations, padded_ld), then the fp32 column vectors of the two folded LayerNorms.
 struct PackedLayout {
     size_t w_qkv, w_proj, w_fc1, w_fc2, cs_qkv, b_qkv, cs_fc1, b_fc1, total;
 };
@@ -121,7 +121,7 @@ static PackedLayout packed_layout(const rs_block_cfg* c) {
     P.w_qkv = take(3 * D * D * 2);
     P.w_proj = take(D * D * 2);
     P.w_fc1 = take(D * Dm * 2);
-    P.w_fc2 = take(D * Dm * 2);
+    P.w_fc2 = take(D * padded_ld(c->Dm) * 2);
     P.cs_qkv = take(3 * D * sizeof(float));
     P.b_qkv = take(3 * D * sizeof(float));
     P.cs_fc1 = take(Dm * sizeof(float));
@@ -146,7 +146,7 @@ static BlockLayout block_layout(const rs_block_cfg* c) {
     L.qkv = take(M * 3 * D * e);
     L.att = take(M * D * e);
     L.x1 = take(M * D * e);
-    L.hid = take(M * Dm * e);
+    L.hid = take(M * (c->dtype == RS_BF16 ? padded_ld(c->Dm) : Dm) * e);
     L.partials = take(M * (size_t)L.slots * kShiftLanes * sizeof(float));
     L.scores = take(M * sizeof(float));
     L.stats = take(M * 2 * sizeof(float));
@@ -501,7 +501,7 @@ static rs_status pack_into(const rs_block_cfg* c, const rs_block_weights* w, voi
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_qkv, w->ln1_g, p + P.w_qkv, D, 3 * D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_proj, nullptr, p + P.w_proj, D, D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc1, w->ln2_g, p + P.w_fc1, D, Dm, st));
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, st));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, st, padded_ld(Dm)));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_qkv, w->ln1_g, w->ln1_b, w->b_qkv, (float*)(p + P.cs_qkv),
                                               (float*)(p + P.b_qkv), D, 3 * D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_fc1, w->ln2_g, w->ln2_b, w->b_fc1, (float*)(p + P.cs_fc1),
@@ -644,6 +644,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     const rs_dtype dt = c.dtype;
     const int64_t M = (int64_t)c.B * c.N;
     const int D = c.D, Dm = c.Dm;
+    const int ld_hid = dt == RS_BF16 ? padded_ld(Dm) : Dm;
     void* u = ws + L.u;
     void* qkv = ws + L.qkv;
     void* att = ws + L.att;
@@ -704,7 +705,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
         RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, x1, (float*)(ws + L.stats), M, D, c.ln_eps, s,
                                              iota_folded ? kept_idx : nullptr, c.N));
         if (need_v) RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
-        RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm_ln(EPI_LN_BIAS_GELU, x1, w1, ln2, hid, M, Dm, D, s));
+        RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm_ln(EPI_LN_BIAS_GELU, x1, w1, ln2, hid, M, Dm, D, s, 0, ld_hid));
     } else {
         RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
         RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm(dt, EPI_BIAS_GELU, RS_DIST_L2, u, w1, w->b_fc1, nullptr, hid, nullptr, nullptr, false, M, Dm, D, s));
@@ -716,7 +717,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     const bool post = c.op == RS_SHIFT_BLOCK || c.op == RS_SHIFT_MLP_STREAM;
     const void* ref = c.op == RS_SHIFT_BLOCK ? x : c.op == RS_SHIFT_MLP_NORMED ? (const void*)u : nullptr;
     RS_LAUNCH_K(K_GEMM_FC2, s, launch_gemm(dt, fc2_scores ? EPI_BIAS_RES_SHIFT : EPI_BIAS_RES, c.dist, hid, w2, w->b_fc2, x1,
-                          xhat, partials, ref, post, M, D, Dm, s));
+                          xhat, partials, ref, post, M, D, Dm, s, ld_hid));
     // the survivors' rows, with the LayerNorm statistics the next block needs if the caller asks for them
     auto gather_out = [&]() -> rs_status {
         if (y_stats && gather_stats_fits(dt, D)) {
