@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.environ.get("RS_OBJ_DIR", os.path.join(HERE, "_build"))
 LIB = os.environ.get("RS_LIB_OUT", os.path.join(HERE, "librs_hip.so"))   # override: experiments only
-SOURCES = ["rs_api.hip", "layernorm.hip", "gemm.hip", "gemm_f32.hip", "attention.hip", "prune.hip"]
+SOURCES = ["rs_api.hip", "layernorm.hip", "gemm.hip", "gemm_f32.hip", "mlp.hip", "attention.hip", "prune.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-Wall", "-Wno-unused-function",

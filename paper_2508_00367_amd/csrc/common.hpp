@@ -185,6 +185,25 @@ hipError_t launch_gemm_f32(GemmEpilogue epi, rs_dist dist, const void* a, const 
 hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded, GemmLnFold ln, void* out,
                           int64_t M, int N, int K, hipStream_t s, int ld = 0, int ldo = 0);
 
+// The MLP half of a bf16 block in one launch (mlp_fused_fits): out = x + fc2(gelu(fc1(LN(x)))), the LayerNorm folded
+// into w1 as for EPI_LN_BIAS_GELU with the statistics of x formed inside; partials as for
+// EPI_BIAS_RES_SHIFT (`shift`); out_stats (optional): the statistics of the rows of `out`; iota_out as in
+// launch_rowstats.
+struct MlpArgs {
+    const void *x, *w1, *w2, *b2, *ref;
+    GemmLnFold ln;  // colsum and bias of fc1
+    void* out;
+    float *partials, *out_stats;
+    int32_t* iota_out;
+    int iota_n;
+    bool post;
+    float eps;
+    int64_t M;
+    int Dm, ld2;  // ld2: elements between the rows of the packed W_fc2
+};
+bool mlp_fused_fits(rs_dtype dt, int64_t M, int D, int Dm);
+hipError_t launch_mlp_fused(const MlpArgs& g, rs_dist dist, bool shift, hipStream_t s);
+
 // `count` independent bf16 products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T, problem p at element offset
 // p * stride from each base pointer (K % 32 == 0, N % 64 == 0; rows of wt_p past N must exist as zeros)
 hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int count, int64_t stride_a,

@@ -701,23 +701,30 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     const bool need_v = want_scores && c.op == RS_SHIFT_MLP_NORMED;  // LN(x1) itself is an operand of the score
     // a block that keeps every token has kept_idx[b, j] = j: written by the statistics pass on its way
     const bool iota_folded = dt == RS_BF16 && !prune && K > 0;
-    if (dt == RS_BF16) {
-        RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, x1, (float*)(ws + L.stats), M, D, c.ln_eps, s,
-                                             iota_folded ? kept_idx : nullptr, c.N));
-        if (need_v) RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
-        RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm_ln(EPI_LN_BIAS_GELU, x1, w1, ln2, hid, M, Dm, D, s, 0, ld_hid));
-    } else {
-        RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
-        RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm(dt, EPI_BIAS_GELU, RS_DIST_L2, u, w1, w->b_fc1, nullptr, hid, nullptr, nullptr, false, M, Dm, D, s));
-    }
     void* xhat = prune ? att : y;  // without pruning the block output goes straight to y
     // every other choice of (f_out, f_in) comes out of fc2's epilogue: f_out is the MLP output or
     // (post) xhat, f_in the residual operand x1 or another tensor still in memory (x, LN(x1))
     const bool fc2_scores = want_scores && !attn_scores;
     const bool post = c.op == RS_SHIFT_BLOCK || c.op == RS_SHIFT_MLP_STREAM;
     const void* ref = c.op == RS_SHIFT_BLOCK ? x : c.op == RS_SHIFT_MLP_NORMED ? (const void*)u : nullptr;
-    RS_LAUNCH_K(K_GEMM_FC2, s, launch_gemm(dt, fc2_scores ? EPI_BIAS_RES_SHIFT : EPI_BIAS_RES, c.dist, hid, w2, w->b_fc2, x1,
-                          xhat, partials, ref, post, M, D, Dm, s, ld_hid));
+    const bool fused = mlp_fused_fits(dt, M, D, Dm);
+    const bool y_stats_done = fused && !prune && y_stats;
+    if (dt == RS_F32 || need_v) RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
+    if (fused) {
+        MlpArgs g{x1, w1, w2, w->b_fc2, ref, ln2, xhat, partials, y_stats_done ? y_stats : nullptr,
+                  iota_folded ? kept_idx : nullptr, c.N, post, c.ln_eps, M, Dm, ld_hid};
+        RS_LAUNCH_K(K_GEMM_FC2, s, launch_mlp_fused(g, c.dist, fc2_scores, s));
+    } else {
+        if (dt == RS_BF16) {
+            RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, x1, (float*)(ws + L.stats), M, D, c.ln_eps, s,
+                                                 iota_folded ? kept_idx : nullptr, c.N));
+            RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm_ln(EPI_LN_BIAS_GELU, x1, w1, ln2, hid, M, Dm, D, s, 0, ld_hid));
+        } else {
+            RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm(dt, EPI_BIAS_GELU, RS_DIST_L2, u, w1, w->b_fc1, nullptr, hid, nullptr, nullptr, false, M, Dm, D, s));
+        }
+        RS_LAUNCH_K(K_GEMM_FC2, s, launch_gemm(dt, fc2_scores ? EPI_BIAS_RES_SHIFT : EPI_BIAS_RES, c.dist, hid, w2, w->b_fc2, x1,
+                              xhat, partials, ref, post, M, D, Dm, s, ld_hid));
+    }
     // the survivors' rows, with the LayerNorm statistics the next block needs if the caller asks for them
     auto gather_out = [&]() -> rs_status {
         if (y_stats && gather_stats_fits(dt, D)) {
@@ -745,6 +752,6 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     // keep the n_keep highest-shift tokens (plus the prefix) and compact them
     if (!iota_folded) RS_LAUNCH_K(K_SELECT, s, launch_select(sc, kept_idx, c.B, c.N, c.n_prefix, c.n_keep, s));
     if (prune) return gather_out();
-    if (y_stats) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, y, y_stats, M, D, c.ln_eps, s));
+    if (y_stats && !y_stats_done) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, y, y_stats, M, D, c.ln_eps, s));
     return RS_OK;
 }
