@@ -405,11 +405,12 @@ __global__ __launch_bounds__(512, 2) void attention_bf16_tail_kernel(
 // LDS: K and V rows of 128 bytes in the tiled kernel's two slot orders (att_swz, att_vswz).
 // ---------------------------------------------------------------------------
 constexpr int SM_MAXN = 256;
+constexpr int SM_SPLIT_WGS = 256;  // one per CU
 
 __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
     const bf16raw* __restrict__ q, const bf16raw* __restrict__ k, const bf16raw* __restrict__ v,
     bf16raw* __restrict__ o, int N, int64_t sb, int64_t sn, int64_t sh, int64_t osb, int64_t osn,
-    int64_t osh, float scale_log2e) {
+    int64_t osh, float scale_log2e, int q_waves) {
     // one array per half and operand: the compiler then knows which copies a half's LDS reads wait for
     __shared__ __attribute__((aligned(1024))) unsigned char s_ka[2 * ATT_BN * 128], s_kb[2 * ATT_BN * 128];
     __shared__ __attribute__((aligned(1024))) unsigned char s_va[2 * ATT_BN * 128], s_vb[2 * ATT_BN * 128];
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
     const int KT = (N + ATT_BN - 1) / ATT_BN;   // key tiles of 64
     const int KF = N / ATT_BN;                  // tiles without padding keys: no masking work in them
 
-    const int q0 = wave * 32;
+    const int q0 = wave < q_waves ? (blockIdx.z * q_waves + wave) * 32 : N;  // N: copies only
     // Q fragments (B operand): column = query row q0 + l32, k-slots = channels 16 kk + 8 g ..
     bf16x8 qf[4];
     {
@@ -671,9 +672,14 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
     if (B == 0 || H == 0 || N == 0) return hipSuccess;
     const float scale_log2e = scale * 1.44269504088896340736f;
     if (dt == RS_BF16 && N <= SM_MAXN) {
-        hipLaunchKernelGGL(attention_bf16_small_kernel, dim3(H, B), dim3(512), 0, s, (const bf16raw*)q,
+        // While every workgroup has a CU to itself a head's query rows go to two workgroups of four busy waves, one
+        // per SIMD (each copies the whole K and V): 1 image x 6 heads x 197 tokens 8.3 -> 7.0 us, 10 x 12 x 197 8.7
+        // -> 7.6; with two on some CUs it costs more than it gives (16 x 12 x 197 9.2 / 9.5, 21 x 12 x 256 11.2 /
+        // 13.3).  A row's arithmetic is the same either way.
+        const int q_waves = N > 128 && (int64_t)B * H * 2 <= SM_SPLIT_WGS ? 4 : 8;
+        hipLaunchKernelGGL(attention_bf16_small_kernel, dim3(H, B, q_waves == 4 ? 2 : 1), dim3(512), 0, s, (const bf16raw*)q,
                            (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh,
-                           scale_log2e);
+                           scale_log2e, q_waves);
     } else if (dt == RS_BF16) {
         // Whether the rows beyond the last full query tile of 256 go to the tail kernel: a CU holds
         // two workgroups, so a round is 512 of them; the tail kernel costs about a fifth of a round.
