@@ -117,9 +117,9 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline size_t elem_size(rs_dtype t) { return t == RS_F32 ? 4 : 2; }
 
 // ---- kernel launchers (one per .hip file) -----------------------------------
-// LayerNorm over the last axis of x[M, D]; gamma/beta may be null.
-hipError_t launch_layernorm(rs_dtype dt, const void* x, const void* gamma, const void* beta,
-                            void* out, int64_t M, int D, float eps, hipStream_t s);
+// LayerNorm over the last axis of x[M, D]; gamma/beta may be null; iota_out as in launch_rowstats.
+hipError_t launch_layernorm(rs_dtype dt, const void* x, const void* gamma, const void* beta, void* out, int64_t M, int D,
+                            float eps, hipStream_t s, int32_t* iota_out = nullptr, int iota_n = 1);
 
 // stats[M] = (mean, 1 / sqrt(population variance + eps)) of each row of x[M, D], as float pairs.
 // iota_out (optional): int32 [M], receives row % iota_n (the kept_idx of a block that keeps every token).

@@ -699,8 +699,8 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
                             partials, nullptr, false, M, D, D, s));
     // xhat = MLP(LN(x1)) + x1, with the shift partial sums of D(MLP(LN(x1)), x1)   Eq. (6), Eq. (4)
     const bool need_v = want_scores && c.op == RS_SHIFT_MLP_NORMED;  // LN(x1) itself is an operand of the score
-    // a block that keeps every token has kept_idx[b, j] = j: written by the statistics pass on its way
-    const bool iota_folded = dt == RS_BF16 && !prune && K > 0;
+    // a block that keeps every token has kept_idx[b, j] = j: written on its way by the pass over x1 in front of fc1
+    const bool iota_folded = !prune && K > 0;
     void* xhat = prune ? att : y;  // without pruning the block output goes straight to y
     // every other choice of (f_out, f_in) comes out of fc2's epilogue: f_out is the MLP output or
     // (post) xhat, f_in the residual operand x1 or another tensor still in memory (x, LN(x1))
@@ -709,7 +709,9 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     const void* ref = c.op == RS_SHIFT_BLOCK ? x : c.op == RS_SHIFT_MLP_NORMED ? (const void*)u : nullptr;
     const bool fused = mlp_fused_fits(dt, M, D, Dm);
     const bool y_stats_done = fused && !prune && y_stats;
-    if (dt == RS_F32 || need_v) RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s));
+    if (dt == RS_F32 || need_v)
+        RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x1, w->ln2_g, w->ln2_b, u, M, D, c.ln_eps, s,
+                                              dt == RS_F32 && iota_folded ? kept_idx : nullptr, c.N));
     if (fused) {
         MlpArgs g{x1, w1, w2, w->b_fc2, ref, ln2, xhat, partials, y_stats_done ? y_stats : nullptr,
                   iota_folded ? kept_idx : nullptr, c.N, post, c.ln_eps, M, Dm, ld_hid};
