@@ -7,19 +7,18 @@
 // half-wave and k' from the high one; which two k these are is free as long as both operands agree, so
 // a lane reads four consecutive k of its token row at once (k = 8 h + 4 g + e feeds step (h, e)).
 //
-// Workgroup tile (32 TM) x 64, four waves that share the tile and split K: of every 64 values of k
+// Workgroup tile 32 x 64, four waves that share the tile and split K: of every 64 values of k
 // wave w takes 16 w .. 16 w + 15, and the four partial tiles are added through LDS in wave order,
-// ((p0 + p1) + (p2 + p3)) per element: one order for every tile height, so results do not depend on
+// ((p0 + p1) + (p2 + p3)) per element: one order in both kernels, so results do not depend on
 // the grid.  No data is shared between waves inside the loop: every wave streams its own operand
 // slices global -> LDS (direct copies) in a ring of its own and waits for nobody, there is no barrier
 // before the final sum.  The K split is what fills the chip at the sizes this path is used at: four
 // images of 197 tokens make 39 64 x 64 tiles (fc2) on 256 CUs.
-// Bound by the matrix cores (119 of 137 TFLOP/s the library reaches at 12608 x 3072 x 768; 76 at
-// 12608 x 768 x 192, where a tile is half prologue and final sum); the plain FMA tiles this replaced ran
+// Bound by the matrix cores (120 of 137 TFLOP/s the library reaches at 12608 x 3072 x 768; 90 at
+// 12608 x 768 x 192, where a tile is three slices long); the plain FMA tiles this replaced ran
 // at 60 and took 71 us for the fc2 of a 4 x 197 x 192 block (9.5 us now).
-//   TM = 2 (64 x 64): 64 KB of LDS ring, two workgroups per CU, 32 matrix instructions (2048 cycles)
-//          per 8 KB slice and wave: bound by the matrix cores.
-//   TM = 1 (32 x 64): twice the workgroups, three stages: for grids that leave CUs idle.
+// Two kernels: 32 x 64 tiles with K split over the waves (three stages, 48 KB of LDS in all) for grids that
+// leave CUs idle, and 64 x 64 tiles shared by the waves (gemm_f32_wide_kernel) for those that fill the chip.
 #include "common.hpp"
 
 namespace rs {
@@ -34,14 +33,92 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_f(const void* base, int64
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
-template <int TM, int EPI, int DIST>
+// Row-major epilogue of a BM x 64 tile, 16 lanes per row, 4 features per lane: load() requests what it needs from
+// memory, run() takes the sums (sum(row, group of 4 features)) once they are in LDS.
+template <int BM, int EPI, int DIST>
+struct F32Epilogue {
+    static constexpr bool RES = EPI == EPI_BIAS_RES || EPI == EPI_BIAS_RES_SHIFT;
+    int tx, ty, n;
+    float bv[4];
+    float4 res4[BM / 16];
+    __device__ __forceinline__ void load(const float* __restrict__ bias, const float* __restrict__ res, int m0, int n0, int M, int N) {
+        tx = threadIdx.x & 15;
+        ty = threadIdx.x >> 4;
+        n = n0 + tx * 4;
+        bv[0] = bv[1] = bv[2] = bv[3] = 0.f;
+        if (bias) {
+            const float4 b4 = *reinterpret_cast<const float4*>(bias + n);
+            bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
+        }
+        if (RES) {
+#pragma unroll
+            for (int p = 0; p < BM / 16; ++p) {
+                const int m = m0 + p * 16 + ty;
+                res4[p] = m < M ? *reinterpret_cast<const float4*>(res + (int64_t)m * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+    }
+    template <typename Sum>
+    __device__ __forceinline__ void run(const Sum& sum, float* __restrict__ out, float* __restrict__ partials,
+                                        const float* __restrict__ ref, int post, int m0, int tn, int slots, int M, int N) {
+#pragma unroll
+        for (int p = 0; p < BM / 16; ++p) {
+            const int r = p * 16 + ty, m = m0 + r;
+            const bool m_ok = m < M;
+            const f32x4 s4 = sum(r, tx);
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = s4[e] + bv[e];
+            if (EPI == EPI_BIAS_GELU) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+            }
+            float p0 = 0.f, p1 = 0.f, p2 = 0.f;
+            if (RES) {
+                const float rr[4] = {res4[p].x, res4[p].y, res4[p].z, res4[p].w};
+                if (EPI == EPI_BIAS_RES_SHIFT && m_ok) {
+                    float fi[4] = {rr[0], rr[1], rr[2], rr[3]};
+                    if (ref) {
+                        const float4 q = *reinterpret_cast<const float4*>(ref + (int64_t)m * N + n);
+                        fi[0] = q.x; fi[1] = q.y; fi[2] = q.z; fi[3] = q.w;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float fo = post ? v[e] + rr[e] : v[e];
+                        if (DIST == RS_DIST_L2) { const float d = fo - fi[e]; p0 += d * d; }
+                        else if (DIST == RS_DIST_L1) { p0 += fabsf(fo - fi[e]); }
+                        else { p0 += fo * fi[e]; p1 += fo * fo; p2 += fi[e] * fi[e]; }
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += rr[e];
+            }
+            if (m_ok) *reinterpret_cast<float4*>(out + (int64_t)m * N + n) = make_float4(v[0], v[1], v[2], v[3]);
+            if (EPI == EPI_BIAS_RES_SHIFT) {
+                // the 16 lanes of a row in a fixed butterfly order; one slot per 64 features
+#pragma unroll
+                for (int off = 8; off >= 1; off >>= 1) {
+                    p0 += __shfl_xor(p0, off, 64);
+                    if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
+                }
+                if (tx == 0 && m_ok) {
+                    float* dst = partials + (int64_t)tn * M + m;
+                    dst[0] = p0;
+                    if (DIST == RS_DIST_COS) { dst[(int64_t)slots * M] = p1; dst[(int64_t)2 * slots * M] = p2; }
+                }
+            }
+        }
+    }
+};
+
+template <int EPI, int DIST>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ bias,
     const float* __restrict__ res, float* __restrict__ out, float* __restrict__ partials,
     const float* __restrict__ ref, int post, int M, int N, int K, int tiles_m,
     int tiles_n) {
-    constexpr int BM = 32 * TM, BN = 64;
-    constexpr int NST = TM == 2 ? 2 : 3;              // ring stages
+    constexpr int BM = 32, BN = 64;
+    constexpr int NST = 3;                            // ring stages
     constexpr int A_BYTES = BM * 64, W_BYTES = 16 * BN * 4, SLICE = A_BYTES + W_BYTES;  // per wave
     constexpr int L = SLICE / 1024;                   // copies per slice
     constexpr int PITCH = BN * 4 + 16;                // staged fp32 row of the final sum
@@ -51,7 +128,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     // partial tiles of waves 0, 1 and 2, 3 go through the first two at the end
     __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE > HALF_RED ? STAGE : HALF_RED];
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE > HALF_RED ? STAGE : HALF_RED];
-    __shared__ __attribute__((aligned(1024))) unsigned char st2[NST == 3 ? STAGE : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -77,13 +154,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     const int w_voff = (lane >> 4) * N * 4 + ((lane & 15) << 4);
     const int w_flip = 128 * (lane & 8 ? -1 : 1);  // byte distance to the chunk of the other half
 
-    f32x16 acc[2][TM];
+    f32x16 acc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
 
     const int S = K >> 6;
 // copies of this wave's share of slice t_; past the last slice the resource is empty (zeros arrive)
@@ -103,9 +178,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     {                                                                                                         \
         const unsigned char* p_ = (st_) + wave * SLICE;                                                       \
         _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                       \
-            f32x4 af[TM];                                                                                     \
-            _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
-                af[j] = *reinterpret_cast<const f32x4*>(p_ + (j * 32 + l32) * 64 + (((2 * h + g) ^ ((l32 >> 2) & 3)) << 4)); \
+            const f32x4 af =                                                                                  \
+                *reinterpret_cast<const f32x4*>(p_ + l32 * 64 + (((2 * h + g) ^ ((l32 >> 2) & 3)) << 4));     \
             float wf[4][2];                                                                                   \
             _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                     \
                 _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                 \
@@ -113,8 +187,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
                                                                (((i * 32 + l32) * 4) ^ (g << 7)));            \
             _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                     \
                 _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                 \
-                    _Pragma("unroll") for (int j = 0; j < TM; ++j)                                            \
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[e][i], af[j][e], acc[i][j], 0, 0, 0); \
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[e][i], af[e], acc[i], 0, 0, 0);          \
         }                                                                                                     \
     }
 // slice t_ from cur_ while the copies of slice t_ + NST - 1 go into free_ (read NST slices ago: those reads
@@ -128,21 +201,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     }
 
     RS_F32_DMA(st0, 0)
-    if constexpr (NST == 3) {
-        RS_F32_DMA(st1, 1)
-        for (int t = 0; t < S; t += 3) {
-            RS_F32_STEP(st0, st2, t)
-            if (t + 1 >= S) break;
-            RS_F32_STEP(st1, st0, t + 1)
-            if (t + 2 >= S) break;
-            RS_F32_STEP(st2, st1, t + 2)
-        }
-    } else {
-        for (int t = 0; t < S; t += 2) {
-            RS_F32_STEP(st0, st1, t)
-            if (t + 1 >= S) break;
-            RS_F32_STEP(st1, st0, t + 1)
-        }
+    RS_F32_DMA(st1, 1)
+    for (int t = 0; t < S; t += 3) {
+        RS_F32_STEP(st0, st2, t)
+        if (t + 1 >= S) break;
+        RS_F32_STEP(st1, st0, t + 1)
+        if (t + 2 >= S) break;
+        RS_F32_STEP(st2, st1, t + 2)
     }
 #undef RS_F32_DMA
 #undef RS_F32_COMPUTE
@@ -153,102 +218,141 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
     __syncthreads();
     unsigned char* red = (wave < 2 ? st0 : st1) + (wave & 1) * BM * PITCH;
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                *reinterpret_cast<f32x4*>(red + (j * 32 + l32) * PITCH + (i * 32 + q * 8 + g * 4) * 4) = v;
-            }
-    const int tx = tid & 15, ty = tid >> 4;
-    const int n = n0 + tx * 4;
-    float bv[4] = {0.f, 0.f, 0.f, 0.f};
-    if (bias) {
-        const float4 b4 = *reinterpret_cast<const float4*>(bias + n);
-        bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
-    }
-    constexpr bool RES = EPI == EPI_BIAS_RES || EPI == EPI_BIAS_RES_SHIFT;
-    float4 res4[BM / 16];
-    if (RES) {
-#pragma unroll
-        for (int p = 0; p < BM / 16; ++p) {
-            const int m = m0 + p * 16 + ty;
-            res4[p] = m < M ? *reinterpret_cast<const float4*>(res + (int64_t)m * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 v = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+            *reinterpret_cast<f32x4*>(red + l32 * PITCH + (i * 32 + q * 8 + g * 4) * 4) = v;
         }
-    }
+    F32Epilogue<BM, EPI, DIST> epi;
+    epi.load(bias, res, m0, n0, M, N);
     __syncthreads();
+    epi.run([&](int r, int c4) {
+        f32x4 s4[4], v;
 #pragma unroll
-    for (int p = 0; p < BM / 16; ++p) {
-        const int r = p * 16 + ty, m = m0 + r;
-        const bool m_ok = m < M;
-        f32x4 s4[4];
+        for (int u = 0; u < 4; ++u) s4[u] = *reinterpret_cast<const f32x4*>((u < 2 ? st0 : st1) + ((u & 1) * BM + r) * PITCH + c4 * 16);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s4[u] = *reinterpret_cast<const f32x4*>((u < 2 ? st0 : st1) + ((u & 1) * BM + r) * PITCH + tx * 16);
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = ((s4[0][e] + s4[1][e]) + (s4[2][e] + s4[3][e])) + bv[e];
-        if (EPI == EPI_BIAS_GELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
-        }
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f;
-        if (RES) {
-            const float rr[4] = {res4[p].x, res4[p].y, res4[p].z, res4[p].w};
-            if (EPI == EPI_BIAS_RES_SHIFT && m_ok) {
-                float fi[4] = {rr[0], rr[1], rr[2], rr[3]};
-                if (ref) {
-                    const float4 q = *reinterpret_cast<const float4*>(ref + (int64_t)m * N + n);
-                    fi[0] = q.x; fi[1] = q.y; fi[2] = q.z; fi[3] = q.w;
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float fo = post ? v[e] + rr[e] : v[e];
-                    if (DIST == RS_DIST_L2) { const float d = fo - fi[e]; p0 += d * d; }
-                    else if (DIST == RS_DIST_L1) { p0 += fabsf(fo - fi[e]); }
-                    else { p0 += fo * fi[e]; p1 += fo * fo; p2 += fi[e] * fi[e]; }
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] += rr[e];
-        }
-        if (m_ok) *reinterpret_cast<float4*>(out + (int64_t)m * N + n) = make_float4(v[0], v[1], v[2], v[3]);
-        if (EPI == EPI_BIAS_RES_SHIFT) {
-            // the 16 lanes of a row in a fixed butterfly order; one slot per 64 features
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-                p0 += __shfl_xor(p0, off, 64);
-                if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
-            }
-            if (tx == 0 && m_ok) {
-                float* dst = partials + (int64_t)tn * M + m;
-                dst[0] = p0;
-                if (DIST == RS_DIST_COS) { dst[(int64_t)slots * M] = p1; dst[(int64_t)2 * slots * M] = p2; }
-            }
-        }
-    }
+        for (int e = 0; e < 4; ++e) v[e] = (s4[0][e] + s4[1][e]) + (s4[2][e] + s4[3][e]);
+        return v;
+    }, out, partials, ref, post, m0, tn, slots, M, N);
 }
 
-// Same results either way: 64-row tiles once they make two rounds of two workgroups per CU, 32-row
-// tiles below.  Measured, 64 against 32 rows: 788 x 192 x 768 (39 tiles of 64 rows) 16.0 / 9.5 us, 3000 x 768
-// x 768 (564) 42.7 / 37.6, 12608 x 192 x 768 (591) 44.0 / 39.1; 6528 x 768 x 192 (1224) 26.1 / 28.0, 12608 x
-// 3072 x 768 (9456) 499 / 558.
+// The same products and sums for grids that fill the chip: 64 x 64 tile, a wave owns a quarter of it (32 rows x 32
+// features) over the whole of K and keeps the four partial sums of an element in four accumulators, so that the
+// final sum is three additions in registers and not 64 KB written to LDS and read back.  The waves share the
+// slices (one barrier each); two workgroups per CU.
+template <int EPI, int DIST>
+__global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
+    const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ bias,
+    const float* __restrict__ res, float* __restrict__ out, float* __restrict__ partials,
+    const float* __restrict__ ref, int post, int M, int N, int K, int tiles_m, int tiles_n) {
+    constexpr int BM = 64, BN = 64, A_BYTES = BM * 64, W_BYTES = 16 * BN * 4, SLICE = A_BYTES + W_BYTES, PITCH = BN * 4 + 16;
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[4 * SLICE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[4 * SLICE];
+    static_assert(BM * PITCH <= 4 * SLICE, "the sums go through one stage");
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int rq = (wave & 1) * 32, fq = (wave >> 1) * 32;  // this wave's quarter
+    const int nblk = tiles_m * tiles_n;
+    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+    const int xq = nblk >> 3, xr = nblk & 7;
+    if (seq >= xq + (xcd < xr ? 1 : 0)) return;  // whole workgroup, before any barrier
+    const int bid = xcd * xq + (xcd < xr ? xcd : xr) + seq;
+    const int tn = bid % tiles_n, slots = tiles_n;
+    const int m0 = bid / tiles_n * BM, n0 = tn * BN;
+
+    // LDS layout and copies as above: region u of a stage holds the 16 k of partial sum u, copied by wave u
+    const __amdgpu_buffer_rsrc_t rs_a = rsrc_f(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 4);
+    const int a_voff = (lane >> 2) * K * 4 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+    const int w_voff = (lane >> 4) * N * 4 + ((lane & 15) << 4);
+    const int w_flip = 128 * (lane & 8 ? -1 : 1);
+    f32x16 acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
+
+    const int S = K >> 6;
+#define RS_F32W_DMA(st_, t_)                                                                                  \
+    if ((t_) < S) {                                                                                           \
+        unsigned char* p_ = (st_) + wave * SLICE;                                                             \
+        const int k_ = (t_) * 64 + wave * 16;                                                                 \
+        _Pragma("unroll") for (int i = 0; i < A_BYTES / 1024; ++i)                                            \
+            dma16_f(rs_a, p_ + i * 1024, a_voff, i * 16 * K * 4 + k_ * 4);                                    \
+        const __amdgpu_buffer_rsrc_t rs_w = rsrc_f(w + (int64_t)k_ * N + n0, (15 * (int64_t)N + BN) * 4);     \
+        _Pragma("unroll") for (int i = 0; i < W_BYTES / 1024; ++i)                                            \
+            dma16_f(rs_w, p_ + A_BYTES + i * 1024, w_voff + (i & 1 ? w_flip : 0), i * 4 * N * 4);             \
+    }
+// slice t_ from cur_; its barrier also says that every wave is done with the slice before, whose stage the next
+// copies fill
+#define RS_F32W_STEP(cur_, other_, t_)                                                                        \
+    {                                                                                                         \
+        __builtin_amdgcn_s_waitcnt(0x0070); /* own copies of this slice, own reads of the one before */       \
+        __builtin_amdgcn_s_barrier();                                                                         \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                                                \
+        RS_F32W_DMA(other_, (t_) + 1)                                                                         \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                       \
+            f32x4 af[4];                                                                                      \
+            float wf[4][4];                                                                                   \
+            _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                                   \
+                const unsigned char* p_ = (cur_) + u * SLICE;                                                 \
+                af[u] = *reinterpret_cast<const f32x4*>(p_ + (rq + l32) * 64 + (((2 * h + g) ^ ((l32 >> 2) & 3)) << 4)); \
+                _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                 \
+                    wf[u][e] = *reinterpret_cast<const float*>(p_ + A_BYTES + (8 * h + 4 * g + e) * 256 +     \
+                                                               (((fq + l32) * 4) ^ (g << 7)));                \
+            }                                                                                                 \
+            _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                     \
+                _Pragma("unroll") for (int u = 0; u < 4; ++u)                                                 \
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], af[u][e], acc[u], 0, 0, 0);       \
+        }                                                                                                     \
+    }
+    RS_F32W_DMA(st0, 0)
+    for (int t = 0; t < S; t += 2) {
+        RS_F32W_STEP(st0, st1, t)
+        if (t + 1 >= S) break;
+        RS_F32W_STEP(st1, st0, t + 1)
+    }
+#undef RS_F32W_DMA
+#undef RS_F32W_STEP
+
+    F32Epilogue<BM, EPI, DIST> epi;
+    epi.load(bias, res, m0, n0, M, N);
+    // through the stage that the last slice does not lie in: no wave reads it any more and no copy is in flight
+    unsigned char* red = (S & 1) ? st1 : st0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (acc[0][4 * q + e] + acc[1][4 * q + e]) + (acc[2][4 * q + e] + acc[3][4 * q + e]);
+        *reinterpret_cast<f32x4*>(red + (rq + l32) * PITCH + (fq + q * 8 + g * 4) * 4) = v;
+    }
+    __syncthreads();
+    epi.run([&](int r, int c4) { return *reinterpret_cast<const f32x4*>(red + r * PITCH + c4 * 16); }, out, partials, ref, post,
+            m0, tn, slots, M, N);
+}
+
+// Same results either way: the shared 64-row tiles once they fill the chip twice over with two workgroups per CU,
+// and already from one round on where K is short (the final sum through LDS is a large part of a tile then); 32-row
+// tiles with K split over the waves below.  Measured, shared / split (us): 788 x 192 x 768 (39 tiles of 64 rows) 16.8 /
+// 9.7, 3000 x 768 x 768 (564) 44.3 / 40.7, 12608 x 192 x 768 (591) 42.6 / 38.5; 12608 x 192 x 192 (591) 15.1 / 15.8,
+// 6528 x 576 x 192 (918) 18.4 / 21.9; beyond, against 64-row tiles with K split: 12608 x 768 x 192 (2364) 41.2 / 45.8,
+// 12608 x 576 x 192 (1773) 33.0 / 34.0, 12608 x 768 x 768 131 / 132, with GELU at K = 768 532 / 526.
 template <int EPI, int DIST>
 static hipError_t launch_t(const void* a, const void* w, const void* bias, const void* res, void* out, float* partials,
                            const void* ref, bool post, int64_t M, int N, int K, hipStream_t s) {
     const int tiles_n = N / 64;
-    const int64_t tiles64 = ((M + 63) / 64) * tiles_n;
-#define RS_F32_LAUNCH(TM_)                                                                                             \
-    {                                                                                                                  \
-        const int64_t tiles_m = (M + 32 * TM_ - 1) / (32 * TM_), nblk = tiles_m * tiles_n;                             \
-        if (nblk >= (int64_t)1 << 31) return hipErrorInvalidValue;                                                     \
-        hipLaunchKernelGGL((gemm_f32_kernel<TM_, EPI, DIST>), dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), 0, s, \
-                           (const float*)a, (const float*)w, (const float*)bias, (const float*)res, (float*)out,       \
-                           partials, (const float*)ref, post ? 1 : 0, (int)M, N, K, (int)tiles_m, tiles_n);            \
-    }
-    if (tiles64 >= 1024) RS_F32_LAUNCH(2)
-    else RS_F32_LAUNCH(1)
-#undef RS_F32_LAUNCH
+    const bool wide = ((M + 63) / 64) * tiles_n >= (K <= 384 ? 512 : 1024);
+    const int64_t tiles_m = wide ? (M + 63) / 64 : (M + 31) / 32, nblk = tiles_m * tiles_n;
+    if (nblk >= (int64_t)1 << 31) return hipErrorInvalidValue;
+    auto go = [&](auto* kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), 0, s, (const float*)a, (const float*)w,
+                           (const float*)bias, (const float*)res, (float*)out, partials, (const float*)ref, post ? 1 : 0, (int)M,
+                           N, K, (int)tiles_m, tiles_n);
+    };
+    if (wide) go(&gemm_f32_wide_kernel<EPI, DIST>);
+    else go(&gemm_f32_kernel<EPI, DIST>);
     return hipGetLastError();
 }
 
