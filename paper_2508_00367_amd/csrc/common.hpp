@@ -239,11 +239,15 @@ hipError_t launch_shift_scores(rs_dtype dt, rs_dist dist, const void* f_out, con
 hipError_t launch_finalize_scores(rs_dist dist, const float* partials, int slots, float* scores,
                                   int64_t M, hipStream_t s);
 // Scores, selection and gather of short images (select_gather_fits) in one launch; stats as in
-// launch_gather_stats, or null.
+// launch_gather_stats, or null; partials null: from the scores.
 bool select_gather_fits(rs_dtype dt, int N, int D);
 hipError_t launch_select_gather(rs_dtype dt, rs_dist dist, const float* partials, int slots, float* scores,
                                 int32_t* kept_idx, const void* src, void* out, float* stats, int B, int N, int n_prefix,
                                 int n_keep, int D, float eps, hipStream_t s);
+// The same for a few longer sequences, from their scores (select_gather_long_fits; 0 < n_keep < N - n_prefix).
+bool select_gather_long_fits(rs_dtype dt, int B, int N, int D);
+hipError_t launch_select_gather_long(rs_dtype dt, const float* scores, int32_t* kept_idx, const void* src, void* out,
+                                     float* stats, int B, int N, int n_prefix, int n_keep, int D, float eps, hipStream_t s);
 // per image: the n_keep highest scores among tokens >= n_prefix, ascending kept_idx[B, K]
 // the two steps above in one launch (a real selection only: n_keep < N - n_prefix, n_keep > 0;
 // N must pass select_from_partials_fits)

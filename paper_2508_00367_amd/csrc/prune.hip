@@ -827,52 +827,20 @@ hipError_t launch_gather_stats(const void* src, const int32_t* kept_idx, void* o
     return hipGetLastError();
 }
 
-// Scores, selection and gather of one short image (N <= 256) in one launch: `parts` workgroups per image,
-// each of which forms the image's scores from the partial sums and selects (a microsecond; the sums
-// are a few KB per image) and then copies its share of the surviving rows, STATS: with their LayerNorm
-// statistics as in gather_rows_stats_kernel.  Against a selection and a gather of their own it saves
-// a launch of every pruning block (vit_s16, eleven of them: 1020 -> 944 us per forward together with the
-// selection by one wave); one workgroup per image would leave the chip idle and copy with too few
-// requests in flight.  MAXC: 16-byte vectors per lane and row.
-constexpr int SG_WAVES = 8;
-template <bool STATS, int MAXC>
-__global__ __launch_bounds__(SG_WAVES * 64) void select_gather_kernel(
-    const float* __restrict__ partials, int slots, int dist, float* __restrict__ scores,
-    int32_t* __restrict__ kept_idx, const u32x4* __restrict__ src, u32x4* __restrict__ out,
-    float2* __restrict__ stats, int N, int n_prefix, int n_keep, int row_vec, int D, float eps) {
-    __shared__ float s_scores[256];
-    __shared__ int32_t s_idx[256];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t b = blockIdx.y;
-    const int K = n_prefix + n_keep;
-    if (tid < N) {
-        const float r = score_from_partials(partials, slots, (int64_t)gridDim.y * N, b * N + tid, dist);
-        s_scores[tid] = r;
-        if (blockIdx.x == 0) scores[b * N + tid] = r;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        uint32_t key[4];
-        int pos[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < N ? score_key(s_scores[r * 64 + lane]) : 0u;
-        wave_select<4>(key, N, n_prefix, n_keep, lane, pos);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (pos[r] >= 0) {
-                s_idx[pos[r]] = r * 64 + lane;
-                if (blockIdx.x == 0) kept_idx[b * K + pos[r]] = r * 64 + lane;
-            }
-    }
-    __syncthreads();
+// A workgroup's share of an image's surviving rows (s_idx: their tokens, in LDS): one wave per row, STATS: with
+// their LayerNorm statistics as in gather_rows_stats_kernel.  MAXC: 16-byte vectors per lane and row.
+template <bool STATS, int MAXC, int NW>
+__device__ __forceinline__ void copy_share(const int32_t* s_idx, const u32x4* __restrict__ src, u32x4* __restrict__ out,
+                                           float2* __restrict__ stats, int64_t b, int N, int K, int row_vec, int D, float eps,
+                                           int lane, int wave) {
     const int per = (K + gridDim.x - 1) / gridDim.x;
     const int j1 = min((int)(blockIdx.x + 1) * per, K);
     constexpr int U = 2;  // rows in flight per wave
-    for (int j0 = blockIdx.x * per + wave; j0 < j1; j0 += SG_WAVES * U) {
+    for (int j0 = blockIdx.x * per + wave; j0 < j1; j0 += NW * U) {
         u32x4 v[U][MAXC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * SG_WAVES;
+            const int j = j0 + u * NW;
             const u32x4* s = src + (b * N + s_idx[min(j, K - 1)]) * row_vec;
 #pragma unroll
             for (int c = 0; c < MAXC; ++c)
@@ -880,7 +848,7 @@ __global__ __launch_bounds__(SG_WAVES * 64) void select_gather_kernel(
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * SG_WAVES;
+            const int j = j0 + u * NW;
             if (j >= j1) break;  // wave-uniform
             u32x4* d = out + (b * K + j) * row_vec;
 #pragma unroll
@@ -900,6 +868,97 @@ __global__ __launch_bounds__(SG_WAVES * 64) void select_gather_kernel(
             }
         }
     }
+}
+
+// Scores, selection and gather of one short image (N <= 256) in one launch: `parts` workgroups per image,
+// each of which forms the image's scores from the partial sums and selects (a microsecond; the sums
+// are a few KB per image) and then copies its share of the surviving rows, STATS: with their LayerNorm
+// statistics as in gather_rows_stats_kernel.  Against a selection and a gather of their own it saves
+// a launch of every pruning block (vit_s16, eleven of them: 1020 -> 944 us per forward together with the
+// selection by one wave); one workgroup per image would leave the chip idle and copy with too few
+// requests in flight.  MAXC: 16-byte vectors per lane and row.
+constexpr int SG_WAVES = 8;
+template <bool STATS, int MAXC>
+__global__ __launch_bounds__(SG_WAVES * 64) void select_gather_kernel(
+    const float* __restrict__ partials, int slots, int dist, float* __restrict__ scores,
+    int32_t* __restrict__ kept_idx, const u32x4* __restrict__ src, u32x4* __restrict__ out,
+    float2* __restrict__ stats, int N, int n_prefix, int n_keep, int row_vec, int D, float eps) {
+    __shared__ float s_scores[256];
+    __shared__ int32_t s_idx[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t b = blockIdx.y;
+    const int K = n_prefix + n_keep;
+    if (tid < N) {
+        const float r = partials ? score_from_partials(partials, slots, (int64_t)gridDim.y * N, b * N + tid, dist) : scores[b * N + tid];
+        s_scores[tid] = r;
+        if (partials && blockIdx.x == 0) scores[b * N + tid] = r;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t key[4];
+        int pos[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) key[r] = r * 64 + lane < N ? score_key(s_scores[r * 64 + lane]) : 0u;
+        wave_select<4>(key, N, n_prefix, n_keep, lane, pos);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (pos[r] >= 0) {
+                s_idx[pos[r]] = r * 64 + lane;
+                if (blockIdx.x == 0) kept_idx[b * K + pos[r]] = r * 64 + lane;
+            }
+    }
+    __syncthreads();
+    copy_share<STATS, MAXC, SG_WAVES>(s_idx, src, out, stats, b, N, K, row_vec, D, eps, lane, wave);
+}
+
+// Selection and gather of longer sequences in one launch: as above with the selection of select_kernel, for so
+// few sequences that their selections leave most of the chip idle anyway (every workgroup repeats its
+// sequence's).
+constexpr int SGL_WAVES = 16;
+template <bool STATS, int MAXC>
+__global__ __launch_bounds__(SGL_WAVES * 64) void select_gather_long_kernel(
+    const float* __restrict__ scores, int32_t* __restrict__ kept_idx, const u32x4* __restrict__ src, u32x4* __restrict__ out,
+    float2* __restrict__ stats, int N, int n_prefix, int n_keep, int row_vec, int D, float eps) {
+    __shared__ SelectShared sh;
+    extern __shared__ float s_scores[];  // N scores, then the K surviving tokens
+    int32_t* s_idx = reinterpret_cast<int32_t*>(s_scores + N);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t b = blockIdx.y;
+    const int K = n_prefix + n_keep;
+    for (int i = tid; i < N; i += SGL_WAVES * 64) s_scores[i] = scores[b * N + i];
+    __syncthreads();
+    block_select_lds<SGL_WAVES * 64>(s_scores, N, n_prefix, n_keep, s_idx, sh, tid);
+    __syncthreads();
+    if (blockIdx.x == 0)
+        for (int j = tid; j < K; j += SGL_WAVES * 64) kept_idx[b * K + j] = s_idx[j];
+    copy_share<STATS, MAXC, SGL_WAVES>(s_idx, src, out, stats, b, N, K, row_vec, D, eps, lane, wave);
+}
+
+// One workgroup per CU over all sequences (two, measured: 4 x 4097 x 1024 28.1 -> 30.2 us, 64 x 300 x 192 11.1 -> 12.4).
+// Score, selection and gather in two launches / three (us): 8 x 1569 x 768 fp32 25.1 / 26.5, 4 x 4097 x 1024 28.1 /
+// 30.1, 20 x 1000 x 768 21.6 / 25.0, 64 x 500 x 768 28.3 / 30.1; beyond, fewer than four workgroups share a sequence's copy.
+constexpr int SGL_WGS = 256;
+
+bool select_gather_long_fits(rs_dtype dt, int B, int N, int D) {
+    return N > 256 && N <= SEL_MAXN / 2 && (size_t)D * elem_size(dt) <= 4 * 1024 && 4 * B <= resident_cus();
+}
+
+hipError_t launch_select_gather_long(rs_dtype dt, const float* scores, int32_t* kept_idx, const void* src, void* out,
+                                     float* stats, int B, int N, int n_prefix, int n_keep, int D, float eps, hipStream_t s) {
+    if (B == 0) return hipSuccess;
+    const int K = n_prefix + n_keep, row_vec = (int)((size_t)D * elem_size(dt) / 16);
+    int parts = SGL_WGS / B;
+    parts = parts < (K + SGL_WAVES - 1) / SGL_WAVES ? parts : (K + SGL_WAVES - 1) / SGL_WAVES;
+    const bool st = stats && dt == RS_BF16;
+    const size_t lds = (size_t)(N + K) * 4;
+#define RS_SGL(ST_, C_)                                                                                                  \
+    hipLaunchKernelGGL((select_gather_long_kernel<ST_, C_>), dim3(parts, B), dim3(SGL_WAVES * 64), lds, s, scores, kept_idx, \
+                       (const u32x4*)src, (u32x4*)out, reinterpret_cast<float2*>(stats), N, n_prefix, n_keep, row_vec, D, eps)
+    if (row_vec <= 64) { if (st) RS_SGL(true, 1); else RS_SGL(false, 1); }
+    else if (row_vec <= 128) { if (st) RS_SGL(true, 2); else RS_SGL(false, 2); }
+    else { if (st) RS_SGL(true, 4); else RS_SGL(false, 4); }
+#undef RS_SGL
+    return hipGetLastError();
 }
 
 bool select_gather_fits(rs_dtype dt, int N, int D) { return N <= 256 && (size_t)D * elem_size(dt) <= 4 * 1024; }

@@ -403,6 +403,19 @@ rs_status rs_shift_topk(const void* f_out, const void* f_in, const void* src, in
         return RS_OK;
     }
     RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * N, D, st));
+    if (gathered && n_keep > 0 && n_keep < N - n_prefix) {  // selection and gather in one launch
+        if (select_gather_long_fits(dtype, B, N, D)) {
+            RS_LAUNCH_K(K_GATHER, st, launch_select_gather_long(dtype, scores, kept_idx, s, gathered, nullptr, B, N, n_prefix, n_keep, D, 0.f, st));
+            return RS_OK;
+        }
+        // short images: 1 x 197 x 384 6.7 / 8.0 us, 16 x 197 x 768 7.9 / 9.7, 128: 23.0 / 25.3, but 512: 95.8 / 93.4 (the
+        // gather alone then has enough rows in flight to run at the memory's pace)
+        if (B <= 256 && select_gather_fits(dtype, N, D)) {
+            RS_LAUNCH_K(K_GATHER, st, launch_select_gather(dtype, dist, nullptr, 0, scores, kept_idx, s, gathered, nullptr, B, N,
+                                                           n_prefix, n_keep, D, 0.f, st));
+            return RS_OK;
+        }
+    }
     RS_LAUNCH_K(K_SELECT, st, launch_select(scores, kept_idx, B, N, n_prefix, n_keep, st));
     if (gathered) RS_LAUNCH_K(K_GATHER, st, launch_gather(dtype, s, kept_idx, gathered, B, N, K, D, st));
     return RS_OK;
@@ -741,6 +754,14 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
         // short images: scores, selection, gather and the statistics of the gathered rows in one launch
         RS_LAUNCH_K(K_GATHER, s, launch_select_gather(dt, c.dist, partials, L.slots, sc, kept_idx, xhat, y, y_stats, c.B, c.N,
                                                     c.n_prefix, c.n_keep, D, c.ln_eps, s));
+        if (y_stats && dt != RS_BF16) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, y, y_stats, (int64_t)c.B * K, D, c.ln_eps, s));
+        return RS_OK;
+    }
+    if (prune && c.n_keep > 0 && select_gather_long_fits(dt, c.B, c.N, D)) {
+        // a few long sequences: scores by a grid over all rows, the rest in one launch
+        RS_LAUNCH_K(K_SCORE, s, launch_finalize_scores(c.dist, partials, L.slots, sc, M, s));
+        RS_LAUNCH_K(K_GATHER, s, launch_select_gather_long(dt, sc, kept_idx, xhat, y, y_stats, c.B, c.N, c.n_prefix, c.n_keep, D,
+                                                           c.ln_eps, s));
         if (y_stats && dt != RS_BF16) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, y, y_stats, (int64_t)c.B * K, D, c.ln_eps, s));
         return RS_OK;
     }
