@@ -204,6 +204,10 @@ struct MlpArgs {
 bool mlp_fused_fits(rs_dtype dt, int64_t M, int D, int Dm);
 hipError_t launch_mlp_fused(const MlpArgs& g, rs_dist dist, bool shift, hipStream_t s);
 
+// out[M, N] = LN(x) W + b for rows of 192 (qkv_rows_fits), folded as for EPI_LN_BIAS; ln.stats null: formed inside.
+bool qkv_rows_fits(rs_dtype dt, int64_t M, int D, int N);
+hipError_t launch_qkv_rows(const void* x, const void* w, GemmLnFold ln, void* out, int64_t M, int N, float eps, hipStream_t s);
+
 // `count` independent bf16 products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T, problem p at element offset
 // p * stride from each base pointer (K % 32 == 0, N % 64 == 0; rows of wt_p past N must exist as zeros)
 hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int count, int64_t stride_a,

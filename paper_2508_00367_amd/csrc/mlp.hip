@@ -228,6 +228,91 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     if (iota_out && g == 0 && m < M) iota_out[m] = m % iota_n;
 }
 
+// The QKV layer behind its LayerNorm for the same narrow tokens: 128 rows per workgroup stay in registers, the weights
+// pass by in two LDS stages of 64 features, and every step ends with its 64 columns of the output.  A row is read once
+// whatever the output width, nothing is computed for columns that do not exist (576 = 2.25 tiles of 256), and
+// the statistics come from the registers when the caller has none.  100864 x 576 x 192: 57 -> 47 us (155 MB: 32 us at
+// the copy rate; with the wait for a step's stores inside the next step 50).
+constexpr int kQkvMaxN = 1024;
+__global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restrict__ x, const bf16raw* __restrict__ w, GemmLnFold ln,
+                                                        bf16raw* __restrict__ out, float eps, int M, int D, int N) {
+    constexpr int STAGE = 64 * kMlpD * 2;
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_epi[4 * 4096];
+    __shared__ __attribute__((aligned(16))) float s_cs[kQkvMaxN], s_b[kQkvMaxN];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int m_base = blockIdx.x * kMlpRows + wave * 32, m = m_base + l32;
+    const int S = N / 64;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(w, (int64_t)N * kMlpD * 2);
+    int voff[6];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const int p = (j * 4 + wave) * 64 + lane, r = p / 24, slot = p - r * 24;
+        voff[j] = r * (kMlpD * 2) + (((slot & 24) | ((slot ^ (r >> 1)) & 7)) << 4);
+    }
+#define RS_QKV_DMA(stage_, s_)                                                                             \
+    if ((s_) < S) {                                                                                        \
+        _Pragma("unroll") for (int j = 0; j < 6; ++j) dma16(rs, (stage_) + (j * 4 + wave) * 1024, voff[j], (s_) * STAGE); \
+    }
+    u32x4 xr[12];
+    const bf16raw* xp = x + (int64_t)min(m, M - 1) * kMlpD + g * 8;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) xr[k] = *reinterpret_cast<const u32x4*>(xp + k * 16);
+    for (int f = tid; f < N; f += 256) {
+        s_cs[f] = ln.colsum[f];
+        s_b[f] = ln.bias[f];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    RS_QKV_DMA(st0, 0)
+    EpiVecs<1, EPI_LN_BIAS> vec;
+    vec.stats[0] = ln.stats ? reinterpret_cast<const float2*>(ln.stats)[min(m, M - 1)] : mlp_row_stats(xr, D, eps);
+    EpiRegions<1> reg;
+    reg.r[0] = s_epi + wave * 4096;
+    const int a1 = l32 * (kMlpD * 2), x1 = (l32 >> 1) & 7;
+
+// Step s: the barrier says that stage s has landed (every wave has waited for its copies) and that the other stage,
+// which the next copies fill, is no longer read.  The wait for these copies comes behind the matrix work and
+// before the step's stores, which so have a whole step to complete.
+#define RS_QKV_STEP(cur_, other_, s_)                                                                      \
+    {                                                                                                      \
+        __builtin_amdgcn_s_waitcnt(0xC07F); /* own LDS reads */                                            \
+        __builtin_amdgcn_s_barrier();                                                                      \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                                             \
+        __builtin_amdgcn_sched_barrier(0);                                                                 \
+        RS_QKV_DMA(other_, (s_) + 1)                                                                       \
+        f32x16 acc[2][1];                                                                                  \
+        _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                      \
+            _Pragma("unroll") for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.f;                             \
+        _Pragma("unroll") for (int k = 0; k < 12; ++k) {                                                   \
+            const int c_ = 2 * k + g, o_ = ((c_ & 24) | ((c_ ^ x1) & 7)) << 4;                             \
+            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                  \
+                acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                       \
+                    *reinterpret_cast<const bf16x8*>((cur_) + a1 + i * 32 * kMlpD * 2 + o_),               \
+                    __builtin_bit_cast(bf16x8, xr[k]), acc[i][0], 0, 0, 0);                                \
+        }                                                                                                  \
+        _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                      \
+            _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                \
+                const int f_ = (s_) * 64 + i * 32 + q * 8 + g * 4;                                         \
+                vec.bv[i][q] = *reinterpret_cast<const f32x4*>(s_b + f_);                                  \
+                vec.cs[i][q] = *reinterpret_cast<const f32x4*>(s_cs + f_);                                 \
+            }                                                                                              \
+        __builtin_amdgcn_sched_barrier(0);                                                                 \
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                                                          \
+        __builtin_amdgcn_sched_barrier(0);                                                                 \
+        gemm_epilogue_acc_layout<1, EPI_LN_BIAS, 0>(acc, reg, vec, out, nullptr, nullptr, 0, M, N, N, 0, 0, m_base, (s_) * 64, lane); \
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    for (int s = 0; s < S; s += 2) {
+        RS_QKV_STEP(st0, st1, s)
+        if (s + 1 >= S) break;
+        RS_QKV_STEP(st1, st0, s + 1)
+    }
+#undef RS_QKV_DMA
+#undef RS_QKV_STEP
+}
+
 // A workgroup's time does not depend on how many there are (30 us at Dm = 768) until every CU has one, that of the
 // separate launches does: two blocks in a row (no token dropped) take 127 / 123 us fused / separate at 12608 rows,
 // 135 / 136 at 14184, 142 / 146 at 16548, 153 / 178 at 22064, 461 / 583 at 100864.  Below the line a workgroup
@@ -236,6 +321,18 @@ constexpr int64_t kMlpMinRows = 128 * kMlpRows;
 
 bool mlp_fused_fits(rs_dtype dt, int64_t M, int D, int Dm) {
     return dt == RS_BF16 && D == kMlpD && Dm % (3 * kMlpChunk) == 0 && Dm <= kMlpMaxDm && gemm_variant() == 0 && M >= kMlpMinRows;
+}
+
+// Two blocks in a row against the tiled GEMM (us): 16548 rows 143 / 142, 25216 154 / 157, 50432 241 / 252, 100864 433 / 458;
+// at 12608 rows, where a workgroup's nine steps are the whole launch, 135 / 124.
+bool qkv_rows_fits(rs_dtype dt, int64_t M, int D, int N) {
+    return dt == RS_BF16 && D == kMlpD && N % 64 == 0 && N <= kQkvMaxN && gemm_variant() == 0 && M >= kMlpMinRows;
+}
+
+hipError_t launch_qkv_rows(const void* x, const void* w, GemmLnFold ln, void* out, int64_t M, int N, float eps, hipStream_t s) {
+    hipLaunchKernelGGL(qkv192_kernel, dim3((unsigned)((M + kMlpRows - 1) / kMlpRows)), dim3(256), 0, s, (const bf16raw*)x,
+                       (const bf16raw*)w, ln, (bf16raw*)out, eps, (int)M, kMlpD, N);
+    return hipGetLastError();
 }
 
 hipError_t launch_mlp_fused(const MlpArgs& g, rs_dist dist, bool shift, hipStream_t s) {

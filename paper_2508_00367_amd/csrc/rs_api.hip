@@ -694,8 +694,13 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     // the raw rows against weights that carry the LayerNorm scale and normalises in its epilogue
     // (a caller that chains blocks hands over the statistics the previous block left for its output)
     if (dt == RS_BF16) {
-        if (!x_stats) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, x, (float*)(ws + L.stats), M, D, c.ln_eps, s));
-        RS_LAUNCH_K(K_GEMM_QKV, s, launch_gemm_ln(EPI_LN_BIAS, x, wq, ln1, qkv, M, 3 * D, D, s));
+        if (qkv_rows_fits(dt, M, D, 3 * D)) {
+            ln1.stats = x_stats;  // null: formed inside
+            RS_LAUNCH_K(K_GEMM_QKV, s, launch_qkv_rows(x, wq, ln1, qkv, M, 3 * D, c.ln_eps, s));
+        } else {
+            if (!x_stats) RS_LAUNCH_K(K_LN, s, launch_rowstats(dt, x, (float*)(ws + L.stats), M, D, c.ln_eps, s));
+            RS_LAUNCH_K(K_GEMM_QKV, s, launch_gemm_ln(EPI_LN_BIAS, x, wq, ln1, qkv, M, 3 * D, D, s));
+        }
     } else {
         RS_LAUNCH_K(K_LN, s, launch_layernorm(dt, x, w->ln1_g, w->ln1_b, u, M, D, c.ln_eps, s));
         RS_LAUNCH_K(K_GEMM_QKV, s, launch_gemm(dt, EPI_BIAS, RS_DIST_L2, u, wq, w->b_qkv, nullptr, qkv, nullptr, nullptr, false, M, 3 * D, D, s));

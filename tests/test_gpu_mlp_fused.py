@@ -55,3 +55,31 @@ def test_mlp_fused_same_bits(B, N, Dm, drop, op, dist):
     for a, b in zip(*outs):
         assert torch.equal(a, b)
     assert not torch.isnan(outs[0][3]).any()
+
+
+@pytest.mark.parametrize("B,N", [(127, 129), (128, 128), (113, 145)])
+def test_statistics_given_or_formed(B, N):
+    """The first LayerNorm's statistics handed over or formed inside the QKV kernel: the same block output, and the
+    separate statistics launch's bits (which a block that keeps every token leaves for its output)."""
+    print("statistics", B, N, flush=True)
+    D, Dm, M = 192, 384, B * N
+    g = torch.Generator(device="cuda").manual_seed(M)
+
+    def normal(*shape, scale=0.05):
+        return (torch.randn(shape, device="cuda", generator=g) * scale).bfloat16()
+    w = {"ln1_g": normal(D) + 1, "ln1_b": normal(D), "w_qkv": normal(D, 3 * D), "b_qkv": normal(3 * D), "w_proj": normal(D, D),
+         "b_proj": normal(D), "ln2_g": normal(D) + 1, "ln2_b": normal(D), "w_fc1": normal(D, Dm), "b_fc1": normal(Dm),
+         "w_fc2": normal(Dm, D), "b_fc2": normal(D)}
+    cfg = rs.make_cfg(B, N, D, 3, Dm, 1, N - 1, torch.bfloat16)
+    ws = torch.empty(rs.rs_block_workspace_size(cfg), dtype=torch.uint8, device="cuda")
+    kept = torch.empty((B, N), device="cuda", dtype=torch.int32)
+    x, mid = normal(B, N, D, scale=2.0), torch.empty((B, N, D), device="cuda", dtype=torch.bfloat16)
+    stats = torch.empty((M, 2), device="cuda")
+    rs.rs_block_fwd_chained(cfg, rs.make_weights(w), x, None, mid, stats, kept, None, ws)
+    outs = []
+    for given in (stats, None):
+        y = torch.empty_like(mid)
+        rs.rs_block_fwd_chained(cfg, rs.make_weights(w), mid, given, y, None, kept, None, ws)
+        torch.cuda.synchronize()
+        outs.append(y.view(torch.int16))
+    assert torch.equal(*outs)
