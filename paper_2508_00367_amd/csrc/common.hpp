@@ -169,7 +169,8 @@ constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine al
 // 26.5 -> 23.7, 384 x 1536 at 12608 rows 24.8 -> 23.0 (128, 192 or 256 extra elements: the same; 32 or less
 // split lines and cost 5-30 %).  vit_s16 -1.1 %, video_vit_b16 -1.8 % per forward, vit_b16 -0.4 %.  (The attention
 // output and W_proj, padded the same way: no change.)
-inline int padded_ld(int K) { return K % 256 == 0 ? K + 64 : K; }
+// Rows under 1 KB stay as they are: such a GEMM has at most four slices of K, and the padding would be a quarter of W_fc2.
+inline int padded_ld(int K) { return K >= 512 && K % 256 == 0 ? K + 64 : K; }
 
 // out[M, N] = epilogue(a[M, K] @ W).  bf16: `w` is the packed [N, K] matrix; fp32: `w` is the
 // caller's [K, N] matrix.  partials: float [kShiftLanes][slots][M] for EPI_BIAS_RES_SHIFT
