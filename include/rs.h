@@ -278,7 +278,7 @@ RS_API rs_status rs_linear_fwd(const void *a, const void *w, const void *bias, c
  *                                                        distance by cfg->dist (default L2)
  *     kept_idx, y  = selection and gather of xhat as in rs_shift_topk.
  *   RS_BF16: the two LayerNorms are applied inside the GEMMs that follow them (their scale is
- *   folded into the packed weights, mean and variance come from a row-statistics pass), so the
+ *   folded into the packed weights, mean and variance are formed per row beside it), so the
  *   normalised rows are never written; results agree with the definition above to bf16 rounding.
  *   x        : [B, N, D] in.            y : [B, K, D] out, must not alias x.
  *   kept_idx : int32 [B, K] out.        scores : float [B, N] out, or NULL.
