@@ -14,6 +14,7 @@
 
 #include <atomic>
 
+#include "gemm_choice.hpp"
 #include "gemm_tile.hpp"
 
 namespace rs {
@@ -1019,38 +1020,22 @@ static void launch_persistent(const GemmArgs& g, hipStream_t s) {
                            g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
-// Choice by shape: the smallest tile of 64 x 64, 128 x 64, 128 x 128, 256 x 128 (slim kernels) and 256 x 256
-// (persistent kernel) that gives every CU at most one workgroup.  A workgroup streams its operands at
-// the pace of one CU whatever else runs, so a smaller tile is faster as long as it does not put two
-// workgroups on some CUs; at 48 slices of K the steps are 12 / 20 / 24 / 34 / 59 us per launch (768 x 3072).
-// Chains of the four layers of a block, sizes on both sides of the steps (us per layer against the
-// next smaller / larger tile): 768 x 3072 at 1182 rows (228 tiles of 64 x 64) -22.5 / -16.0 against the 128 x 128
-// ring kernel, at 1576 rows (300) -12.0 / -15.2; at 3152 rows (150 of 128 x 128) -11.1 / -0.3; at 8471
-// rows (204 of 256 x 128) -4.5 / -24.7; 384 x 1152 at 12608 rows (250 of 256 x 256) 18.9 us persistent, 24 ring.
-// Beyond one round:
-//  - K <= 384: a tile is mostly epilogue; the ring kernels (two workgroups per CU, one's epilogue under the
-//    other's K loop): 1536 x 384 at 25216 rows -5 us of 62 against the persistent kernel.
-//  - K < 2048 and up to 1.45 rounds of 256 x 256 tiles: the 256 x 128 tiles, whose last round costs half as much
-//    (768 x 768 at 25216 rows -7 us of 53, 2304 x 768 at 10047 rows -4 of 50; at 1.59 rounds +5).
-//  - otherwise the persistent kernel; with K >= 2048 and a last round at most half full the rows that make up
-//    whole rounds go to it and the rows behind them to the tile that suits them, in a second launch
-//    (a round is long there: 768 x 3072 at 50432 rows -19 us of 260).
+// The kernels that the choice by shape (gemm_choice.hpp) names, from the first row to the last.
 template <int EPI, int DIST>
 static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
-    const int64_t cus = device_cus();
-    auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-    if (tiles(64, 64) <= cus) return launch_slim<2, 1, 1, 4, EPI, DIST>(g, s);
-    if (tiles(128, 64) <= cus) return launch_slim<4, 1, 1, 4, EPI, DIST>(g, s);
-    if (tiles(128, 128) <= cus) return launch_slim<2, 2, 2, 3, EPI, DIST>(g, s);
-    if (tiles(256, 128) <= cus) return launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
-    const int64_t t = tiles(256, 256), rounds = t / cus, rem = t - rounds * cus;
-    if (rounds == 0 || rem == 0) return launch_persistent<EPI, DIST>(g, s);
-    if (g.K <= 384) return launch_ring_auto<EPI, DIST>(g, s);
-    if (g.K < 2048 && 100 * t <= 145 * cus) return launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
-    if (g.K < 2048 || 2 * rem > cus) return launch_persistent<EPI, DIST>(g, s);
-    const int64_t m1 = rounds * cus / ((g.N + 255) / 256) * 256;  // row panels that fill whole rounds
-    launch_persistent<EPI, DIST>(g.rows(0, m1), s);
-    launch_by_shape<EPI, DIST>(g.rows(m1, g.M), s);
+    for (int64_t r = 0; r < g.M;) {
+        const GemmChoice c = gemm_choose(g.M - r, g.N, g.K, device_cus());
+        const GemmArgs part = g.rows(r, r + c.rows);
+        switch (c.tile) {
+            case GemmTile::Slim64x64: launch_slim<2, 1, 1, 4, EPI, DIST>(part, s); break;
+            case GemmTile::Slim128x64: launch_slim<4, 1, 1, 4, EPI, DIST>(part, s); break;
+            case GemmTile::Slim128x128: launch_slim<2, 2, 2, 3, EPI, DIST>(part, s); break;
+            case GemmTile::Slim256x128: launch_slim<4, 2, 2, 3, EPI, DIST>(part, s); break;
+            case GemmTile::Ring: launch_ring_auto<EPI, DIST>(part, s); break;
+            case GemmTile::Persistent: launch_persistent<EPI, DIST>(part, s); break;
+        }
+        r += c.rows;
+    }
 }
 
 template <int EPI, int DIST>

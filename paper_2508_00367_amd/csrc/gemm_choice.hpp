@@ -1,0 +1,48 @@
+// Which bf16 GEMM kernel takes which rows of a problem: host arithmetic only, no HIP.
+#pragma once
+
+#include <stdint.h>
+
+namespace rs {
+
+enum class GemmTile { Slim64x64, Slim128x64, Slim128x128, Slim256x128, Ring, Persistent };
+
+// The kernel for the first `rows` rows; rows < M: the rows behind them are a problem of their own.
+struct GemmChoice {
+    GemmTile tile;
+    int64_t rows;
+};
+
+// Choice by shape: the smallest tile of 64 x 64, 128 x 64, 128 x 128, 256 x 128 (slim kernels) and 256 x 256
+// (persistent kernel) that gives every CU at most one workgroup.  A workgroup streams its operands at
+// the pace of one CU whatever else runs, so a smaller tile is faster as long as it does not put two
+// workgroups on some CUs; at 48 slices of K the steps are 12 / 20 / 24 / 34 / 59 us per launch (768 x 3072).
+// Chains of the four layers of a block, sizes on both sides of the steps (us per layer against the
+// next smaller / larger tile): 768 x 3072 at 1182 rows (228 tiles of 64 x 64) -22.5 / -16.0 against the 128 x 128
+// ring kernel, at 1576 rows (300) -12.0 / -15.2; at 3152 rows (150 of 128 x 128) -11.1 / -0.3; at 8471
+// rows (204 of 256 x 128) -4.5 / -24.7; 384 x 1152 at 12608 rows (250 of 256 x 256) 18.9 us persistent, 24 ring.
+// Beyond one round:
+//  - K <= 384: a tile is mostly epilogue; the ring kernels (two workgroups per CU, one's epilogue under the
+//    other's K loop): 1536 x 384 at 25216 rows -5 us of 62 against the persistent kernel.
+//  - K < 2048 and up to 1.45 rounds of 256 x 256 tiles: the 256 x 128 tiles, whose last round costs half as much
+//    (768 x 768 at 25216 rows -7 us of 53, 2304 x 768 at 10047 rows -4 of 50; at 1.59 rounds +5).
+//  - otherwise the persistent kernel; with K >= 2048 and a last round at most half full the rows that make up
+//    whole rounds go to it and the rows behind them to the tile that suits them, in a second launch
+//    (a round is long there: 768 x 3072 at 50432 rows -19 us of 260).  A row panel of more tiles than the whole
+//    rounds hold (N > 256 * cus) cannot be cut that way and stays whole.
+inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
+    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (tiles(64, 64) <= cus) return {GemmTile::Slim64x64, M};
+    if (tiles(128, 64) <= cus) return {GemmTile::Slim128x64, M};
+    if (tiles(128, 128) <= cus) return {GemmTile::Slim128x128, M};
+    if (tiles(256, 128) <= cus) return {GemmTile::Slim256x128, M};
+    const int64_t t = tiles(256, 256), rounds = t / cus, rem = t - rounds * cus;
+    if (rounds == 0 || rem == 0) return {GemmTile::Persistent, M};
+    if (K <= 384) return {GemmTile::Ring, M};
+    if (K < 2048 && 100 * t <= 145 * cus) return {GemmTile::Slim256x128, M};
+    if (K < 2048 || 2 * rem > cus) return {GemmTile::Persistent, M};
+    const int64_t m1 = rounds * cus / ((N + 255) / 256) * 256;  // row panels that fill whole rounds: fewer than all of them
+    return {GemmTile::Persistent, m1 > 0 ? m1 : M};
+}
+
+}  // namespace rs

@@ -51,3 +51,31 @@ def test_tile_choice(M, K, N, epi):
         mag = np.abs(ah) @ np.abs(wh).T + np.abs(to_host(b)) + np.abs(to_host(res[rows]))
         err = np.abs(to_host(outs[0][rows]) - ref)
         assert (err <= 2.0 ** -8 * np.abs(ref) + (K + 3) * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(64, 2048, 65600), (257, 2048, 65600)])
+def test_one_row_panel_wider_than_a_round(M, K, N):
+    """More column tiles in one row panel than the chip has CUs, one panel and one row behind it: the same bits as the
+    128 x 128 tiles', and sampled columns within a fp32 sum's error plus one rounding to bf16."""
+    print("wide panel", M, K, N, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a = torch.randn((M, K), device="cuda", generator=g).bfloat16()
+    w = (torch.randn((N, K), device="cuda", generator=g) * 0.05).bfloat16()
+    b = torch.randn((N,), device="cuda", generator=g).bfloat16()
+    outs = []
+    try:
+        for variant in (0, 3):
+            rs.rs_tune_gemm_variant(variant)
+            out = torch.full((M + 1, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+            rs.rs_linear_fwd(a, w, b, None, out[:M], rs.RS_EPI_BIAS)
+            torch.cuda.synchronize()
+            assert torch.isnan(out[M].float()).all()
+            outs.append(out[:M].view(torch.int16))
+    finally:
+        rs.rs_tune_gemm_variant(0)
+    assert torch.equal(*outs)
+    cols = np.r_[0:40, 65500:N]
+    ah, wh, bh = to_host(a), to_host(w[cols]), to_host(b[cols])
+    ref, mag = ah @ wh.T + bh, np.abs(ah) @ np.abs(wh).T + np.abs(bh)
+    err = np.abs(to_host(outs[0].view(torch.bfloat16)[:, cols]) - ref)
+    assert (err <= 2.0 ** -8 * np.abs(ref) + (K + 3) * 2.0 ** -24 * mag).all()
