@@ -595,9 +595,11 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx);  // finite: every tile holds at least one real key
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
-        const float mb = m_new * scale_log2e;
+        // While every score this wave has seen is -inf (keys masked through a channel or an overflow: its first tile may
+        // hold nothing else) the maximum is -inf too: the exponents are taken from 0 then, so that such keys weigh 0.
+        const float m_new = fmaxf(m_run, mx), m_exp = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_exp) * scale_log2e);
+        const float mb = m_exp * scale_log2e;
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
@@ -640,7 +642,8 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     float L = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) L += s_l[w][l32] * __builtin_amdgcn_exp2f((s_m[w][l32] - m_all) * scale_log2e);
-    const float f = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / L;  // 0 for a wave without tiles
+    // 0 for a wave without tiles or with no score above -inf; a row without any such score is NaN, as its softmax is
+    const float f = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / L;
     float* part = reinterpret_cast<float*>(s_k[wave]);  // [32 rows][64 channels], this wave's own tile
 #pragma unroll
     for (int db = 0; db < 2; ++db)

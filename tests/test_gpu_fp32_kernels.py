@@ -58,3 +58,40 @@ def test_fp32_attention_key_split_edges(N):
     err = norm_err(to_host(o), oracle.attention(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], 0.125))
     _say("  err %.2e" % err)
     assert err < TOL["f32"]
+
+
+# the keys whose scores are -inf: the first tile of each wave that shares the keys (0-31, 32-63, 64-95, 96-127), all of
+# one wave's tiles, all but one key, and the keys of a whole image (a row without any score is NaN, as its softmax is)
+MASKED = {"first": range(0, 32), "second": range(32, 64), "third": range(64, 96), "fourth": range(96, 128),
+          "padding": range(96, 161), "two_waves": [*range(32, 96), *range(160, 161)], "wave": [*range(0, 32), *range(128, 160)],
+          "all_but_one": [i for i in range(161) if i != 70], "all": range(161)}
+
+
+@pytest.mark.parametrize("how", ["infinite", "overflow"])
+@pytest.mark.parametrize("N", [128, 129, 161])
+@pytest.mark.parametrize("masked", list(MASKED))
+def test_fp32_attention_masked_keys(masked, N, how):
+    """Keys masked through a reserved channel: -inf in k, or a product that overflows, against the fp64 softmax."""
+    B, H = 2, 2
+    _say("fp32 attention masked", masked, N, how)
+    keys = [i for i in MASKED[masked] if i < N]
+    qkv = si.generic(45, 1, (B, N, 3, H, 64))
+    qkv[:, :, 0, :, 63], qkv[:, :, 1, :, 63] = (1.0 if how == "infinite" else 2.0), 0.0
+    seen = np.setdiff1d(np.arange(N), keys)
+    ref = np.full((B, N, H, 64), np.nan)
+    if len(seen):
+        q, k, v = (qkv[:, :, i].astype(np.float64).transpose(0, 2, 1, 3) for i in range(3))
+        s = q @ k[:, :, seen].transpose(0, 1, 3, 2) * 0.125
+        p = np.exp(s - s.max(axis=-1, keepdims=True))
+        ref = (p @ v[:, :, seen] / p.sum(axis=-1, keepdims=True)).transpose(0, 2, 1, 3)
+    qkv[:, keys, 1, :, 63] = -np.inf if how == "infinite" else -3e38
+    d = to_dev(qkv, "f32")
+    o = torch.full((B, N, H, 64), 7.0, device="cuda")
+    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
+    torch.cuda.synchronize()
+    if not len(seen):
+        assert torch.isnan(o).all()
+        return
+    err = norm_err(to_host(o), ref)
+    _say("  err %.2e" % err)
+    assert err < TOL["f32"]
