@@ -163,7 +163,8 @@ void set_gemm_variant(int v);
 int gemm_shift_slots(rs_dtype dt, int N);
 constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine all three)
 
-// Row pitch (elements) of the MLP's hidden activations and of the packed W_fc2 behind them: the rows of an operand
+// Row pitch (elements) of the MLP's hidden activations and of the W_fc2 a caller has packed (a block that packs on every
+// call keeps the plain pitch for both): the rows of an operand
 // tile are requested together, and when the pitch is a multiple of 512 bytes they meet in a few of the
 // L2's channels.  One extra line per row spreads them: 768 x 3072 at 50432 rows 252 -> 243 us, at 3152 rows
 // 26.5 -> 23.7, 384 x 1536 at 12608 rows 24.8 -> 23.0 (128, 192 or 256 extra elements: the same; 32 or less

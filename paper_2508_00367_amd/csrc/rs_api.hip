@@ -102,18 +102,22 @@ static hipError_t timed(int cls, hipStream_t s, F launch) {
     } while (0)
 
 // ---- workspace layout of rs_block_fwd ---------------------------------------
+// The padded pitch of the hidden activations (padded_ld) makes the workspace no larger than it is without: in bf16
+// u is needed only behind the attention and shares qkv's place, and hid has the room u would take.  Weights
+// packed into the workspace keep the plain pitch, the hidden activations with them.
 struct BlockLayout {
     size_t packed, u, qkv, att, x1, hid, partials, scores, stats, total;
     int slots;
 };
 
 // Packed bf16 weights: the four matrices as [out, in] (LayerNorm scales folded into W_qkv and
-// W_fc1; W_fc2 with the row pitch of its activations, padded_ld), then the fp32 column vectors of the two folded LayerNorms.
+// W_fc1; W_fc2 with the row pitch of its activations, ld), then the fp32 column vectors of the two folded LayerNorms.
 struct PackedLayout {
     size_t w_qkv, w_proj, w_fc1, w_fc2, cs_qkv, b_qkv, cs_fc1, b_fc1, total;
+    int ld;
 };
 
-static PackedLayout packed_layout(const rs_block_cfg* c) {
+static PackedLayout packed_layout(const rs_block_cfg* c, bool caller_owned) {
     PackedLayout P;
     const size_t D = c->D, Dm = c->Dm;
     size_t off = 0;
@@ -121,7 +125,8 @@ static PackedLayout packed_layout(const rs_block_cfg* c) {
     P.w_qkv = take(3 * D * D * 2);
     P.w_proj = take(D * D * 2);
     P.w_fc1 = take(D * Dm * 2);
-    P.w_fc2 = take(D * padded_ld(c->Dm) * 2);
+    P.ld = caller_owned ? padded_ld(c->Dm) : c->Dm;
+    P.w_fc2 = take(D * P.ld * 2);
     P.cs_qkv = take(3 * D * sizeof(float));
     P.b_qkv = take(3 * D * sizeof(float));
     P.cs_fc1 = take(Dm * sizeof(float));
@@ -130,8 +135,8 @@ static PackedLayout packed_layout(const rs_block_cfg* c) {
     return P;
 }
 
-static size_t packed_bytes(const rs_block_cfg* c) {
-    return c->dtype == RS_BF16 ? packed_layout(c).total : 0;
+static size_t packed_bytes(const rs_block_cfg* c, bool caller_owned) {
+    return c->dtype == RS_BF16 ? packed_layout(c, caller_owned).total : 0;
 }
 
 static BlockLayout block_layout(const rs_block_cfg* c) {
@@ -141,12 +146,13 @@ static BlockLayout block_layout(const rs_block_cfg* c) {
     L.slots = gemm_shift_slots(c->dtype, c->D);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes, 256); return o; };
-    L.packed = take(packed_bytes(c));
-    L.u = take(M * D * e);
+    L.packed = take(packed_bytes(c, false));
     L.qkv = take(M * 3 * D * e);
     L.att = take(M * D * e);
     L.x1 = take(M * D * e);
-    L.hid = take(M * (c->dtype == RS_BF16 ? padded_ld(c->Dm) : Dm) * e);
+    L.hid = take(M * Dm * e);
+    L.u = take(M * D * e);  // at least M * (padded_ld(Dm) - Dm) elements: D >= 64
+    if (c->dtype == RS_BF16) L.u = L.qkv;
     L.partials = take(M * (size_t)L.slots * kShiftLanes * sizeof(float));
     L.scores = take(M * sizeof(float));
     L.stats = take(M * 2 * sizeof(float));
@@ -504,17 +510,16 @@ rs_status rs_grid_token_prune(const void* f_out, const void* f_in, const void* s
 
 size_t rs_packed_weights_size(const rs_block_cfg* cfg) {
     if (!cfg || cfg->D <= 0 || cfg->Dm <= 0) return 0;
-    return packed_bytes(cfg);
+    return packed_bytes(cfg, true);
 }
 
-static rs_status pack_into(const rs_block_cfg* c, const rs_block_weights* w, void* dst, hipStream_t st) {
-    const PackedLayout P = packed_layout(c);
+static rs_status pack_into(const rs_block_cfg* c, const rs_block_weights* w, const PackedLayout& P, void* dst, hipStream_t st) {
     char* p = (char*)dst;
     const int D = c->D, Dm = c->Dm;
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_qkv, w->ln1_g, p + P.w_qkv, D, 3 * D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_proj, nullptr, p + P.w_proj, D, D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc1, w->ln2_g, p + P.w_fc1, D, Dm, st));
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, st, padded_ld(Dm)));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, st, P.ld));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_qkv, w->ln1_g, w->ln1_b, w->b_qkv, (float*)(p + P.cs_qkv),
                                               (float*)(p + P.b_qkv), D, 3 * D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_fc1, w->ln2_g, w->ln2_b, w->b_fc1, (float*)(p + P.cs_fc1),
@@ -543,7 +548,7 @@ rs_status rs_pack_weights(const rs_block_cfg* cfg, const rs_block_weights* w, vo
     if (cfg->dtype == RS_F32) return RS_OK;  // the fp32 path reads the caller's layout
     RS_REQUIRE(packed_out != nullptr && aligned16(packed_out), RS_ERR_INVALID_ARG,
                "packed_out must be a 16-byte aligned buffer");
-    return pack_into(cfg, w, packed_out, (hipStream_t)hip_stream);
+    return pack_into(cfg, w, packed_layout(cfg, true), packed_out, (hipStream_t)hip_stream);
 }
 
 rs_status rs_pack_linear(const void* w, void* wt, int32_t K, int32_t N, rs_dtype dtype, void* hip_stream) {
@@ -657,7 +662,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     const rs_dtype dt = c.dtype;
     const int64_t M = (int64_t)c.B * c.N;
     const int D = c.D, Dm = c.Dm;
-    const int ld_hid = dt == RS_BF16 ? padded_ld(Dm) : Dm;
+    int ld_hid = Dm;
     void* u = ws + L.u;
     void* qkv = ws + L.qkv;
     void* att = ws + L.att;
@@ -673,12 +678,13 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     GemmLnFold ln1{}, ln2{};
     if (dt == RS_BF16) {
         const char* pk = (const char*)w->packed;
+        const PackedLayout P = packed_layout(cfg, pk != nullptr);
         if (!pk) {
-            st = pack_into(cfg, w, ws + L.packed, s);
+            st = pack_into(cfg, w, P, ws + L.packed, s);
             if (st != RS_OK) return st;
             pk = ws + L.packed;
         }
-        const PackedLayout P = packed_layout(cfg);
+        ld_hid = P.ld;
         wq = pk + P.w_qkv;
         wp = pk + P.w_proj;
         w1 = pk + P.w_fc1;

@@ -3,6 +3,10 @@ the header declares, and rejects bad arguments before touching a device."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
+
+import pytest
 
 import paper_2508_00367_amd as rs
 from paper_2508_00367_amd import binding
@@ -312,3 +316,46 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         binding.lib()
     with pytest.raises(ImportError):
         rs.rs_version()
+
+
+def _workspace_bytes(B, N, D, Dm, dtype):
+    """The scratch tensors of a block, each rounded up to 256 bytes: weights as packed (bf16), LN(x), qkv, attention
+    output, x', hidden activations, shift sums, scores, row statistics."""
+    up = lambda n: (n + 255) // 256 * 256
+    e, M = (2 if dtype == rs.RS_BF16 else 4), B * N
+    packed = 0
+    if dtype == rs.RS_BF16:
+        packed = sum(map(up, (6 * D * D, 2 * D * D, 2 * D * Dm, 2 * D * Dm, 12 * D, 12 * D, 4 * Dm, 4 * Dm)))
+    return packed + sum(map(up, (M * D * e, 3 * M * D * e, M * D * e, M * D * e, M * Dm * e, 3 * M * (D // 64) * 4, M * 4, M * 8)))
+
+
+def test_workspace_size_counts_no_padding():
+    """The pitch the kernels choose for the hidden activations is their own business: it takes no more scratch, so that
+    a block that fits the static buffer goes on fitting it."""
+    for B, N, D, Dm in [(1, 1, 64, 64), (3, 7, 64, 512), (1, 1, 64, 4096), (130, 131, 192, 768), (41, 197, 384, 1536),
+                        (17, 200, 768, 3072), (15, 135, 1024, 4096), (1, 14, 1664, 6656), (1, 5, 4096, 512)]:
+        for dtype in (rs.RS_F32, rs.RS_BF16):
+            cfg = rs.make_cfg(B, N, D, D // 64, Dm, 0, N, dtype)
+            assert rs.rs_block_workspace_size(cfg) == _workspace_bytes(B, N, D, Dm, dtype), (B, N, D, Dm, dtype)
+
+
+STATIC_CALL = """
+import ctypes, sys
+import paper_2508_00367_amd as rs
+from paper_2508_00367_amd import binding
+B, N, D = map(int, sys.argv[1:])
+cfg = rs.make_cfg(B, N, D, D // 64, 4 * D, 1, N - 2, rs.RS_BF16)
+w = binding.RsBlockWeights()
+for name, _ in binding.RsBlockWeights._fields_:
+    setattr(w, name, 0x1000)
+print(rs.lib().rs_block_fwd_static(ctypes.byref(cfg), ctypes.byref(w), 0x1000, 0x2000, 0x3000, None, None))
+"""
+
+
+@pytest.mark.parametrize("B,N,D", [(130, 131, 192), (41, 197, 384), (17, 200, 768), (15, 135, 1024)])
+def test_static_scratch_takes_the_blocks_that_fill_it(B, N, D):
+    """In a process that sees no GPU: the call gets as far as the device (RS_ERR_DEVICE) and is not refused for its size."""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1", PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", STATIC_CALL, str(B), str(N), str(D)], capture_output=True, text=True, env=env,
+                       cwd=ROOT, timeout=120)
+    assert r.returncode == 0 and r.stdout.split()[-1] == str(rs.RS_ERR_DEVICE), (r.stdout, r.stderr[-300:])
