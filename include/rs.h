@@ -105,7 +105,8 @@ typedef struct {
  * (static storage, never NULL). */
 RS_API const char *rs_last_error(void);
 
-/* Library version as major*10000 + minor*100 + patch. */
+/* Library version as major*10000 + minor*100 + patch.  Buffers that rs_pack_weights has written are valid for the
+ * version that wrote them and must be packed again for another one (300: wider row pitch of W_fc2). */
 RS_API int32_t rs_version(void);
 
 /* Host string (static storage): the tile configurations the matrix kernels were built with.
@@ -201,7 +202,8 @@ RS_API rs_status rs_shift_topk(const void *f_out, const void *f_in, const void *
  * One-off re-layout of a block's four weight matrices for the matrix-core
  * GEMMs (weights are static at inference; the method is training-free).
  * `packed_out` must hold rs_packed_weights_size(cfg) bytes and is then passed
- * as rs_block_weights.packed.  Only cfg->D, Dm, dtype are read.
+ * as rs_block_weights.packed.  Only cfg->D, Dm, dtype are read.  The layout is this library
+ * version's own: a program that keeps the buffer in a file keeps rs_version() with it and packs again when that differs.
  */
 RS_API size_t rs_packed_weights_size(const rs_block_cfg *cfg);
 RS_API rs_status rs_pack_weights(const rs_block_cfg *cfg, const rs_block_weights *w,

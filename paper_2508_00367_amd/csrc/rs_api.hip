@@ -227,7 +227,7 @@ extern "C" {
 
 const char* rs_last_error(void) { return g_err; }
 
-int32_t rs_version(void) { return 200; }
+int32_t rs_version(void) { return 300; }
 
 const char* rs_build_info(void) { return gemm_build_info(); }
 

@@ -359,3 +359,14 @@ def test_static_scratch_takes_the_blocks_that_fill_it(B, N, D):
     r = subprocess.run([sys.executable, "-c", STATIC_CALL, str(B), str(N), str(D)], capture_output=True, text=True, env=env,
                        cwd=ROOT, timeout=120)
     assert r.returncode == 0 and r.stdout.split()[-1] == str(rs.RS_ERR_DEVICE), (r.stdout, r.stderr[-300:])
+
+
+def test_packed_layout_has_a_version_of_its_own():
+    """W_fc2 with one extra line per row (Dm >= 512, Dm % 256 == 0): a program tells such buffers from older ones by
+    rs_version(), which was 200 while the rows lay Dm elements apart."""
+    plain = lambda D, Dm: (4 * D * D + 2 * D * Dm) * 2 + 2 * (3 * D + Dm) * 4
+    for D, Dm in [(192, 768), (768, 3072), (64, 512)]:
+        assert rs.rs_packed_weights_size(_cfg(D=D, H=D // 64, Dm=Dm)) == plain(D, Dm) + D * 64 * 2
+        assert rs.rs_version() >= 300
+    for D, Dm in [(64, 256), (192, 576), (128, 448)]:
+        assert rs.rs_packed_weights_size(_cfg(D=D, H=D // 64, Dm=Dm)) == plain(D, Dm)
