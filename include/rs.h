@@ -202,8 +202,9 @@ RS_API rs_status rs_shift_topk(const void *f_out, const void *f_in, const void *
  * One-off re-layout of a block's four weight matrices for the matrix-core
  * GEMMs (weights are static at inference; the method is training-free).
  * `packed_out` must hold rs_packed_weights_size(cfg) bytes and is then passed
- * as rs_block_weights.packed.  Only cfg->D, Dm, dtype are read.  The layout is this library
- * version's own: a program that keeps the buffer in a file keeps rs_version() with it and packs again when that differs.
+ * as rs_block_weights.packed.  Only cfg->D, Dm, dtype are read.  Every byte of the buffer is written, the
+ * same ones for the same weights.  The layout is this library version's own: a program that keeps the buffer in a file
+ * keeps rs_version() with it and packs again when that differs.
  */
 RS_API size_t rs_packed_weights_size(const rs_block_cfg *cfg);
 RS_API rs_status rs_pack_weights(const rs_block_cfg *cfg, const rs_block_weights *w,

@@ -227,7 +227,7 @@ hipError_t launch_attn_unpack(const void* oh, void* o, int B, int H, int N, int6
                               hipStream_t s);
 
 // bf16 [K, N] row-major -> [N, K] row-major; with `gamma` ([K] bf16) row k is scaled by gamma[k]
-// (product rounded to bf16).
+// (product rounded to bf16).  ld: elements between the rows of wt (0 = K); those past K are written as zeros.
 hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld = 0);
 // colsum[n] = sum_k bf16(gamma[k] * w[k][n]),  bias_out[n] = sum_k beta[k] * w[k][n] + bias[n]
 // (w [K, N] bf16; gamma, beta, bias bf16 or null = 1, 0, 0; outputs fp32).

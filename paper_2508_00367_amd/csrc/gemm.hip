@@ -1145,14 +1145,15 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16raw* __re
     __syncthreads();
     for (int r = ty; r < 64; r += 4) {
         const int n = n0 + r, k = k0 + tx;
-        if (n < N && k < K) wt[(int64_t)n * ld + k] = tile[tx][r];
+        if (n < N && k < ld) wt[(int64_t)n * ld + k] = tile[tx][r];  // zeros past K
     }
 }
 
 hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld) {
-    dim3 grid((N + 63) / 64, (K + 63) / 64);
+    ld = ld ? ld : K;
+    dim3 grid((N + 63) / 64, (ld + 63) / 64);
     hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, (const bf16raw*)w, (const bf16raw*)gamma,
-                       (bf16raw*)wt, K, N, ld ? ld : K);
+                       (bf16raw*)wt, K, N, ld);
     return hipGetLastError();
 }
 

@@ -77,3 +77,16 @@ def test_static_buffer_filled_to_the_end(B, N, D):
         outs.append((y.view(torch.int16), kept, scores))
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("D,Dm", [(64, 64), (64, 512), (192, 768), (128, 576)])
+def test_packed_buffer_is_whole(D, Dm):
+    """Every byte is written, so that two buffers packed from the same weights are the same."""
+    print("packed buffer", D, Dm, flush=True)
+    w, _ = _block(1, 1, D, Dm)
+    cfg = rs.make_cfg(1, 1, D, D // 64, Dm, 0, 1, torch.bfloat16)
+    bufs = [torch.full((rs.rs_packed_weights_size(cfg),), fill, device="cuda", dtype=torch.uint8) for fill in (0x5A, 0xA5)]
+    for b in bufs:
+        rs.rs_pack_weights(cfg, rs.make_weights(w), b)
+    torch.cuda.synchronize()
+    assert torch.equal(*bufs)
