@@ -520,7 +520,11 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
 // 4 x 197 x 3 and 45 us at 64 x 197 x 3, where one query row per thread took 148 and 168 us.
 // ---------------------------------------------------------------------------
 constexpr int F32_BN = 32;
+constexpr int64_t F32_FAR = (int64_t)1 << 27;  // row stride (elements) at which four rows leave 32-bit byte offsets
 
+// FAR: rows F32_FAR elements apart and more; a tile's rows then pass through registers, each read at its own
+// 64-bit address.  Everything behind the copies is the same.
+template <bool FAR>
 __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     float* __restrict__ o, int N, int64_t sb, int64_t sn, int64_t sh, int64_t osb, int64_t osn,
@@ -539,13 +543,20 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     const int q0 = blockIdx.x * 32;
     const int KT = (N + F32_BN - 1) / F32_BN;
 
-    // copy i brings rows 4 i .. 4 i + 3 of a tile through a resource of its own (64-bit base, so that the
-    // row stride is limited by four rows only); rows past N read as zeros
-    const int sn4 = (int)(sn * 4);
+    // copy i brings rows 4 i .. 4 i + 3 of a tile through a resource of its own (64-bit base, so that only
+    // four rows have to lie within 32-bit offsets); rows past N read as zeros
+    const int sn4 = FAR ? 0 : (int)(sn * 4);
     const int k_voff = (lane >> 4) * sn4;
 #define F32_COPY(dst_, src_, kt_, CHUNK)                                                                          \
     _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                               \
         const int row_ = (kt_) * F32_BN + 4 * i, rows_ = min(N - row_, 4);                                        \
+        if constexpr (FAR) {                                                                                      \
+            f32x4 t_ = {0.f, 0.f, 0.f, 0.f};                                                                      \
+            if ((lane >> 4) < rows_)                                                                              \
+                t_ = *reinterpret_cast<const f32x4*>((src_) + base + (row_ + (lane >> 4)) * sn + ((CHUNK) << 2)); \
+            *reinterpret_cast<f32x4*>((dst_)[wave] + i * 1024 + lane * 16) = t_;                                  \
+            continue;                                                                                             \
+        }                                                                                                         \
         const __amdgpu_buffer_rsrc_t rs_ = __builtin_amdgcn_make_buffer_rsrc(                                     \
             const_cast<float*>((src_) + base + (rows_ > 0 ? (int64_t)row_ * sn : 0)), 0,                          \
             rows_ > 0 ? (rows_ - 1) * sn4 + DH * 4 : 0, 0x00020000);                                              \
@@ -704,8 +715,8 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
                                osh, scale_log2e, H, q_tiles * bm);
     } else {
         dim3 grid((N + 31) / 32, H, B);
-        hipLaunchKernelGGL(attention_f32_kernel, grid, dim3(256), 0, s, (const float*)q,
-                           (const float*)k, (const float*)v, (float*)o, N, sb, sn, sh, osb, osn, osh,
+        hipLaunchKernelGGL(sn < F32_FAR ? attention_f32_kernel<false> : attention_f32_kernel<true>, grid, dim3(256), 0, s,
+                           (const float*)q, (const float*)k, (const float*)v, (float*)o, N, sb, sn, sh, osb, osn, osh,
                            scale_log2e);
     }
     return hipGetLastError();

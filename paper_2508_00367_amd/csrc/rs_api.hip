@@ -290,9 +290,6 @@ rs_status rs_attention_fwd(const void* q, const void* k, const void* v, void* o,
     // up to 256 rows past the last one (those read as zeros)
     RS_REQUIRE(dtype != RS_BF16 || ((int64_t)N + 256) * stride_n * 2 < (int64_t)0x7fffffff, RS_ERR_UNSUPPORTED,
                "(N + 256) * stride_n * 2 bytes must stay below 2 GiB for bf16 attention");
-    // the fp32 kernel addresses four rows at a time
-    RS_REQUIRE(dtype != RS_F32 || stride_n < (int64_t)1 << 27, RS_ERR_UNSUPPORTED,
-               "stride_n must stay below 2^27 elements for fp32 attention");
     RS_LAUNCH_K(K_ATTN, (hipStream_t)hip_stream, launch_attention(dtype, q, k, v, o, B, H, N, stride_b, stride_n, stride_h, o_stride_b,
                                o_stride_n, o_stride_h, scale, (hipStream_t)hip_stream));
     return RS_OK;

@@ -370,3 +370,21 @@ def test_packed_layout_has_a_version_of_its_own():
         assert rs.rs_version() >= 300
     for D, Dm in [(64, 256), (192, 576), (128, 448)]:
         assert rs.rs_packed_weights_size(_cfg(D=D, H=D // 64, Dm=Dm)) == plain(D, Dm)
+
+
+FAR_CALL = """
+import ctypes, sys
+import paper_2508_00367_amd as rs
+i64 = ctypes.c_int64
+s = int(sys.argv[1])
+p = [ctypes.c_void_p(0x1000 * i) for i in (1, 2, 3, 4)]
+print(rs.lib().rs_attention_fwd(*p, 1, 1, 3, 64, i64(0), i64(s), i64(64), i64(0), i64(64), i64(64), ctypes.c_float(0.125), rs.RS_F32, None))
+"""
+
+
+@pytest.mark.parametrize("stride", [(1 << 27) - 8, 1 << 27, 1 << 34])
+def test_fp32_attention_has_no_stride_limit(stride):
+    """In a process that sees no GPU: the call gets as far as the device."""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1", PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", FAR_CALL, str(stride)], capture_output=True, text=True, env=env, cwd=ROOT, timeout=120)
+    assert r.returncode == 0 and r.stdout.split()[-1] == str(rs.RS_ERR_DEVICE), (r.stdout, r.stderr[-300:])

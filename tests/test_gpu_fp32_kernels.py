@@ -95,3 +95,22 @@ def test_fp32_attention_masked_keys(masked, N, how):
     err = norm_err(to_host(o), ref)
     _say("  err %.2e" % err)
     assert err < TOL["f32"]
+
+
+@pytest.mark.parametrize("stride", [(1 << 27) - 8, 1 << 27, (1 << 27) + 8])
+@pytest.mark.parametrize("N", [1, 3, 37])
+def test_fp32_attention_far_rows(N, stride):
+    """Token strides around 2^27 elements (four rows beyond 32-bit byte offsets): the bits of the same rows side by side."""
+    _say("fp32 attention far rows", N, stride)
+    rows = to_dev(si.generic(46, 1, (1, N, 3, 1, 64)), "f32")
+    buf = torch.empty(((N - 1) * stride + 192,), device="cuda")
+    far = buf.as_strided((1, N, 3, 1, 64), (0, stride, 64, 64, 1))
+    far.copy_(rows)
+    outs = []
+    for d in (rows, far):
+        o = torch.full((1, N + 1, 1, 64), float("nan"), device="cuda")
+        rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o[:, :N], 0.125)
+        torch.cuda.synchronize()
+        assert torch.isnan(o[:, N]).all() and torch.isfinite(o[:, :N]).all()
+        outs.append(o[:, :N])
+    assert torch.equal(*outs)
