@@ -273,7 +273,11 @@ hipError_t launch_gather_stats(const void* src, const int32_t* kept_idx, void* o
                                int K, int D, float eps, hipStream_t s);
 
 // scores, kept_idx and gathered = f_in[kept_idx] of every image in one launch that reads f_out and
-// f_in once (images whose f_in rows fit a compute unit's registers: shift_topk_resident_fits)
+// f_in once (images whose f_in rows fit a compute unit's registers, shift_topk_resident_form, and enough of
+// them, shift_topk_resident_fits); its scores for any number of images: launch_shift_scores_paired
+bool shift_topk_resident_form(rs_dtype dt, int N, int D);
+hipError_t launch_shift_scores_paired(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in, float* scores, int64_t M,
+                                      int D, hipStream_t s);
 bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D);
 hipError_t launch_shift_topk_resident(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in,
                                       float* scores, int32_t* kept_idx, void* gathered, int B, int N, int D,

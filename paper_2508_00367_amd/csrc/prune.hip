@@ -646,15 +646,86 @@ static int resident_cus() {
     return cus;
 }
 
+// The scores of the one-pass kernel, bit for bit, by a grid over the rows: which kernel an image goes through depends on
+// how many there are, and its scores must not.  A lane takes 16 bytes of a row, that is the bytes of lanes 2 sub
+// and 2 sub + 1 of the one-pass kernel's wave, and keeps their two sums apart up to the butterfly's last step.  G lanes
+// per row (the next power of two of its 16-byte vectors, at most 32), CH vectors of each.  The whole call with the scores
+// in shift_scores_kernel's order / in this one: 1 x 197 x 384 6.8 / 7.0 us, 16 x 197 x 768 8.0 / 8.0, 128: 22.6 / 22.1, 64 x 197 x 64
+// 8.5 / 7.4 (four rows per thread: 8.2, and 15.0 instead of 14.5 at 64 x 197 x 768).
+template <typename T, int DIST, int G, int CH>
+__global__ __launch_bounds__(256) void shift_scores_paired_kernel(const T* __restrict__ f_out, const T* __restrict__ f_in,
+                                                                  float* __restrict__ scores, int64_t M, int row_vec) {
+    const int sub = threadIdx.x % G;
+    const int64_t row = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G;
+    const u32x4 *a = reinterpret_cast<const u32x4*>(f_out), *b = reinterpret_cast<const u32x4*>(f_in);
+    u32x4 x[CH], y[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const bool on = row < M && sub + c * G < row_vec;
+        x[c] = on ? a[row * row_vec + sub + c * G] : u32x4{0u, 0u, 0u, 0u};
+        y[c] = on ? b[row * row_vec + sub + c * G] : u32x4{0u, 0u, 0u, 0u};
+    }
+    float p[2][3] = {};
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float fx[4], fy[4];
+            unpack8<T>(u32x2{x[c][2 * h], x[c][2 * h + 1]}, fx);
+            unpack8<T>(u32x2{y[c][2 * h], y[c][2 * h + 1]}, fy);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dist_term<DIST>(fx[e], fy[e], p[h][0], p[h][1], p[h][2]);
+        }
+#pragma unroll
+    for (int i = 0; i < (DIST == RS_DIST_COS ? 3 : 1); ++i)
+#pragma unroll
+        for (int off = G / 2; off >= 1; off >>= 1) {
+            p[0][i] += __shfl_xor(p[0][i], off, kWave);
+            p[1][i] += __shfl_xor(p[1][i], off, kWave);
+        }
+    if (sub == 0 && row < M) scores[row] = dist_value<DIST>(p[0][0] + p[1][0], p[0][1] + p[1][1], p[0][2] + p[1][2]);
+}
+
+template <typename T>
+static hipError_t launch_paired_t(rs_dist dist, const void* f_out, const void* f_in, float* scores, int64_t M, int D, hipStream_t s) {
+    const int row_vec = (int)((size_t)D * sizeof(T) / 16);
+#define RS_PAIRED(DIST_, G_, CH_)                                                                                      \
+    hipLaunchKernelGGL((shift_scores_paired_kernel<T, DIST_, G_, CH_>), dim3((unsigned)((M + 256 / G_ - 1) / (256 / G_))), \
+                       dim3(256), 0, s, (const T*)f_out, (const T*)f_in, scores, M, row_vec)
+#define RS_PAIRED_D(DIST_)                                                                                             \
+    if (row_vec <= 8) RS_PAIRED(DIST_, 8, 1);                                                                          \
+    else if (row_vec <= 16) RS_PAIRED(DIST_, 16, 1);                                                                   \
+    else if (row_vec <= 32) RS_PAIRED(DIST_, 32, 1);                                                                   \
+    else if (row_vec <= 64) RS_PAIRED(DIST_, 32, 2);                                                                   \
+    else RS_PAIRED(DIST_, 32, 3);
+    if (dist == RS_DIST_L2) { RS_PAIRED_D(RS_DIST_L2) }
+    else if (dist == RS_DIST_L1) { RS_PAIRED_D(RS_DIST_L1) }
+    else { RS_PAIRED_D(RS_DIST_COS) }
+#undef RS_PAIRED_D
+#undef RS_PAIRED
+    return hipGetLastError();
+}
+
+hipError_t launch_shift_scores_paired(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in, float* scores, int64_t M,
+                                      int D, hipStream_t s) {
+    if (M == 0) return hipSuccess;
+    return dt == RS_F32 ? launch_paired_t<float>(dist, f_out, f_in, scores, M, D, s)
+                        : launch_paired_t<bf16raw>(dist, f_out, f_in, scores, M, D, s);
+}
+
+// Sequences that fit the one-pass kernel, however many.
+bool shift_topk_resident_form(rs_dtype dt, int N, int D) { return N <= RES_MAXN && (size_t)D * elem_size(dt) <= 512 * 3; }
+
 // Where the one-pass kernel is the faster way.  Its workgroup holds one image whatever its length and
 // works through it serially, so it needs images that fill the registers (more than half of the rows it
-// has room for) and rounds of the chip that are at least three quarters full; otherwise the
-// three launches, each spread over all rows, win although they read the kept rows twice.  bf16, D 768,
-// one pass / three launches in us: 197 tokens 16 images 25.4 / 10.2, 128: 30.2 / 28.7, 192: 34.5 / 38.3,
-// 256: 39.3 / 47.7, 320: 72.7 / 61.2, 512: 101 / 95, 1024: 193 / 220; 64 tokens 256: 24.1 / 20.1, 1024: 84 / 63.
-// (D 192 and 384 cross at the same places.)
+// has room for) and rounds of the chip that are at least three quarters full; otherwise the separate
+// launches, each spread over all rows, win although they read the kept rows twice.  bf16, nine tenths kept, one pass /
+// separate launches in us: 197 x 768 192 images 33.5 / 36.9, 256: 38.7 / 47.2, 384: 82.7 / 72.8, 512: 102 / 98, 576: 132 / 125,
+// 640: 133 / 145, 768: 148 / 170, 1024: 195 / 221, 2048: 367 / 421 (between one round and two and a half the inputs no
+// longer fit the caches, and the line at three quarters is too low by up to 13 %); 197 x 384 192: 23.4 / 22.2, 256: 25.2 / 27.5;
+// 150 x 768 256: 33.1 / 37.1, 110 x 768 256: 29.0 / 29.0, 1024: 124 / 124; below, 16 x 197 x 768 25.4 / 8.0.
 bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D) {
-    if (N > RES_MAXN || (size_t)D * elem_size(dt) > 512 * 3) return false;
+    if (!shift_topk_resident_form(dt, N, D)) return false;
     const int64_t cus = resident_cus(), rounds = (B + cus - 1) / cus;
     return 2 * N > RES_MAXN && 4 * (int64_t)B >= 3 * rounds * cus;
 }

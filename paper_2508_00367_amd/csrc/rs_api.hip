@@ -399,13 +399,17 @@ rs_status rs_shift_topk(const void* f_out, const void* f_in, const void* src, in
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
     const int K = n_prefix + n_keep;
-    if (gathered && s == f_in && K > 0 && shift_topk_resident_fits(dtype, B, N, D)) {
+    const bool one_pass_form = gathered && s == f_in && K > 0 && shift_topk_resident_form(dtype, N, D);
+    if (one_pass_form && shift_topk_resident_fits(dtype, B, N, D)) {
         // many small images: one pass over memory, the rows to keep never leave the registers
         RS_LAUNCH_K(K_SCORE, st, launch_shift_topk_resident(dtype, dist, f_out, f_in, scores, kept_idx, gathered, B, N, D,
                                                           n_prefix, n_keep, st));
         return RS_OK;
     }
-    RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * N, D, st));
+    if (one_pass_form)  // the bits an image gets do not depend on how many there are
+        RS_LAUNCH_K(K_SCORE, st, launch_shift_scores_paired(dtype, dist, f_out, f_in, scores, (int64_t)B * N, D, st));
+    else
+        RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * N, D, st));
     if (gathered && n_keep > 0 && n_keep < N - n_prefix) {  // selection and gather in one launch
         if (select_gather_long_fits(dtype, B, N, D)) {
             RS_LAUNCH_K(K_GATHER, st, launch_select_gather_long(dtype, scores, kept_idx, s, gathered, nullptr, B, N, n_prefix, n_keep, D, 0.f, st));

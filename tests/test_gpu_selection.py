@@ -105,3 +105,29 @@ def test_block_prune_step(B, N, D, P, K, dtype):
     idx = kept.long()[:, :, None]
     assert torch.equal(y, torch.take_along_dim(y_all, idx, dim=1))
     assert torch.equal(stats, torch.take_along_dim(stats_all, idx, dim=1))
+
+
+# images whose rows fit the one-pass kernel's registers: up to 16, 32 and 64 16-byte vectors and beyond, odd ones among them
+@pytest.mark.parametrize("dist", [rs.RS_DIST_L2, rs.RS_DIST_L1, rs.RS_DIST_COS])
+@pytest.mark.parametrize("N,D,dtype", [(105, 8, "bf16"), (130, 64, "bf16"), (197, 72, "bf16"), (208, 136, "bf16"), (197, 192, "bf16"),
+                                       (197, 384, "bf16"), (119, 520, "bf16"), (197, 768, "bf16"), (105, 8, "f32"), (197, 40, "f32"),
+                                       (208, 64, "f32"), (197, 192, "f32"), (130, 264, "f32"), (197, 384, "f32")])
+def test_an_image_does_not_depend_on_the_batch(N, D, dtype, dist):
+    """The one-pass kernel (256 images) and the separate launches (3, 1): the same scores, survivors and rows, bit for bit."""
+    print("batch", N, D, dtype, dist, flush=True)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(N + D)
+    f_in = torch.randn((256, N, D), device="cuda", generator=g).to(t)
+    f_out = (f_in.float() * 1.1 + 0.3 * torch.randn((256, N, D), device="cuda", generator=g)).to(t)
+    outs = []
+    for B in (256, 3, 1):
+        scores = torch.full((B, N), float("nan"), device="cuda")
+        kept = torch.full((B, N // 2), -1, device="cuda", dtype=torch.int32)
+        rows = torch.zeros((B, N // 2, D), device="cuda", dtype=t)
+        rs.rs_shift_topk(f_out[:B], f_in[:B], None, 1, N // 2 - 1, scores, kept, rows, dist=dist)
+        torch.cuda.synchronize()
+        outs.append((scores, kept, rows))
+    for B, out in zip((3, 1), outs[1:]):
+        for a, b in zip(outs[0], out):
+            assert torch.equal(a[:B], b)
+    assert not torch.isnan(outs[0][0]).any()
