@@ -291,7 +291,7 @@ hipError_t launch_grid_gather(rs_dtype dt, const void* src, const int32_t* kept_
                               void* out, int B, int H, int W, int R, int Q, int C, hipStream_t s);
 
 // line scores and both selections in one launch (grid_line_select_fits)
-bool grid_line_select_fits(int H, int W);
+bool grid_line_select_fits(int B, int H, int W);
 hipError_t launch_grid_line_select(const float* scores, float* row_scores, float* col_scores, int32_t* kept_rows,
                                    int32_t* kept_cols, int B, int H, int W, int R, int Q, hipStream_t s);
 // token-wise grid pruning in two launches (grid_token_fused_fits): scores, kept_cols and (unless null) the

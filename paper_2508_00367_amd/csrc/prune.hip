@@ -1174,8 +1174,9 @@ __global__ __launch_bounds__(512) void grid_line_select_kernel(const float* __re
         if (pos[r] >= 0) out[pos[r]] = r * 64 + lane;
 }
 
-bool grid_line_select_fits(int H, int W) {
-    return H <= GRID_LINE && W <= GRID_LINE && (size_t)H * W * sizeof(float) <= GRID_LDS - 4096;
+// A launch holds less than 2^32 threads (one beyond that is refused or, worse, runs modulo 2^32): 2^23 workgroups of 512.
+bool grid_line_select_fits(int B, int H, int W) {
+    return H <= GRID_LINE && W <= GRID_LINE && (size_t)H * W * sizeof(float) <= GRID_LDS - 4096 && B < 1 << 23;
 }
 
 hipError_t launch_grid_line_select(const float* scores, float* row_scores, float* col_scores, int32_t* kept_rows,

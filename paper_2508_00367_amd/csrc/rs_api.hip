@@ -451,7 +451,7 @@ rs_status rs_grid_line_prune(const void* f_out, const void* f_in, const void* sr
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
     RS_LAUNCH_K(K_SCORE, st, launch_shift_scores(dtype, dist, f_out, f_in, scores, (int64_t)B * H * W, C, st));
-    if (grid_line_select_fits(H, W)) {
+    if (grid_line_select_fits(B, H, W)) {
         RS_LAUNCH_K(K_SELECT, st, launch_grid_line_select(scores, row_scores, col_scores, kept_rows, kept_cols, B, H, W,
                                                         keep_rows, keep_cols, st));
     } else {

@@ -1,0 +1,25 @@
+"""Calls of so many small items that a launch reaches 2^32 threads: the largest the fused kernels take, the first that goes
+through the separate launches, and the largest those take.  A position's score is the same everywhere, so the
+whole of every output is known."""
+import pytest
+import torch
+
+import paper_2508_00367_amd as rs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B", [(1 << 23) - 1, 1 << 23, (1 << 24) - 1])
+def test_grid_lines_of_many_maps(B):
+    print("grid lines", B, flush=True)
+    f_in = torch.zeros((B, 1, 2, 8), device="cuda", dtype=torch.bfloat16)
+    f_out = torch.ones_like(f_in)
+    scores, row_scores, col_scores = (torch.full((B, n), -1.0, device="cuda") for n in (2, 1, 2))
+    kept_rows, kept_cols = (torch.full((B, 1), -1, device="cuda", dtype=torch.int32) for _ in range(2))
+    gathered = torch.zeros((B, 1, 1, 8), device="cuda", dtype=torch.bfloat16)
+    rs.rs_grid_line_prune(f_out, f_in, None, 1, 1, scores.view(B, 1, 2), row_scores, col_scores, kept_rows, kept_cols, gathered,
+                          dist=rs.RS_DIST_L1)
+    torch.cuda.synchronize()
+    for t in (scores, row_scores, col_scores):
+        assert (t == 8.0).all()
+    assert (kept_rows == 0).all() and (kept_cols == 0).all() and (gathered == 1).all()
