@@ -296,7 +296,7 @@ hipError_t launch_grid_line_select(const float* scores, float* row_scores, float
                                    int32_t* kept_cols, int B, int H, int W, int R, int Q, hipStream_t s);
 // token-wise grid pruning in two launches (grid_token_fused_fits): scores, kept_cols and (unless null) the
 // compacted col_scores; then kept_rows and (unless null) the gathered map
-bool grid_token_fused_fits(int64_t B, int H, int W);
+bool grid_token_fused_fits(int64_t B, int H, int W, int Q);
 hipError_t launch_grid_row_select(rs_dtype dt, rs_dist dist, const void* f_out, const void* f_in, float* scores,
                                   int32_t* kept_cols, float* col_scores, int B, int H, int W, int C, int Q, hipStream_t s);
 hipError_t launch_grid_col_gather(rs_dtype dt, const void* src, const int32_t* kept_cols, const float* col_scores,

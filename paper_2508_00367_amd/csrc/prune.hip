@@ -1313,7 +1313,12 @@ __global__ __launch_bounds__(256) void grid_row_select_kernel(const T* __restric
     else select(std::integral_constant<int, 4>{});
 }
 
-bool grid_token_fused_fits(int64_t B, int H, int W) { return H <= GRID_LINE && W <= GRID_LINE && B * H < (int64_t)1 << 30; }
+// Both launches round their workgroups of 256 (a grid row each; four columns each) up to a multiple of 8 and hold less
+// than 2^32 threads.
+bool grid_token_fused_fits(int64_t B, int H, int W, int Q) {
+    constexpr int64_t most = ((int64_t)1 << 24) - 8;
+    return H <= GRID_LINE && W <= GRID_LINE && B * H <= most && B * ((Q + 3) / 4) <= most;
+}
 
 template <typename T, int DIST>
 static hipError_t launch_grid_row_select_t(const void* f_out, const void* f_in, float* scores, int32_t* kept_cols,

@@ -487,7 +487,7 @@ rs_status rs_grid_token_prune(const void* f_out, const void* f_in, const void* s
                "tensors must be 16-byte aligned");
     RS_REQUIRE(gathered == nullptr || gathered != s, RS_ERR_INVALID_ARG, "gathered must not alias src");
     hipStream_t st = (hipStream_t)hip_stream;
-    if (keep_cols > 0 && grid_token_fused_fits(B, H, W)) {
+    if (keep_cols > 0 && grid_token_fused_fits(B, H, W, keep_cols)) {
         RS_LAUNCH_K(K_SCORE, st, launch_grid_row_select(dtype, dist, f_out, f_in, scores, kept_cols,
                                                       keep_rows > 0 ? col_scores : nullptr, B, H, W, C, keep_cols, st));
         if (keep_rows > 0)

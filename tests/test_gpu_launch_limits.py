@@ -23,3 +23,17 @@ def test_grid_lines_of_many_maps(B):
     for t in (scores, row_scores, col_scores):
         assert (t == 8.0).all()
     assert (kept_rows == 0).all() and (kept_cols == 0).all() and (gathered == 1).all()
+
+
+@pytest.mark.parametrize("B,H", [((1 << 24) - 8, 1), ((1 << 24) - 7, 1), ((1 << 23) - 1, 2), ((1 << 24) - 1, 1)])
+def test_grid_tokens_of_many_rows(B, H):
+    print("grid tokens", B, H, flush=True)
+    f_in = torch.zeros((B, H, 2, 8), device="cuda", dtype=torch.bfloat16)
+    f_out = torch.ones_like(f_in)
+    scores, col_scores = torch.full((B, H, 2), -1.0, device="cuda"), torch.full((B, 1, H), -1.0, device="cuda")
+    kept_cols, kept_rows = (torch.full(s, -1, device="cuda", dtype=torch.int32) for s in ((B, H, 1), (B, 1, 1)))
+    gathered = torch.zeros((B, 1, 1, 8), device="cuda", dtype=torch.bfloat16)
+    rs.rs_grid_token_prune(f_out, f_in, None, 1, 1, scores, kept_cols, col_scores, kept_rows, gathered, dist=rs.RS_DIST_L1)
+    torch.cuda.synchronize()
+    assert (scores == 8.0).all() and (col_scores == 8.0).all()
+    assert (kept_rows == 0).all() and (kept_cols == 0).all() and (gathered == 1).all()
