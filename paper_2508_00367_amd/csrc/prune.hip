@@ -724,8 +724,10 @@ bool shift_topk_resident_form(rs_dtype dt, int N, int D) { return N <= RES_MAXN 
 // 640: 133 / 145, 768: 148 / 170, 1024: 195 / 221, 2048: 367 / 421 (between one round and two and a half the inputs no
 // longer fit the caches, and the line at three quarters is too low by up to 13 %); 197 x 384 192: 23.4 / 22.2, 256: 25.2 / 27.5;
 // 150 x 768 256: 33.1 / 37.1, 110 x 768 256: 29.0 / 29.0, 1024: 124 / 124; below, 16 x 197 x 768 25.4 / 8.0.
+// From 2^26 rows on the separate launches would reach 2^32 threads (a wave per gathered row), its own never does.
 bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D) {
     if (!shift_topk_resident_form(dt, N, D)) return false;
+    if ((int64_t)B * N >= (int64_t)1 << 26) return true;
     const int64_t cus = resident_cus(), rounds = (B + cus - 1) / cus;
     return 2 * N > RES_MAXN && 4 * (int64_t)B >= 3 * rounds * cus;
 }

@@ -37,3 +37,22 @@ def test_grid_tokens_of_many_rows(B, H):
     torch.cuda.synchronize()
     assert (scores == 8.0).all() and (col_scores == 8.0).all()
     assert (kept_rows == 0).all() and (kept_cols == 0).all() and (gathered == 1).all()
+
+
+@pytest.mark.parametrize("B,N,D", [((1 << 20) - 1, 64, 264), (1 << 20, 64, 264), ((1 << 20) + 1, 64, 264), (1 << 26, 1, 512)])
+def test_topk_of_many_images(B, N, D):
+    """Short images of long rows, 35 GB and more per tensor."""
+    print("topk", B, N, D, flush=True)
+    f_in = torch.zeros((B, N, D), device="cuda", dtype=torch.bfloat16)
+    f_out = torch.zeros_like(f_in)
+    f_out[:, :, 0] = 1.0
+    f_out[:, N // 2, 0] = 2.0
+    scores = torch.full((B, N), -1.0, device="cuda")
+    kept = torch.full((B, 1), -1, device="cuda", dtype=torch.int32)
+    gathered = torch.full((B, 1, D), 3.0, device="cuda", dtype=torch.bfloat16)
+    rs.rs_shift_topk(f_out, f_in, None, 0, 1, scores, kept, gathered, dist=rs.RS_DIST_L1)
+    torch.cuda.synchronize()
+    assert (scores[:, N // 2] == 2.0).all() and (scores == 1.0).sum() == B * (N - 1)
+    assert (kept == N // 2).all() and (gathered == 0.0).all()
+    del f_in, f_out, scores, kept, gathered
+    torch.cuda.empty_cache()
