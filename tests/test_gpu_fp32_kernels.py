@@ -114,3 +114,26 @@ def test_fp32_attention_far_rows(N, stride):
         assert torch.isnan(o[:, N]).all() and torch.isfinite(o[:, :N]).all()
         outs.append(o[:, :N])
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("where", ["q", "k", "v"])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_fp32_attention_special_values(where, value):
+    """One NaN or infinity: the rows it reaches are those of the softmax written out, all others are as without it."""
+    B, N, H, n, c = 1, 140, 2, 77, 9
+    _say("fp32 attention special", where, value)
+    qkv = si.generic(47, 1, (B, N, 3, H, 64))
+    qkv[0, n, "qkv".index(where), 1, c] = value
+    with np.errstate(invalid="ignore", over="ignore"):
+        q, k, v = (qkv[:, :, i].astype(np.float64).transpose(0, 2, 1, 3) for i in range(3))
+        s = q @ k.transpose(0, 1, 3, 2) * 0.125
+        p = np.exp(s - np.max(s, axis=-1, keepdims=True))
+        ref = (p @ v / p.sum(axis=-1, keepdims=True)).transpose(0, 2, 1, 3)
+    d = to_dev(qkv, "f32")
+    o = torch.full((B, N, H, 64), 7.0, device="cuda")
+    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
+    torch.cuda.synchronize()
+    got, fin = to_host(o), np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), fin) and np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    assert norm_err(got[fin], ref[fin]) < TOL["f32"]
