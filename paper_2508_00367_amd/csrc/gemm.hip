@@ -701,11 +701,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     constexpr int STAGE = (BM + BN) * RB;
     constexpr bool RES = epi_res(EPI);
     static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split evenly over the wave copies");
-    static_assert(NST >= 2 && NST <= 4, "ring of two to four stages");
+    static_assert(NST == 3 || NST == 4, "ring of three or four stages");
+    static_assert(NW % 2 == 0, "the parity of a copy's rows >> 3 is that of its wave");
     static_assert(LPW * (NST - 1) <= 63, "copies in flight must fit the counter");
     __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
-    __shared__ __attribute__((aligned(1024))) unsigned char st2[NST >= 3 ? STAGE : 16];
+    __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st3[NST == 4 ? STAGE : 16];
     // residual rows requested up front when there is room for them next to the ring
     constexpr bool PRE_RES = RES && NST * STAGE + NW * TM * 4096 <= 160 * 1024;
@@ -731,18 +732,17 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     }
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
     const int l32 = lane & 31, g = lane >> 5;
     const int m_base = m0 + wm * WM, n_base = n0 + wn * WN;
 
     // LDS layout as in gemm_bf16_kernel: chunk c of row r in slot c ^ (r & 7) ^ ((r >> 3) & 1).  Wave copy i of
-    // wave w fills rows (NW i + w) 8 .. + 7; with an odd number of waves the parity of row >> 3 depends on i.
+    // wave w fills rows (NW i + w) 8 .. + 7 (NW is even, so row >> 3 has the parity of w).
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
     const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
     const int ld_r = lane >> 3, ld_p = lane & 7;
-    const int voff0 = ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
-    const int voff1 = NW == 1 ? (ld_r * ld + ((ld_p ^ ld_r ^ 1) << 3)) * 2 : voff0;
+    const int voff = ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
     const int pass_bytes = NW * RPI * ld * 2;
     const int S = K / 64;
     const int a_row0 = wm * WM + l32, w_row0 = wn * WN + l32;
@@ -753,9 +753,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
         const bool real_ = (t_) < S;                                                                      \
         const int kb_ = (t_) * RB;                                                                        \
         _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i)                                               \
-            dma16(rs_a, (stage_) + (i * NW + wave) * 1024, (i & 1) ? voff1 : voff0, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+            dma16(rs_a, (stage_) + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
         _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i)                                               \
-            dma16(rs_w, (stage_) + BM * RB + (i * NW + wave) * 1024, (i & 1) ? voff1 : voff0, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+            dma16(rs_w, (stage_) + BM * RB + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
     }
 #define RS_SLIM_FRAGS(f_, stage_, kk_)                                                                    \
     {                                                                                                     \
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
 #define RS_SLIM_WAIT(n_)                                                                                  \
     {                                                                                                     \
         __builtin_amdgcn_s_waitcnt(((n_) & 15) | (((n_) >> 4) << 14) | 0x0070);                           \
-        if (NW > 1) __builtin_amdgcn_s_barrier();                                                         \
+        __builtin_amdgcn_s_barrier();                                                                     \
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); /* LDS reads stay below the barrier */     \
         __builtin_amdgcn_sched_barrier(0);                                                                \
     }
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     __builtin_amdgcn_sched_barrier(0);
     RS_SLIM_DMA(st0, 0)
     RS_SLIM_DMA(st1, 1)
-    if constexpr (NST >= 3) RS_SLIM_DMA(st2, 2)
+    RS_SLIM_DMA(st2, 2)
     if constexpr (NST == 4) RS_SLIM_DMA(st3, 3)
 
     f32x16 acc[TN][TM];
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     // Whole trips of the ring, then the slices that are left (fewer than a trip; all of them have been
     // requested by then).  No way out inside a trip: every exit would keep its own copy of the accumulators,
     // and the compiler would lose track of which copies a stage's reads wait for.
-    constexpr int TRIP = NST == 3 ? 6 : NST;
+    constexpr int TRIP = NST == 3 ? 6 : 4;
     const int full = S / TRIP * TRIP;
     if constexpr (NST == 3) {
         for (int t = 0; t < full; t += 6) {
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
             if (left > 3) RS_SLIM_SLICE(st0, st1, f1, f0, full + 3)
             if (left > 4) RS_SLIM_SLICE(st1, st2, f0, f1, full + 4)
         }
-    } else if constexpr (NST == 4) {
+    } else {
         for (int t = 0; t < full; t += 4) {
             RS_SLIM_SLICE(st0, st1, f0, f1, t)
             RS_SLIM_SLICE(st1, st2, f1, f0, t + 1)
@@ -871,15 +871,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
                 if (left > 2) RS_SLIM_ALL_MFMA(f0)
             }
         }
-    } else {
-        for (int t = 0; t < full; t += 2) {
-            RS_SLIM_SLICE(st0, st1, f0, f1, t)
-            RS_SLIM_SLICE(st1, st0, f1, f0, t + 1)
-        }
-        if (S > full) RS_SLIM_ALL_MFMA(f0)
     }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & 0xC07F);  // trailing (empty) copies and reads: the stages get reused
-    if (!PRE_RES && NW > 1) __builtin_amdgcn_s_barrier();
+    if (!PRE_RES) __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if constexpr (RES && !PRE_RES) epi_request_residual<TM>(reg, res, M, N, m_base, n_base, lane);
     if constexpr (!PRE_VEC) vec.load(bias, ln, M, N, m_base, n_base, lane);
