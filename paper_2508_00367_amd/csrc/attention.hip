@@ -405,7 +405,6 @@ __global__ __launch_bounds__(512, 2) void attention_bf16_tail_kernel(
 // LDS: K and V rows of 128 bytes in the tiled kernel's two slot orders (att_swz, att_vswz).
 // ---------------------------------------------------------------------------
 constexpr int SM_MAXN = 256;
-constexpr int SM_SPLIT_WGS = 256;  // one per CU
 
 __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
     const bf16raw* __restrict__ q, const bf16raw* __restrict__ k, const bf16raw* __restrict__ v,
@@ -690,7 +689,7 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
         // per SIMD (each copies the whole K and V): 1 image x 6 heads x 197 tokens 8.3 -> 7.0 us, 10 x 12 x 197 8.7
         // -> 7.6; with two on some CUs it costs more than it gives (16 x 12 x 197 9.2 / 9.5, 21 x 12 x 256 11.2 /
         // 13.3).  A row's arithmetic is the same either way.
-        const int q_waves = N > 128 && (int64_t)B * H * 2 <= SM_SPLIT_WGS ? 4 : 8;
+        const int q_waves = N > 128 && (int64_t)B * H * 2 <= device_cus() ? 4 : 8;
         hipLaunchKernelGGL(attention_bf16_small_kernel, dim3(H, B, q_waves == 4 ? 2 : 1), dim3(512), 0, s, (const bf16raw*)q,
                            (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh,
                            scale_log2e, q_waves);

@@ -114,6 +114,8 @@ void set_error(const char* fmt, ...);
 rs_status device_error(const char* what, hipError_t e);
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// compute units of the device in use at the first call (256 where there is none to ask)
+int device_cus();
 inline size_t elem_size(rs_dtype t) { return t == RS_F32 ? 4 : 2; }
 
 // ---- kernel launchers (one per .hip file) -----------------------------------

@@ -901,7 +901,7 @@ struct GemmCfg {
     static constexpr int WN = BN / WGN;
 };
 
-static int device_cus() {
+int device_cus() {
     static const int cus = [] {
         int dev = 0, n = 0;
         if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;

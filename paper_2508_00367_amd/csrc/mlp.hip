@@ -316,17 +316,17 @@ __global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restric
 // A workgroup's time does not depend on how many there are (30 us at Dm = 768) until every CU has one, that of the
 // separate launches does: two blocks in a row (no token dropped) take 127 / 123 us fused / separate at 12608 rows,
 // 135 / 136 at 14184, 142 / 146 at 16548, 153 / 178 at 22064, 461 / 583 at 100864.  Below the line a workgroup
-// each for half of the 256 CUs.  A forced tile variant runs the separate launches.
-constexpr int64_t kMlpMinRows = 128 * kMlpRows;
+// each for half of the CUs.  A forced tile variant runs the separate launches.
+static int64_t mlp_min_rows() { return (int64_t)(device_cus() / 2) * kMlpRows; }
 
 bool mlp_fused_fits(rs_dtype dt, int64_t M, int D, int Dm) {
-    return dt == RS_BF16 && D == kMlpD && Dm % (3 * kMlpChunk) == 0 && Dm <= kMlpMaxDm && gemm_variant() == 0 && M >= kMlpMinRows;
+    return dt == RS_BF16 && D == kMlpD && Dm % (3 * kMlpChunk) == 0 && Dm <= kMlpMaxDm && gemm_variant() == 0 && M >= mlp_min_rows();
 }
 
-// Two blocks in a row against the tiled GEMM (us): 16548 rows 143 / 142, 25216 154 / 157, 50432 241 / 252, 100864 433 / 458;
-// at 12608 rows, where a workgroup's nine steps are the whole launch, 135 / 124.
+// Two blocks in a row against the tiled GEMM (us): 25216 rows 154 / 157, 50432 241 / 252, 100864 433 / 458, the same at 16548 (143 / 142);
+// at 12608 rows, where a workgroup's nine steps are the whole launch, 135 / 124.  The line is that of the MLP kernel.
 bool qkv_rows_fits(rs_dtype dt, int64_t M, int D, int N) {
-    return dt == RS_BF16 && D == kMlpD && N % 64 == 0 && N <= kQkvMaxN && gemm_variant() == 0 && M >= kMlpMinRows;
+    return dt == RS_BF16 && D == kMlpD && N % 64 == 0 && N <= kQkvMaxN && gemm_variant() == 0 && M >= mlp_min_rows();
 }
 
 hipError_t launch_qkv_rows(const void* x, const void* w, GemmLnFold ln, void* out, int64_t M, int N, float eps, hipStream_t s) {

@@ -637,15 +637,6 @@ __global__ __launch_bounds__(RES_WAVES * 64) void shift_topk_resident_kernel(
     }
 }
 
-static int resident_cus() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 // The scores of the one-pass kernel, bit for bit, by a grid over the rows: which kernel an image goes through depends on
 // how many there are, and its scores must not.  A lane takes 16 bytes of a row, that is the bytes of lanes 2 sub
 // and 2 sub + 1 of the one-pass kernel's wave, and keeps their two sums apart up to the butterfly's last step.  G lanes
@@ -728,7 +719,7 @@ bool shift_topk_resident_form(rs_dtype dt, int N, int D) { return N <= RES_MAXN 
 bool shift_topk_resident_fits(rs_dtype dt, int B, int N, int D) {
     if (!shift_topk_resident_form(dt, N, D)) return false;
     if ((int64_t)B * N >= (int64_t)1 << 26) return true;
-    const int64_t cus = resident_cus(), rounds = (B + cus - 1) / cus;
+    const int64_t cus = device_cus(), rounds = (B + cus - 1) / cus;
     return 2 * N > RES_MAXN && 4 * (int64_t)B >= 3 * rounds * cus;
 }
 
@@ -750,7 +741,7 @@ hipError_t launch_shift_topk_resident(rs_dtype dt, rs_dist dist, const void* f_o
                                       float* scores, int32_t* kept_idx, void* gathered, int B, int N, int D,
                                       int n_prefix, int n_keep, hipStream_t s) {
     if (B == 0 || N == 0) return hipSuccess;
-    const int cus = resident_cus();
+    const int cus = device_cus();
     const int grid = B < cus ? B : cus;  // one workgroup fills a compute unit's register file
     const int ch = (int)(((size_t)D * elem_size(dt) + 511) / 512);
 #define RS_RES_CH(T_)                                                                                                   \
@@ -1010,17 +1001,15 @@ __global__ __launch_bounds__(SGL_WAVES * 64) void select_gather_long_kernel(
 // One workgroup per CU over all sequences (two, measured: 4 x 4097 x 1024 28.1 -> 30.2 us, 64 x 300 x 192 11.1 -> 12.4).
 // Score, selection and gather in two launches / three (us): 8 x 1569 x 768 fp32 25.1 / 26.5, 4 x 4097 x 1024 28.1 /
 // 30.1, 20 x 1000 x 768 21.6 / 25.0, 64 x 500 x 768 28.3 / 30.1; beyond, fewer than four workgroups share a sequence's copy.
-constexpr int SGL_WGS = 256;
-
 bool select_gather_long_fits(rs_dtype dt, int B, int N, int D) {
-    return N > 256 && N <= SEL_MAXN / 2 && (size_t)D * elem_size(dt) <= 4 * 1024 && 4 * B <= resident_cus();
+    return N > 256 && N <= SEL_MAXN / 2 && (size_t)D * elem_size(dt) <= 4 * 1024 && 4 * B <= device_cus();
 }
 
 hipError_t launch_select_gather_long(rs_dtype dt, const float* scores, int32_t* kept_idx, const void* src, void* out,
                                      float* stats, int B, int N, int n_prefix, int n_keep, int D, float eps, hipStream_t s) {
     if (B == 0) return hipSuccess;
     const int K = n_prefix + n_keep, row_vec = (int)((size_t)D * elem_size(dt) / 16);
-    int parts = SGL_WGS / B;
+    int parts = device_cus() / B;
     parts = parts < (K + SGL_WAVES - 1) / SGL_WAVES ? parts : (K + SGL_WAVES - 1) / SGL_WAVES;
     const bool st = stats && dt == RS_BF16;
     const size_t lds = (size_t)(N + K) * 4;

@@ -415,8 +415,9 @@ rs_status rs_shift_topk(const void* f_out, const void* f_in, const void* src, in
             RS_LAUNCH_K(K_GATHER, st, launch_select_gather_long(dtype, scores, kept_idx, s, gathered, nullptr, B, N, n_prefix, n_keep, D, 0.f, st));
             return RS_OK;
         }
-        // short images: 1 x 197 x 384 6.7 / 8.0 us, 16 x 197 x 768 7.9 / 9.7, 128: 23.0 / 25.3, but 512: 95.8 / 93.4 (the
-        // gather alone then has enough rows in flight to run at the memory's pace)
+        // short images, one launch / two (whole call, us): 1 x 197 x 384 6.7 / 8.0, 128 x 197 x 768 26.7 / 29.3, 256: 52.3 / 53.8, but
+        // 320: 75.8 / 72.5, 512: 123 / 117 (the gather alone then has enough rows in flight to run at the memory's pace).  Shorter
+        // rows cross later (384 values at 448 images, 64 tokens not up to 768): the line is that of the longest.
         if (B <= 256 && select_gather_fits(dtype, N, D)) {
             RS_LAUNCH_K(K_GATHER, st, launch_select_gather(dtype, dist, nullptr, 0, scores, kept_idx, s, gathered, nullptr, B, N,
                                                            n_prefix, n_keep, D, 0.f, st));
