@@ -177,8 +177,15 @@ def main():
     instr_ms_per_step = (time.perf_counter() - t0) / a.steps * 1e3
     rs.rs_profile_enable(False)
 
-    # algorithmic work per step, per kernel class
+    # algorithmic work per step, per kernel class.  Blocks of narrow tokens and many rows run their whole MLP as one
+    # launch, counted as fc2 (no fc1 launch, no statistics pass): the largest ones
     fl = stack_flops(stack)
+    n_fused = (prof["gemm_fc2"][1] - prof["gemm_fc1"][1]) // a.steps
+    fused = set(sorted(range(L), key=lambda l: -sched[l][0])[:n_fused])
+    for l in fused:
+        moved = 2.0 * B * sched[l][0] * D * Dm
+        fl["gemm_fc1"] -= moved
+        fl["gemm_fc2"] += moved
     by = {k: 0.0 for k in ("attention", "layernorm", "prune")}
     slots = D // 64                                    # score partial sums per row left by the GEMM epilogue
     for l, (n_in, n_keep) in enumerate(sched):
@@ -188,7 +195,7 @@ def main():
         # the one in front of the attention only in the first block, later blocks get the statistics the
         # block before them left for its output: from its gather when it prunes, else from a pass over y
         prunes = n_keep < n_in - P
-        n_stat = M * (2 if l == 0 else 1) + (B * (P + n_keep) if (not prunes and l + 1 < L) else 0)
+        n_stat = 0 if l in fused else M * (2 if l == 0 else 1) + (B * (P + n_keep) if (not prunes and l + 1 < L) else 0)
         by["layernorm"] += n_stat * (D * e + 8.0)
         if prunes:                                     # partial sums in, scores + kept_idx out, gather of K rows (+ their statistics)
             K = P + n_keep
