@@ -17,6 +17,8 @@
 // Row max / row sum need one exchange between the two half-waves per tile.
 //
 // fp32 path (v_mfma_f32_32x32x2_f32, parity configuration): the same transposed form.
+#include <float.h>
+
 #include "common.hpp"
 
 namespace rs {
@@ -580,7 +582,10 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    // Keys masked by -inf or a very low value may be all that a wave's first tile holds.  The maximum starts at the
+    // lowest value whose multiple by the scale, rounded, is still within 128 of the exact one: such keys weigh 0 (from
+    // -inf - -inf or from a lower maximum, whose rounding error alone would overflow the exponential, they would be NaN)
+    float m_run = fmaxf(-0x1p32f * __builtin_amdgcn_rcpf(scale_log2e), -FLT_MAX), l_run = 0.f;
 
     for (int kt = wave; kt < KT; kt += 4) {
         f32x16 sacc;
@@ -605,11 +610,9 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        // While every score this wave has seen is -inf (keys masked through a channel or an overflow: its first tile may
-        // hold nothing else) the maximum is -inf too: the exponents are taken from 0 then, so that such keys weigh 0.
-        const float m_new = fmaxf(m_run, mx), m_exp = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_exp) * scale_log2e);
-        const float mb = m_exp * scale_log2e;
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+        const float mb = m_new * scale_log2e;
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll

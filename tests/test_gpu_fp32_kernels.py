@@ -67,27 +67,28 @@ MASKED = {"first": range(0, 32), "second": range(32, 64), "third": range(64, 96)
           "all_but_one": [i for i in range(161) if i != 70], "all": range(161)}
 
 
-@pytest.mark.parametrize("how", ["infinite", "overflow"])
+@pytest.mark.parametrize("how", ["infinite", "overflow", "large scale"])
 @pytest.mark.parametrize("N", [128, 129, 161])
 @pytest.mark.parametrize("masked", list(MASKED))
 def test_fp32_attention_masked_keys(masked, N, how):
     """Keys masked through a reserved channel: -inf in k, or a product that overflows, against the fp64 softmax."""
     B, H = 2, 2
+    scale = 2.0 if how == "large scale" else 0.125
     _say("fp32 attention masked", masked, N, how)
     keys = [i for i in MASKED[masked] if i < N]
     qkv = si.generic(45, 1, (B, N, 3, H, 64))
-    qkv[:, :, 0, :, 63], qkv[:, :, 1, :, 63] = (1.0 if how == "infinite" else 2.0), 0.0
+    qkv[:, :, 0, :, 63], qkv[:, :, 1, :, 63] = (2.0 if how == "overflow" else 1.0), 0.0
     seen = np.setdiff1d(np.arange(N), keys)
     ref = np.full((B, N, H, 64), np.nan)
     if len(seen):
         q, k, v = (qkv[:, :, i].astype(np.float64).transpose(0, 2, 1, 3) for i in range(3))
-        s = q @ k[:, :, seen].transpose(0, 1, 3, 2) * 0.125
+        s = q @ k[:, :, seen].transpose(0, 1, 3, 2) * scale
         p = np.exp(s - s.max(axis=-1, keepdims=True))
         ref = (p @ v[:, :, seen] / p.sum(axis=-1, keepdims=True)).transpose(0, 2, 1, 3)
-    qkv[:, keys, 1, :, 63] = -np.inf if how == "infinite" else -3e38
+    qkv[:, keys, 1, :, 63] = -3e38 if how == "overflow" else -np.inf
     d = to_dev(qkv, "f32")
     o = torch.full((B, N, H, 64), 7.0, device="cuda")
-    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
+    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, scale)
     torch.cuda.synchronize()
     if not len(seen):
         assert torch.isnan(o).all()
@@ -137,3 +138,26 @@ def test_fp32_attention_special_values(where, value):
     assert np.array_equal(np.isfinite(got), fin) and np.array_equal(np.isnan(got), np.isnan(ref))
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
     assert norm_err(got[fin], ref[fin]) < TOL["f32"]
+
+
+@pytest.mark.parametrize("value", [-1e4, -1e9, -1e10, -1e11, -1e30, float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("N,masked", [(31, range(0, 22)), (128, range(0, 127)), (128, range(96, 128)), (161, range(32, 64)),
+                                      (161, range(0, 96)), (200, [*range(0, 40), *range(64, 200)])])
+def test_fp32_attention_low_values_as_a_mask(N, masked, value):
+    """Low finite values through a reserved channel swallow the rest of a score: such keys weigh nothing beside others."""
+    B, H = 2, 2
+    _say("fp32 attention low value", N, masked, value)
+    qkv = si.generic(48, 1, (B, N, 3, H, 64))
+    qkv[:, :, 0, :, 63], qkv[:, :, 1, :, 63] = 1.0, 0.0
+    seen = np.setdiff1d(np.arange(N), list(masked))
+    q, k, v = (qkv[:, :, i].astype(np.float64).transpose(0, 2, 1, 3) for i in range(3))
+    s = q @ k[:, :, seen].transpose(0, 1, 3, 2) * 0.125
+    p = np.exp(s - s.max(axis=-1, keepdims=True))
+    ref = (p @ v[:, :, seen] / p.sum(axis=-1, keepdims=True)).transpose(0, 2, 1, 3)
+    qkv[:, list(masked), 1, :, 63] = value
+    d = to_dev(qkv, "f32")
+    o = torch.full((B, N, H, 64), 7.0, device="cuda")
+    rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
+    torch.cuda.synchronize()
+    err = norm_err(to_host(o), ref)
+    assert err < TOL["f32"]
