@@ -67,15 +67,15 @@ def parse():
 # figure is carried here together with the build string it was measured under; a library built with
 # other tile configurations gets no carried figure.
 _MEASURED_BUILD = ("bf16 gemm: persistent tiles (BM,BN,BK,stages,waves m,waves n) 256, 256, 64, 2, 2, 4, three activation stages "
-                   "when K >= 2048; ring tiles 128x256x32 and 128x128x32, 3 stages, 4 waves, 2 workgroups per CU, up to 0.5 rounds "
-                   "(1.5 if K <= 512); rows behind whole rounds go to a ring kernel when K >= 2048 and the last round is under "
-                   "0.5 full")
+                   "when K >= 2048; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU (256x128 up to 1.45 rounds "
+                   "of 256x256 when K < 2048); ring tiles 128x128x32 and 128x256x32 beyond one round when K <= 384; rows behind whole "
+                   "rounds apart when K >= 2048 and the last round is at most 0.5 full")
 MEASURED_HBM_BYTES_PER_LAUNCH = {
     # (workload, unpruned, kernel class): (bytes per layer launch, rs_build_info() of the measured build)
-    ("vit_b16", False, "gemm_fc1"): (575.0e6, _MEASURED_BUILD),
-    ("vit_b16", False, "gemm_fc2"): (576.2e6, _MEASURED_BUILD),   # persistent kernel + ring kernel of the layer
-    ("vit_b16", False, "gemm_qkv"): (448.6e6, _MEASURED_BUILD),
-    ("vit_b16", False, "gemm_proj"): (235.8e6, _MEASURED_BUILD),
+    ("vit_b16", False, "gemm_fc1"): (574.3e6, _MEASURED_BUILD),
+    ("vit_b16", False, "gemm_fc2"): (588.3e6, _MEASURED_BUILD),   # persistent kernel + slim kernel of the layer
+    ("vit_b16", False, "gemm_qkv"): (445.0e6, _MEASURED_BUILD),
+    ("vit_b16", False, "gemm_proj"): (247.2e6, _MEASURED_BUILD),
 }
 
 

@@ -321,7 +321,7 @@ RS_API rs_status rs_block_fwd_chained(const rs_block_cfg *cfg, const rs_block_we
  * device code: every GPU the library runs on holds its own copy from the first use until the
  * process ends.  The call allocates nothing and frees nothing.
  *   - cfg must satisfy rs_block_workspace_size(cfg) <= rs_block_static_scratch_size(), else
- *     RS_ERR_UNSUPPORTED (a ViT-B/16 block in bf16 fits up to 16 images of 197 tokens; larger
+ *     RS_ERR_UNSUPPORTED (a ViT-B/16 block in bf16 fits up to 17 images of 197 tokens; larger
  *     batches go through rs_block_fwd).
  *   - x, y, kept_idx, scores: as in rs_block_fwd, caller-owned.
  *   - All calls on one GPU share that GPU's buffer: calls that overlap in time on one GPU (two

@@ -170,7 +170,7 @@ constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine al
 // tile are requested together, and when the pitch is a multiple of 512 bytes they meet in a few of the
 // L2's channels.  One extra line per row spreads them: 768 x 3072 at 50432 rows 252 -> 243 us, at 3152 rows
 // 26.5 -> 23.7, 384 x 1536 at 12608 rows 24.8 -> 23.0 (128, 192 or 256 extra elements: the same; 32 or less
-// split lines and cost 5-30 %).  vit_s16 -1.1 %, video_vit_b16 -1.8 % per forward, vit_b16 -0.4 %.  (The attention
+// split lines and cost 5-30 %).  vit_s16 -1.1 %, video_vit_b16 -1.8 % per forward, vit_b16 within noise.  (The attention
 // output and W_proj, padded the same way: no change.)
 // Rows under 1 KB stay as they are: such a GEMM has at most four slices of K, and the padding would be a quarter of W_fc2.
 inline int padded_ld(int K) { return K >= 512 && K % 256 == 0 ? K + 64 : K; }

@@ -7,11 +7,10 @@
 // four consecutive hidden features of ONE token per register quad; one half-wave exchange per pair of
 // registers (v_permlane32_swap) turns them into the B operand of fc2, so there is no trip through LDS either.
 //
-// Measured at 100864 x 192 x 768: 89 us against 145 us for the launches it replaces (statistics 13, fc1 77, fc2 55).
-// What bounds it is issue: per step and wave 24 MFMAs (768 cycles) and some 230 plain and 32 transcendental
-// instructions (1300 cycles), which do not overlap, neither within a wave (interleaving them by hand: no
-// change) nor between the two waves of a SIMD.  Without the GELU it would take 65 us, without two thirds of the LDS
-// reads 85, without the copies of the weights 89.
+// Measured at 100864 x 192 x 768 inside a block (events on the stream): 114 us against 162 us for the launches it
+// replaces (statistics 15, fc1 76, fc2 71).  What bounds it is issue: per step and wave 24 MFMAs and some 230 plain and
+// 32 transcendental instructions; the counters show the matrix cores busy 28 % of the cycles, other
+// instructions 47 %, both at once 11 % (LDS conflicts 1 %).  Interleaving the two by hand: no change.
 #include "gemm_tile.hpp"
 
 namespace rs {
@@ -231,8 +230,9 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
 // The QKV layer behind its LayerNorm for the same narrow tokens: 128 rows per workgroup stay in registers, the weights
 // pass by in two LDS stages of 64 features, and every step ends with its 64 columns of the output.  A row is read once
 // whatever the output width, nothing is computed for columns that do not exist (576 = 2.25 tiles of 256), and
-// the statistics come from the registers when the caller has none.  100864 x 576 x 192: 57 -> 47 us (155 MB: 32 us at
-// the copy rate; with the wait for a step's stores inside the next step 50).
+// the statistics come from the registers when the caller has none.  100864 x 576 x 192 inside a block: 49 us, statistics
+// included, against 57 and 15 for theirs (155 MB: 32 us at the copy rate); the wait for a step's stores inside
+// the next step costs 3 us.
 constexpr int kQkvMaxN = 1024;
 __global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restrict__ x, const bf16raw* __restrict__ w, GemmLnFold ln,
                                                         bf16raw* __restrict__ out, float eps, int M, int D, int N) {
