@@ -257,6 +257,8 @@ def test_shift_topk(dtype, dist, B, N, D, P, K):
 # Images whose rows fit a compute unit's registers take the one-pass kernel when the rows to gather
 # are f_in's own (src NULL): rows per wave from 1 to 13, row chunks of 1, 2 and 3 x 512 bytes with
 # ragged ends, more images than workgroups (the grid is persistent), prefix-only and keep-all.
+# images that fit the one-pass kernel but are too few for it: the separate launches, scores in its order (the kernel
+# itself: test_one_pass_kernel in test_gpu_selection.py)
 RESIDENT_CASES = [  # B, N, D, n_prefix, n_keep
     (3, 17, 64, 1, 7), (4, 197, 768, 1, 177), (2, 208, 384, 0, 100), (300, 33, 192, 1, 20), (2, 1, 8, 1, 0),
     (2, 197, 192, 1, 196), (3, 100, 520, 2, 0), (2, 16, 256, 0, 16), (1, 207, 760, 1, 1)]
@@ -267,7 +269,7 @@ RESIDENT_CASES = [  # B, N, D, n_prefix, n_keep
 @pytest.mark.parametrize("B,N,D,P,K", RESIDENT_CASES)
 def test_shift_topk_one_pass(dtype, dist, B, N, D, P, K):
     if dtype == "f32" and D * 4 > 1536:
-        pytest.skip("fp32 rows beyond 1536 bytes take the three-launch path (covered by test_shift_topk)")
+        pytest.skip("fp32 rows beyond 1536 bytes do not fit the kernel (covered by test_shift_topk)")
     _say("shift_topk one pass", dtype, dist, B, N, D, P, K)
     f_in = host_round(si.tokens(3, B, N, D, spread=0.5), dtype)
     f_out = host_round(f_in + si.generic(3, 8, (B, N, D), std=0.3) * np.exp(si.generic(3, 9, (B, N, 1), std=0.7)), dtype)
@@ -280,7 +282,7 @@ def test_shift_topk_one_pass(dtype, dist, B, N, D, P, K):
     np.testing.assert_array_equal(kept, oracle.topk(s, P, K))           # exact on the GPU's own scores, every image
     check_kept_admissible(kept[sample], s[sample], s_ref, P, K)
     np.testing.assert_array_equal(g, oracle.gather(f_in, kept))         # every image: a copy of the kept rows
-    # the three-launch path (taken when the rows come from another tensor) agrees
+    # rows from another tensor: scores in the order of the row-per-wave kernel
     s3, kept3, g3 = _run_shift_topk(f_out, f_in, f_in.copy(), P, K, dist, dtype)
     assert np.abs(s3 - s).max() <= 1e-6 * max(np.abs(s).max(), 1.0)
     same = (kept3 == kept).all(axis=1)

@@ -151,7 +151,7 @@ def test_block_prune_step_in_two_launches(B, N, D, P, K, dtype):
     (192, 197, 192, 1, 196, "bf16"), (255, 130, 256, 0, 130, "bf16"), (192, 207, 760, 1, 1, "bf16"), (192, 197, 384, 1, 177, "f32"),
     (449, 105, 8, 0, 1, "f32"), (192, 160, 264, 2, 158, "f32")])
 def test_one_pass_kernel(B, N, D, P, K, dtype, dist):
-    """Against the checker: a sample of the scores (fp32 sums of D terms; 1 - cos carries a few ulps of 1), every image's
+    """Against the oracle: a sample of the scores (fp32 sums of D terms; 1 - cos carries a few ulps of 1), every image's
     survivors exact on the call's own scores, every kept row."""
     print("one pass kernel", B, N, D, P, K, dtype, dist, flush=True)
     f_in = host_round(si.tokens(5, B, N, D, spread=0.5), dtype)
