@@ -1,4 +1,4 @@
-// Which bf16 GEMM kernel takes which rows of a problem: host arithmetic only, no HIP.
+// Which GEMM kernel takes which rows of a problem: host arithmetic only, no HIP.
 #pragma once
 
 #include <stdint.h>
@@ -44,5 +44,9 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
     const int64_t m1 = rounds * cus / ((N + 255) / 256) * 256;  // row panels that fill whole rounds: fewer than all of them
     return {GemmTile::Persistent, m1 > 0 ? m1 : M};
 }
+
+// fp32: the rows of one launch, in whole tiles of `bm` x 64: it has 256 threads per tile, tiles rounded up to a multiple of
+// 8, and holds less than 2^32 of them.
+inline int64_t gemm_f32_launch_rows(int N, int bm) { return (((int64_t)1 << 24) - 8) / ((N + 63) / 64) * bm; }
 
 }  // namespace rs

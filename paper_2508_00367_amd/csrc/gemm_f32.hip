@@ -20,6 +20,7 @@
 // Two kernels: 32 x 64 tiles with K split over the waves (three stages, 48 KB of LDS in all) for grids that
 // leave CUs idle, and 64 x 64 tiles shared by the waves (gemm_f32_wide_kernel) for those that fill the chip.
 #include "common.hpp"
+#include "gemm_choice.hpp"
 
 namespace rs {
 
@@ -344,15 +345,19 @@ static hipError_t launch_t(const void* a, const void* w, const void* bias, const
                            const void* ref, bool post, int64_t M, int N, int K, hipStream_t s) {
     const int tiles_n = N / 64;
     const bool wide = ((M + 63) / 64) * tiles_n >= (K <= 384 ? 512 : 1024);
-    const int64_t tiles_m = wide ? (M + 63) / 64 : (M + 31) / 32, nblk = tiles_m * tiles_n;
-    if (nblk >= (int64_t)1 << 31) return hipErrorInvalidValue;
-    auto go = [&](auto* kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), 0, s, (const float*)a, (const float*)w,
-                           (const float*)bias, (const float*)res, (float*)out, partials, (const float*)ref, post ? 1 : 0, (int)M,
-                           N, K, (int)tiles_m, tiles_n);
-    };
-    if (wide) go(&gemm_f32_wide_kernel<EPI, DIST>);
-    else go(&gemm_f32_kernel<EPI, DIST>);
+    const int bm = wide ? 64 : 32;
+    const int64_t rows = gemm_f32_launch_rows(N, bm);
+    if (partials && M > rows) return hipErrorInvalidValue;  // the sums' slots lie M apart: one launch (rows of 4096 values at most)
+    for (int64_t r = 0; r < M; r += rows) {
+        const int64_t m = M - r < rows ? M - r : rows, tiles_m = (m + bm - 1) / bm, nblk = tiles_m * tiles_n;
+        auto go = [&](auto* kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), 0, s, (const float*)a + r * K,
+                               (const float*)w, (const float*)bias, res ? (const float*)res + r * N : nullptr, (float*)out + r * N,
+                               partials, ref ? (const float*)ref + r * N : nullptr, post ? 1 : 0, (int)m, N, K, (int)tiles_m, tiles_n);
+        };
+        if (wide) go(&gemm_f32_wide_kernel<EPI, DIST>);
+        else go(&gemm_f32_kernel<EPI, DIST>);
+    }
     return hipGetLastError();
 }
 

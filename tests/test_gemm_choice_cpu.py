@@ -44,6 +44,15 @@ int main() {
                     ++problems;
                 }
     }
+    for (int64_t n = 64; n <= (1 << 20); n += 64)
+        for (int bm : {32, 64}) {
+            const int64_t rows = rs::gemm_f32_launch_rows((int)n, bm), tiles = rows / bm * (n / 64);
+            const bool full = tiles + n / 64 > (1 << 24) - 8;   // one more row of tiles would be too many
+            if (rows < bm || rows % bm || (tiles + 7) / 8 * 8 * 256 >= (int64_t)1 << 32 || !full) {
+                printf("fp32 N %lld tiles of %d rows: %lld rows per launch\n", (long long)n, bm, (long long)rows);
+                return 1;
+            }
+        }
     printf("ok %ld\n", problems);
     return 0;
 }
