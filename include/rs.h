@@ -80,8 +80,8 @@ typedef struct {
     const void *w_fc1, *b_fc1;     /* [D, Dm], [Dm]       */
     const void *w_fc2, *b_fc2;     /* [Dm, D], [D]        */
     /* Optional: buffer of rs_packed_weights_size() bytes filled by rs_pack_weights()
-     * from the tensors above: the four matrices as [out, in], with the LayerNorm scales
-     * folded into W_qkv and W_fc1 (rounded to bf16), plus the fp32 column sums and the
+     * from the tensors above: the four matrices in the order the matrix instructions
+     * read them (32 x 16 fragments of 1 KB), with the LayerNorm scales folded into W_qkv and W_fc1 (rounded to bf16), plus the fp32 column sums and the
      * biases beta W + b those two GEMMs need to apply the normalisation in their
      * epilogues.  It depends on every pointer above except b_proj and b_fc2: re-pack when
      * any of them changes.  NULL = the library re-packs into the workspace on every
@@ -106,7 +106,7 @@ typedef struct {
 RS_API const char *rs_last_error(void);
 
 /* Library version as major*10000 + minor*100 + patch.  Buffers that rs_pack_weights has written are valid for the
- * version that wrote them and must be packed again for another one (300: wider row pitch of W_fc2). */
+ * version that wrote them and must be packed again for another one (400: fragments in place of rows). */
 RS_API int32_t rs_version(void);
 
 /* Host string (static storage): the tile configurations the matrix kernels were built with.

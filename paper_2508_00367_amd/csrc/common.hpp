@@ -165,27 +165,27 @@ void set_gemm_variant(int v);
 int gemm_shift_slots(rs_dtype dt, int N);
 constexpr int kShiftLanes = 3;  // sums per slot (L2/L1 use the first, cosine all three)
 
-// Row pitch (elements) of the MLP's hidden activations and of the W_fc2 a caller has packed (a block that packs on every
-// call keeps the plain pitch for both): the rows of an operand
+// Row pitch (elements) of the MLP's hidden activations in a block whose caller has packed the weights (one that packs on
+// every call keeps the plain pitch, its scratch has no room for another): the rows of an operand
 // tile are requested together, and when the pitch is a multiple of 512 bytes they meet in a few of the
 // L2's channels.  One extra line per row spreads them: 768 x 3072 at 50432 rows 252 -> 243 us, at 3152 rows
 // 26.5 -> 23.7, 384 x 1536 at 12608 rows 24.8 -> 23.0 (128, 192 or 256 extra elements: the same; 32 or less
-// split lines and cost 5-30 %).  vit_s16 -1.1 %, video_vit_b16 -1.8 % per forward, vit_b16 within noise.  (The attention
-// output and W_proj, padded the same way: no change.)
-// Rows under 1 KB stay as they are: such a GEMM has at most four slices of K, and the padding would be a quarter of W_fc2.
+// split lines and cost 5-30 %), measured with W_fc2 in rows of the same pitch.  (The attention output, padded the
+// same way: no change.)  Rows under 1 KB stay as they are: such a GEMM has at most four slices of K.
 inline int padded_ld(int K) { return K >= 512 && K % 256 == 0 ? K + 64 : K; }
 
-// out[M, N] = epilogue(a[M, K] @ W).  bf16: `w` is the packed [N, K] matrix; fp32: `w` is the
-// caller's [K, N] matrix.  partials: float [kShiftLanes][slots][M] for EPI_BIAS_RES_SHIFT
+// out[M, N] = epilogue(a[M, K] @ W).  bf16: `w` is the packed [N, K] matrix, or (frag: EPI_BIAS_RES and
+// EPI_BIAS_RES_SHIFT) a matrix in fragment order; fp32: `w` is the caller's [K, N] matrix.  partials: float [kShiftLanes][slots][M] for EPI_BIAS_RES_SHIFT
 // (rows innermost: the epilogues store and the selection reads whole lines).  ld: elements between the rows
-// of a and of the packed w (bf16; 0 = K), ldo: of out (0 = N).
+// of a (bf16; 0 = K), ldo: of out (0 = N).
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials,
-                       const void* ref, bool post, int64_t M, int N, int K, hipStream_t s, int ld = 0, int ldo = 0);
+                       const void* ref, bool post, int64_t M, int N, int K, hipStream_t s, bool frag = false,
+                       int ld = 0, int ldo = 0);
 hipError_t launch_gemm_f32(GemmEpilogue epi, rs_dist dist, const void* a, const void* w, const void* bias,
                            const void* res, void* out, float* partials, const void* ref, bool post, int64_t M, int N,
                            int K, hipStream_t s);
-// bf16 GEMM behind a LayerNorm (EPI_LN_BIAS / EPI_LN_BIAS_GELU).
+// bf16 GEMM behind a LayerNorm (EPI_LN_BIAS / EPI_LN_BIAS_GELU), weights in fragment order.
 hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded, GemmLnFold ln, void* out,
                           int64_t M, int N, int K, hipStream_t s, int ld = 0, int ldo = 0);
 
@@ -203,7 +203,7 @@ struct MlpArgs {
     bool post;
     float eps;
     int64_t M;
-    int Dm, ld2;  // ld2: elements between the rows of the packed W_fc2
+    int Dm;
 };
 bool mlp_fused_fits(rs_dtype dt, int64_t M, int D, int Dm);
 hipError_t launch_mlp_fused(const MlpArgs& g, rs_dist dist, bool shift, hipStream_t s);
@@ -228,9 +228,11 @@ hipError_t launch_attn_map_scores(const void* map, float* partial, float* s_cls,
 hipError_t launch_attn_unpack(const void* oh, void* o, int B, int H, int N, int64_t osb, int64_t osn, int64_t osh,
                               hipStream_t s);
 
-// bf16 [K, N] row-major -> [N, K] row-major; with `gamma` ([K] bf16) row k is scaled by gamma[k]
-// (product rounded to bf16).  ld: elements between the rows of wt (0 = K); those past K are written as zeros.
-hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld = 0);
+// bf16 [K, N] row-major -> [N, K] row-major
+hipError_t launch_pack_transpose(const void* w, void* wt, int K, int N, hipStream_t s);
+// bf16 [K, N] row-major (multiples of 64) -> fragment order (frag_off); with `gamma` ([K] bf16) row k is scaled by gamma[k]
+// (product rounded to bf16); `tail` elements behind the fragments are written as zeros.
+hipError_t launch_pack_frag(const void* w, const void* gamma, void* wf, int K, int N, int64_t tail, hipStream_t s);
 // colsum[n] = sum_k bf16(gamma[k] * w[k][n]),  bias_out[n] = sum_k beta[k] * w[k][n] + bias[n]
 // (w [K, N] bf16; gamma, beta, bias bf16 or null = 1, 0, 0; outputs fp32).
 hipError_t launch_pack_ln_fold(const void* w, const void* gamma, const void* beta, const void* bias,

@@ -21,7 +21,10 @@ namespace rs {
 
 // ---------------------------------------------------------------------------
 // bf16 MFMA GEMM:  out[m, n] = epi( sum_k a[m, k] * wt[n, k] )
-//   a  : [M, K] bf16 (token rows),  wt : [N, K] bf16 (packed weights),  K % 64 == 0.
+//   a  : [M, K] bf16 (token rows),  K % 64 == 0;  wt : [N, K] bf16, in rows (WF false: rs_linear_fwd) or in
+//   fragment order (WF true: the weights a block has packed; LDS then holds whole fragments, no swizzle).
+// The compiler knows which copies a fragment read need not wait for only through few steps of address
+// arithmetic from the stage's array: a lane's offset is one number (wlane), added to the array at once.
 // Workgroup tile BM x BN, K slices of BK, WGM x WGN waves, a ring of LDS stages.
 // LDS rows are 64 bf16 = 8 slots of 16 B; chunk c of row r sits in slot c ^ ((r ^ (r >> 3)) & 7).
 // The LDS has 64 banks of 4 bytes and serves a 16-byte-per-lane read 16 lanes at a time, so the
@@ -47,7 +50,7 @@ struct GemmBatch {
 // tail branches.  Operand fragments are double buffered in registers and each LDS read is
 // interleaved with its share of the previous K step's MFMAs (sched_group_barrier).  One
 // workgroup per CU; the register budget is that of NW / 4 waves per SIMD.
-template <int BM, int BN, int BK, int NSTAGE, int WGM, int WGN, int EPI, int DIST>
+template <int BM, int BN, int BK, int NSTAGE, int WGM, int WGN, int EPI, int DIST, bool WF>
 __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
@@ -138,7 +141,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     // global -> LDS: wave copy i of wave w fills rows (NW*i + w)*RPI .. +RPI-1 (lane l: row l / SPR,
     // slot l % SPR), so the lane fetches chunk (l % SPR) ^ f(row).
     __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
-    __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
+    const int ldw = WF ? K : ld, wlane = wn * TN * KK * 1024 + lane * 16, wvoff = frag_off(wave / KK, wave % KK, K) + lane * 16;
+    __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ldw, (int64_t)min(N - n0, BN) * ldw * 2);
     const int ld_r = lane / SPR, ld_p = lane % SPR;
     // lane byte offset inside a wave copy (NW is even, so row >> 3 = NW*i + w has the parity of w)
     const int voff = SPR == 8 ? ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2
@@ -165,8 +169,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     {                                                                                                     \
         const bool real_ = (t_) < S;                                                                      \
         const int kb_ = (t_) * RB;                                                                        \
-        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i)                                               \
-            dma16(rs_w, (sw_) + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd);   \
+        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i) {                                             \
+            const int f_ = i * NW + wave;                                                                 \
+            if constexpr (WF) dma16(rs_w, (sw_) + f_ * 1024, wvoff, real_ ? frag_off(i * NW / KK, i * NW % KK, K) + (t_) * (KK * 1024) : kPastEnd); \
+            else dma16(rs_w, (sw_) + f_ * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd);           \
+        }                                                                                                 \
     }
 #define RS_GEMM_DMA(stage_, t_)                                                                           \
     {                                                                                                     \
@@ -177,7 +184,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     {                                                                                                     \
         const int c_ = ((((kk_) * 2 + g) ^ sw) << 4);                                                     \
         _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
-            (f_).w[i] = *reinterpret_cast<const bf16x8*>((sw_) + (w_row0 + i * 32) * RB + c_);            \
+            (f_).w[i] = *reinterpret_cast<const bf16x8*>(                                                 \
+                (sw_) + (WF ? wlane + (i * KK + (kk_)) * 1024 : (w_row0 + i * 32) * RB + c_));            \
         _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
             (f_).a[j] = *reinterpret_cast<const bf16x8*>((sa_) + (a_row0 + j * 32) * RB + c_);            \
     }
@@ -346,7 +354,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
     if (more) {
         RS_GEMM_DECODE(seq, m0, n0)
         rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
-        rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
+        rs_w = make_rsrc(wt + (int64_t)n0 * ldw, (int64_t)min(N - n0, BN) * ldw * 2);
     }
 
     // ---- epilogue, staged through LDS so that global traffic is row-contiguous.
@@ -520,7 +528,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
 // slice three ahead into the freed stage and reads the next slice's first fragments under the
 // second step's MFMAs.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int EPI, int DIST>
+template <int BM, int BN, int WGM, int WGN, int EPI, int DIST, bool WF>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
@@ -572,7 +580,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
     // l % 4 holds chunk (l % 4) ^ f(row), f(r) = (r >> 2) & 3: the 16 rows an operand read touches
     // fall into 16 different 16-byte bank groups)
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
+    const int ldw = WF ? K : ld, wlane = BM * RB + wn * TN * 2048 + lane * 16, wvoff = frag_off(wave / 2, wave % 2, K) + lane * 16;
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ldw, (int64_t)min(N - n0, BN) * ldw * 2);
     const int ld_r = lane >> 2, ld_p = lane & 3;
     const int voff = ((wave * RPI + ld_r) * ld + ((ld_p ^ ((ld_r >> 2) & 3)) << 3)) * 2;
     const int pass_bytes = NW * RPI * ld * 2;
@@ -587,14 +596,18 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
         const int kb_ = (t_) * RB;                                                                        \
         _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i)                                               \
             dma16(rs_a, (stage_) + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
-        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i)                                               \
-            dma16(rs_w, (stage_) + BM * RB + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i) {                                             \
+            const int f_ = i * NW + wave;                                                                 \
+            if constexpr (WF) dma16(rs_w, (stage_) + BM * RB + f_ * 1024, wvoff, real_ ? frag_off(i * NW / 2, i * NW % 2, K) + (t_) * 2048 : kPastEnd); \
+            else dma16(rs_w, (stage_) + BM * RB + f_ * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+        }                                                                                                 \
     }
 #define RS_RING_FRAGS(f_, stage_, kk_)                                                                    \
     {                                                                                                     \
         const int co_ = ((((kk_) * 2 + g) ^ sw) << 4);                                                    \
         _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
-            (f_).w[i] = *reinterpret_cast<const bf16x8*>((stage_) + (BM + w_row0 + i * 32) * RB + co_);   \
+            (f_).w[i] = *reinterpret_cast<const bf16x8*>(                                                 \
+                (stage_) + (WF ? wlane + (i * 2 + (kk_)) * 1024 : (BM + w_row0 + i * 32) * RB + co_)); \
         _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
             (f_).a[j] = *reinterpret_cast<const bf16x8*>((stage_) + (a_row0 + j * 32) * RB + co_);        \
     }
@@ -689,7 +702,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_ring_kernel(
 // statistics -- is requested before the first slice instead of after the last.
 // Same MFMA, same order of the sums as the other kernels: the same bits.
 // ---------------------------------------------------------------------------
-template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
+template <int WGM, int WGN, int TM, int NST, int EPI, int DIST, bool WF>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
     const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
@@ -740,7 +753,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     // LDS layout as in gemm_bf16_kernel: chunk c of row r in slot c ^ (r & 7) ^ ((r >> 3) & 1).  Wave copy i of
     // wave w fills rows (NW i + w) 8 .. + 7 (NW is even, so row >> 3 has the parity of w).
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ld, (int64_t)min(N - n0, BN) * ld * 2);
+    const int ldw = WF ? K : ld, wlane = BM * RB + wn * TN * 4096 + lane * 16, wvoff = frag_off(wave / 4, wave % 4, K) + lane * 16;
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wt + (int64_t)n0 * ldw, (int64_t)min(N - n0, BN) * ldw * 2);
     const int ld_r = lane >> 3, ld_p = lane & 7;
     const int voff = ((wave * RPI + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
     const int pass_bytes = NW * RPI * ld * 2;
@@ -754,14 +768,18 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
         const int kb_ = (t_) * RB;                                                                        \
         _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i)                                               \
             dma16(rs_a, (stage_) + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
-        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i)                                               \
-            dma16(rs_w, (stage_) + BM * RB + (i * NW + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+        _Pragma("unroll") for (int i = 0; i < W_LOADS; ++i) {                                             \
+            const int f_ = i * NW + wave;                                                                 \
+            if constexpr (WF) dma16(rs_w, (stage_) + BM * RB + f_ * 1024, wvoff, real_ ? frag_off(i * NW / 4, i * NW % 4, K) + (t_) * 4096 : kPastEnd); \
+            else dma16(rs_w, (stage_) + BM * RB + f_ * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+        }                                                                                                 \
     }
 #define RS_SLIM_FRAGS(f_, stage_, kk_)                                                                    \
     {                                                                                                     \
         const int co_ = ((((kk_) * 2 + g) ^ sw) << 4);                                                    \
         _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
-            (f_).w[i] = *reinterpret_cast<const bf16x8*>((stage_) + (BM + w_row0 + i * 32) * RB + co_);   \
+            (f_).w[i] = *reinterpret_cast<const bf16x8*>(                                                 \
+                (stage_) + (WF ? wlane + (i * 4 + (kk_)) * 1024 : (BM + w_row0 + i * 32) * RB + co_)); \
         _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
             (f_).a[j] = *reinterpret_cast<const bf16x8*>((stage_) + (a_row0 + j * 32) * RB + co_);        \
     }
@@ -888,6 +906,195 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
     gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, ldo, slots, ldp, m_base, n_base, lane);
 }
 
+// ---------------------------------------------------------------------------
+// Direct kernel, for weights in fragment order: the weights go from memory straight into the registers of the one
+// wave that needs them, only the activations pass through LDS.  Workgroup tile 128 rows x 256 features, four waves of 128 x 64,
+// two workgroups per CU.
+//
+// What bounds these layers at K = 768 is that a tile's epilogue (GELU, residual, 128 KB of stores) is as long as a third of
+// its K loop, and in the persistent kernel, one workgroup per CU, the matrix cores wait for it.  Two
+// workgroups out of step cover it, but the ring kernel, which has two, pays for that in its K loop: three
+// stages of both operands leave room for slices of 32 only, 64-byte row segments, and every line is fetched into L1
+// twice.  Without the weights in LDS (a wave's 64 features are no other wave's) four stages of 64-wide activation
+// slices take 64 KB, LDS traffic falls from 125 to 78 bytes per cycle of full matrix rate, and every
+// request is of whole lines.
+//
+// A slice: the weights of K step k are requested again, for the next slice, as soon as its matrix
+// instructions have been issued (32 registers, 3/4 .. 1 slice ahead); the activation copies run three slices ahead but,
+// answers coming in order, are waited for with the weights behind them, one slice later.  Deeper rings (48 or 64
+// registers of weights) measured the same: what is left is traffic (8192^3: 810 us; without the copies 734, without
+// the weight loads 690, without both 520), not latency.
+// In a block (us, persistent kernel / this): 50432 x 768 -> 2304 191 / 162, -> 768 with residual 83 / 64, -> 3072 with
+// GELU 274 / 230, 50432 x 3072 -> 768 234 / 225, 16388 x 1024 -> 4096 with GELU 162 / 130.
+// Same MFMA, same order of the sums as the other kernels: the same bits.
+// ---------------------------------------------------------------------------
+template <int EPI, int DIST>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_direct_kernel(
+    const bf16raw* __restrict__ a, const bf16raw* __restrict__ wt, const bf16raw* __restrict__ bias,
+    const bf16raw* __restrict__ res, bf16raw* __restrict__ out, float* __restrict__ partials,
+    const bf16raw* __restrict__ ref, int post, GemmLnFold ln, int M, int N, int K, int ld, int ldo, int tiles_m,
+    int tiles_n, int slots, int64_t ldp, int gm) {
+    constexpr int TM = 4, TN = 2, BM = 128, BN = 256, RB = 128, STAGE = BM * RB;
+    constexpr bool RES = epi_res(EPI);
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char st3[STAGE];
+
+    const int nblk = tiles_m * tiles_n;
+    const int xcd = blockIdx.x & 7;
+    const int xq = nblk >> 3, xr = nblk & 7;
+    const int x_cnt = xq + (xcd < xr ? 1 : 0), x_start = xcd * xq + (xcd < xr ? xcd : xr);
+    const int seq = blockIdx.x >> 3;
+    if (seq >= x_cnt) return;  // whole workgroup, before any barrier
+    int m0, n0;
+    {
+        const int bid = x_start + seq;
+        const int per_group = gm * tiles_n;
+        const int grp = bid / per_group, rem = bid - grp * per_group;
+        const int first_m = grp * gm;
+        const int gsz = min(tiles_m - first_m, gm);
+        const int tn = rem / gsz;
+        n0 = tn * BN;
+        m0 = (first_m + rem - tn * gsz) * BM;
+    }
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int n_base = n0 + wave * 64;
+    const int S = K / 64;
+
+    // activations: LDS layout and copies as in gemm_bf16_kernel.  Weights: the wave's two rows of fragments; a wave
+    // whose features lie past N has an empty resource and reads zeros
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(a + (int64_t)m0 * ld, (int64_t)min(M - m0, BM) * ld * 2);
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(n_base < N ? wt + (int64_t)n_base * K : wt, n_base < N ? (int64_t)K * 128 : 0);
+    const int ld_r = lane >> 3, ld_p = lane & 7;
+    const int voff = ((wave * 8 + ld_r) * ld + ((ld_p ^ ld_r ^ (wave & 1)) << 3)) * 2;
+    const int pass_bytes = 32 * ld * 2;
+    const int sw = (l32 & 7) ^ ((l32 >> 3) & 1);
+    const int woff0 = lane * 16, woff1 = woff0 + K * 64;
+
+#define RS_DIRECT_DMA(stage_, t_)                                                                         \
+    {                                                                                                     \
+        const bool real_ = (t_) < S;                                                                      \
+        const int kb_ = (t_) * RB;                                                                        \
+        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                     \
+            dma16(rs_a, (stage_) + (i * 4 + wave) * 1024, voff, real_ ? i * pass_bytes + kb_ : kPastEnd); \
+    }
+// weights of K step kk_ of slice t_
+#define RS_DIRECT_W(kk_, t_)                                                                              \
+    {                                                                                                     \
+        const int so_ = (t_) < S ? ((t_) * 4 + (kk_)) * 1024 : kPastEnd;                                  \
+        w[kk_][0] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_w, woff0, so_, 0)); \
+        w[kk_][1] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_w, woff1, so_, 0)); \
+    }
+#define RS_DIRECT_FRAGS(f_, stage_, kk_)                                                                  \
+    {                                                                                                     \
+        const int co_ = ((((kk_) * 2 + g) ^ sw) << 4);                                                    \
+        _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                    \
+            f_[j] = *reinterpret_cast<const bf16x8*>((stage_) + (l32 + j * 32) * RB + co_);               \
+    }
+#define RS_DIRECT_MFMA(f_, kk_)                                                                           \
+    {                                                                                                     \
+        _Pragma("unroll") for (int i = 0; i < TN; ++i)                                                    \
+            _Pragma("unroll") for (int j = 0; j < TM; ++j)                                                \
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kk_][i], f_[j], acc[i][j], 0, 0, 0); \
+    }
+// one K step: an LDS read of the next step's rows, two MFMAs, a request
+#define RS_DIRECT_INTERLEAVE()                                                                            \
+    {                                                                                                     \
+        _Pragma("unroll") for (int s_ = 0; s_ < TM; ++s_) {                                               \
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                            \
+            __builtin_amdgcn_sched_group_barrier(0x008, TN, 0);                                           \
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                            \
+        }                                                                                                 \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+    }
+// Everything but the newest n_ requests has been answered, and this wave's LDS reads all have.
+#define RS_DIRECT_WAIT(n_)                                                                                \
+    {                                                                                                     \
+        __builtin_amdgcn_s_waitcnt(((n_) & 15) | (((n_) >> 4) << 14) | 0x0070);                           \
+        __builtin_amdgcn_s_barrier();                                                                     \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); /* LDS reads stay below the barrier */     \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+    }
+// Slice t from cur_ (its first fragments are in f0).  fre_ held slice t - 1, which every wave has read before the last
+// barrier: the copies of slice t + 3 go there.  At this slice's barrier those of slice t + 1 must have landed: behind them
+// lie at least the copies of slices t + 2 and t + 3 and this slice's 6 weight loads.
+#define RS_DIRECT_SLICE(cur_, nxt_, fre_, t_)                                                             \
+    {                                                                                                     \
+        RS_DIRECT_DMA(fre_, (t_) + 3)                                                                     \
+        RS_DIRECT_FRAGS(f1, cur_, 1)                                                                      \
+        RS_DIRECT_MFMA(f0, 0)                                                                             \
+        RS_DIRECT_INTERLEAVE()                                                                            \
+        RS_DIRECT_W(0, (t_) + 1)                                                                          \
+        RS_DIRECT_FRAGS(f0, cur_, 2)                                                                      \
+        RS_DIRECT_MFMA(f1, 1)                                                                             \
+        RS_DIRECT_INTERLEAVE()                                                                            \
+        RS_DIRECT_W(1, (t_) + 1)                                                                          \
+        RS_DIRECT_FRAGS(f1, cur_, 3)                                                                      \
+        RS_DIRECT_MFMA(f0, 2)                                                                             \
+        RS_DIRECT_INTERLEAVE()                                                                            \
+        RS_DIRECT_W(2, (t_) + 1)                                                                          \
+        RS_DIRECT_WAIT(14)                                                                                \
+        RS_DIRECT_FRAGS(f0, nxt_, 0)                                                                      \
+        RS_DIRECT_MFMA(f1, 3)                                                                             \
+        RS_DIRECT_INTERLEAVE()                                                                            \
+        RS_DIRECT_W(3, (t_) + 1)                                                                          \
+    }
+
+    bf16x8 w[4][TN], f0[TM], f1[TM];
+    f32x16 acc[TN][TM];
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    RS_DIRECT_DMA(st0, 0)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) RS_DIRECT_W(kk, 0)
+    __builtin_amdgcn_sched_barrier(0);
+    RS_DIRECT_DMA(st1, 1)
+    RS_DIRECT_DMA(st2, 2)
+    RS_DIRECT_WAIT(16)  // slice 0 has landed: behind it 8 weight loads and two slices' copies
+    RS_DIRECT_FRAGS(f0, st0, 0)
+    // whole trips of the ring, then the slices that are left; no way out inside a trip (every exit would keep its own
+    // copy of the accumulators)
+    const int full = S & ~3, left = S & 3;
+    for (int t = 0; t < full; t += 4) {
+        RS_DIRECT_SLICE(st0, st1, st3, t)
+        RS_DIRECT_SLICE(st1, st2, st0, t + 1)
+        RS_DIRECT_SLICE(st2, st3, st1, t + 2)
+        RS_DIRECT_SLICE(st3, st0, st2, t + 3)
+    }
+    if (left > 0) {
+        RS_DIRECT_SLICE(st0, st1, st3, full)
+        if (left > 1) RS_DIRECT_SLICE(st1, st2, st0, full + 1)
+        if (left > 2) RS_DIRECT_SLICE(st2, st3, st1, full + 2)
+    }
+    RS_DIRECT_WAIT(0)  // trailing (empty) copies: the stages get reused
+#undef RS_DIRECT_DMA
+#undef RS_DIRECT_W
+#undef RS_DIRECT_FRAGS
+#undef RS_DIRECT_MFMA
+#undef RS_DIRECT_INTERLEAVE
+#undef RS_DIRECT_WAIT
+#undef RS_DIRECT_SLICE
+
+    EpiRegions<TM> reg;
+    unsigned char* const base = wave == 0 ? st0 : wave == 1 ? st1 : wave == 2 ? st2 : st3;
+#pragma unroll
+    for (int j = 0; j < TM; ++j) reg.r[j] = base + j * 4096;
+    EpiVecs<TM, EPI> vec;
+    if constexpr (RES) epi_request_residual<TM>(reg, res, M, N, m0, n_base, lane);
+    vec.load(bias, ln, M, N, m0, n_base, lane);
+    if constexpr (RES) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
+    gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, ldo, slots, ldp, m0, n_base, lane);
+}
+
 // Tile configuration of the bf16 GEMM: BM, BN, BK, NSTAGE, waves along tokens, waves along features.
 #ifndef RS_GEMM_GM
 #define RS_GEMM_GM 8
@@ -911,7 +1118,7 @@ int device_cus() {
 }
 
 // Which bf16 tile variant runs: 0 = chosen by shape (below), 1 = 256 x 256 persistent kernel,
-// 2 = 256 x 128 slim kernel, 3 = 128 x 128 and 4 = 128 x 256 ring kernel.  Every variant gives the same bits; the
+// 2 = 256 x 128 slim kernel, 3 = 128 x 128 ring kernel, 4 = 128 x 256 direct kernel (weights in rows: ring).  Every variant gives the same bits; the
 // switch exists for tuning and for the test that checks exactly that.  Initial value from the
 // environment variable RS_GEMM_FORCE.
 static std::atomic<int> g_gemm_variant{-1};
@@ -953,22 +1160,22 @@ struct GemmArgs {
     }
 };
 
-template <int BM, int BN, int EPI, int DIST>
+template <int BM, int BN, int EPI, int DIST, bool WF>
 static void launch_ring(const GemmArgs& g, hipStream_t s) {
     const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (g.N + BN - 1) / BN;
     const int nblk = tiles_m * tiles_n;
     constexpr int WGN = BN / 64, WGM = 4 / WGN;  // four waves, each 64 features wide
-    hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(256), 0, s,
+    hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WGM, WGN, EPI, DIST, WF>), dim3(8 * ((nblk + 7) / 8)), dim3(256), 0, s,
                        g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m,
                        tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM, GemmBatch{0, 0, 0});
 }
 
-template <int WGM, int WGN, int TM, int NST, int EPI, int DIST>
+template <int WGM, int WGN, int TM, int NST, int EPI, int DIST, bool WF>
 static void launch_slim(const GemmArgs& g, hipStream_t s) {
     constexpr int BM = 32 * TM * WGM, BN = 64 * WGN;
     const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (g.N + BN - 1) / BN;
     const int nblk = tiles_m * tiles_n;
-    hipLaunchKernelGGL((gemm_bf16_slim_kernel<WGM, WGN, TM, NST, EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(WGM * WGN * 64), 0, s,
+    hipLaunchKernelGGL((gemm_bf16_slim_kernel<WGM, WGN, TM, NST, EPI, DIST, WF>), dim3(8 * ((nblk + 7) / 8)), dim3(WGM * WGN * 64), 0, s,
                        g.a, g.wt, g.bias, g.res, g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m,
                        tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
@@ -981,8 +1188,8 @@ template <int EPI, int DIST>
 static void launch_ring_auto(const GemmArgs& g, hipStream_t s) {
     const int cus = device_cus();
     const int64_t n128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);  // workgroups of the 128 x 128 tiling
-    if ((n128 > cus && n128 <= 2 * cus) || n128 >= 4 * cus) launch_ring<128, 256, EPI, DIST>(g, s);
-    else launch_ring<128, 128, EPI, DIST>(g, s);
+    if ((n128 > cus && n128 <= 2 * cus) || n128 >= 4 * cus) launch_ring<128, 256, EPI, DIST, false>(g, s);
+    else launch_ring<128, 128, EPI, DIST, false>(g, s);
 }
 
 // With a long K (at least 2048, and a slice count that the six-slice trip of the deeper ring pads
@@ -996,7 +1203,7 @@ static bool gemm_deep_stages(int K) {
     return K >= 2048 && 20 * pad <= S;
 }
 
-template <int EPI, int DIST>
+template <int EPI, int DIST, bool WF>
 static void launch_persistent(const GemmArgs& g, hipStream_t s) {
     using C = GemmCfg;
     const int tiles_m = (int)((g.M + C::BM - 1) / C::BM), tiles_n = (g.N + C::BN - 1) / C::BN;
@@ -1005,55 +1212,69 @@ static void launch_persistent(const GemmArgs& g, hipStream_t s) {
     const int share = (tiles_m * tiles_n + 7) / 8;
     const int per_xcd = share < cus / 8 ? share : cus / 8;
     if (gemm_deep_stages(g.K))
-        hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 3, C::WGM, C::WGN, EPI, DIST>),
+        hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 3, C::WGM, C::WGN, EPI, DIST, WF>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
                            g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
     else
-        hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 2, C::WGM, C::WGN, EPI, DIST>),
+        hipLaunchKernelGGL((gemm_bf16_kernel<C::BM, C::BN, C::BK, 2, C::WGM, C::WGN, EPI, DIST, WF>),
                            dim3(8 * per_xcd), dim3(C::WGM * C::WGN * 64), 0, s, g.a, g.wt, g.bias, g.res, g.out, g.partials,
                            g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64, g.ldp, RS_GEMM_GM);
 }
 
-// The kernels that the choice by shape (gemm_choice.hpp) names, from the first row to the last.
+// Weights in fragment order only.
 template <int EPI, int DIST>
+static void launch_direct(const GemmArgs& g, hipStream_t s) {
+    const int tiles_m = (int)((g.M + 127) / 128), tiles_n = (g.N + 255) / 256;
+    const int nblk = tiles_m * tiles_n;
+    hipLaunchKernelGGL((gemm_bf16_direct_kernel<EPI, DIST>), dim3(8 * ((nblk + 7) / 8)), dim3(256), 0, s, g.a, g.wt, g.bias, g.res,
+                       g.out, g.partials, g.ref, g.post, g.ln, (int)g.M, g.N, g.K, g.ld, g.ldo, tiles_m, tiles_n, (g.N + 63) / 64,
+                       g.ldp, 2 * RS_GEMM_GM);
+}
+
+// The kernels that the choice by shape (gemm_choice.hpp) names, from the first row to the last.
+template <int EPI, int DIST, bool WF>
 static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
     for (int64_t r = 0; r < g.M;) {
-        const GemmChoice c = gemm_choose(g.M - r, g.N, g.K, device_cus());
+        const GemmChoice c = WF ? gemm_choose_frag(g.M - r, g.N, g.K, device_cus()) : gemm_choose(g.M - r, g.N, g.K, device_cus());
         const GemmArgs part = g.rows(r, r + c.rows);
         switch (c.tile) {
-            case GemmTile::Slim64x64: launch_slim<2, 1, 1, 4, EPI, DIST>(part, s); break;
-            case GemmTile::Slim128x64: launch_slim<4, 1, 1, 4, EPI, DIST>(part, s); break;
-            case GemmTile::Slim128x128: launch_slim<2, 2, 2, 3, EPI, DIST>(part, s); break;
-            case GemmTile::Slim256x128: launch_slim<4, 2, 2, 3, EPI, DIST>(part, s); break;
-            case GemmTile::Ring: launch_ring_auto<EPI, DIST>(part, s); break;
-            case GemmTile::Persistent: launch_persistent<EPI, DIST>(part, s); break;
+            case GemmTile::Slim64x64: launch_slim<2, 1, 1, 4, EPI, DIST, WF>(part, s); break;
+            case GemmTile::Slim128x64: launch_slim<4, 1, 1, 4, EPI, DIST, WF>(part, s); break;
+            case GemmTile::Slim128x128: launch_slim<2, 2, 2, 3, EPI, DIST, WF>(part, s); break;
+            case GemmTile::Slim256x128: launch_slim<4, 2, 2, 3, EPI, DIST, WF>(part, s); break;
+            case GemmTile::Ring: if constexpr (!WF) launch_ring_auto<EPI, DIST>(part, s); break;
+            case GemmTile::Direct: if constexpr (WF) launch_direct<EPI, DIST>(part, s); break;
+            case GemmTile::Persistent: launch_persistent<EPI, DIST, WF>(part, s); break;
         }
         r += c.rows;
     }
 }
 
-template <int EPI, int DIST>
+template <int EPI, int DIST, bool WF>
 static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, const void* res,
                               void* out, float* partials, const void* ref, bool post, GemmLnFold ln,
                               int64_t M, int N, int K, int ld, int ldo, hipStream_t s) {
     const GemmArgs g{(const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)bias, (const bf16raw*)res,
                      (const bf16raw*)ref, (bf16raw*)out, partials, post ? 1 : 0, ln, M, N, K, ld, ldo, M};
     const int variant = gemm_variant();
-    if (variant == 1) launch_persistent<EPI, DIST>(g, s);
-    else if (variant == 2) launch_slim<4, 2, 2, 3, EPI, DIST>(g, s);
-    else if (variant == 3) launch_ring<128, 128, EPI, DIST>(g, s);
-    else if (variant == 4) launch_ring<128, 256, EPI, DIST>(g, s);
-    else launch_by_shape<EPI, DIST>(g, s);
+    if (variant == 1) launch_persistent<EPI, DIST, WF>(g, s);
+    else if (variant == 2) launch_slim<4, 2, 2, 3, EPI, DIST, WF>(g, s);
+    else if (variant == 3) launch_ring<128, 128, EPI, DIST, WF>(g, s);
+    else if (variant == 4) {
+        if constexpr (WF) launch_direct<EPI, DIST>(g, s);
+        else launch_ring<128, 256, EPI, DIST, WF>(g, s);
+    } else launch_by_shape<EPI, DIST, WF>(g, s);
     return hipGetLastError();
 }
 
 #define RS_STR2(...) #__VA_ARGS__
 #define RS_STR(...) RS_STR2(__VA_ARGS__)
 const char* gemm_build_info() {
-    return "bf16 gemm: persistent tiles (BM,BN,BK,stages,waves m,waves n) " RS_STR(RS_GEMM_CFG)
-           ", three activation stages when K >= 2048; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU"
-           " (256x128 up to 1.45 rounds of 256x256 when K < 2048); ring tiles 128x128x32 and 128x256x32 beyond one round when K <= 384"
-           "; rows behind whole rounds apart when K >= 2048 and the last round is at most 0.5 full";
+    return "bf16 gemm, block: weights in fragments; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU, direct tiles"
+           " 128x256 beyond, persistent tiles (BM,BN,BK,stages,waves m,waves n) " RS_STR(RS_GEMM_CFG) ", three activation stages when"
+           " K >= 2048, when K >= 1536 and the last round is more than 0.5 full; rs_linear_fwd: weights in rows; slim (256x128 up to 1.45"
+           " rounds of 256x256 when K < 2048), persistent, ring tiles 128x128x32 and 128x256x32 beyond one round when K <= 384"
+           ", rows behind whole rounds apart when K >= 2048 and the last round is at most 0.5 full";
 }
 
 // `count` independent products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T (bf16, no bias), problem p at
@@ -1064,14 +1285,14 @@ hipError_t launch_gemm_batched(const void* a, const void* wt, void* out, int cou
     const GemmBatch gb{stride_a, stride_w, stride_out};
     if (N <= 64) {  // one 64-wide wave column: 256 x 64 tiles, four waves along the rows
         const int tiles_m = (M + 255) / 256;
-        hipLaunchKernelGGL((gemm_bf16_ring_kernel<256, 64, 4, 1, EPI_BIAS, 0>), dim3(8 * ((tiles_m + 7) / 8), count), dim3(256), 0, s,
+        hipLaunchKernelGGL((gemm_bf16_ring_kernel<256, 64, 4, 1, EPI_BIAS, 0, false>), dim3(8 * ((tiles_m + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
                            (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, K, N, tiles_m, 1,
                            1, (int64_t)0, RS_GEMM_GM, gb);
     } else {
         const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
         const int nblk = tiles_m * tiles_n;
-        hipLaunchKernelGGL((gemm_bf16_ring_kernel<128, 128, 2, 2, EPI_BIAS, 0>), dim3(8 * ((nblk + 7) / 8), count), dim3(256), 0, s,
+        hipLaunchKernelGGL((gemm_bf16_ring_kernel<128, 128, 2, 2, EPI_BIAS, 0, false>), dim3(8 * ((nblk + 7) / 8), count), dim3(256), 0, s,
                            (const bf16raw*)a, (const bf16raw*)wt, (const bf16raw*)nullptr, (const bf16raw*)nullptr,
                            (bf16raw*)out, (float*)nullptr, (const bf16raw*)nullptr, 0, GemmLnFold{}, M, N, K, K, N, tiles_m,
                            tiles_n, (N + 63) / 64, (int64_t)0, RS_GEMM_GM, gb);
@@ -1086,22 +1307,26 @@ int gemm_shift_slots(rs_dtype dt, int N) {
 
 hipError_t launch_gemm(rs_dtype dt, GemmEpilogue epi, rs_dist dist, const void* a, const void* w,
                        const void* bias, const void* res, void* out, float* partials, const void* ref,
-                       bool post, int64_t M, int N, int K, hipStream_t s, int ld, int ldo) {
+                       bool post, int64_t M, int N, int K, hipStream_t s, bool frag, int ld, int ldo) {
     if (M == 0) return hipSuccess;
     if (dt == RS_F32) return launch_gemm_f32(epi, dist, a, w, bias, res, out, partials, ref, post, M, N, K, s);
     const GemmLnFold ln{};
     ld = ld ? ld : K;
     ldo = ldo ? ldo : N;
-    switch (epi) {
-        case EPI_BIAS: return launch_bf16<EPI_BIAS, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-        case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-        case EPI_BIAS_RES: return launch_bf16<EPI_BIAS_RES, 0>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-        case EPI_BIAS_RES_SHIFT:
-            if (dist == RS_DIST_L2) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L2>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-            if (dist == RS_DIST_L1) return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_L1>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-            return launch_bf16<EPI_BIAS_RES_SHIFT, RS_DIST_COS>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s);
-        default: break;  // the LayerNorm-folded epilogues go through launch_gemm_ln
+#define RS_GEMM_GO(EPI_, DIST_, WF_) return launch_bf16<EPI_, DIST_, WF_>(a, w, bias, res, out, partials, ref, post, ln, M, N, K, ld, ldo, s)
+    if (!frag) {
+        if (epi == EPI_BIAS) RS_GEMM_GO(EPI_BIAS, 0, false);
+        if (epi == EPI_BIAS_GELU) RS_GEMM_GO(EPI_BIAS_GELU, 0, false);
+        if (epi == EPI_BIAS_RES) RS_GEMM_GO(EPI_BIAS_RES, 0, false);
+    } else {  // the block's layers; those behind a LayerNorm go through launch_gemm_ln
+        if (epi == EPI_BIAS_RES) RS_GEMM_GO(EPI_BIAS_RES, 0, true);
+        if (epi == EPI_BIAS_RES_SHIFT) {
+            if (dist == RS_DIST_L2) RS_GEMM_GO(EPI_BIAS_RES_SHIFT, RS_DIST_L2, true);
+            if (dist == RS_DIST_L1) RS_GEMM_GO(EPI_BIAS_RES_SHIFT, RS_DIST_L1, true);
+            RS_GEMM_GO(EPI_BIAS_RES_SHIFT, RS_DIST_COS, true);
+        }
     }
+#undef RS_GEMM_GO
     return hipErrorInvalidValue;
 }
 
@@ -1111,48 +1336,75 @@ hipError_t launch_gemm_ln(GemmEpilogue epi, const void* x, const void* w_folded,
     ld = ld ? ld : K;
     ldo = ldo ? ldo : N;
     if (epi == EPI_LN_BIAS)
-        return launch_bf16<EPI_LN_BIAS, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
+        return launch_bf16<EPI_LN_BIAS, 0, true>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
     if (epi == EPI_LN_BIAS_GELU)
-        return launch_bf16<EPI_LN_BIAS_GELU, 0>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
+        return launch_bf16<EPI_LN_BIAS_GELU, 0, true>(x, w_folded, nullptr, nullptr, out, nullptr, nullptr, false, ln, M, N, K, ld, ldo, s);
     return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------
-// Weight re-layout for the bf16 path: [K, N] row-major -> [N, K] row-major, optionally with
-// row k scaled by gamma[k] (a LayerNorm scale folded into the weights; the product is rounded
-// to bf16).  64 x 64 tiles through LDS, coalesced on both sides.
+// Weight re-layout for the bf16 path: [K, N] row-major -> [N, K] row-major (rs_pack_linear), or into the
+// fragment order of the block's kernels, there optionally with row k scaled by gamma[k] (a LayerNorm
+// scale folded into the weights; the product is rounded to bf16).  64 x 64 tiles through LDS, coalesced on both sides.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bf16raw fold_gamma(bf16raw w, const bf16raw* gamma, int k) {
     return gamma ? f2bf(bf2f(gamma[k]) * bf2f(w)) : w;
 }
 
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16raw* __restrict__ w,
-                                                             const bf16raw* __restrict__ gamma,
-                                                             bf16raw* __restrict__ wt, int K, int N, int ld) {
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16raw* __restrict__ w, bf16raw* __restrict__ wt, int K, int N) {
     __shared__ bf16raw tile[64][66];
     const int k0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int r = ty; r < 64; r += 4) {
         const int k = k0 + r, n = n0 + tx;
-        tile[r][tx] = (k < K && n < N) ? fold_gamma(w[(int64_t)k * N + n], gamma, k) : (bf16raw)0;
+        tile[r][tx] = (k < K && n < N) ? w[(int64_t)k * N + n] : (bf16raw)0;
     }
     __syncthreads();
     for (int r = ty; r < 64; r += 4) {
         const int n = n0 + r, k = k0 + tx;
-        if (n < N && k < ld) wt[(int64_t)n * ld + k] = tile[tx][r];  // zeros past K
+        if (n < N && k < K) wt[(int64_t)n * K + k] = tile[tx][r];
     }
 }
 
-hipError_t launch_pack_transpose(const void* w, const void* gamma, void* wt, int K, int N, hipStream_t s, int ld) {
-    ld = ld ? ld : K;
-    dim3 grid((N + 63) / 64, (ld + 63) / 64);
-    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, (const bf16raw*)w, (const bf16raw*)gamma,
-                       (bf16raw*)wt, K, N, ld);
+hipError_t launch_pack_transpose(const void* w, void* wt, int K, int N, hipStream_t s) {
+    dim3 grid((N + 63) / 64, (K + 63) / 64);
+    hipLaunchKernelGGL(transpose_bf16_kernel, grid, dim3(256), 0, s, (const bf16raw*)w, (bf16raw*)wt, K, N);
+    return hipGetLastError();
+}
+
+// [K, N] row-major -> fragment order (frag_off), optionally with row k scaled by gamma[k]; N and K are multiples of 64.  A
+// workgroup takes 64 x 64 elements through LDS: 2 x 4 fragments, written 16 bytes per lane.  `tail` elements behind the
+// last fragment are written as zeros (the buffer's size does not depend on how it is laid out).
+__global__ __launch_bounds__(256) void pack_frag_kernel(const bf16raw* __restrict__ w, const bf16raw* __restrict__ gamma,
+                                                        bf16raw* __restrict__ wf, int K, int N, int64_t tail) {
+    __shared__ bf16raw tile[64][66];
+    const int k0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    for (int r = ty; r < 64; r += 4) tile[r][tx] = fold_gamma(w[(int64_t)(k0 + r) * N + n0 + tx], gamma, k0 + r);
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int f = h, kk = ty, n = f * 32 + (tx & 31), k = kk * 16 + (tx >> 5) * 8;
+        uint32_t v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = tile[k + 2 * e][n] | (uint32_t)tile[k + 2 * e + 1][n] << 16;
+        const int64_t at = ((int64_t)(n0 / 32 + f) * (K / 16) + k0 / 16 + kk) * 512 + tx * 8;
+        *reinterpret_cast<uint4*>(wf + at) = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+    if (tail > 0) {
+        const int64_t id = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, step = (int64_t)gridDim.x * gridDim.y * 256;
+        for (int64_t i = id; i < tail; i += step) wf[(int64_t)N * K + i] = 0;
+    }
+}
+
+hipError_t launch_pack_frag(const void* w, const void* gamma, void* wf, int K, int N, int64_t tail, hipStream_t s) {
+    hipLaunchKernelGGL(pack_frag_kernel, dim3(N / 64, K / 64), dim3(256), 0, s, (const bf16raw*)w, (const bf16raw*)gamma,
+                       (bf16raw*)wf, K, N, tail);
     return hipGetLastError();
 }
 
 // Column vectors of a LayerNorm folded into the linear layer behind it:
-//   colsum[n] = sum_k bf16(gamma_k w_kn)   -- over exactly the values transpose_bf16_kernel stores,
+//   colsum[n] = sum_k bf16(gamma_k w_kn)   -- over exactly the values pack_frag_kernel stores,
 //                                             so that mean * colsum cancels the mean's share of acc
 //   bias_out[n] = sum_k beta_k w_kn + bias[n]
 // One thread per column, 4 row groups per workgroup reduced through LDS; fp64 sums (one-off work).

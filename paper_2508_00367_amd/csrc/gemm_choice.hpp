@@ -5,7 +5,7 @@
 
 namespace rs {
 
-enum class GemmTile { Slim64x64, Slim128x64, Slim128x128, Slim256x128, Ring, Persistent };
+enum class GemmTile { Slim64x64, Slim128x64, Slim128x128, Slim256x128, Ring, Direct, Persistent };
 
 // The kernel for the first `rows` rows; rows < M: the rows behind them are a problem of their own.
 struct GemmChoice {
@@ -43,6 +43,27 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
     if (K < 2048 || 2 * rem > cus) return {GemmTile::Persistent, M};
     const int64_t m1 = rounds * cus / ((N + 255) / 256) * 256;  // row panels that fill whole rounds: fewer than all of them
     return {GemmTile::Persistent, m1 > 0 ? m1 : M};
+}
+
+// The same for weights in fragment order (a block's layers).  The small slim tiles as above; the direct kernel (128 x 256 tiles, two
+// workgroups per CU) takes the place of the ring and of most of what the persistent kernel does, and cuts off no rows
+// behind whole rounds: its workgroups hand a free slot on, and a CU with only one runs it faster.  us, the best of the
+// others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
+// 384 -> 1536 at 50432 95 / 84, at 12608 37 / 29.
+//  - up to one 256 x 128 slim tile per CU (eight waves, residual rows requested early): those, but for 768 <= K < 1536 and more
+//    than 0.7 tiles per CU.  slim / direct: 768 x 768 at 6280 rows (150 tiles) 15.2 / 16.1, 1536 -> 384 at 12608 (198) 24.0 / 28.0,
+//    384 x 384 there 11.3 / 12.2; 768 -> 2304 at 3144 (225) 17.7 / 16.2, 1024 x 1024 at 8036 (252) 26.9 / 23.2.
+//  - K >= 1536 and a last round of 256 x 256 tiles more than half full: the persistent kernel, which moves two thirds of the
+//    bytes per flop.  persistent / direct: 3072 -> 768 at 41216 rows 176 / 189, 21760 91 / 96, 12552 72 / 75; with a last round half
+//    empty 25216 152 / 130, 30208 157 / 140.
+inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus) {
+    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    if (tiles(64, 64) <= cus) return {GemmTile::Slim64x64, M};
+    if (tiles(128, 64) <= cus) return {GemmTile::Slim128x64, M};
+    if (tiles(128, 128) <= cus) return {GemmTile::Slim128x128, M};
+    if (tiles(256, 128) <= cus && (K < 768 || K >= 1536 || 10 * tiles(256, 128) <= 7 * cus)) return {GemmTile::Slim256x128, M};
+    const int64_t rem = tiles(256, 256) % cus;
+    return {K >= 1536 && (rem == 0 || 2 * rem > cus) ? GemmTile::Persistent : GemmTile::Direct, M};
 }
 
 // fp32: the rows of one launch, in whole tiles of `bm` x 64: it has 256 threads per tile, tiles rounded up to a multiple of

@@ -53,6 +53,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, in
 }
 constexpr int kPastEnd = 0x7ff00000;
 
+// Fragment order of the weights a block has packed: [N / 32][K / 16] fragments of 32 features x 16 k, 1 KB each, lane l's 16
+// bytes of a matrix instruction's A operand in a row: feature l & 31, k 8 (l >> 5) .. + 7.  One wave-wide load of
+// a fragment, into registers or LDS, is 1 KB of whole lines, and an LDS read of it meets no bank twice.
+// Fragments of 32 features lie K * 64 bytes apart; features past N are past the end of a tile's resource.
+__device__ __forceinline__ int frag_off(int f, int kk, int K) { return f * (K * 64) + kk * 1024; }
+
 // s_waitcnt immediate for "at most n vector-memory operations outstanding" (gfx9 encoding,
 // other counters left at their maximum).
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }

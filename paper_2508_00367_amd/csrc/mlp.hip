@@ -71,14 +71,13 @@ __device__ __forceinline__ float2 mlp_row_stats(const u32x4 (&v)[12], int D, flo
 // outputs (96 accumulators) for the whole kernel; weights stream through a ring of three LDS stages, stage
 // s = {rows 32 (s + 1) .. of W_fc1, columns 32 s .. of W_fc2}: fc1 runs one step ahead of fc2, so that its matrix
 // work stands next to the GELU of the step before it.  One barrier per step of 24 MFMAs per wave.
-// W_fc1 rows of 384 bytes: chunk c of row r in slot c ^ ((r >> 1) & 7) (within its group of 8); W_fc2 rows of 64
-// bytes: slot c ^ ((r >> 2) & 3): 16 consecutive rows fall into 16 different bank groups.
+// The weights come in fragment order: a stage is 12 fragments of W_fc1 (32 features, a row of fragments) and 6 x 2 of W_fc2.
 template <int EPI, int DIST>
 __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     const bf16raw* __restrict__ x, const bf16raw* __restrict__ w1, const float* __restrict__ colsum,
     const float* __restrict__ bias1, const bf16raw* __restrict__ w2, const bf16raw* __restrict__ b2,
     bf16raw* __restrict__ out, float* __restrict__ partials, const bf16raw* __restrict__ ref, int post, float eps,
-    int32_t* __restrict__ iota_out, int iota_n, float2* __restrict__ out_stats, int M, int D, int Dm, int ld2) {
+    int32_t* __restrict__ iota_out, int iota_n, float2* __restrict__ out_stats, int M, int D, int Dm) {
     constexpr int W1_BYTES = kMlpChunk * kMlpD * 2, STAGE = 2 * W1_BYTES, COPIES = 6;
     __shared__ __attribute__((aligned(1024))) unsigned char st0[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
@@ -90,22 +89,16 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     const int T = Dm / kMlpChunk;
 
     const __amdgpu_buffer_rsrc_t rs1 = make_rsrc(w1, (int64_t)Dm * kMlpD * 2);
-    const __amdgpu_buffer_rsrc_t rs2 = make_rsrc(w2, ((int64_t)(kMlpD - 1) * ld2 + Dm) * 2);
-    int voff1[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const int p = (j * 4 + wave) * 64 + lane, r = p / 24, slot = p - r * 24;
-        voff1[j] = r * (kMlpD * 2) + (((slot & 24) | ((slot ^ (r >> 1)) & 7)) << 4);
-    }
-    const int voff2 = (wave * 16 + (lane >> 2)) * ld2 * 2 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+    const __amdgpu_buffer_rsrc_t rs2 = make_rsrc(w2, (int64_t)kMlpD * Dm * 2);
+    const int voff1 = wave * 1024 + lane * 16, voff2 = frag_off(wave >> 1, wave & 1, Dm) + lane * 16;
 
 #define RS_MLP_DMA(stage_, s_)                                                                             \
     {                                                                                                      \
         const int o1_ = (s_) + 1 < T ? ((s_) + 1) * W1_BYTES : kPastEnd;                                   \
         const bool r2_ = (s_) < T;                                                                         \
-        _Pragma("unroll") for (int j = 0; j < 3; ++j) dma16(rs1, (stage_) + (j * 4 + wave) * 1024, voff1[j], o1_); \
+        _Pragma("unroll") for (int j = 0; j < 3; ++j) dma16(rs1, (stage_) + (j * 4 + wave) * 1024, voff1, o1_ + j * 4096); \
         _Pragma("unroll") for (int j = 0; j < 3; ++j)                                                      \
-            dma16(rs2, (stage_) + W1_BYTES + (j * 4 + wave) * 1024, voff2, r2_ ? j * 64 * ld2 * 2 + (s_) * kMlpChunk * 2 : kPastEnd); \
+            dma16(rs2, (stage_) + W1_BYTES + (j * 4 + wave) * 1024, voff2, r2_ ? frag_off(2 * j, 2 * (s_), Dm) : kPastEnd); \
     }
 
     // this wave's rows (rows past M are computed on a copy of the last one and never stored) and fc1's first step,
@@ -113,11 +106,11 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     u32x4 xr[12], wr[12];
     {
         const bf16raw* xp = x + (int64_t)min(m, M - 1) * kMlpD + g * 8;
-        const bf16raw* wp = w1 + l32 * kMlpD + g * 8;
+        const bf16raw* wp = w1 + lane * 8;
 #pragma unroll
         for (int k = 0; k < 12; ++k) xr[k] = *reinterpret_cast<const u32x4*>(xp + k * 16);
 #pragma unroll
-        for (int k = 0; k < 12; ++k) wr[k] = *reinterpret_cast<const u32x4*>(wp + k * 16);
+        for (int k = 0; k < 12; ++k) wr[k] = *reinterpret_cast<const u32x4*>(wp + k * 512);
     }
     for (int f = tid; f < Dm; f += 256) {
         s_cs[f] = colsum[f];
@@ -138,8 +131,7 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     for (int k = 0; k < 12; ++k)
         acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wr[k]), __builtin_bit_cast(bf16x8, xr[k]), acc1, 0, 0, 0);
 
-    const int a1 = l32 * (kMlpD * 2), x1 = (l32 >> 1) & 7;
-    const int a2 = W1_BYTES + l32 * 64, x2 = (l32 >> 2) & 3;
+    const int at = lane * 16;
 
 // Step s: GELU of the hidden features 32 s .. (in acc1), fc1 of the next 32, then fc2 over these 32.
 #define RS_MLP_STEP(cur_, ahead_, s_)                                                                      \
@@ -152,8 +144,7 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
         f32x16 nx_;                                                                                        \
         _Pragma("unroll") for (int r = 0; r < 16; ++r) nx_[r] = 0.f;                                       \
         _Pragma("unroll") for (int k = 0; k < 12; ++k) {                                                   \
-            const int c_ = 2 * k + g;                                                                      \
-            const bf16x8 w_ = *reinterpret_cast<const bf16x8*>((cur_) + a1 + (((c_ & 24) | ((c_ ^ x1) & 7)) << 4)); \
+            const bf16x8 w_ = *reinterpret_cast<const bf16x8*>((cur_) + k * 1024 + at);                    \
             nx_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_, __builtin_bit_cast(bf16x8, xr[k]), nx_, 0, 0, 0); \
         }                                                                                                  \
         uint32_t h_[8];                                                                                    \
@@ -172,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
             half_swap(h_[4 * k + 1], h_[4 * k + 3]);                                                       \
             const bf16x8 b_ = __builtin_bit_cast(bf16x8, (u32x4{h_[4 * k], h_[4 * k + 1], h_[4 * k + 2], h_[4 * k + 3]})); \
             _Pragma("unroll") for (int i = 0; i < 6; ++i) {                                                \
-                const bf16x8 w_ = *reinterpret_cast<const bf16x8*>((cur_) + a2 + i * 2048 + (((2 * k + g) ^ x2) << 4)); \
+                const bf16x8 w_ = *reinterpret_cast<const bf16x8*>((cur_) + W1_BYTES + (2 * i + k) * 1024 + at); \
                 acc2[i >> 1][i & 1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_, b_, acc2[i >> 1][i & 1][0], 0, 0, 0); \
             }                                                                                              \
         }                                                                                                  \
@@ -195,8 +186,8 @@ __global__ __launch_bounds__(256, 2) void mlp192_kernel(
     EpiRegions<1> reg[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const int at = (wave * 3 + j) * 4096;
-        reg[j].r[0] = at < STAGE ? st0 + at : st1 + (at - STAGE);
+        const int r0 = (wave * 3 + j) * 4096;
+        reg[j].r[0] = r0 < STAGE ? st0 + r0 : st1 + (r0 - STAGE);
     }
     const int sw = epi_swz(l32);
 #pragma unroll
@@ -246,15 +237,10 @@ __global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restric
     const int m_base = blockIdx.x * kMlpRows + wave * 32, m = m_base + l32;
     const int S = N / 64;
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(w, (int64_t)N * kMlpD * 2);
-    int voff[6];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const int p = (j * 4 + wave) * 64 + lane, r = p / 24, slot = p - r * 24;
-        voff[j] = r * (kMlpD * 2) + (((slot & 24) | ((slot ^ (r >> 1)) & 7)) << 4);
-    }
+    const int voff = wave * 1024 + lane * 16;
 #define RS_QKV_DMA(stage_, s_)                                                                             \
     if ((s_) < S) {                                                                                        \
-        _Pragma("unroll") for (int j = 0; j < 6; ++j) dma16(rs, (stage_) + (j * 4 + wave) * 1024, voff[j], (s_) * STAGE); \
+        _Pragma("unroll") for (int j = 0; j < 6; ++j) dma16(rs, (stage_) + (j * 4 + wave) * 1024, voff, (s_) * STAGE + j * 4096); \
     }
     u32x4 xr[12];
     const bf16raw* xp = x + (int64_t)min(m, M - 1) * kMlpD + g * 8;
@@ -270,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restric
     vec.stats[0] = ln.stats ? reinterpret_cast<const float2*>(ln.stats)[min(m, M - 1)] : mlp_row_stats(xr, D, eps);
     EpiRegions<1> reg;
     reg.r[0] = s_epi + wave * 4096;
-    const int a1 = l32 * (kMlpD * 2), x1 = (l32 >> 1) & 7;
+    const int at = lane * 16;
 
 // Step s: the barrier says that stage s has landed (every wave has waited for its copies) and that the other stage,
 // which the next copies fill, is no longer read.  The wait for these copies comes behind the matrix work and
@@ -286,10 +272,9 @@ __global__ __launch_bounds__(256, 2) void qkv192_kernel(const bf16raw* __restric
         _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                      \
             _Pragma("unroll") for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.f;                             \
         _Pragma("unroll") for (int k = 0; k < 12; ++k) {                                                   \
-            const int c_ = 2 * k + g, o_ = ((c_ & 24) | ((c_ ^ x1) & 7)) << 4;                             \
             _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                  \
                 acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(                                       \
-                    *reinterpret_cast<const bf16x8*>((cur_) + a1 + i * 32 * kMlpD * 2 + o_),               \
+                    *reinterpret_cast<const bf16x8*>((cur_) + (i * 12 + k) * 1024 + at),                   \
                     __builtin_bit_cast(bf16x8, xr[k]), acc[i][0], 0, 0, 0);                                \
         }                                                                                                  \
         _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                      \
@@ -341,7 +326,7 @@ hipError_t launch_mlp_fused(const MlpArgs& g, rs_dist dist, bool shift, hipStrea
     hipLaunchKernelGGL((mlp192_kernel<EPI_, DIST_>), grid, block, 0, s, (const bf16raw*)g.x, (const bf16raw*)g.w1, \
                        g.ln.colsum, g.ln.bias, (const bf16raw*)g.w2, (const bf16raw*)g.b2, (bf16raw*)g.out, g.partials, \
                        (const bf16raw*)g.ref, g.post ? 1 : 0, g.eps, g.iota_out, g.iota_n, (float2*)g.out_stats, (int)g.M, \
-                       kMlpD, g.Dm, g.ld2)
+                       kMlpD, g.Dm)
     if (!shift) RS_MLP_GO(EPI_BIAS_RES, RS_DIST_L2);
     else if (dist == RS_DIST_L2) RS_MLP_GO(EPI_BIAS_RES_SHIFT, RS_DIST_L2);
     else if (dist == RS_DIST_L1) RS_MLP_GO(EPI_BIAS_RES_SHIFT, RS_DIST_L1);

@@ -103,15 +103,17 @@ static hipError_t timed(int cls, hipStream_t s, F launch) {
 
 // ---- workspace layout of rs_block_fwd ---------------------------------------
 // The padded pitch of the hidden activations (padded_ld) makes the workspace no larger than it is without: in bf16
-// u is needed only behind the attention and shares qkv's place, and hid has the room u would take.  Weights
-// packed into the workspace keep the plain pitch, the hidden activations with them.
+// u is needed only behind the attention and shares qkv's place, and hid has the room u would take.  A block that
+// packs its weights into the workspace keeps the plain pitch.
 struct BlockLayout {
     size_t packed, u, qkv, att, x1, hid, partials, scores, stats, total;
     int slots;
 };
 
-// Packed bf16 weights: the four matrices as [out, in] (LayerNorm scales folded into W_qkv and
-// W_fc1; W_fc2 with the row pitch of its activations, ld), then the fp32 column vectors of the two folded LayerNorms.
+// Packed bf16 weights: the four matrices in fragment order (LayerNorm scales folded into W_qkv and
+// W_fc1), then the fp32 column vectors of the two folded LayerNorms.  ld is the row pitch of the hidden activations; a
+// caller's buffer has room for W_fc2 at that pitch (zeros behind the fragments), so that its size is what it was when
+// the matrices lay in rows.
 struct PackedLayout {
     size_t w_qkv, w_proj, w_fc1, w_fc2, cs_qkv, b_qkv, cs_fc1, b_fc1, total;
     int ld;
@@ -227,7 +229,7 @@ extern "C" {
 
 const char* rs_last_error(void) { return g_err; }
 
-int32_t rs_version(void) { return 300; }
+int32_t rs_version(void) { return 400; }
 
 const char* rs_build_info(void) { return gemm_build_info(); }
 
@@ -518,10 +520,10 @@ size_t rs_packed_weights_size(const rs_block_cfg* cfg) {
 static rs_status pack_into(const rs_block_cfg* c, const rs_block_weights* w, const PackedLayout& P, void* dst, hipStream_t st) {
     char* p = (char*)dst;
     const int D = c->D, Dm = c->Dm;
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_qkv, w->ln1_g, p + P.w_qkv, D, 3 * D, st));
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_proj, nullptr, p + P.w_proj, D, D, st));
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc1, w->ln2_g, p + P.w_fc1, D, Dm, st));
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, st, P.ld));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_frag(w->w_qkv, w->ln1_g, p + P.w_qkv, D, 3 * D, 0, st));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_frag(w->w_proj, nullptr, p + P.w_proj, D, D, 0, st));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_frag(w->w_fc1, w->ln2_g, p + P.w_fc1, D, Dm, 0, st));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_frag(w->w_fc2, nullptr, p + P.w_fc2, Dm, D, (int64_t)D * (P.ld - Dm), st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_qkv, w->ln1_g, w->ln1_b, w->b_qkv, (float*)(p + P.cs_qkv),
                                               (float*)(p + P.b_qkv), D, 3 * D, st));
     RS_LAUNCH_K(K_PACK, st, launch_pack_ln_fold(w->w_fc1, w->ln2_g, w->ln2_b, w->b_fc1, (float*)(p + P.cs_fc1),
@@ -559,7 +561,7 @@ rs_status rs_pack_linear(const void* w, void* wt, int32_t K, int32_t N, rs_dtype
     if (dtype == RS_F32) return RS_OK;  // the fp32 path reads the caller's layout
     RS_REQUIRE(w && wt && w != wt, RS_ERR_INVALID_ARG, "w and wt must be distinct non-NULL buffers");
     hipStream_t st = (hipStream_t)hip_stream;
-    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w, nullptr, wt, K, N, st));
+    RS_LAUNCH_K(K_PACK, st, launch_pack_transpose(w, wt, K, N, st));
     return RS_OK;
 }
 
@@ -722,7 +724,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
     // the shift around the attention layer, case (i), comes out of the projection's epilogue
     const bool attn_scores = want_scores && c.op == RS_SHIFT_ATTN;
     RS_LAUNCH_K(K_GEMM_PROJ, s, launch_gemm(dt, attn_scores ? EPI_BIAS_RES_SHIFT : EPI_BIAS_RES, c.dist, att, wp, w->b_proj, x, x1,
-                            partials, nullptr, false, M, D, D, s));
+                            partials, nullptr, false, M, D, D, s, dt == RS_BF16));
     // xhat = MLP(LN(x1)) + x1, with the shift partial sums of D(MLP(LN(x1)), x1)   Eq. (6), Eq. (4)
     const bool need_v = want_scores && c.op == RS_SHIFT_MLP_NORMED;  // LN(x1) itself is an operand of the score
     // a block that keeps every token has kept_idx[b, j] = j: written on its way by the pass over x1 in front of fc1
@@ -740,7 +742,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
                                               dt == RS_F32 && iota_folded ? kept_idx : nullptr, c.N));
     if (fused) {
         MlpArgs g{x1, w1, w2, w->b_fc2, ref, ln2, xhat, partials, y_stats_done ? y_stats : nullptr,
-                  iota_folded ? kept_idx : nullptr, c.N, post, c.ln_eps, M, Dm, ld_hid};
+                  iota_folded ? kept_idx : nullptr, c.N, post, c.ln_eps, M, Dm};
         RS_LAUNCH_K(K_GEMM_FC2, s, launch_mlp_fused(g, c.dist, fc2_scores, s));
     } else {
         if (dt == RS_BF16) {
@@ -751,7 +753,7 @@ static rs_status block_fwd(const rs_block_cfg* cfg, const rs_block_weights* w, c
             RS_LAUNCH_K(K_GEMM_FC1, s, launch_gemm(dt, EPI_BIAS_GELU, RS_DIST_L2, u, w1, w->b_fc1, nullptr, hid, nullptr, nullptr, false, M, Dm, D, s));
         }
         RS_LAUNCH_K(K_GEMM_FC2, s, launch_gemm(dt, fc2_scores ? EPI_BIAS_RES_SHIFT : EPI_BIAS_RES, c.dist, hid, w2, w->b_fc2, x1,
-                              xhat, partials, ref, post, M, D, Dm, s, ld_hid));
+                              xhat, partials, ref, post, M, D, Dm, s, dt == RS_BF16, ld_hid));
     }
     // the survivors' rows, with the LayerNorm statistics the next block needs if the caller asks for them
     auto gather_out = [&]() -> rs_status {
