@@ -14,8 +14,8 @@
 // slices global -> LDS (direct copies) in a ring of its own and waits for nobody, there is no barrier
 // before the final sum.  The K split is what fills the chip at the sizes this path is used at: four
 // images of 197 tokens make 39 64 x 64 tiles (fc2) on 256 CUs.
-// Bound by the matrix cores (120 of 137 TFLOP/s the library reaches at 12608 x 3072 x 768; 90 at
-// 12608 x 768 x 192, where a tile is three slices long); the plain FMA tiles this replaced ran
+// Bound by the matrix cores (132 TFLOP/s at 12608 x 3072 x 768, the library's rate there; 105 at
+// 12608 x 768 x 192, where a tile is six slices of 32 long); the plain FMA tiles this replaced ran
 // at 60 and took 71 us for the fc2 of a 4 x 197 x 192 block (9.5 us now).
 // Two kernels: 32 x 64 tiles with K split over the waves (three stages, 48 KB of LDS in all) for grids that
 // leave CUs idle, and 64 x 64 tiles shared by the waves (gemm_f32_wide_kernel) for those that fill the chip.
@@ -241,16 +241,18 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
 // The same products and sums for grids that fill the chip: 64 x 64 tile, a wave owns a quarter of it (32 rows x 32
 // features) over the whole of K and keeps the four partial sums of an element in four accumulators, so that the
 // final sum is three additions in registers and not 64 KB written to LDS and read back.  The waves share the
-// slices (one barrier each); two workgroups per CU.
+// slices (one barrier each).  Slices of 32 k, so that two stages are 32 KB and four workgroups share a CU: tiles are a
+// few slices long, and what three of them wait for (first slice, stores) the fourth fills.  Slices of 64 and two workgroups
+// before: 12608 x 768 x 192 40.6 us, 35.5 now, with GELU 50.5 / 41.3, 12608 x 768 x 768 128.6 / 117.
 template <int EPI, int DIST>
-__global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
+__global__ __launch_bounds__(256, 4) void gemm_f32_wide_kernel(
     const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ bias,
     const float* __restrict__ res, float* __restrict__ out, float* __restrict__ partials,
     const float* __restrict__ ref, int post, int M, int N, int K, int tiles_m, int tiles_n) {
     constexpr int BM = 64, BN = 64, A_BYTES = BM * 64, W_BYTES = 16 * BN * 4, SLICE = A_BYTES + W_BYTES, PITCH = BN * 4 + 16;
-    __shared__ __attribute__((aligned(1024))) unsigned char st0[4 * SLICE];
-    __shared__ __attribute__((aligned(1024))) unsigned char st1[4 * SLICE];
-    static_assert(BM * PITCH <= 4 * SLICE, "the sums go through one stage");
+    __shared__ __attribute__((aligned(1024))) unsigned char st0[BM * PITCH];  // the sums go through it at the end
+    __shared__ __attribute__((aligned(1024))) unsigned char st1[2 * SLICE];
+    static_assert(BM * PITCH >= 2 * SLICE, "a stage: two partial sums' k");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -264,7 +266,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
     const int tn = bid % tiles_n, slots = tiles_n;
     const int m0 = bid / tiles_n * BM, n0 = tn * BN;
 
-    // LDS layout and copies as above: region u of a stage holds the 16 k of partial sum u, copied by wave u
+    // LDS layout and copies as above: region u of the even slices holds the 16 k of partial sums 0 and 1, of the odd ones of
+    // 2 and 3; waves 0, 1 copy the activation rows of a region each, waves 2, 3 the weights
     const __amdgpu_buffer_rsrc_t rs_a = rsrc_f(a + (int64_t)m0 * K, (int64_t)min(M - m0, BM) * K * 4);
     const int a_voff = (lane >> 2) * K * 4 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
     const int w_voff = (lane >> 4) * N * 4 + ((lane & 15) << 4);
@@ -275,29 +278,32 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
 
-    const int S = K >> 6;
+    const int S = K >> 5;  // even: K % 64 == 0
 #define RS_F32W_DMA(st_, t_)                                                                                  \
     if ((t_) < S) {                                                                                           \
-        unsigned char* p_ = (st_) + wave * SLICE;                                                             \
-        const int k_ = (t_) * 64 + wave * 16;                                                                 \
-        _Pragma("unroll") for (int i = 0; i < A_BYTES / 1024; ++i)                                            \
-            dma16_f(rs_a, p_ + i * 1024, a_voff, i * 16 * K * 4 + k_ * 4);                                    \
-        const __amdgpu_buffer_rsrc_t rs_w = rsrc_f(w + (int64_t)k_ * N + n0, (15 * (int64_t)N + BN) * 4);     \
-        _Pragma("unroll") for (int i = 0; i < W_BYTES / 1024; ++i)                                            \
-            dma16_f(rs_w, p_ + A_BYTES + i * 1024, w_voff + (i & 1 ? w_flip : 0), i * 4 * N * 4);             \
+        unsigned char* p_ = (st_) + (wave & 1) * SLICE;                                                       \
+        const int k_ = (t_) * 32 + (wave & 1) * 16;                                                           \
+        if (wave < 2) {                                                                                       \
+            _Pragma("unroll") for (int i = 0; i < A_BYTES / 1024; ++i)                                        \
+                dma16_f(rs_a, p_ + i * 1024, a_voff, i * 16 * K * 4 + k_ * 4);                                \
+        } else {                                                                                              \
+            const __amdgpu_buffer_rsrc_t rs_w = rsrc_f(w + (int64_t)k_ * N + n0, (15 * (int64_t)N + BN) * 4); \
+            _Pragma("unroll") for (int i = 0; i < W_BYTES / 1024; ++i)                                        \
+                dma16_f(rs_w, p_ + A_BYTES + i * 1024, w_voff + (i & 1 ? w_flip : 0), i * 4 * N * 4);         \
+        }                                                                                                     \
     }
-// slice t_ from cur_; its barrier also says that every wave is done with the slice before, whose stage the next
-// copies fill
-#define RS_F32W_STEP(cur_, other_, t_)                                                                        \
+// slice t_ from cur_ into partial sums u0_ and u0_ + 1; its barrier also says that every wave is done with the slice
+// before, whose stage the next copies fill
+#define RS_F32W_STEP(cur_, other_, t_, u0_)                                                                   \
     {                                                                                                         \
         __builtin_amdgcn_s_waitcnt(0x0070); /* own copies of this slice, own reads of the one before */       \
         __builtin_amdgcn_s_barrier();                                                                         \
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                                                \
         RS_F32W_DMA(other_, (t_) + 1)                                                                         \
         _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                       \
-            f32x4 af[4];                                                                                      \
-            float wf[4][4];                                                                                   \
-            _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                                   \
+            f32x4 af[2];                                                                                      \
+            float wf[2][4];                                                                                   \
+            _Pragma("unroll") for (int u = 0; u < 2; ++u) {                                                   \
                 const unsigned char* p_ = (cur_) + u * SLICE;                                                 \
                 af[u] = *reinterpret_cast<const f32x4*>(p_ + (rq + l32) * 64 + (((2 * h + g) ^ ((l32 >> 2) & 3)) << 4)); \
                 _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                 \
@@ -305,15 +311,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
                                                                (((fq + l32) * 4) ^ (g << 7)));                \
             }                                                                                                 \
             _Pragma("unroll") for (int e = 0; e < 4; ++e)                                                     \
-                _Pragma("unroll") for (int u = 0; u < 4; ++u)                                                 \
-                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], af[u][e], acc[u], 0, 0, 0);       \
+                _Pragma("unroll") for (int u = 0; u < 2; ++u)                                                 \
+                    acc[(u0_) + u] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], af[u][e], acc[(u0_) + u], 0, 0, 0); \
         }                                                                                                     \
     }
     RS_F32W_DMA(st0, 0)
     for (int t = 0; t < S; t += 2) {
-        RS_F32W_STEP(st0, st1, t)
-        if (t + 1 >= S) break;
-        RS_F32W_STEP(st1, st0, t + 1)
+        RS_F32W_STEP(st0, st1, t, 0)
+        RS_F32W_STEP(st1, st0, t + 1, 2)
     }
 #undef RS_F32W_DMA
 #undef RS_F32W_STEP
@@ -321,7 +326,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
     F32Epilogue<BM, EPI, DIST> epi;
     epi.load(bias, res, m0, n0, M, N);
     // through the stage that the last slice does not lie in: no wave reads it any more and no copy is in flight
-    unsigned char* red = (S & 1) ? st1 : st0;
+    unsigned char* red = st0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f32x4 v;
@@ -334,17 +339,22 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_wide_kernel(
             m0, tn, slots, M, N);
 }
 
-// Same results either way: the shared 64-row tiles once they fill the chip twice over with two workgroups per CU,
-// and already from one round on where K is short (the final sum through LDS is a large part of a tile then); 32-row
-// tiles with K split over the waves below.  Measured, shared / split (us): 788 x 192 x 768 (39 tiles of 64 rows) 16.8 /
-// 9.7, 3000 x 768 x 768 (564) 44.3 / 40.7, 12608 x 192 x 768 (591) 42.6 / 38.5; 12608 x 192 x 192 (591) 15.1 / 15.8,
-// 6528 x 576 x 192 (918) 18.4 / 21.9; beyond, against 64-row tiles with K split: 12608 x 768 x 192 (2364) 41.2 / 45.8,
-// 12608 x 576 x 192 (1773) 33.0 / 34.0, 12608 x 768 x 768 131 / 132, with GELU at K = 768 532 / 526.
+// Same results either way.  The shared 64-row tiles where they fill the chip: four rounds of one tile per CU, 1.5 where K is
+// short (the sum through LDS of the split tiles is a large part of a tile then), and in between where the last round is
+// at least 0.9 full, a tile being a long unit of work at long K; 32-row tiles with K split over the waves below.
+// Measured, shared / split (us, tiles of 64 rows in brackets): K = 192: 3152 x 576 (450) 9.5 / 12.0, 10088 x 192 (474) 9.8 / 12.5, 6304 x 192
+// (297) 9.3 / 9.7, 1576 x 768 with GELU (300) 11.9 / 11.8; K = 768: 10088 x 192 (474) 27.7 / 30.0, 20000 x 192 (939) 50.6 / 56.2,
+// 12608 x 192 (591) 38.7 / 36.8, 8192 x 192 (384) 27.0 / 23.4, 788 x 192 (39) 15.9 / 9.5; 3072 -> 768 at 4000 rows (756) 143 / 150, at 2000 (384) 97 / 77.
+static bool f32_wide(int64_t M, int N, int K) {
+    const int64_t tiles = ((M + 63) / 64) * (N / 64), cus = device_cus();
+    if (tiles >= 4 * cus || (K <= 384 && 2 * tiles >= 3 * cus)) return true;
+    return tiles > cus && 10 * tiles >= 9 * cus * ((tiles + cus - 1) / cus);
+}
 template <int EPI, int DIST>
 static hipError_t launch_t(const void* a, const void* w, const void* bias, const void* res, void* out, float* partials,
                            const void* ref, bool post, int64_t M, int N, int K, hipStream_t s) {
     const int tiles_n = N / 64;
-    const bool wide = ((M + 63) / 64) * tiles_n >= (K <= 384 ? 512 : 1024);
+    const bool wide = f32_wide(M, N, K);
     const int bm = wide ? 64 : 32;
     const int64_t rows = gemm_f32_launch_rows(N, bm);
     if (partials && M > rows) return hipErrorInvalidValue;  // the sums' slots lie M apart: one launch (rows of 4096 values at most)

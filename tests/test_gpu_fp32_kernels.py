@@ -161,3 +161,20 @@ def test_fp32_attention_low_values_as_a_mask(N, masked, value):
     torch.cuda.synchronize()
     err = norm_err(to_host(o), ref)
     assert err < TOL["f32"]
+
+
+@pytest.mark.parametrize("M,K,N", [(6208, 64, 256), (24576, 64, 64), (24513, 448, 64), (10088, 768, 192), (9601, 832, 192), (21845, 192, 192)])
+def test_fp32_shared_tiles_same_bits(M, K, N):
+    """Sizes that go to the 64-row tiles the waves share (1.5 rounds at short K, a last round at least 0.9 full at long K; 2, 6,
+    14, 24 and 26 slices): the bits of the same rows in calls too small for them."""
+    _say("fp32 shared tiles", M, K, N)
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a, w = torch.randn((M, K), device="cuda", generator=g), torch.randn((K, N), device="cuda", generator=g)
+    b, res = torch.randn((N,), device="cuda", generator=g), torch.randn((M, N), device="cuda", generator=g)
+    whole, parts = (torch.full((M + 1, N), float("nan"), device="cuda") for _ in range(2))
+    rs.rs_linear_fwd(a, w, b, res, whole[:M], rs.RS_EPI_BIAS_RES)
+    step = 1024 if N > 64 else 2048
+    for r in range(0, M, step):
+        rs.rs_linear_fwd(a[r:r + step], w, b, res[r:r + step], parts[r:min(r + step, M)], rs.RS_EPI_BIAS_RES)
+    torch.cuda.synchronize()
+    assert torch.isnan(whole[M]).all() and torch.equal(whole[:M], parts[:M]) and torch.isfinite(whole[:M]).all()
