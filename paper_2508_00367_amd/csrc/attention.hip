@@ -32,6 +32,10 @@ constexpr int DH = 64;
 __device__ __forceinline__ int att_swz(int r, int c) { return r * 128 + (((c ^ r ^ (r >> 3)) & 7) << 4); }
 
 typedef __attribute__((address_space(3))) void* att_lds_ptr;
+// 16 bytes per lane from a buffer resource straight into LDS (lane l at dst + 16 l)
+__device__ __forceinline__ void att_copy(__amdgpu_buffer_rsrc_t rsrc, unsigned char* dst, int voff, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (att_lds_ptr)dst, 16, voff, soff, 0, 0);
+}
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16* lds_v4i16;
 
@@ -82,7 +86,7 @@ __device__ __forceinline__ void att_tile(const unsigned char* sk, const unsigned
     float mx = fmaxf(sacc[0][0], sacc[1][0]);
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(fmaxf(mx, sacc[0][r]), sacc[1][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = half_max(mx);
     const float m_new = fmaxf(m_run, mx);  // finite: every tile holds at least one real key
     const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
     const float mb = m_new * scale_log2e;
@@ -144,11 +148,12 @@ __device__ __forceinline__ void att_tile(const unsigned char* sk, const unsigned
     l_run = l_run * alpha + psum;
 }
 
-// Long sequences: workgroup = 256 query rows (8 waves x 32 rows) of one (image, head); two
-// workgroups share a CU (at most 128 registers), four waves per SIMD.  K and V tiles stream
+// Long sequences: workgroup = 256 or 128 query rows (NW = 8 or 4 waves x 32 rows) of one (image, head); two or
+// four workgroups share a CU (at most 128 registers), four waves per SIMD.  K and V tiles stream
 // global -> LDS directly (buffer_load ... lds, rows past N read as zero through the buffer
 // resource).  Two stages each; the copies of tile t+1 are issued before the MFMAs of tile t, one barrier per tile.
-__global__ __launch_bounds__(512, 4) void attention_bf16_kernel(
+template <int NW>
+__global__ __launch_bounds__(NW * 64, 4) void attention_bf16_kernel(
     const bf16raw* __restrict__ q, const bf16raw* __restrict__ k, const bf16raw* __restrict__ v,
     bf16raw* __restrict__ o, int N, int64_t sb, int64_t sn, int64_t sh, int64_t osb, int64_t osn,
     int64_t osh, float scale_log2e, int H, int BH, int q_tiles) {
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_kernel(
     const int head = xcd + 8 * (local / q_tiles);
     if (head >= BH) return;  // whole workgroup, before any barrier
     const int b = head / H, h = head - b * H;
-    const int q0 = (local % q_tiles) * ATT_BM + wave * 32;
+    const int q0 = (local % q_tiles) * (NW * 32) + wave * 32;
     const int64_t base = (int64_t)b * sb + (int64_t)h * sh;
 
     // Q fragments: B operand, column = query row q0 + l32, k-slots = 8 channels 16*kk + 8*g ..
@@ -179,26 +184,29 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_kernel(
         for (int kk = 0; kk < 4; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + g * 8);
     }
 
-    // K copies: wave w fills LDS rows 8w .. 8w+7 of the tile (lane l: row l/8, slot l%8 holds
+    // K copies: copy i of wave w fills LDS rows 8 (w + NW i) .. + 7 of the tile (lane l: row l/8, slot l%8 holds
     // chunk (l%8) ^ f(row)); the resource ends with key N-1, so later rows arrive as zeros.
+    constexpr int CP = 8 / NW;
     const int64_t k_bytes = ((int64_t)(N - 1) * sn + DH) * 2;
     const __amdgpu_buffer_rsrc_t rs_k = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16raw*>(k + base), 0, (int)(k_bytes < 0xffffffffll ? k_bytes : 0xffffffffll), 0x00020000);
     const int k_lr = lane >> 3;
-    const int k_voff = (int)(((int64_t)(wave * 8 + k_lr) * sn + (((lane & 7) ^ k_lr ^ wave) << 3)) * 2);
+    int k_voff[CP];
+#pragma unroll
+    for (int i = 0; i < CP; ++i)
+        k_voff[i] = (int)(((int64_t)((wave + NW * i) * 8 + k_lr) * sn + (((lane & 7) ^ k_lr ^ (wave + NW * i)) << 3)) * 2);
     const int k_tile_bytes = (int)(ATT_BN * sn * 2);
 
     // V copies: the same rows and lanes as K, chunk (l%8) ^ att_vswz(row) in slot l%8.
     const __amdgpu_buffer_rsrc_t rs_v = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16raw*>(v + base), 0, (int)(k_bytes < 0xffffffffll ? k_bytes : 0xffffffffll), 0x00020000);
     const int v_voff = (int)(((int64_t)(wave * 8 + k_lr) * sn + (((lane & 7) ^ att_vswz(k_lr)) << 3)) * 2);
+    const int v_pass = (int)(NW * 8 * sn * 2);
 
 #define ATT_LOAD_NEXT(SKn, SVn, kt_)                                                                     \
-    {                                                                                                    \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_k, (att_lds_ptr)((SKn) + wave * 1024), 16, k_voff,    \
-                                                 (kt_) * k_tile_bytes, 0, 0);                            \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_v, (att_lds_ptr)((SVn) + wave * 1024), 16, v_voff,    \
-                                                 (kt_) * k_tile_bytes, 0, 0);                            \
+    _Pragma("unroll") for (int i = 0; i < CP; ++i) {                                                     \
+        att_copy(rs_k, (SKn) + (wave + NW * i) * 1024, k_voff[i], (kt_) * k_tile_bytes);                 \
+        att_copy(rs_v, (SVn) + (wave + NW * i) * 1024, v_voff, (kt_) * k_tile_bytes + i * v_pass);       \
     }
 // tile kt_ is resident in (SKc, SVc); tile kt_+1 is fetched into (SKn, SVn) meanwhile
 #define ATT_STEP(SKc, SVc, SKn, SVn, kt_, MASK_)                                                              \
@@ -609,7 +617,7 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
         float mx = sacc[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = half_max(mx);
         const float m_new = fmaxf(m_run, mx);
         const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
         const float mb = m_new * scale_log2e;
@@ -697,20 +705,29 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
                            (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh,
                            scale_log2e, q_waves);
     } else if (dt == RS_BF16) {
-        // Whether the rows beyond the last full query tile of 256 go to the tail kernel: a CU holds
-        // two workgroups, so a round is 512 of them; the tail kernel costs about a fifth of a round.
+        // Query rows per workgroup, and whether the rows beyond the last full tile of 256 go to the tail kernel, by what
+        // the busiest CU of an XCD gets, in workgroups of 4 waves (it holds four of them, or two of 8 waves; a head
+        // stays on one XCD; the tail kernel costs about 0.6 per head of a CU and 8 us).  us, 8 waves / 4 waves / 8 waves + tail:
+        // 8 x 1569 x 12 heads 92 / 82 / 105, 4 x 1407 x 16 53 / 46, 20 x 785 x 12 64 / 57 / 65, 3 x 1569 x 12 55 / 45 / 49, 1 x 1569 x 12
+        // 31.5 / 23.6 / 46, 4 x 4097 x 16 312 / 324 / 311, 1 x 4097 x 16 127 / 104 / 97, and with the same number on both sides
+        // 4 x 2869 x 16 153 / 160, 4 x 2009 x 16 79 / 83, 2 x 2353 x 12 46.5 / 48.6: the larger tile, which copies K and V half as often.
         const int BH = B * H;
+        const int64_t heads = (BH + 7) / 8, cus = device_cus() / 8;
+        auto busiest = [&](int64_t tiles) { return (heads * tiles + cus - 1) / cus; };
         const int rem = N % ATT_BM;
         const bool tail_ok = rem > 0 && rem <= ATT_TAIL_ROWS && N > ATT_BM;
-        const float cost_plain = (float)(((int64_t)BH * ((N + ATT_BM - 1) / ATT_BM) + 511) / 512);
-        const float cost_tail = (float)(((int64_t)BH * (N / ATT_BM) + 511) / 512) + 0.22f * (float)((BH + 255) / 256);
-        const bool best_tail = tail_ok && cost_tail < cost_plain;
-        const int bm = ATT_BM;
+        const int64_t c8 = 20 * busiest((N + ATT_BM - 1) / ATT_BM), c4 = 10 * busiest((N + ATT_BM / 2 - 1) / (ATT_BM / 2));
+        const int64_t c_tail = 20 * busiest(N / ATT_BM) + 6 * busiest(1) + 9000 / N;
+        const bool best_tail = tail_ok && c_tail < c8 && c_tail < c4;
+        const int bm = best_tail || c8 <= c4 ? ATT_BM : ATT_BM / 2;
         const int q_tiles = best_tail ? N / bm : (N + bm - 1) / bm;
         dim3 grid(8 * ((BH + 7) / 8) * q_tiles);
-        hipLaunchKernelGGL(attention_bf16_kernel, grid, dim3(512), 0, s, (const bf16raw*)q, (const bf16raw*)k,
-                           (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh, scale_log2e, H, BH,
-                           q_tiles);
+#define ATT_GO(NW_)                                                                                                  \
+    hipLaunchKernelGGL((attention_bf16_kernel<NW_>), grid, dim3(NW_ * 64), 0, s, (const bf16raw*)q, (const bf16raw*)k, \
+                       (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh, scale_log2e, H, BH, q_tiles)
+        if (bm == ATT_BM) ATT_GO(8);
+        else ATT_GO(4);
+#undef ATT_GO
         if (best_tail)
             hipLaunchKernelGGL(attention_bf16_tail_kernel, dim3(BH), dim3(512), 0, s, (const bf16raw*)q,
                                (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn,

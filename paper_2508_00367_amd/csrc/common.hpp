@@ -77,6 +77,13 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// The larger of a lane's value and that of its partner 32 lanes away, by v_permlane32_swap: no trip through the LDS
+// pipe, whose latency would stand in the middle of a softmax's chain, and no lane arithmetic for its address.
+__device__ __forceinline__ float half_max(float v) {
+    const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // Statistics of a row a wave holds as MAXC chunks of 8 values per lane (lane l: chunks l, l + 64,
 // ...; chunks at or past nchunk are not read): (mean, 1 / sqrt(population variance + eps)), the
 // variance taken over the deviations from the mean.  One fixed order of additions, shared by
