@@ -148,6 +148,33 @@ __device__ __forceinline__ void att_tile(const unsigned char* sk, const unsigned
     l_run = l_run * alpha + psum;
 }
 
+// Normalises and stores a wave's 32 output rows (lane: O[row l32][db*32 + 8j + 4g + i] in oacc[db][4j + i]) through 4 KB of
+// LDS that nobody else reads any more, so that rows leave as whole 128-byte lines: straight from the accumulators a store
+// covers 16 bytes of each of 32 lines.  `o`: row 0 of the wave, `rows` of them inside N.
+constexpr int64_t ATT_O_FAR = (int64_t)1 << 24;  // output row stride (elements) at which 32 rows leave 32-bit byte offsets
+__device__ __forceinline__ void att_store(const f32x16 (&oacc)[2], float inv, unsigned char* buf, bf16raw* __restrict__ o,
+                                          int64_t osn, int rows, int lane) {
+    const int l32 = lane & 31, g = lane >> 5;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint2 w;
+            w.x = pack2bf(oacc[db][4 * j] * inv, oacc[db][4 * j + 1] * inv);
+            w.y = pack2bf(oacc[db][4 * j + 2] * inv, oacc[db][4 * j + 3] * inv);
+            *reinterpret_cast<uint2*>(buf + att_swz(l32, db * 4 + j) + g * 8) = w;
+        }
+    const __amdgpu_buffer_rsrc_t rs_o =
+        __builtin_amdgcn_make_buffer_rsrc(o, 0, osn < ATT_O_FAR ? (int)(((rows - 1) * osn + DH) * 2) : 0, 0x00020000);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {  // LDS accesses of one wave are served in order
+        const int r = p * 8 + (lane >> 3), c = lane & 7;
+        const uint4 v = *reinterpret_cast<const uint4*>(buf + att_swz(r, c));
+        if (osn < ATT_O_FAR) store16_wt(rs_o, r < rows ? (int)(r * osn + c * 8) * 2 : 0x7ff00000, v);
+        else if (r < rows) *reinterpret_cast<uint4*>(o + r * osn + c * 8) = v;
+    }
+}
+
 // Long sequences: workgroup = 256 or 128 query rows (NW = 8 or 4 waves x 32 rows) of one (image, head); two or
 // four workgroups share a CU (at most 128 registers), four waves per SIMD.  K and V tiles stream
 // global -> LDS directly (buffer_load ... lds, rows past N read as zero through the buffer
@@ -247,22 +274,11 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_bf16_kernel(
 #undef ATT_LOAD_NEXT
 #undef ATT_STEP
 
-    // ---- normalise and store: lane holds O[q][db*32 + 8j + 4g + i] in oacc[db][4j + i]
+    // every wave is past its last tile: the stages are free
+    if (!active) return;
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    const float inv = 1.0f / l_tot;
-    const int qr = q0 + l32;
-    if (qr < N) {
-        bf16raw* op = o + (int64_t)b * osb + (int64_t)qr * osn + (int64_t)h * osh;
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint2 w;
-                w.x = pack2bf(oacc[db][4 * j] * inv, oacc[db][4 * j + 1] * inv);
-                w.y = pack2bf(oacc[db][4 * j + 2] * inv, oacc[db][4 * j + 3] * inv);
-                *reinterpret_cast<uint2*>(op + db * 32 + j * 8 + g * 4) = w;
-            }
-    }
+    unsigned char* const buf = (NW == 4 ? (wave < 2 ? sk0 : sk1) : wave < 2 ? sk0 : wave < 4 ? sk1 : wave < 6 ? sv0 : sv1) + (wave & 1) * 4096;
+    att_store(oacc, 1.0f / l_tot, buf, o + (int64_t)b * osb + (int64_t)q0 * osn + (int64_t)h * osh, osn, min(N - q0, 32), lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -494,24 +510,13 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
     SM_HALF(s_ka, s_va, 0, 0x0F74)  // vmcnt(4): all but the newest four copies
     SM_HALF(s_kb, s_vb, 2, 0x0F70)
 #undef SM_HALF
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // no copy is in flight when the wave ends
+    __builtin_amdgcn_s_waitcnt(0x0070);  // no copy is in flight, and every read has been answered
+    __builtin_amdgcn_s_barrier();        // K and V are free
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if (q0 >= N) return;
-
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    const float inv = 1.0f / l_tot;
-    const int qr = q0 + l32;
-    if (qr < N) {
-        bf16raw* op = o + (int64_t)b * osb + (int64_t)qr * osn + (int64_t)h * osh;
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint2 w;
-                w.x = pack2bf(oacc[db][4 * j] * inv, oacc[db][4 * j + 1] * inv);
-                w.y = pack2bf(oacc[db][4 * j + 2] * inv, oacc[db][4 * j + 3] * inv);
-                *reinterpret_cast<uint2*>(op + db * 32 + j * 8 + g * 4) = w;
-            }
-    }
+    unsigned char* const buf = (wave < 4 ? s_ka : s_va) + (wave & 3) * 4096;
+    att_store(oacc, 1.0f / l_tot, buf, o + (int64_t)b * osb + (int64_t)q0 * osn + (int64_t)h * osh, osn, min(N - q0, 32), lane);
 }
 
 // ---------------------------------------------------------------------------

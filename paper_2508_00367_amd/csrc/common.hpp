@@ -32,6 +32,22 @@ __device__ __forceinline__ uint32_t pack2bf(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// Stores of a kernel's output that go through the L2 to memory at once (sc1, the scope of the whole GPU) instead of staying
+// there dirty: every kernel ends with a write-back of its XCDs' L2s, and the next one, whose tiles lie elsewhere on the
+// chip, finds the lines in the memory-side cache either way.  For stores of whole lines only.  us per forward, GEMM epilogues alone:
+// vit_s16 961 -> 923, video_vit_b16 1750 -> 1712, video_vit_l14 8540 -> 8466, deit_t 1766 -> 1745; bf16 attention, its rows gathered
+// into lines in LDS first: deit_t 1690 -> 1652, video_vit_l14 8300 -> 8210; fp32 GEMMs: deit_t_fp32 1423 -> 1366; the prune step's
+// rows: vit_s16 882 -> 877.  (Slower: half lines per instruction, as fp32 attention and LayerNorm store,
+// deit_t_fp32 +2 %; 8 bytes per lane and row, bf16 attention's accumulators, +5 %; non-temporal stores, which also pass by the
+// memory-side cache, deit_t and one image +3.5 %.)
+constexpr int kWriteThrough = 16;  // cache policy of a buffer store: sc1
+__device__ __forceinline__ void store16_wt(__amdgpu_buffer_rsrc_t rsrc, int voff, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, voff, 0, kWriteThrough);
+}
+__device__ __forceinline__ void store16_wt(__amdgpu_buffer_rsrc_t rsrc, int voff, uint4 v) {
+    store16_wt(rsrc, voff, u32x4{v.x, v.y, v.z, v.w});
+}
+
 // Storage-type traits: load/store 8 consecutive elements as fp32.
 template <typename T> struct Elem;
 template <> struct Elem<float> {

@@ -407,6 +407,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
                                                            : make_uint4(0u, 0u, 0u, 0u);                  \
         }                                                                                                 \
     }
+        // the wave tile's rows inside M (a wave whose features lie past N stores nothing)
+        const int m_w = m0_cur + wm * WM, n_w = n0_cur + wn * WN;
+        const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(m_w < M && n_w < N ? out + (int64_t)m_w * ldo + n_w : out,
+                                                        m_w < M && n_w < N ? ((int64_t)(min(M - m_w, WM) - 1) * ldo + WN) * 2 : 0);
         RS_GEMM_LOAD_RES(0)
 #pragma unroll
         for (int j = 0; j < TM; ++j) {
@@ -481,7 +485,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] += rr[e];
                 }
-                if (ok) Elem<bf16raw>::store8(out + (int64_t)m * ldo + n, v);
+                store16_wt(rs_out, ok ? ((j * 32 + r) * ldo + oc) * 2 : kPastEnd,
+                           make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])));
                 if (EPI == EPI_BIAS_RES_SHIFT) {
                     // sum over the LPR lanes that share the row (fixed butterfly order)
 #pragma unroll

@@ -62,6 +62,7 @@ struct F32Epilogue {
     template <typename Sum>
     __device__ __forceinline__ void run(const Sum& sum, float* __restrict__ out, float* __restrict__ partials,
                                         const float* __restrict__ ref, int post, int m0, int tn, int slots, int M, int N) {
+        const __amdgpu_buffer_rsrc_t rs_out = rsrc_f(out + (int64_t)m0 * N + tn * 64, ((int64_t)(min(M - m0, BM) - 1) * N + 64) * 4);
 #pragma unroll
         for (int p = 0; p < BM / 16; ++p) {
             const int r = p * 16 + ty, m = m0 + r;
@@ -94,7 +95,8 @@ struct F32Epilogue {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += rr[e];
             }
-            if (m_ok) *reinterpret_cast<float4*>(out + (int64_t)m * N + n) = make_float4(v[0], v[1], v[2], v[3]);
+            store16_wt(rs_out, m_ok ? (r * N + tx * 4) * 4 : 0x7ff00000,
+                       make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
             if (EPI == EPI_BIAS_RES_SHIFT) {
                 // the 16 lanes of a row in a fixed butterfly order; one slot per 64 features
 #pragma unroll

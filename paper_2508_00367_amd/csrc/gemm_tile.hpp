@@ -169,6 +169,8 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
     const int l32 = lane & 31, g = lane >> 5;
 
     const int sw = epi_swz(l32);
+    const __amdgpu_buffer_rsrc_t rs_out =  // the wave tile's rows inside M
+        make_rsrc(out + (int64_t)m_base * ldo + n_base, ((int64_t)(min(M - m_base, 32 * TM) - 1) * ldo + 64) * 2);
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
         const int m = m_base + j * 32 + l32;
@@ -245,7 +247,7 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
             const int r = p * 8 + (lane >> 3), cc = lane & 7;
             const uint4 o4 = *reinterpret_cast<const uint4*>(buf + r * 128 + ((cc ^ epi_swz(r)) << 4));
             const int mo = m_base + j * 32 + r;
-            if (mo < M) *reinterpret_cast<uint4*>(out + (int64_t)mo * ldo + n_base + cc * 8) = o4;
+            store16_wt(rs_out, mo < M ? ((j * 32 + r) * ldo + cc * 8) * 2 : kPastEnd, o4);
         }
     }
 }

@@ -29,3 +29,25 @@ def test_row_tiles_same_bits(N, heads):
     if 0 < N % 256 <= 64:
         return                                # the rows behind whole tiles may be the tail kernel's, which splits the keys
     assert torch.equal(one[0, :N, 0].view(torch.int16), many[0, :N, h].view(torch.int16))
+
+
+@pytest.mark.parametrize("stride", [64, 72, (1 << 24) - 8, 1 << 24])
+@pytest.mark.parametrize("N", [1, 31, 33, 65, 129, 257])
+def test_output_rows_at_any_stride(N, stride):
+    """Output rows side by side, ragged and around 2^24 elements apart (32 rows beyond 32-bit byte offsets): the same bits,
+    and nothing between the rows or behind the last one."""
+    print("attention output stride", N, stride, flush=True)
+    if N > 129 and stride > 72:
+        N = 131 if stride & 8 else 257        # one of the far strides for the long kernel, 8.6 GB
+    g = torch.Generator(device="cuda").manual_seed(N)
+    qkv = torch.randn((1, N, 3, 1, 64), device="cuda", generator=g).bfloat16()
+    near = torch.empty((1, N, 1, 64), device="cuda", dtype=torch.bfloat16)
+    buf = torch.full((N * stride + 64,), 7.0, device="cuda", dtype=torch.bfloat16)
+    far = buf.as_strided((1, N, 1, 64), (0, stride, 64, 1))
+    for o in (near, far):
+        rs.rs_attention_fwd(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], o, 0.125)
+    torch.cuda.synchronize()
+    assert torch.equal(near, far)
+    if stride > 64:
+        assert (buf[:N * stride].view(N, stride)[:, 64:128] == 7.0).all()
+    assert (buf[N * stride:] == 7.0).all()
