@@ -521,17 +521,18 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
 
 // ---------------------------------------------------------------------------
 // fp32 path (v_mfma_f32_32x32x2_f32, true fp32 products): workgroup = 32 query rows of one
-// (image, head), its four waves split the KEYS (wave w: tiles of 32 keys w, w + 4, ...), each with its
-// own K and V tile in LDS and no barrier in the loop; the four partial results are merged through
+// (image, head), its four waves split the KEYS (wave w: tiles of 32 keys w, w + 4, ...), K in registers, V in an LDS
+// tile of the wave's own, no barrier in the loop; the four partial results are merged through
 // LDS in wave order.  Transposed like the bf16 kernels: S^T = K Q^T, and a lane's scores (query l32,
 // keys 8 j + 4 g + i in register 4 j + i) feed O^T = V^T P^T as they are: one k step of the instruction
-// takes one key from each half-wave.  The copies of the next K tile run under the softmax and the PV
-// product, those of the next V tile under the next scores.
+// takes one key from each half-wave.  The first half of the next K tile is requested before the softmax, the second
+// at the top of its turn, the copies of the next V tile under the next scores.
 // The key split is there for small batches: four images of 197 tokens and three heads are 84 blocks
 // of 32 rows, which leave two thirds of the CUs empty and would walk seven key tiles one after the other.
-// LDS: 16 KB per wave; two workgroups per CU cover each other's waits.  Matrix-core bound at long
-// sequences (92 of the 137 TFLOP/s the chip gives fp32 products at 20 x 689 x 12 heads); 10 us at
-// 4 x 197 x 3 and 45 us at 64 x 197 x 3, where one query row per thread took 148 and 168 us.
+// A wave has one or two tiles at N = 197, so most of its time is waiting and merging: what counts is how many
+// workgroups share a CU.  V alone takes 32 KB of LDS and half a K tile of registers leaves 128: four (K in LDS as well:
+// two).  us, two / four: 64 x 197 x 3 heads 44.1 / 37.3, 64 x 158 x 3 29.8 / 23.4, 20 x 260 x 12 73.8 / 60, 8 x 689 x 12 138 / 122 (97 TFLOP/s of
+// the 137 the chip gives fp32 products); with a whole K tile in registers and three workgroups 39.0, 25.0, 62.5, 124.
 // ---------------------------------------------------------------------------
 constexpr int F32_BN = 32;
 constexpr int64_t F32_FAR = (int64_t)1 << 27;  // row stride (elements) at which four rows leave 32-bit byte offsets
@@ -539,13 +540,12 @@ constexpr int64_t F32_FAR = (int64_t)1 << 27;  // row stride (elements) at which
 // FAR: rows F32_FAR elements apart and more; a tile's rows then pass through registers, each read at its own
 // 64-bit address.  Everything behind the copies is the same.
 template <bool FAR>
-__global__ __launch_bounds__(256, 2) void attention_f32_kernel(
+__global__ __launch_bounds__(256, FAR ? 2 : 4) void attention_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     float* __restrict__ o, int N, int64_t sb, int64_t sn, int64_t sh, int64_t osb, int64_t osn,
     int64_t osh, float scale_log2e) {
-    // [32 keys][64 channels] per wave.  K: 16-byte chunk c of key r in slot c ^ (r & 15); V: the two
-    // 128-byte halves of a row swapped where (r >> 2) is odd (the half-waves read rows 4 apart)
-    __shared__ __attribute__((aligned(1024))) unsigned char s_k[4][F32_BN * 256];
+    // V: [32 keys][64 channels] per wave, the two 128-byte halves of a row swapped where (r >> 2) is odd (the half-waves
+    // read rows 4 apart)
     __shared__ __attribute__((aligned(1024))) unsigned char s_v[4][F32_BN * 256];
     __shared__ float s_m[4][32], s_l[4][32];
 
@@ -560,25 +560,31 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     // copy i brings rows 4 i .. 4 i + 3 of a tile through a resource of its own (64-bit base, so that only
     // four rows have to lie within 32-bit offsets); rows past N read as zeros
     const int sn4 = FAR ? 0 : (int)(sn * 4);
-    const int k_voff = (lane >> 4) * sn4;
-#define F32_COPY(dst_, src_, kt_, CHUNK)                                                                          \
+    const int v_voff = (lane >> 4) * sn4;
+#define F32_COPY_V(kt_)                                                                                           \
     _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                               \
         const int row_ = (kt_) * F32_BN + 4 * i, rows_ = min(N - row_, 4);                                        \
+        const int chunk_ = (lane & 15) ^ ((i & 1) << 3);                                                          \
         if constexpr (FAR) {                                                                                      \
             f32x4 t_ = {0.f, 0.f, 0.f, 0.f};                                                                      \
             if ((lane >> 4) < rows_)                                                                              \
-                t_ = *reinterpret_cast<const f32x4*>((src_) + base + (row_ + (lane >> 4)) * sn + ((CHUNK) << 2)); \
-            *reinterpret_cast<f32x4*>((dst_)[wave] + i * 1024 + lane * 16) = t_;                                  \
+                t_ = *reinterpret_cast<const f32x4*>(v + base + (row_ + (lane >> 4)) * sn + (chunk_ << 2));       \
+            *reinterpret_cast<f32x4*>(s_v[wave] + i * 1024 + lane * 16) = t_;                                     \
             continue;                                                                                             \
         }                                                                                                         \
         const __amdgpu_buffer_rsrc_t rs_ = __builtin_amdgcn_make_buffer_rsrc(                                     \
-            const_cast<float*>((src_) + base + (rows_ > 0 ? (int64_t)row_ * sn : 0)), 0,                          \
+            const_cast<float*>(v + base + (rows_ > 0 ? (int64_t)row_ * sn : 0)), 0,                               \
             rows_ > 0 ? (rows_ - 1) * sn4 + DH * 4 : 0, 0x00020000);                                              \
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, (att_lds_ptr)((dst_)[wave] + i * 1024), 16,                 \
-                                                 k_voff + ((CHUNK) << 4), 0, 0, 0);                               \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_, (att_lds_ptr)(s_v[wave] + i * 1024), 16,                    \
+                                                 v_voff + (chunk_ << 4), 0, 0, 0);                                \
     }
-#define F32_COPY_K(kt_) F32_COPY(s_k, k, kt_, (lane & 15) ^ ((4 * i + (lane >> 4)) & 15))
-#define F32_COPY_V(kt_) F32_COPY(s_v, v, kt_, (lane & 15) ^ ((i & 1) << 3))
+// Four of the eight chunks of a K tile, straight into the registers of the matrix instruction's A operand: lane l32 holds channels
+// 8 s + 4 g .. of key l32 of the tile (keys past the end: a copy of the last one, masked below)
+#define F32_LOAD_K(kf_, kt_, s0_)                                                                                 \
+    {                                                                                                             \
+        const float* kp_ = k + base + (int64_t)min((kt_) * F32_BN + l32, N - 1) * sn + 4 * g + 8 * (s0_);         \
+        _Pragma("unroll") for (int s = 0; s < 4; ++s) kf_[s] = *reinterpret_cast<const f32x4*>(kp_ + 8 * s);      \
+    }
 
     f32x4 qf[8];  // channels 8 s + 4 g .. + 3 of query row q0 + l32
     {
@@ -588,7 +594,8 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
 #pragma unroll
         for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const f32x4*>(qp + 8 * s + 4 * g);
     }
-    F32_COPY_K(wave)
+    f32x4 kf[4];
+    F32_LOAD_K(kf, wave, 0)
     F32_COPY_V(wave)
     f32x16 oacc[2];
 #pragma unroll
@@ -604,15 +611,17 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
         f32x16 sacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // K has landed (V, requested later, may be in flight)
+        f32x4 kg[4];
+        F32_LOAD_K(kg, kt, 4)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const f32x4 kf = *reinterpret_cast<const f32x4*>(s_k[wave] + l32 * 256 + (((2 * s + g) ^ (l32 & 15)) << 4));
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[s][e], sacc, 0, 0, 0);
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K tile has been read: its place is free
-        F32_COPY_K(kt + 4)
+            for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s][e], qf[s][e], sacc, 0, 0, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kg[s][e], qf[4 + s][e], sacc, 0, 0, 0);
+        F32_LOAD_K(kf, kt + 4, 0)
         const int key0 = kt * F32_BN;
         if (key0 + F32_BN > N) {  // keys past the end
 #pragma unroll
@@ -637,7 +646,7 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
-        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // V has landed (the next K may be in flight)
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // V has landed (the next K may be in flight)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -650,9 +659,8 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         F32_COPY_V(kt + 4)
     }
-#undef F32_COPY_K
+#undef F32_LOAD_K
 #undef F32_COPY_V
-#undef F32_COPY
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // trailing (empty) copies: the tiles get reused
 
     // ---- merge the four partials
@@ -670,7 +678,7 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     for (int w = 0; w < 4; ++w) L += s_l[w][l32] * __builtin_amdgcn_exp2f((s_m[w][l32] - m_all) * scale_log2e);
     // 0 for a wave without tiles or with no score above -inf; a row without any such score is NaN, as its softmax is
     const float f = __builtin_amdgcn_exp2f((m_run - m_all) * scale_log2e) / L;
-    float* part = reinterpret_cast<float*>(s_k[wave]);  // [32 rows][64 channels], this wave's own tile
+    float* part = reinterpret_cast<float*>(s_v[wave]);  // [32 rows][64 channels], this wave's own tile
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -686,7 +694,7 @@ __global__ __launch_bounds__(256, 2) void attention_f32_kernel(
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const float* pw = reinterpret_cast<const float*>(s_k[w]) + r * 64;
+        const float* pw = reinterpret_cast<const float*>(s_v[w]) + r * 64;
         const f32x4 lo = *reinterpret_cast<const f32x4*>(pw + (((2 * c8) ^ (r & 15)) << 2));
         const f32x4 hi = *reinterpret_cast<const f32x4*>(pw + (((2 * c8 + 1) ^ (r & 15)) << 2));
 #pragma unroll
