@@ -929,6 +929,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_slim_kernel(
 // answers coming in order, are waited for with the weights behind them, one slice later.  Deeper rings (48 or 64
 // registers of weights) measured the same: what is left is traffic (8192^3: 810 us; without the copies 734, without
 // the weight loads 690, without both 520), not latency.
+// The LayerNorm vectors and statistics that the epilogue wants are copied into 3 KB of LDS before the loop (requested after
+// it: 768 -> 2304 at 50432 rows +4 %, 768 -> 3072 at 25216 +3 %).
 // In a block (us, persistent kernel / this): 50432 x 768 -> 2304 191 / 162, -> 768 with residual 83 / 64, -> 3072 with
 // GELU 274 / 230, 50432 x 3072 -> 768 234 / 225, 16388 x 1024 -> 4096 with GELU 162 / 130.
 // Same MFMA, same order of the sums as the other kernels: the same bits.
@@ -945,6 +947,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_direct_kernel(
     __shared__ __attribute__((aligned(1024))) unsigned char st1[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st2[STAGE];
     __shared__ __attribute__((aligned(1024))) unsigned char st3[STAGE];
+    constexpr bool LN = epi_ln(EPI);
+    __shared__ __attribute__((aligned(1024))) unsigned char s_vec[LN ? 3072 : 16];  // what the epilogue reads besides the sums
 
     const int nblk = tiles_m * tiles_n;
     const int xcd = blockIdx.x & 7;
@@ -1064,7 +1068,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_direct_kernel(
     __builtin_amdgcn_sched_barrier(0);
     RS_DIRECT_DMA(st1, 1)
     RS_DIRECT_DMA(st2, 2)
-    RS_DIRECT_WAIT(16)  // slice 0 has landed: behind it 8 weight loads and two slices' copies
+    if constexpr (LN) EpiVecs<TM, EPI>::request(s_vec, ln, M, N, m0, n0, wave, lane);
+    RS_DIRECT_WAIT(16)  // slice 0 has landed: behind it at least 8 weight loads and two slices' copies
     RS_DIRECT_FRAGS(f0, st0, 0)
     // whole trips of the ring, then the slices that are left; no way out inside a trip (every exit would keep its own
     // copy of the accumulators)
@@ -1095,7 +1100,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_direct_kernel(
     for (int j = 0; j < TM; ++j) reg.r[j] = base + j * 4096;
     EpiVecs<TM, EPI> vec;
     if constexpr (RES) epi_request_residual<TM>(reg, res, M, N, m0, n_base, lane);
-    vec.load(bias, ln, M, N, m0, n_base, lane);
+    if constexpr (LN) vec.from_lds(s_vec, wave * 64, lane);
+    else vec.load(bias, ln, M, N, m0, n_base, lane);
     if constexpr (RES) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // every residual row of the tile has landed
     gemm_epilogue_acc_layout<TM, EPI, DIST>(acc, reg, vec, out, partials, ref, post, M, N, ldo, slots, ldp, m0, n_base, lane);
 }

@@ -130,6 +130,28 @@ struct EpiVecs {
             }
         }
     }
+    // The LayerNorm vectors from LDS: 1 KB each of colsum and bias' of the tile's 256 features and of the statistics of its 128
+    // rows, this wave's 64 features from `f0` on (request() below has fetched them).
+    __device__ __forceinline__ void from_lds(const unsigned char* s, int f0, int lane) {
+        const int l32 = lane & 31, g = lane >> 5;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = (f0 + i * 32 + q * 8 + g * 4) * 4;
+                cs[LN ? i : 0][q] = *reinterpret_cast<const f32x4*>(s + at);
+                bv[LN ? i : 0][q] = *reinterpret_cast<const f32x4*>(s + 1024 + at);
+            }
+#pragma unroll
+        for (int j = 0; j < TM; ++j) stats[LN ? j : 0] = *reinterpret_cast<const float2*>(s + 2048 + (j * 32 + l32) * 8);
+    }
+    // One copy per wave (waves 0, 1, 2) into the 3 KB at `s`; past N and M zeros, of which nothing is stored.
+    static __device__ __forceinline__ void request(unsigned char* s, const GemmLnFold& ln, int M, int N, int m0, int n0, int wave, int lane) {
+        const int f = min(N - n0, 256) * 4;
+        const __amdgpu_buffer_rsrc_t rs = wave == 0 ? make_rsrc(ln.colsum + n0, f) : wave == 1 ? make_rsrc(ln.bias + n0, f)
+                                                    : make_rsrc(ln.stats + 2 * (int64_t)m0, min(M - m0, 128) * 8);
+        if (wave < 3) dma16(rs, s + wave * 1024, lane * 16, 0);
+    }
     __device__ __forceinline__ float bias_at(int i, int q, int e) const {
         if constexpr (LN) return bv[i][q][e];
         else return __uint_as_float((e & 1) ? (raw[i][q][e >> 1] & 0xffff0000u) : (raw[i][q][e >> 1] << 16));
