@@ -276,7 +276,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_bf16_kernel(
 
     // every wave is past its last tile: the stages are free
     if (!active) return;
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = half_sum(l_run);
     unsigned char* const buf = (NW == 4 ? (wave < 2 ? sk0 : sk1) : wave < 2 ? sk0 : wave < 4 ? sk1 : wave < 6 ? sv0 : sv1) + (wave & 1) * 4096;
     att_store(oacc, 1.0f / l_tot, buf, o + (int64_t)b * osb + (int64_t)q0 * osn + (int64_t)h * osh, osn, min(N - q0, 32), lane);
 }
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(512, 2) void attention_bf16_tail_kernel(
     // ---- merge the eight partials
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-        const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32, 64);
+        const float l_tot = half_sum(l_run[qb]);
         if (g == 0) {
             s_m[wave][qb][l32] = m_run[qb];
             s_l[wave][qb][l32] = l_tot;
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
     __builtin_amdgcn_s_barrier();        // K and V are free
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if (q0 >= N) return;
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = half_sum(l_run);
     unsigned char* const buf = (wave < 4 ? s_ka : s_va) + (wave & 3) * 4096;
     att_store(oacc, 1.0f / l_tot, buf, o + (int64_t)b * osb + (int64_t)q0 * osn + (int64_t)h * osh, osn, min(N - q0, 32), lane);
 }
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(256, FAR ? 2 : 4) void attention_f32_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // trailing (empty) copies: the tiles get reused
 
     // ---- merge the four partials
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = half_sum(l_run);
     if (g == 0) {
         s_m[wave][l32] = m_run;
         s_l[wave][l32] = l_tot;
@@ -823,8 +823,7 @@ __global__ __launch_bounds__(256) void attn_softmax_rows_kernel(bf16raw* __restr
         for (int i = 0; i < 8; ++i)
             if (c + i < N) mx = fmaxf(mx, x[i]);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    mx = lanes_reduce<64>(mx, [](float a, float b) { return fmaxf(a, b); });
     const float mb = mx * scale_log2e;
     float sum = 0.f;
     for (int c = lane * 8; c < Np; c += 512) {

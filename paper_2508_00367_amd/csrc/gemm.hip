@@ -489,11 +489,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, WGM* WGN / 4) void gemm_bf16_kernel(
                            make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7])));
                 if (EPI == EPI_BIAS_RES_SHIFT) {
                     // sum over the LPR lanes that share the row (fixed butterfly order)
-#pragma unroll
-                    for (int off = LPR / 2; off >= 1; off >>= 1) {
-                        p0 += __shfl_xor(p0, off, 64);
-                        if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
-                    }
+                    p0 = lanes_sum<LPR>(p0);
+                    if (DIST == RS_DIST_COS) { p1 = lanes_sum<LPR>(p1); p2 = lanes_sum<LPR>(p2); }
                     const int slot = (n0_cur + wn * WN) / WN;
                     if ((lane % LPR) == 0 && m < M && slot < slots) {
                         float* dst = partials + slot * ldp + m;

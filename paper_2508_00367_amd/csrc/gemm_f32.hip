@@ -99,11 +99,8 @@ struct F32Epilogue {
                        make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
             if (EPI == EPI_BIAS_RES_SHIFT) {
                 // the 16 lanes of a row in a fixed butterfly order; one slot per 64 features
-#pragma unroll
-                for (int off = 8; off >= 1; off >>= 1) {
-                    p0 += __shfl_xor(p0, off, 64);
-                    if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, 64); p2 += __shfl_xor(p2, off, 64); }
-                }
+                p0 = lanes_sum<16>(p0);
+                if (DIST == RS_DIST_COS) { p1 = lanes_sum<16>(p1); p2 = lanes_sum<16>(p2); }
                 if (tx == 0 && m_ok) {
                     float* dst = partials + (int64_t)tn * M + m;
                     dst[0] = p0;

@@ -234,9 +234,9 @@ __device__ __forceinline__ void gemm_epilogue_acc_layout(
                             for (int e = 0; e < 4; ++e) shift_term<DIST>(post ? v[e] + rr[e] : v[e], fi[e], s0, s1, s2);
                         }
                         // g = 1 restarts from the sum of g = 0 (its own first pass is discarded)
-                        const float h0 = __shfl_xor(s0, 32, 64);
+                        const float h0 = half_pair(s0).x;
                         float t0 = h0, t1 = 0.f, t2 = 0.f;
-                        if (DIST == RS_DIST_COS) { t1 = __shfl_xor(s1, 32, 64); t2 = __shfl_xor(s2, 32, 64); }
+                        if (DIST == RS_DIST_COS) { t1 = half_pair(s1).x; t2 = half_pair(s2).x; }
                         if (m_ok) {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) shift_term<DIST>(post ? v[e] + rr[e] : v[e], fi[e], t0, t1, t2);

@@ -5,6 +5,24 @@
 
 namespace rs {
 
+// Chunk `ch` (8 elements) of a row; zeros past its end.
+__device__ __forceinline__ void row_load8(__amdgpu_buffer_rsrc_t row, int ch, const bf16raw*, float (&v)[8]) {
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(row, ch * 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[2 * i] = __uint_as_float(w[i] << 16);
+        v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ void row_load8(__amdgpu_buffer_rsrc_t row, int ch, const float*, float (&v)[8]) {
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(row, ch * 32, 0, 0), b = __builtin_amdgcn_raw_buffer_load_b128(row, ch * 32 + 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = __uint_as_float(a[i]);
+        v[4 + i] = __uint_as_float(b[i]);
+    }
+}
+
 // MAXC = 8-element chunks a lane may hold: D <= MAXC * 64 * 8.
 template <typename T, int MAXC>
 __global__ __launch_bounds__(256) void layernorm_kernel(const T* __restrict__ x,
@@ -13,53 +31,41 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const T* __restrict__ x,
                                                         T* __restrict__ out, int64_t M, int D, float eps,
                                                         int32_t* __restrict__ iota_out, int iota_n) {
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (row >= M) return;
-    if (iota_out && lane == 0) iota_out[row] = (int32_t)(row % iota_n);
-    const int nchunk = D >> 3;
-    const T* xr = x + row * D;
+    const int nchunk = D >> 3, bytes = D * (int)sizeof(T);
+    const __amdgpu_buffer_rsrc_t rs_x = row_rsrc(x + row * D, bytes);
     float v[MAXC][8];
-    float sum = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int ch = lane + c * 64;
-        if (ch < nchunk) {
-            Elem<T>::load8(xr + ch * 8, v[c]);
+    for (int c = 0; c < MAXC; ++c) row_load8(rs_x, lane + c * 64, x, v[c]);
+    // gamma and beta on the way while the statistics are formed, where the registers allow
+    constexpr int EARLY = MAXC <= 2 ? MAXC : 0;
+    float g[EARLY ? EARLY : 1][8], b[EARLY ? EARLY : 1][8];
+    const __amdgpu_buffer_rsrc_t rs_g = row_rsrc(gamma, gamma ? bytes : 0), rs_b = row_rsrc(beta, beta ? bytes : 0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sum += v[c][i];
-        }
+    for (int c = 0; c < EARLY; ++c) {
+        row_load8(rs_g, lane + c * 64, gamma, g[c]);
+        row_load8(rs_b, lane + c * 64, beta, b[c]);
     }
-    const float mean = wave_sum(sum) / (float)D;
-    float sq = 0.f;
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int ch = lane + c * 64;
-        if (ch < nchunk) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                v[c][i] -= mean;
-                sq += v[c][i] * v[c][i];
-            }
-        }
-    }
-    const float inv = rsqrtf(wave_sum(sq) / (float)D + eps);
+    if (iota_out && lane == 0) iota_out[row] = (int32_t)(row % iota_n);
+    const float2 st = wave_row_stats<MAXC>(v, nchunk, lane, D, eps);
     T* orow = out + row * D;
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
-        const int ch = lane + c * 64;
-        if (ch < nchunk) {
-            float g[8], b[8], r[8];
-            if (gamma) Elem<T>::load8(gamma + ch * 8, g);
-            if (beta) Elem<T>::load8(beta + ch * 8, b);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                float t = v[c][i] * inv;
-                if (gamma) t *= g[i];
-                if (beta) t += b[i];
-                r[i] = t;
-            }
-            Elem<T>::store8(orow + ch * 8, r);
+        const int ch = lane + c * 64, e = EARLY ? c : 0;
+        if (!EARLY) {
+            row_load8(rs_g, ch, gamma, g[0]);
+            row_load8(rs_b, ch, beta, b[0]);
         }
+        float r[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float t = (v[c][i] - st.x) * st.y;
+            if (gamma) t *= g[e][i];
+            if (beta) t += b[e][i];
+            r[i] = t;
+        }
+        if (ch < nchunk) Elem<T>::store8(orow + ch * 8, r);
     }
 }
 
@@ -83,26 +89,17 @@ __global__ __launch_bounds__(256) void layernorm_narrow_kernel(const T* __restri
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) sum += v[i];
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    sum = lanes_sum<32>(sum);
     const float mean = sum / (float)D;
-    float sq = 0.f;
-    if (on) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            v[i] -= mean;
-            sq += v[i] * v[i];
-        }
-    }
-#pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, kWave);
+    float sq = on ? chunk_sq(v, mean) : 0.f;
+    sq = lanes_sum<32>(sq);
     const float inv = rsqrtf(sq / (float)D + eps);
     if (!on) return;
     if (iota_out && sub == 0) iota_out[row] = (int32_t)(row % iota_n);
     float r[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        float t = v[i] * inv;
+        float t = (v[i] - mean) * inv;
         if (gamma) t *= g[i];
         if (beta) t += b[i];
         r[i] = t;
@@ -113,22 +110,22 @@ __global__ __launch_bounds__(256) void layernorm_narrow_kernel(const T* __restri
 // Row statistics only: stats[row] = (mean, 1 / sqrt(var + eps)), same two-pass arithmetic as above.
 // The bf16 block feeds them to the GEMM that follows the LayerNorm, which applies the
 // normalisation in its epilogue (the normalised rows are never written).
+// Bound by issue and by the wave's one trip to memory rather than by bytes.  All of a row is requested before anything is
+// summed, in branch-free loads, and the sums go by DPP: 50432 x 768 23.4 us with a branch and a wait per chunk and sums
+// through the LDS pipe, 21.0 with the latter by DPP, 18.1 so (events around it included: about 5.1 TB/s); two or four rows per
+// wave 19.6.  16388 x 1024 10.7 / 10.1 / 9.3, 12552 x 768 8.6 / 8.0 / 7.1.
 template <typename T, int MAXC>
 __global__ __launch_bounds__(256) void rowstats_kernel(const T* __restrict__ x, float2* __restrict__ stats,
                                                        int64_t M, int D, float eps,
                                                        int32_t* __restrict__ iota_out, int iota_n) {
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (row >= M) return;
-    const int nchunk = D >> 3;
-    const T* xr = x + row * D;
+    const __amdgpu_buffer_rsrc_t rs_x = row_rsrc(x + row * D, D * (int)sizeof(T));
     float v[MAXC][8];
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int ch = lane + c * 64;
-        if (ch < nchunk) Elem<T>::load8(xr + ch * 8, v[c]);
-    }
-    const float2 st = wave_row_stats<MAXC>(v, nchunk, lane, D, eps);
+    for (int c = 0; c < MAXC; ++c) row_load8(rs_x, lane + c * 64, x, v[c]);
+    const float2 st = wave_row_stats<MAXC>(v, D >> 3, lane, D, eps);
     if (lane == 0) {
         stats[row] = st;
         if (iota_out) iota_out[row] = (int32_t)(row % iota_n);
@@ -154,19 +151,10 @@ __global__ __launch_bounds__(256) void rowstats_narrow_kernel(const T* __restric
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) sum += v[i];
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    sum = lanes_sum<G>(sum);
     const float mean = sum / (float)D;
-    float sq = 0.f;
-    if (on) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const float d = v[i] - mean;
-            sq += d * d;
-        }
-    }
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, kWave);
+    float sq = on ? chunk_sq(v, mean) : 0.f;
+    sq = lanes_sum<G>(sq);
     if (sub == 0 && row < M) {
         stats[row] = make_float2(mean, rsqrtf(sq / (float)D + eps));
         if (iota_out) iota_out[row] = (int32_t)(row % iota_n);
@@ -184,13 +172,19 @@ hipError_t launch_rowstats(rs_dtype dt, const void* x, float* stats, int64_t M, 
         else hipLaunchKernelGGL((rowstats_narrow_kernel<bf16raw, 32>), dim3((unsigned)((M + 7) / 8)), block, 0, s, xb, st, M, D, eps, iota_out, iota_n);
         return hipGetLastError();
     }
+#define RS_STATS(T_, MAXC_) \
+    hipLaunchKernelGGL((rowstats_kernel<T_, MAXC_>), grid, block, 0, s, (const T_*)x, st, M, D, eps, iota_out, iota_n)
     if (dt == RS_F32) {
-        if (D <= 2 * 512) hipLaunchKernelGGL((rowstats_kernel<float, 2>), grid, block, 0, s, (const float*)x, st, M, D, eps, iota_out, iota_n);
-        else hipLaunchKernelGGL((rowstats_kernel<float, 8>), grid, block, 0, s, (const float*)x, st, M, D, eps, iota_out, iota_n);
+        if (D <= 2 * 512) RS_STATS(float, 2);
+        else RS_STATS(float, 8);
+    } else if (D <= 512) {
+        RS_STATS(bf16raw, 1);
+    } else if (D <= 2 * 512) {
+        RS_STATS(bf16raw, 2);
     } else {
-        if (D <= 2 * 512) hipLaunchKernelGGL((rowstats_kernel<bf16raw, 2>), grid, block, 0, s, (const bf16raw*)x, st, M, D, eps, iota_out, iota_n);
-        else hipLaunchKernelGGL((rowstats_kernel<bf16raw, 8>), grid, block, 0, s, (const bf16raw*)x, st, M, D, eps, iota_out, iota_n);
+        RS_STATS(bf16raw, 8);
     }
+#undef RS_STATS
     return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ __device__ __forceinline__ float mlp_row_sum(const float (&s)[12]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) u[k] = t[k] + t[k + 4];
     const float w = (u[0] + u[2]) + (u[1] + u[3]);
-    return w + __shfl_xor(w, 32, kWave);
+    return half_sum(w);
 }
 __device__ __forceinline__ float2 mlp_row_stats(const u32x4 (&v)[12], int D, float eps) {
     float s[12];
@@ -53,7 +53,7 @@ __device__ __forceinline__ float2 mlp_row_stats(const u32x4 (&v)[12], int D, flo
     const float mean = mlp_row_sum(s) / (float)D;
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-        // written out as the compiler contracts the sum of the other kernels: the second square is the rounded one
+        // chunk_sq, element by element: the second square is the rounded one
         float d[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -67,11 +67,8 @@ __device__ __forceinline__ float group_score(const float (&x)[8], const float (&
     float p0 = 0.f, p1 = 0.f, p2 = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) dist_term<DIST>(x[i], y[i], p0, p1, p2);
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) {
-        p0 += __shfl_xor(p0, off, kWave);
-        if (DIST == RS_DIST_COS) { p1 += __shfl_xor(p1, off, kWave); p2 += __shfl_xor(p2, off, kWave); }
-    }
+    p0 = lanes_sum<G>(p0);
+    if (DIST == RS_DIST_COS) { p1 = lanes_sum<G>(p1); p2 = lanes_sum<G>(p2); }
     return dist_value<DIST>(p0, p1, p2);
 }
 
@@ -181,11 +178,7 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 template <int NT>
 __device__ __forceinline__ int block_scan_incl(int v, int* s_wave /*[NT / 64]*/, int tid) {
     const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int t = __shfl_up(v, off, 64);
-        if (lane >= off) v += t;
-    }
+    v = wave_scan_incl(v);
     __syncthreads();  // protects s_wave against the previous use
     if (lane == 63) s_wave[wave] = v;
     __syncthreads();
@@ -228,11 +221,8 @@ __device__ __forceinline__ void block_select_lds(float* sc, int N, int n_prefix,
         k_and &= key;
         k_or |= key;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        k_and &= __shfl_xor(k_and, off, 64);
-        k_or |= __shfl_xor(k_or, off, 64);
-    }
+    k_and = lanes_reduce<64>(k_and, [](uint32_t a, uint32_t b) { return a & b; });
+    k_or = lanes_reduce<64>(k_or, [](uint32_t a, uint32_t b) { return a | b; });
     if (lane == 0) { sh.wave[wave] = (int)k_and; sh.wave[16 + wave] = (int)k_or; }
     if (tid < 256) sh.hist[tid] = 0;
     if (tid == 0) sh.count = 0;
@@ -255,11 +245,7 @@ __device__ __forceinline__ void block_select_lds(float* sc, int N, int n_prefix,
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { c[e] = sh.hist[255 - 4 * lane - e]; incl += c[e]; }
                 const int own = incl;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int t = __shfl_up(incl, off, 64);
-                    if (lane >= off) incl += t;
-                }
+                incl = wave_scan_incl(incl);
                 int above = incl - own;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -315,15 +301,10 @@ __device__ __forceinline__ void block_select_lds(float* sc, int N, int n_prefix,
         for (int t0 = 0; t0 < words; t0 += 64) {
             const int t = t0 + lane;
             const int g = t < words ? sh.gt[t] : 0, e = t < words ? sh.eq[t] : 0;
-            int ig = g, ie = e;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int ug = __shfl_up(ig, off, 64), ue = __shfl_up(ie, off, 64);
-                if (lane >= off) { ig += ug; ie += ue; }
-            }
+            const int ig = wave_scan_incl(g), ie = wave_scan_incl(e);
             if (t < words) { sh.gt[t] = bg + ig - g; sh.eq[t] = be + ie - e; }
-            bg += __shfl(ig, 63, 64);
-            be += __shfl(ie, 63, 64);
+            bg += __builtin_amdgcn_readlane(ig, 63);
+            be += __builtin_amdgcn_readlane(ie, 63);
         }
     }
     __syncthreads();
@@ -668,12 +649,10 @@ __global__ __launch_bounds__(256) void shift_scores_paired_kernel(const T* __res
             for (int e = 0; e < 4; ++e) dist_term<DIST>(fx[e], fy[e], p[h][0], p[h][1], p[h][2]);
         }
 #pragma unroll
-    for (int i = 0; i < (DIST == RS_DIST_COS ? 3 : 1); ++i)
-#pragma unroll
-        for (int off = G / 2; off >= 1; off >>= 1) {
-            p[0][i] += __shfl_xor(p[0][i], off, kWave);
-            p[1][i] += __shfl_xor(p[1][i], off, kWave);
-        }
+    for (int i = 0; i < (DIST == RS_DIST_COS ? 3 : 1); ++i) {
+        p[0][i] = lanes_sum<G>(p[0][i]);
+        p[1][i] = lanes_sum<G>(p[1][i]);
+    }
     if (sub == 0 && row < M) scores[row] = dist_value<DIST>(p[0][0] + p[1][0], p[0][1] + p[1][1], p[0][2] + p[1][2]);
 }
 
@@ -850,25 +829,26 @@ __global__ __launch_bounds__(256) void gather_rows_stats_kernel(const bf16raw* _
                                                                 float2* __restrict__ stats, int64_t rows, int N,
                                                                 int K, int D, float eps) {
     const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (r >= rows) return;
     const int64_t b = r / K;
     const bf16raw* s = src + (b * N + kept_idx[r]) * D;
     bf16raw* d = out + r * D;
     const int nchunk = D >> 3;
+    u32x4 raw[MAXC];
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) {
+        raw[c] = u32x4{0u, 0u, 0u, 0u};
+        if (lane + c * 64 < nchunk) raw[c] = *reinterpret_cast<const u32x4*>(s + (lane + c * 64) * 8);
+    }
     float v[MAXC][8];
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
-        const int ch = lane + c * 64;
-        if (ch < nchunk) {
-            const uint4 raw = *reinterpret_cast<const uint4*>(s + ch * 8);
-            *reinterpret_cast<uint4*>(d + ch * 8) = raw;
-            const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        if (lane + c * 64 < nchunk) *reinterpret_cast<u32x4*>(d + (lane + c * 64) * 8) = raw[c];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[c][2 * i] = __uint_as_float(w[i] << 16);
-                v[c][2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-            }
+        for (int i = 0; i < 4; ++i) {
+            v[c][2 * i] = __uint_as_float(raw[c][i] << 16);
+            v[c][2 * i + 1] = __uint_as_float(raw[c][i] & 0xffff0000u);
         }
     }
     const float2 st = wave_row_stats<MAXC>(v, nchunk, lane, D, eps);
