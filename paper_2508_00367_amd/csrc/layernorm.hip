@@ -1,6 +1,6 @@
 // LayerNorm of Eqs. (5),(6), Sec. 3.3: one wavefront per token row, the row held in
 // registers, mean then variance of the deviations (population variance), fp32 statistics.
-// HBM-bound: one read and one write of the row.
+// Bound by one read and one write of the row.
 #include "common.hpp"
 
 namespace rs {
