@@ -1243,7 +1243,7 @@ static void launch_direct(const GemmArgs& g, hipStream_t s) {
 template <int EPI, int DIST, bool WF>
 static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
     for (int64_t r = 0; r < g.M;) {
-        const GemmChoice c = WF ? gemm_choose_frag(g.M - r, g.N, g.K, device_cus()) : gemm_choose(g.M - r, g.N, g.K, device_cus());
+        const GemmChoice c = WF ? gemm_choose_frag(g.M - r, g.N, g.K, device_cus(), epi_res(EPI)) : gemm_choose(g.M - r, g.N, g.K, device_cus());
         const GemmArgs part = g.rows(r, r + c.rows);
         switch (c.tile) {
             case GemmTile::Slim64x64: launch_slim<2, 1, 1, 4, EPI, DIST, WF>(part, s); break;

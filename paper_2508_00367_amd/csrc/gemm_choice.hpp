@@ -45,23 +45,28 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
     return {GemmTile::Persistent, m1 > 0 ? m1 : M};
 }
 
-// The same for weights in fragment order (a block's layers).  The small slim tiles as above; the direct kernel (128 x 256 tiles, two
-// workgroups per CU) takes the place of the ring and of most of what the persistent kernel does, and cuts off no rows
-// behind whole rounds: its workgroups hand a free slot on, and a CU with only one runs it faster.  us, the best of the
-// others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
+// The same for weights in fragment order (a block's layers; `res`: with a residual in the epilogue).  The small slim tiles as above; the
+// direct kernel (128 x 256 tiles, two workgroups per CU) takes the place of the ring and of most of what the persistent kernel
+// does, and cuts off no rows behind whole rounds: its workgroups hand a free slot on, and a CU with only one runs it faster.  us, the
+// best of the others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
 // 384 -> 1536 at 50432 95 / 84, at 12608 37 / 29.
-//  - up to one 256 x 128 slim tile per CU (eight waves, residual rows requested early): those, but for 768 <= K < 1536 and more
-//    than 0.7 tiles per CU.  slim / direct: 768 x 768 at 6280 rows (150 tiles) 15.2 / 16.1, 1536 -> 384 at 12608 (198) 24.0 / 28.0,
-//    384 x 384 there 11.3 / 12.2; 768 -> 2304 at 3144 (225) 17.7 / 16.2, 1024 x 1024 at 8036 (252) 26.9 / 23.2.
+//  - up to one 256 x 128 slim tile per CU (eight waves, residual rows requested early): those.  Only without a residual, at 768 <= K < 1536
+//    and more than 0.7 tiles per CU, the direct kernel where it too has at most one tile per CU.  slim / direct in a block: with
+//    residual 768 x 768 at 9244 rows 18.0 / 19.4, 1024 x 1024 at 8036 22.4 / 23.1, 1344 -> 256 at 24600 25.3 / 28.1; without 768 -> 2304 at 3368
+//    18.1 / 16.8, 1024 -> 3072 at 2064 19.5 / 18.5, but 1088 -> 832 at 9100 (288 direct tiles) 23.6 / 31.6, 832 x 832 there 19.7 / 27.3.
+//  - N is no multiple of 256 and the direct kernel would have more than two tiles per CU, the slim one at most two: slim.  slim /
+//    direct: 1088 x 1088 at 13664 41.1 / 47.5, 832 -> 576 at 23564 39.8 / 43.8, 1280 -> 320 at 33000 41.8 / 50.7, 256 -> 1344 at 10944 21.3 / 24.0.
 //  - K >= 1536 and a last round of 256 x 256 tiles more than half full: the persistent kernel, which moves two thirds of the
 //    bytes per flop.  persistent / direct: 3072 -> 768 at 41216 rows 176 / 189, 21760 91 / 96, 12552 72 / 75; with a last round half
 //    empty 25216 152 / 130, 30208 157 / 140.
-inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus) {
+inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus, bool res) {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (tiles(64, 64) <= cus) return {GemmTile::Slim64x64, M};
     if (tiles(128, 64) <= cus) return {GemmTile::Slim128x64, M};
     if (tiles(128, 128) <= cus) return {GemmTile::Slim128x128, M};
-    if (tiles(256, 128) <= cus && (K < 768 || K >= 1536 || 10 * tiles(256, 128) <= 7 * cus)) return {GemmTile::Slim256x128, M};
+    const int64_t slim = tiles(256, 128), direct = tiles(128, 256);
+    if (slim <= cus) return {!res && K >= 768 && K < 1536 && 10 * slim > 7 * cus && direct <= cus ? GemmTile::Direct : GemmTile::Slim256x128, M};
+    if (slim <= 2 * cus && direct > 2 * cus) return {GemmTile::Slim256x128, M};
     const int64_t rem = tiles(256, 256) % cus;
     return {K >= 1536 && (rem == 0 || 2 * rem > cus) ? GemmTile::Persistent : GemmTile::Direct, M};
 }

@@ -14,7 +14,8 @@ CASES = [  # B, N, D, Dm
     (1, 1, 64, 64), (1, 127, 64, 128), (1, 128, 128, 192), (3, 43, 192, 320), (1, 257, 256, 64), (2, 192, 320, 448), (5, 77, 448, 832),
     (2, 197, 576, 256), (40, 197, 384, 1536),                                  # by shape: direct for every layer but the projection
     (17, 197, 768, 3072),                                                      # by shape: slim, direct and 128 x 128
-    (66, 197, 768, 3072)]                                                      # by shape: direct, and persistent for fc2
+    (66, 197, 768, 3072),                                                      # by shape: direct, and persistent for fc2
+    (60, 197, 832, 576), (120, 197, 576, 832)]                                 # by shape: slim 256 x 128, up to one round and two
 
 
 @pytest.mark.parametrize("dist", [rs.RS_DIST_L2, rs.RS_DIST_COS])
