@@ -47,8 +47,8 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
 
 // The same for weights in fragment order (a block's layers; `res`: with a residual in the epilogue).  The small slim tiles as above; the
 // direct kernel (128 x 256 tiles, two workgroups per CU) takes the place of the ring and of most of what the persistent kernel
-// does, and cuts off no rows behind whole rounds: its workgroups hand a free slot on, and a CU with only one runs it faster.  us, the
-// best of the others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
+// does: its workgroups hand a free slot on, and a CU with only one runs it faster, so that a last round half full costs about
+// half of one.  us, the best of the others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
 // 384 -> 1536 at 50432 95 / 84, at 12608 37 / 29.
 //  - up to one 256 x 128 slim tile per CU (eight waves, residual rows requested early): those.  Only without a residual, at 768 <= K < 1536
 //    and more than 0.7 tiles per CU, the direct kernel where it too has at most one tile per CU.  slim / direct in a block: with
@@ -56,9 +56,14 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
 //    18.1 / 16.8, 1024 -> 3072 at 2064 19.5 / 18.5, but 1088 -> 832 at 9100 (288 direct tiles) 23.6 / 31.6, 832 x 832 there 19.7 / 27.3.
 //  - N is no multiple of 256 and the direct kernel would have more than two tiles per CU, the slim one at most two: slim.  slim /
 //    direct: 1088 x 1088 at 13664 41.1 / 47.5, 832 -> 576 at 23564 39.8 / 43.8, 1280 -> 320 at 33000 41.8 / 50.7, 256 -> 1344 at 10944 21.3 / 24.0.
-//  - K >= 1536 and a last round of 256 x 256 tiles more than half full: the persistent kernel, which moves two thirds of the
-//    bytes per flop.  persistent / direct: 3072 -> 768 at 41216 rows 176 / 189, 21760 91 / 96, 12552 72 / 75; with a last round half
-//    empty 25216 152 / 130, 30208 157 / 140.
+//  - K >= 2048 and a last round of 256 x 256 tiles at most a sixth full: a few tiles alone cost the direct kernel two thirds of a
+//    round.  The rows of whole rounds go to the persistent kernel, those behind them to the tile that suits them, in a second launch.
+//    us, cut / direct: 4096 -> 1024 at 16388 rows 130 / 145, 18000 136 / 147, 20000 (0.23) 159 / 150, 33200 249 / 272; 3072 -> 768 at 23000
+//    103 / 115, 25216 (0.16) 112 / 116, 27392 (0.25) 137 / 124, 45568 202 / 213, 48000 (0.2) 213 / 215; 2560 -> 640 at 22000 89 / 96; 2048 -> 512 at
+//    33000 82.5 / 84.4; 1792 -> 448 there 71.3 / 72.7, at 36000 76.2 / 75.1.  A row panel of more tiles than the whole rounds hold stays whole.
+//  - K >= 1536 and a last round more than half full (0.6 below K = 3072): the persistent kernel, which moves two thirds of the
+//    bytes per flop.  persistent / direct: 3072 -> 768 at 41216 rows (0.89) 170 / 182, 33536 (0.54) 155 / 167, 21760 89.5 / 90.2, 12552 63.5 / 71.9, 28800
+//    (0.32) 147 / 124; 1536 -> 384 at 25216 40.1 / 44.0, 50432 (0.54) 91 / 83; 2048 -> 512 at 50000 (0.53) 129 / 123; 2560 -> 640 at 33684 (0.55) 139 / 136.
 inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus, bool res) {
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     if (tiles(64, 64) <= cus) return {GemmTile::Slim64x64, M};
@@ -67,8 +72,12 @@ inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus, boo
     const int64_t slim = tiles(256, 128), direct = tiles(128, 256);
     if (slim <= cus) return {!res && K >= 768 && K < 1536 && 10 * slim > 7 * cus && direct <= cus ? GemmTile::Direct : GemmTile::Slim256x128, M};
     if (slim <= 2 * cus && direct > 2 * cus) return {GemmTile::Slim256x128, M};
-    const int64_t rem = tiles(256, 256) % cus;
-    return {K >= 1536 && (rem == 0 || 2 * rem > cus) ? GemmTile::Persistent : GemmTile::Direct, M};
+    const int64_t t = tiles(256, 256), rem = t % cus;
+    if (K >= 2048 && t > cus && rem > 0 && 6 * rem <= cus) {
+        const int64_t m1 = (t - rem) / ((N + 255) / 256) * 256;  // row panels that fill whole rounds
+        if (m1 > 0) return {GemmTile::Persistent, m1};
+    }
+    return {K >= 1536 && (rem == 0 || 10 * rem > (K < 3072 ? 6 : 5) * cus) ? GemmTile::Persistent : GemmTile::Direct, M};
 }
 
 // fp32: the rows of one launch, in whole tiles of `bm` x 64: it has 256 threads per tile, tiles rounded up to a multiple of

@@ -15,7 +15,8 @@ CASES = [  # B, N, D, Dm
     (2, 197, 576, 256), (40, 197, 384, 1536),                                  # by shape: direct for every layer but the projection
     (17, 197, 768, 3072),                                                      # by shape: slim, direct and 128 x 128
     (66, 197, 768, 3072),                                                      # by shape: direct, and persistent for fc2
-    (60, 197, 832, 576), (120, 197, 576, 832)]                                 # by shape: slim 256 x 128, up to one round and two
+    (60, 197, 832, 576), (120, 197, 576, 832),                                 # by shape: slim 256 x 128, up to one round and two
+    (113, 197, 768, 3072)]                                                     # by shape: fc2 persistent, its last 501 rows apart
 
 
 @pytest.mark.parametrize("dist", [rs.RS_DIST_L2, rs.RS_DIST_COS])

@@ -14,7 +14,7 @@ def _run(tmp_path, body):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     src, exe = tmp_path / "choice.cpp", tmp_path / "choice"
-    src.write_text('#include <stdio.h>\n#include "gemm_choice.hpp"\nusing namespace rs;\nint main() {\n' + body + "\nreturn 0;\n}\n")
+    src.write_text('#include <stdio.h>\n#include <initializer_list>\n#include "gemm_choice.hpp"\nusing namespace rs;\nint main() {\n' + body + "\nreturn 0;\n}\n")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2508_00367_amd", "csrc"),
                     str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
@@ -67,3 +67,35 @@ def test_fragments_two_slim_tiles_per_cu(tmp_path):
     _whole(tmp_path, [(13664, 1088, 1088, 1, "slim 256x128"), (23564, 576, 832, 1, "slim 256x128"), (33000, 320, 1280, 1, "slim 256x128"),
                       (10944, 1344, 256, 0, "slim 256x128"), (36000, 384, 1536, 1, "slim 256x128"),
                       (25216, 768, 768, 1, "direct"), (43800, 384, 1536, 1, "direct"), (20280, 768, 640, 0, "direct")])
+
+
+def test_fragments_few_tiles_beyond_whole_rounds(tmp_path):
+    """Long K and a last round of 256 x 256 tiles at most a sixth full: whole rounds to the persistent kernel, the rest to a tile of its own."""
+    got = _frag(tmp_path, [(16388, 1024, 4096, 1), (23000, 768, 3072, 1), (45568, 768, 3072, 1), (33200, 1024, 4096, 1)])
+    assert got == [[("persistent", 16384), ("slim 64x64", 4)], [("persistent", 21760), ("slim 64x64", 1240)],
+                   [("persistent", 43520), ("slim 128x64", 2048)], [("persistent", 32768), ("slim 64x64", 432)]]
+    _whole(tmp_path, [(20000, 1024, 4096, 1, "direct"), (27392, 768, 3072, 1, "direct"), (50432, 768, 3072, 1, "direct"),
+                      (36000, 448, 1792, 1, "direct"), (16384, 1024, 4096, 1, "persistent"), (21760, 768, 3072, 1, "persistent"),
+                      (33536, 768, 3072, 1, "persistent"), (41216, 768, 3072, 1, "persistent"), (50432, 384, 1536, 1, "direct"),
+                      (50000, 512, 2048, 1, "direct"), (25216, 384, 1536, 1, "persistent")])
+
+
+def test_fragments_every_row_goes_to_one_kernel(tmp_path):
+    """The choice ends, and leaves no row out and no launch empty, at all widths and chips."""
+    out = _run(tmp_path, r"""
+    long n = 0;
+    for (int64_t cus : {8, 64, 256, 304})
+        for (int64_t p : {0, 1, 2, 3, 7, 64, 85, 86, 197, 4096})
+            for (int64_t d : {-1, 0, 1, 64, 65, 255})
+                for (int64_t N : {64, 128, 192, 320, 768, 1024, 3072, 65536, 65600, 196608, 1048576})
+                    for (int K : {64, 384, 512, 576, 768, 1472, 1536, 2048, 4096})
+                        for (int res : {0, 1}) {
+                            int64_t left = p * 256 + d;
+                            for (int parts = 0; left > 0; ++n) {
+                                const GemmChoice c = gemm_choose_frag(left, N, K, cus, res);
+                                if (c.rows < 1 || c.rows > left || (c.rows < left && c.rows % 256) || ++parts > 64) return 1;
+                                left -= c.rows;
+                            }
+                        }
+    printf("ok\n");""")
+    assert out == ["ok"]
