@@ -1250,7 +1250,10 @@ static void launch_by_shape(const GemmArgs& g, hipStream_t s) {
             case GemmTile::Slim128x64: launch_slim<4, 1, 1, 4, EPI, DIST, WF>(part, s); break;
             case GemmTile::Slim128x128: launch_slim<2, 2, 2, 3, EPI, DIST, WF>(part, s); break;
             case GemmTile::Slim256x128: launch_slim<4, 2, 2, 3, EPI, DIST, WF>(part, s); break;
-            case GemmTile::Ring: if constexpr (!WF) launch_ring_auto<EPI, DIST>(part, s); break;
+            case GemmTile::Ring:
+                if constexpr (WF) launch_ring<128, 128, EPI, DIST, true>(part, s);
+                else launch_ring_auto<EPI, DIST>(part, s);
+                break;
             case GemmTile::Direct: if constexpr (WF) launch_direct<EPI, DIST>(part, s); break;
             case GemmTile::Persistent: launch_persistent<EPI, DIST, WF>(part, s); break;
         }

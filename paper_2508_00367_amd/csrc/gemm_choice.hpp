@@ -46,14 +46,18 @@ inline GemmChoice gemm_choose(int64_t M, int64_t N, int K, int64_t cus) {
 }
 
 // The same for weights in fragment order (a block's layers; `res`: with a residual in the epilogue).  The small slim tiles as above; the
-// direct kernel (128 x 256 tiles, two workgroups per CU) takes the place of the ring and of most of what the persistent kernel
-// does: its workgroups hand a free slot on, and a CU with only one runs it faster, so that a last round half full costs about
+// direct kernel (128 x 256 tiles, two workgroups per CU) takes the place of most of what the ring and the persistent kernel
+// do: its workgroups hand a free slot on, and a CU with only one runs it faster, so that a last round half full costs about
 // half of one.  us, the best of the others / direct: 768 x 768 at 50432 rows 85 / 72, at 25216 48 / 38; 768 -> 3072 at 50432 287 / 242, at 6280 52 / 39;
 // 384 -> 1536 at 50432 95 / 84, at 12608 37 / 29.
 //  - up to one 256 x 128 slim tile per CU (eight waves, residual rows requested early): those.  Only without a residual, at 768 <= K < 1536
 //    and more than 0.7 tiles per CU, the direct kernel where it too has at most one tile per CU.  slim / direct in a block: with
 //    residual 768 x 768 at 9244 rows 18.0 / 19.4, 1024 x 1024 at 8036 22.4 / 23.1, 1344 -> 256 at 24600 25.3 / 28.1; without 768 -> 2304 at 3368
 //    18.1 / 16.8, 1024 -> 3072 at 2064 19.5 / 18.5, but 1088 -> 832 at 9100 (288 direct tiles) 23.6 / 31.6, 832 x 832 there 19.7 / 27.3.
+//  - N <= 128 beyond that: a 256-wide tile would be half empty or more.  The ring kernel's 128 x 128 tiles to K = 512, the slim tiles from there.
+//    us, ring / slim / direct: 64 x 64 at 91520 rows 10.3 / 14.7 / 14.7, at 372288 32 / 39 / 42; 256 -> 64 at 91520 18.4 / 23.7 / 29.3; 128 x 128 at 75680
+//    14.5 / 18.2 / 18.2; 448 -> 128 at 86840 25.4 / 30.1 / 35.2; 512 -> 128 at 300320 118 / 119 / 134; 1024 -> 128 at 165252 114 / 112 / 125; 2048 -> 64
+//    at 121512 150 / 145 / 159.
 //  - N is no multiple of 256 and the direct kernel would have more than two tiles per CU, the slim one at most two: slim.  slim /
 //    direct: 1088 x 1088 at 13664 41.1 / 47.5, 832 -> 576 at 23564 39.8 / 43.8, 1280 -> 320 at 33000 41.8 / 50.7, 256 -> 1344 at 10944 21.3 / 24.0.
 //  - K >= 2048 and a last round of 256 x 256 tiles at most a sixth full: a few tiles alone cost the direct kernel two thirds of a
@@ -71,6 +75,7 @@ inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus, boo
     if (tiles(128, 128) <= cus) return {GemmTile::Slim128x128, M};
     const int64_t slim = tiles(256, 128), direct = tiles(128, 256);
     if (slim <= cus) return {!res && K >= 768 && K < 1536 && 10 * slim > 7 * cus && direct <= cus ? GemmTile::Direct : GemmTile::Slim256x128, M};
+    if (N <= 128) return {K <= 512 ? GemmTile::Ring : GemmTile::Slim256x128, M};
     if (slim <= 2 * cus && direct > 2 * cus) return {GemmTile::Slim256x128, M};
     const int64_t t = tiles(256, 256), rem = t % cus;
     if (K >= 2048 && t > cus && rem > 0 && 6 * rem <= cus) {

@@ -16,7 +16,8 @@ CASES = [  # B, N, D, Dm
     (17, 197, 768, 3072),                                                      # by shape: slim, direct and 128 x 128
     (66, 197, 768, 3072),                                                      # by shape: direct, and persistent for fc2
     (60, 197, 832, 576), (120, 197, 576, 832),                                 # by shape: slim 256 x 128, up to one round and two
-    (113, 197, 768, 3072)]                                                     # by shape: fc2 persistent, its last 501 rows apart
+    (113, 197, 768, 3072),                                                     # by shape: fc2 persistent, its last 501 rows apart
+    (335, 197, 64, 576), (335, 197, 128, 256)]                                 # by shape: ring; fc2 of the first slim 256 x 128, of the second ring
 
 
 @pytest.mark.parametrize("dist", [rs.RS_DIST_L2, rs.RS_DIST_COS])

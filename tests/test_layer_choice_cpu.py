@@ -69,6 +69,13 @@ def test_fragments_two_slim_tiles_per_cu(tmp_path):
                       (25216, 768, 768, 1, "direct"), (43800, 384, 1536, 1, "direct"), (20280, 768, 640, 0, "direct")])
 
 
+def test_fragments_narrow(tmp_path):
+    """At most 128 features: tiles no wider than that."""
+    _whole(tmp_path, [(65536, 64, 64, 1, "slim 256x128"), (65537, 64, 64, 1, "ring"), (372288, 64, 64, 1, "ring"), (91520, 64, 256, 1, "ring"),
+                      (75680, 128, 128, 1, "ring"), (300320, 128, 512, 1, "ring"), (300320, 128, 576, 1, "slim 256x128"),
+                      (165252, 128, 1024, 1, "slim 256x128"), (121512, 64, 2048, 1, "slim 256x128"), (75732, 192, 64, 0, "direct")])
+
+
 def test_fragments_few_tiles_beyond_whole_rounds(tmp_path):
     """Long K and a last round of 256 x 256 tiles at most a sixth full: whole rounds to the persistent kernel, the rest to a tile of its own."""
     got = _frag(tmp_path, [(16388, 1024, 4096, 1), (23000, 768, 3072, 1), (45568, 768, 3072, 1), (33200, 1024, 4096, 1)])
