@@ -89,4 +89,26 @@ inline GemmChoice gemm_choose_frag(int64_t M, int64_t N, int K, int64_t cus, boo
 // 8, and holds less than 2^32 of them.
 inline int64_t gemm_f32_launch_rows(int N, int bm) { return (((int64_t)1 << 24) - 8) / ((N + 63) / 64) * bm; }
 
+// fp32: tiles shared by the waves (64 x 64), with 3 or 4 workgroups per CU, or (0) 32 x 64 tiles with K split over the waves.  Same results
+// either way.
+//  - The shared tiles where they fill the chip: four rounds of one tile per CU, 1.5 where K is short (the sum through LDS of the split tiles
+//    is a large part of a tile then), and in between where the last round is at least 0.9 full, a tile being a long unit of work at long K.
+//    us, shared / split (tiles in brackets): K = 192: 3152 x 576 (450) 9.5 / 12.0, 10088 x 192 (474) 9.8 / 12.5, 6304 x 192 (297) 9.3 / 9.7, 1576 x 768
+//    with GELU (300) 11.9 / 11.8; K = 768: 10088 x 192 (474) 27.7 / 30.0, 20000 x 192 (939) 50.6 / 56.2, 12608 x 192 (591) 38.7 / 36.8, 8192 x 192 (384)
+//    27.0 / 23.4, 788 x 192 (39) 15.9 / 9.5; 3072 -> 768 at 4000 rows (756) 143 / 150, at 2000 (384) 97 / 77.
+//  - Not a single column of them at long K between four and 5.5 rounds, which reads its rows in 128-byte pieces that no other tile
+//    shares: 2048 -> 64 at 76800 rows (1200) 247 (three per CU) / 215, at 82560 256 / 232, at 96000 262 / 259; at 48640 (760) 121 / 146, at 114560 (1790) 278 / 290.
+//  - Three per CU between four and five rounds, where a fourth leaves a lone tile behind, and at long K.  us, three / four: 2048 -> 2304
+//    at 2176 rows (1224) 161 / 187, 768 -> 192 at 25600 (1200) 66 / 76, 1024 x 1024 at 4800 (1200) 83 / 91, 4096 -> 1024 at 7168 (1792) 433 / 473;
+//    beyond, at K = 768 and 192, three cost 1 to 2 and 5 %.
+struct GemmF32Choice {
+    int per_cu;
+};
+inline GemmF32Choice gemm_f32_choose(int64_t M, int N, int K, int64_t cus) {
+    const int64_t tiles = ((M + 63) / 64) * (N / 64);
+    const bool fills = tiles >= 4 * cus || (K <= 384 && 2 * tiles >= 3 * cus) || (tiles > cus && 10 * tiles >= 9 * cus * ((tiles + cus - 1) / cus));
+    if (!fills || (N == 64 && K > 1024 && tiles > 4 * cus && tiles < 6 * cus)) return {0};
+    return {tiles > 4 * cus && (tiles < 5 * cus || K > 1024) ? 3 : 4};
+}
+
 }  // namespace rs

@@ -243,6 +243,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(
 // slices (one barrier each).  Slices of 32 k, so that two stages are 32 KB and four workgroups share a CU: tiles are a
 // few slices long, and what three of them wait for (first slice, stores) the fourth fills.  Slices of 64 and two workgroups
 // before: 12608 x 768 x 192 40.6 us, 35.5 now, with GELU 50.5 / 41.3, 12608 x 768 x 768 128.6 / 117.
+// Where the choice asks for three workgroups per CU, a launch claims kWidePad bytes of LDS more, which nobody uses.
+constexpr unsigned kWidePad = 8192;
 template <int EPI, int DIST>
 __global__ __launch_bounds__(256, 4) void gemm_f32_wide_kernel(
     const float* __restrict__ a, const float* __restrict__ w, const float* __restrict__ bias,
@@ -252,6 +254,8 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_wide_kernel(
     __shared__ __attribute__((aligned(1024))) unsigned char st0[BM * PITCH];  // the sums go through it at the end
     __shared__ __attribute__((aligned(1024))) unsigned char st1[2 * SLICE];
     static_assert(BM * PITCH >= 2 * SLICE, "a stage: two partial sums' k");
+    constexpr int LDS = BM * PITCH + 2 * SLICE, CU_LDS = 160 * 1024;
+    static_assert(4 * LDS <= CU_LDS && 3 * (LDS + (int)kWidePad) <= CU_LDS && 4 * (LDS + (int)kWidePad) > CU_LDS, "four, or with the padding three workgroups");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -338,34 +342,25 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_wide_kernel(
             m0, tn, slots, M, N);
 }
 
-// Same results either way.  The shared 64-row tiles where they fill the chip: four rounds of one tile per CU, 1.5 where K is
-// short (the sum through LDS of the split tiles is a large part of a tile then), and in between where the last round is
-// at least 0.9 full, a tile being a long unit of work at long K; 32-row tiles with K split over the waves below.
-// Measured, shared / split (us, tiles of 64 rows in brackets): K = 192: 3152 x 576 (450) 9.5 / 12.0, 10088 x 192 (474) 9.8 / 12.5, 6304 x 192
-// (297) 9.3 / 9.7, 1576 x 768 with GELU (300) 11.9 / 11.8; K = 768: 10088 x 192 (474) 27.7 / 30.0, 20000 x 192 (939) 50.6 / 56.2,
-// 12608 x 192 (591) 38.7 / 36.8, 8192 x 192 (384) 27.0 / 23.4, 788 x 192 (39) 15.9 / 9.5; 3072 -> 768 at 4000 rows (756) 143 / 150, at 2000 (384) 97 / 77.
-static bool f32_wide(int64_t M, int N, int K) {
-    const int64_t tiles = ((M + 63) / 64) * (N / 64), cus = device_cus();
-    if (tiles >= 4 * cus || (K <= 384 && 2 * tiles >= 3 * cus)) return true;
-    return tiles > cus && 10 * tiles >= 9 * cus * ((tiles + cus - 1) / cus);
-}
 template <int EPI, int DIST>
 static hipError_t launch_t(const void* a, const void* w, const void* bias, const void* res, void* out, float* partials,
                            const void* ref, bool post, int64_t M, int N, int K, hipStream_t s) {
     const int tiles_n = N / 64;
-    const bool wide = f32_wide(M, N, K);
+    const GemmF32Choice c = gemm_f32_choose(M, N, K, device_cus());
+    const bool wide = c.per_cu > 0;
     const int bm = wide ? 64 : 32;
+    const unsigned lds = c.per_cu == 3 ? kWidePad : 0;
     const int64_t rows = gemm_f32_launch_rows(N, bm);
     if (partials && M > rows) return hipErrorInvalidValue;  // the sums' slots lie M apart: one launch (rows of 4096 values at most)
     for (int64_t r = 0; r < M; r += rows) {
         const int64_t m = M - r < rows ? M - r : rows, tiles_m = (m + bm - 1) / bm, nblk = tiles_m * tiles_n;
-        auto go = [&](auto* kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), 0, s, (const float*)a + r * K,
+        auto go = [&](auto* kernel, unsigned pad) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * ((nblk + 7) / 8))), dim3(256), pad, s, (const float*)a + r * K,
                                (const float*)w, (const float*)bias, res ? (const float*)res + r * N : nullptr, (float*)out + r * N,
                                partials, ref ? (const float*)ref + r * N : nullptr, post ? 1 : 0, (int)m, N, K, (int)tiles_m, tiles_n);
         };
-        if (wide) go(&gemm_f32_wide_kernel<EPI, DIST>);
-        else go(&gemm_f32_kernel<EPI, DIST>);
+        if (wide) go(&gemm_f32_wide_kernel<EPI, DIST>, lds);
+        else go(&gemm_f32_kernel<EPI, DIST>, 0u);
     }
     return hipGetLastError();
 }

@@ -163,7 +163,8 @@ def test_fp32_attention_low_values_as_a_mask(N, masked, value):
     assert err < TOL["f32"]
 
 
-@pytest.mark.parametrize("M,K,N", [(6208, 64, 256), (24576, 64, 64), (24513, 448, 64), (10088, 768, 192), (9601, 832, 192), (21845, 192, 192)])
+@pytest.mark.parametrize("M,K,N", [(6208, 64, 256), (24576, 64, 64), (24513, 448, 64), (10088, 768, 192), (9601, 832, 192), (21845, 192, 192),
+                                   (25601, 768, 192), (4545, 1088, 1024)])  # three workgroups per CU: four to five rounds
 def test_fp32_shared_tiles_same_bits(M, K, N):
     """Sizes that go to the 64-row tiles the waves share (1.5 rounds at short K, a last round at least 0.9 full at long K; 2, 6,
     14, 24 and 26 slices): the bits of the same rows in calls too small for them."""

@@ -106,3 +106,18 @@ def test_fragments_every_row_goes_to_one_kernel(tmp_path):
                         }
     printf("ok\n");""")
     assert out == ["ok"]
+
+
+def _f32(tmp_path, cases):
+    """Workgroups per CU on shared tiles, 0 = split tiles, of each problem (M, N, K)."""
+    return [int(l) for l in _run(tmp_path, "".join('printf("%%d\\n", gemm_f32_choose(%d, %d, %d, 256).per_cu);\n' % c for c in cases))]
+
+
+def test_fp32_tiles(tmp_path):
+    """A tile alone behind four rounds is what three workgroups per CU avoid; split tiles where the shared ones leave the chip empty."""
+    cases = [((2176, 2304, 2048), 3), ((6544, 768, 3072), 3), ((25600, 192, 768), 3), ((4800, 1024, 1024), 3), ((7168, 1024, 4096), 3),
+             ((30000, 192, 192), 4), ((65536, 64, 192), 4), ((65537, 64, 192), 3), ((81919, 64, 192), 4), ((81857, 64, 192), 4), ((81856, 64, 192), 3),
+             ((12608, 768, 192), 4), ((12608, 768, 768), 4), ((3152, 576, 192), 4), ((10088, 192, 768), 4), ((20000, 192, 768), 4),
+             ((12608, 192, 768), 0), ((8192, 192, 768), 0), ((788, 192, 768), 0), ((2000, 768, 3072), 0), ((4000, 768, 3072), 4),
+             ((76800, 64, 2048), 0), ((48640, 64, 2048), 4), ((65536, 64, 2048), 4), ((65537, 64, 2048), 0), ((90048, 64, 2048), 0), ((90112, 64, 2048), 3), ((76800, 64, 1024), 3), ((1, 64, 64), 0)]
+    assert _f32(tmp_path, [c for c, _ in cases]) == [n for _, n in cases]
