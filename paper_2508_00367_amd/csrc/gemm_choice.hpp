@@ -107,7 +107,7 @@ struct GemmF32Choice {
 inline GemmF32Choice gemm_f32_choose(int64_t M, int N, int K, int64_t cus) {
     const int64_t tiles = ((M + 63) / 64) * (N / 64);
     const bool fills = tiles >= 4 * cus || (K <= 384 && 2 * tiles >= 3 * cus) || (tiles > cus && 10 * tiles >= 9 * cus * ((tiles + cus - 1) / cus));
-    if (!fills || (N == 64 && K > 1024 && tiles > 4 * cus && tiles < 6 * cus)) return {0};
+    if (!fills || (N == 64 && K > 1024 && tiles > 4 * cus && 2 * tiles < 11 * cus)) return {0};
     return {tiles > 4 * cus && (tiles < 5 * cus || K > 1024) ? 3 : 4};
 }
 
