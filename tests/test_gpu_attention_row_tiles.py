@@ -32,7 +32,7 @@ def test_row_tiles_same_bits(N, heads):
 
 
 @pytest.mark.parametrize("stride", [64, 72, (1 << 24) - 8, 1 << 24])
-@pytest.mark.parametrize("N", [1, 31, 33, 65, 129, 257])
+@pytest.mark.parametrize("N", [1, 31, 33, 48, 49, 65, 129, 257])
 def test_output_rows_at_any_stride(N, stride):
     """Output rows side by side, ragged and around 2^24 elements apart (32 rows beyond 32-bit byte offsets): the same bits,
     and nothing between the rows or behind the last one."""
@@ -48,6 +48,7 @@ def test_output_rows_at_any_stride(N, stride):
         rs.rs_attention_fwd(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], o, 0.125)
     torch.cuda.synchronize()
     assert torch.equal(near, far)
+    assert norm_err(to_host(near), oracle.attention(*(to_host(qkv[:, :, i]) for i in range(3)), 0.125)) < TOL["bf16"]
     if stride > 64:
         assert (buf[:N * stride].view(N, stride)[:, 64:128] == 7.0).all()
     assert (buf[N * stride:] == 7.0).all()
