@@ -20,10 +20,10 @@
 #include <float.h>
 
 #include "common.hpp"
+#include "attention_choice.hpp"
 
 namespace rs {
 
-constexpr int ATT_BM = 256;  // query rows per workgroup (8 waves x 32)
 constexpr int ATT_BN = 64;   // keys per tile
 constexpr int DH = 64;
 
@@ -306,7 +306,6 @@ __global__ __launch_bounds__(NW * 64, 4) void attention_bf16_kernel(
 // (running maximum, row sum, unnormalised output) are merged through LDS in wave order, so the
 // result does not depend on timing.
 // ---------------------------------------------------------------------------
-constexpr int ATT_TAIL_ROWS = 64;
 
 __global__ __launch_bounds__(512, 2) void attention_bf16_tail_kernel(
     const bf16raw* __restrict__ q, const bf16raw* __restrict__ k, const bf16raw* __restrict__ v,
@@ -741,33 +740,20 @@ hipError_t launch_attention(rs_dtype dt, const void* q, const void* k, const voi
                            (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh,
                            scale_log2e, q_waves);
     } else if (dt == RS_BF16) {
-        // Query rows per workgroup, and whether the rows beyond the last full tile of 256 go to the tail kernel, by what
-        // the busiest CU of an XCD gets, in workgroups of 4 waves (it holds four of them, or two of 8 waves; a head
-        // stays on one XCD; the tail kernel costs about 0.6 per head of a CU and 8 us).  us, 8 waves / 4 waves / 8 waves + tail:
-        // 8 x 1569 x 12 heads 92 / 82 / 105, 4 x 1407 x 16 53 / 46, 20 x 785 x 12 64 / 57 / 65, 3 x 1569 x 12 55 / 45 / 49, 1 x 1569 x 12
-        // 31.5 / 23.6 / 46, 4 x 4097 x 16 312 / 324 / 311, 1 x 4097 x 16 127 / 104 / 97, and with the same number on both sides
-        // 4 x 2869 x 16 153 / 160, 4 x 2009 x 16 79 / 83, 2 x 2353 x 12 46.5 / 48.6: the larger tile, which copies K and V half as often.
         const int BH = B * H;
-        const int64_t heads = (BH + 7) / 8, cus = device_cus() / 8;
-        auto busiest = [&](int64_t tiles) { return (heads * tiles + cus - 1) / cus; };
-        const int rem = N % ATT_BM;
-        const bool tail_ok = rem > 0 && rem <= ATT_TAIL_ROWS && N > ATT_BM;
-        const int64_t c8 = 20 * busiest((N + ATT_BM - 1) / ATT_BM), c4 = 10 * busiest((N + ATT_BM / 2 - 1) / (ATT_BM / 2));
-        const int64_t c_tail = 20 * busiest(N / ATT_BM) + 6 * busiest(1) + 9000 / N;
-        const bool best_tail = tail_ok && c_tail < c8 && c_tail < c4;
-        const int bm = best_tail || c8 <= c4 ? ATT_BM : ATT_BM / 2;
-        const int q_tiles = best_tail ? N / bm : (N + bm - 1) / bm;
+        const AttentionPlan plan = attention_plan(BH, N, device_cus());
+        const int q_tiles = plan.q_tiles;
         dim3 grid(8 * ((BH + 7) / 8) * q_tiles);
 #define ATT_GO(NW_)                                                                                                  \
     hipLaunchKernelGGL((attention_bf16_kernel<NW_>), grid, dim3(NW_ * 64), 0, s, (const bf16raw*)q, (const bf16raw*)k, \
                        (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn, osh, scale_log2e, H, BH, q_tiles)
-        if (bm == ATT_BM) ATT_GO(8);
+        if (plan.rows == ATT_BM) ATT_GO(8);
         else ATT_GO(4);
 #undef ATT_GO
-        if (best_tail)
+        if (plan.tail)
             hipLaunchKernelGGL(attention_bf16_tail_kernel, dim3(BH), dim3(512), 0, s, (const bf16raw*)q,
                                (const bf16raw*)k, (const bf16raw*)v, (bf16raw*)o, N, sb, sn, sh, osb, osn,
-                               osh, scale_log2e, H, q_tiles * bm);
+                               osh, scale_log2e, H, q_tiles * ATT_BM);
     } else {
         dim3 grid((N + 31) / 32, H, B);
         hipLaunchKernelGGL(sn < F32_FAR ? attention_f32_kernel<false> : attention_f32_kernel<true>, grid, dim3(256), 0, s,

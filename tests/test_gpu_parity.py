@@ -45,22 +45,30 @@ def test_attention_packed_qkv(dtype, B, N, H):
     assert err < TOL[dtype]
 
 
-# (B, N, H) chosen so that the launcher takes each of its long-sequence plans (a round is 512
-# workgroups of 256 rows): every row in the tiled kernel, the last workgroup of a head holding one
-# row and seven idle waves (128 heads x 3 tiles fit one round); the one row beyond the last full
-# tile in the tail kernel (128 x 5 tiles would start a second round); 36 tail rows with a padded
-# last key tile; no rows left over.
-@pytest.mark.parametrize("B,N,H", [(8, 513, 16), (8, 1025, 16), (8, 1060, 16), (8, 1024, 12)])
+# (B, N, H) and the query rows per workgroup of each long-sequence plan on 256 CUs (negative: the rows beyond the last full tile in
+# the tail kernel); the rule itself is held to this list on the CPU.  128 rows: the last workgroup with one row and three idle
+# waves, with 36 rows and a padded last key tile, no rows left over.  256 rows: two busy waves and six idle ones, a full second
+# half, and no rows left over.  Tail: one row; 41 rows (a second block of 32) with a padded last key tile; 64.
+ATT_PLANS = [(8, 513, 16, 128), (8, 1025, 16, 128), (8, 1060, 16, 128), (8, 1024, 12, 128), (8, 300, 16, 256), (8, 400, 16, 256),
+             (8, 512, 16, 256), (7, 2305, 7, -256), (7, 2345, 7, -256), (7, 2368, 7, -256)]
+
+
+@pytest.mark.parametrize("B,N,H", [p[:3] for p in ATT_PLANS])
 def test_attention_long_sequence_plans(B, N, H):
     _say("attention plans", B, N, H)
     qkv = host_round(si.generic(7, 1, (B, N, 3, H, 64)), "bf16")
-    ref = oracle.attention(qkv[:, :, 0], qkv[:, :, 1], qkv[:, :, 2], 0.125)
     d = to_dev(qkv, "bf16")
     o = torch.full((B, N, H, 64), float("nan"), device="cuda", dtype=torch.bfloat16)
     rs.rs_attention_fwd(d[:, :, 0], d[:, :, 1], d[:, :, 2], o, 0.125)
     torch.cuda.synchronize()
     got = to_host(o)
     assert np.isfinite(got).all()
+    if N > 2000:   # the oracle on two of the heads of the first and the last image
+        pick = lambda t: t[::B - 1, :, ::H - 1]
+        got = pick(got)
+    else:
+        pick = lambda t: t
+    ref = oracle.attention(*(np.ascontiguousarray(pick(qkv[:, :, i])) for i in range(3)), 0.125)
     err = norm_err(got, ref)
     err_tail = norm_err(got[:, -40:], ref[:, -40:])
     _say("  err %.3e, last 40 rows %.3e" % (err, err_tail))

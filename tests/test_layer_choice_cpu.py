@@ -1,4 +1,4 @@
-"""The rules on sizes that pick a kernel for a block's layers, on the host.  The expected kernels are those that measured faster on 256 CUs
+"""The rules on sizes that pick a kernel for a block's layers and for attention, on the host.  The expected kernels are those that measured faster on 256 CUs
 at sizes on both sides of each line."""
 import os
 import shutil
@@ -14,7 +14,7 @@ def _run(tmp_path, body):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     src, exe = tmp_path / "choice.cpp", tmp_path / "choice"
-    src.write_text('#include <stdio.h>\n#include <initializer_list>\n#include "gemm_choice.hpp"\nusing namespace rs;\nint main() {\n' + body + "\nreturn 0;\n}\n")
+    src.write_text('#include <stdio.h>\n#include <initializer_list>\n#include "gemm_choice.hpp"\n#include "attention_choice.hpp"\nusing namespace rs;\nint main() {\n' + body + "\nreturn 0;\n}\n")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2508_00367_amd", "csrc"),
                     str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
@@ -121,3 +121,29 @@ def test_fp32_tiles(tmp_path):
              ((12608, 192, 768), 0), ((8192, 192, 768), 0), ((788, 192, 768), 0), ((2000, 768, 3072), 0), ((4000, 768, 3072), 4),
              ((76800, 64, 2048), 0), ((48640, 64, 2048), 4), ((65536, 64, 2048), 4), ((65537, 64, 2048), 0), ((90048, 64, 2048), 0), ((90112, 64, 2048), 3), ((76800, 64, 1024), 3), ((1, 64, 64), 0)]
     assert _f32(tmp_path, [c for c, _ in cases]) == [n for _, n in cases]
+
+
+def _attention(tmp_path, cases):
+    """(query rows per workgroup, workgroups per head, tail) of each (heads in all, N)."""
+    body = "".join('{ const AttentionPlan p = attention_plan(%d, %d, 256); printf("%%d %%d %%d\\n", p.rows, p.q_tiles, (int)p.tail); }\n' % c for c in cases)
+    return [tuple(map(int, l.split())) for l in _run(tmp_path, body)]
+
+
+def test_attention_plans_reach_what_the_gpu_tests_say(tmp_path):
+    from test_gpu_attention_row_tiles import ROW_TILES
+    from test_gpu_parity import ATT_PLANS
+    got = _attention(tmp_path, [(B * H, N) for B, N, H, _ in ATT_PLANS])
+    assert [-r if tail else r for r, _, tail in got] == [p[3] for p in ATT_PLANS]
+    assert {p[3] for p in ATT_PLANS} == {128, 256, -256}
+    assert [p[0:3:2] for p in _attention(tmp_path, [(h, N) for N, h in ROW_TILES])] == [(256, 0)] * len(ROW_TILES)
+    assert [p[0:3:2] for p in _attention(tmp_path, [(1, N) for N, _ in ROW_TILES])] == [(128, 0)] * len(ROW_TILES)
+
+
+def test_attention_plan_covers_every_row(tmp_path):
+    cases = [(bh, n) for bh in (1, 7, 8, 49, 96, 128, 1000) for n in list(range(257, 2700, 7)) + [2304, 2305, 2368, 2369, 4096, 4097, 4160]]
+    for (bh, n), (rows, tiles, tail) in zip(cases, _attention(tmp_path, cases)):
+        assert rows in (128, 256)
+        if tail:
+            assert rows == 256 and 0 < n - rows * tiles <= 64, (bh, n)
+        else:
+            assert (tiles - 1) * rows < n <= tiles * rows, (bh, n)
