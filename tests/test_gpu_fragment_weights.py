@@ -10,14 +10,21 @@ import paper_2508_00367_amd as rs
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # B, N, D, Dm
+SMALL = [  # B, N, D, Dm
     (1, 1, 64, 64), (1, 127, 64, 128), (1, 128, 128, 192), (3, 43, 192, 320), (1, 257, 256, 64), (2, 192, 320, 448), (5, 77, 448, 832),
-    (2, 197, 576, 256), (40, 197, 384, 1536),                                  # by shape: direct for every layer but the projection
-    (17, 197, 768, 3072),                                                      # by shape: slim, direct and 128 x 128
-    (66, 197, 768, 3072),                                                      # by shape: direct, and persistent for fc2
-    (60, 197, 832, 576), (120, 197, 576, 832),                                 # by shape: slim 256 x 128, up to one round and two
-    (113, 197, 768, 3072),                                                     # by shape: fc2 persistent, its last 501 rows apart
-    (335, 197, 64, 576), (335, 197, 128, 256)]                                 # by shape: ring; fc2 of the first slim 256 x 128, of the second ring
+    (2, 197, 576, 256)]
+# and with the kernels that the choice by shape takes on 256 CUs, for the layers qkv, proj, fc1, fc2 (the CPU tests hold it to that)
+BY_SHAPE = [
+    ((30, 197, 384, 1536), ["slim 256x128", "slim 128x128", "direct", "slim 128x128"]),
+    ((40, 197, 384, 1536), ["direct", "slim 128x128", "direct", "slim 128x128"]),
+    ((17, 197, 768, 3072), ["direct", "slim 128x128", "direct", "slim 128x128"]),
+    ((66, 197, 768, 3072), ["direct", "direct", "direct", "persistent"]),
+    ((223, 197, 384, 1536), ["direct", "direct", "direct", "direct"]),                         # fc2 with a last round a third full
+    ((46, 197, 832, 576), ["direct", "slim 256x128", "direct", "slim 256x128"]),               # up to one round
+    ((120, 197, 576, 832), ["direct", "slim 256x128", "direct", "slim 256x128"]),              # up to two
+    ((113, 197, 768, 3072), ["direct", "direct", "direct", "persistent + slim 64x64"]),        # 501 rows beyond whole rounds
+    ((335, 197, 64, 576), ["direct", "ring", "direct", "slim 256x128"]), ((335, 197, 128, 256), ["direct", "ring", "direct", "ring"])]
+CASES = SMALL + [c for c, _ in BY_SHAPE]
 
 
 @pytest.mark.parametrize("dist", [rs.RS_DIST_L2, rs.RS_DIST_COS])

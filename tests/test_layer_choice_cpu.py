@@ -147,3 +147,10 @@ def test_attention_plan_covers_every_row(tmp_path):
             assert rows == 256 and 0 < n - rows * tiles <= 64, (bh, n)
         else:
             assert (tiles - 1) * rows < n <= tiles * rows, (bh, n)
+
+
+def test_fragment_kernels_of_the_gpu_tests(tmp_path):
+    from test_gpu_fragment_weights import BY_SHAPE
+    got = _frag(tmp_path, [p for (B, N, D, Dm), _ in BY_SHAPE for p in ((B * N, 3 * D, D, 0), (B * N, D, D, 1), (B * N, Dm, D, 0), (B * N, D, Dm, 1))])
+    names = [" + ".join(k for k, _ in g) for g in got]
+    assert [names[i:i + 4] for i in range(0, len(names), 4)] == [want for _, want in BY_SHAPE]
