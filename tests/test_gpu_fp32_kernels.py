@@ -163,11 +163,15 @@ def test_fp32_attention_low_values_as_a_mask(N, masked, value):
     assert err < TOL["f32"]
 
 
-@pytest.mark.parametrize("M,K,N", [(6208, 64, 256), (24576, 64, 64), (24513, 448, 64), (10088, 768, 192), (9601, 832, 192), (21845, 192, 192),
-                                   (25601, 768, 192), (4545, 1088, 1024)])  # three workgroups per CU: four to five rounds
+# M, K, N that go to the 64-row tiles the waves share on 256 CUs, and the workgroups per CU (the CPU tests hold the choice to that): 1.5
+# rounds at short K, a last round at least 0.9 full at long K, four to five and more rounds; 2, 6, 14, 24, 26 and 34 slices; one row in the last tile
+SHARED_TILES = [(6208, 64, 256, 4), (24576, 64, 64, 4), (29505, 448, 64, 4), (10088, 768, 192, 4), (9857, 832, 192, 4), (21845, 192, 192, 3), (8193, 192, 768, 4),
+                (25601, 768, 192, 3), (4545, 1088, 1024, 3)]
+
+
+@pytest.mark.parametrize("M,K,N", [c[:3] for c in SHARED_TILES])
 def test_fp32_shared_tiles_same_bits(M, K, N):
-    """Sizes that go to the 64-row tiles the waves share (1.5 rounds at short K, a last round at least 0.9 full at long K; 2, 6,
-    14, 24 and 26 slices): the bits of the same rows in calls too small for them."""
+    """The bits of the same rows in calls too small for the shared tiles."""
     _say("fp32 shared tiles", M, K, N)
     g = torch.Generator(device="cuda").manual_seed(M + K)
     a, w = torch.randn((M, K), device="cuda", generator=g), torch.randn((K, N), device="cuda", generator=g)

@@ -154,3 +154,11 @@ def test_fragment_kernels_of_the_gpu_tests(tmp_path):
     got = _frag(tmp_path, [p for (B, N, D, Dm), _ in BY_SHAPE for p in ((B * N, 3 * D, D, 0), (B * N, D, D, 1), (B * N, Dm, D, 0), (B * N, D, Dm, 1))])
     names = [" + ".join(k for k, _ in g) for g in got]
     assert [names[i:i + 4] for i in range(0, len(names), 4)] == [want for _, want in BY_SHAPE]
+
+
+def test_fp32_sizes_of_the_gpu_tests(tmp_path):
+    """The whole call on shared tiles, the calls it is compared with on split ones."""
+    from test_gpu_fp32_kernels import SHARED_TILES
+    assert _f32(tmp_path, [(M, N, K) for M, K, N, _ in SHARED_TILES]) == [c[3] for c in SHARED_TILES]
+    parts = [(m, N, K) for M, K, N, _ in SHARED_TILES for step in [1024 if N > 64 else 2048] for m in (step, M % step or step)]
+    assert set(_f32(tmp_path, parts)) == {0}
