@@ -547,8 +547,9 @@ __global__ __launch_bounds__(512, 4) void attention_bf16_small_kernel(
 // tile of the wave's own, no barrier in the loop; the four partial results are merged through
 // LDS in wave order.  Transposed like the bf16 kernels: S^T = K Q^T, and a lane's scores (query l32,
 // keys 8 j + 4 g + i in register 4 j + i) feed O^T = V^T P^T as they are: one k step of the instruction
-// takes one key from each half-wave.  The first half of the next K tile is requested before the softmax, the second
-// at the top of its turn, the copies of the next V tile under the next scores.
+// takes one key from each half-wave.  The first half of the next K tile is requested before the softmax, the copies of the
+// next V tile behind the products that read the present one, and the second half of K at the top of its turn: answers come in
+// order, so what covers V is the first half of the scores, and the second half waits for V as well.
 // The key split is there for small batches: four images of 197 tokens and three heads are 84 blocks
 // of 32 rows, which leave two thirds of the CUs empty and would walk seven key tiles one after the other.
 // A wave has one or two tiles at N = 197, so most of its time is waiting and merging: what counts is how many
@@ -668,7 +669,7 @@ __global__ __launch_bounds__(256, FAR ? 2 : 4) void attention_f32_kernel(
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
-        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // V has landed (the next K may be in flight)
+        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // V has landed (as it had before the second half of K; the next K may be in flight)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll

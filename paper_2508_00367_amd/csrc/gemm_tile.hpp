@@ -64,7 +64,7 @@ __device__ __forceinline__ int frag_off(int f, int kk, int K) { return f * (K * 
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
 // ---------------------------------------------------------------------------
-// Epilogue in the accumulator layout (ring kernels below).
+// Epilogue in the accumulator layout (the direct, slim and ring kernels and those of 192-wide blocks).
 //
 // A wave owns WM = 32 TM token rows x 64 features; lane (l32, g) holds, for row 32 j + l32 of
 // every 32-row group j, features 32 i + 8 q + 4 g + e in register 4 q + e of acc[i][j].  All the

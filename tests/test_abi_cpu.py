@@ -362,12 +362,13 @@ def test_static_scratch_takes_the_blocks_that_fill_it(B, N, D):
 
 
 def test_packed_layout_has_a_version_of_its_own():
-    """W_fc2 with one extra line per row (Dm >= 512, Dm % 256 == 0): a program tells such buffers from older ones by
-    rs_version(), which was 200 while the rows lay Dm elements apart."""
+    """The matrices lie in fragments; where Dm >= 512 and Dm % 256 == 0 the buffer keeps the room that W_fc2 took when it had one extra
+    line per row (zeros behind the fragments).  Such a buffer has the size of one in rows, so a program that keeps packed weights
+    tells them apart by rs_version(): 200 and 300 while the matrices lay in rows."""
     plain = lambda D, Dm: (4 * D * D + 2 * D * Dm) * 2 + 2 * (3 * D + Dm) * 4
     for D, Dm in [(192, 768), (768, 3072), (64, 512)]:
         assert rs.rs_packed_weights_size(_cfg(D=D, H=D // 64, Dm=Dm)) == plain(D, Dm) + D * 64 * 2
-        assert rs.rs_version() >= 300
+        assert rs.rs_version() >= 400
     for D, Dm in [(64, 256), (192, 576), (128, 448)]:
         assert rs.rs_packed_weights_size(_cfg(D=D, H=D // 64, Dm=Dm)) == plain(D, Dm)
 
