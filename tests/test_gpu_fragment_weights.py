@@ -55,3 +55,37 @@ def test_kernels_on_fragments_same_bits(B, N, D, Dm, dist):
     assert not torch.isnan(outs[0][0].view(torch.bfloat16).float()).any()
     for o in outs[1:]:
         assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2, 4])
+@pytest.mark.parametrize("B,N", [(1, 127), (1, 129), (3, 43), (40, 197)])
+def test_row_statistics_at_eight_byte_alignment(B, N, variant):
+    """x_stats need be 8-byte aligned only; the direct kernel copies them 16 bytes at a time, two rows, also the last one of an odd count."""
+    print("statistics alignment", B, N, variant, flush=True)
+    D, Dm = 384, 256
+    g = torch.Generator(device="cuda").manual_seed(B + N)
+    nrm = lambda *s, std=0.05: (torch.randn(s, device="cuda", generator=g) * std).bfloat16()
+    w = {"ln1_g": nrm(D) + 1, "ln1_b": nrm(D), "w_qkv": nrm(D, 3 * D), "b_qkv": nrm(3 * D), "w_proj": nrm(D, D), "b_proj": nrm(D),
+         "ln2_g": nrm(D) + 1, "ln2_b": nrm(D), "w_fc1": nrm(D, Dm), "b_fc1": nrm(Dm), "w_fc2": nrm(Dm, D), "b_fc2": nrm(D)}
+    x = nrm(B, N, D, std=2.0)
+    cfg = rs.make_cfg(B, N, D, D // 64, Dm, 1, N - 1, torch.bfloat16)
+    ws = torch.empty(rs.rs_block_workspace_size(cfg), dtype=torch.uint8, device="cuda")
+    stats = torch.empty((B * N, 2), device="cuda")
+    xf = x.view(B * N, D).float()
+    stats[:, 0], stats[:, 1] = xf.mean(1), torch.rsqrt(xf.var(1, unbiased=False) + 1e-6)
+    outs = []
+    try:
+        for v, shift in ((3, 0), (variant, 0), (variant, 2)):
+            rs.rs_tune_gemm_variant(v)
+            buf = torch.full((B * N * 2 + 4,), float("nan"), device="cuda")
+            at = buf[shift:shift + B * N * 2].view(B * N, 2)
+            at.copy_(stats)
+            assert at.data_ptr() % 16 == 4 * shift
+            y, kept = torch.full((B, N, D), float("nan"), device="cuda", dtype=torch.bfloat16), torch.zeros((B, N), device="cuda", dtype=torch.int32)
+            rs.rs_block_fwd_chained(cfg, rs.make_weights(w), x, at, y, None, kept, None, ws)
+            torch.cuda.synchronize()
+            outs.append(y.view(torch.int16))
+    finally:
+        rs.rs_tune_gemm_variant(0)
+    assert torch.isfinite(outs[0].view(torch.bfloat16).float()).all()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
