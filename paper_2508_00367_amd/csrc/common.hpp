@@ -91,7 +91,7 @@ template <> struct Elem<bf16raw> {
 // for an op that does not care which of two comes first.  The partner comes by lane swaps and DPP moves that the
 // compiler folds into the op, one or two instructions a step; through __shfl_xor a step is a trip through the LDS pipe
 // plus address arithmetic and a wait (row statistics of 50432 x 768 23.4 -> 21.0 us, scores, selection and copy of 8 x 1569 x 768
-// 25.7 -> 24.5, one image through 12 blocks 442 -> 434).
+// out of the caches 25.7 -> 24.5, one image through 12 blocks 442 -> 434).
 //   32, 16 apart: v_permlane32_swap / v_permlane16_swap of a value with itself leave both halves' values in every lane.
 //   8 apart: a rotation of the 16-lane row by 8; 4 apart: by 4, where the lanes 8 apart already agree.
 template <int CTRL, typename T>

@@ -1281,11 +1281,13 @@ static hipError_t launch_bf16(const void* a, const void* wt, const void* bias, c
 #define RS_STR2(...) #__VA_ARGS__
 #define RS_STR(...) RS_STR2(__VA_ARGS__)
 const char* gemm_build_info() {
-    return "bf16 gemm, block: weights in fragments; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU, direct tiles"
-           " 128x256 beyond, persistent tiles (BM,BN,BK,stages,waves m,waves n) " RS_STR(RS_GEMM_CFG) ", three activation stages when"
-           " K >= 2048, when K >= 1536 and the last round is more than 0.5 full; rs_linear_fwd: weights in rows; slim (256x128 up to 1.45"
-           " rounds of 256x256 when K < 2048), persistent, ring tiles 128x128x32 and 128x256x32 beyond one round when K <= 384"
-           ", rows behind whole rounds apart when K >= 2048 and the last round is at most 0.5 full";
+    return "bf16 gemm, block: weights in fragments; slim tiles 64x64, 128x64, 128x128, 256x128 up to one workgroup per CU (256x128 to two"
+           " where the direct tiles are more), direct tiles 128x256 beyond, ring tiles 128x128x32 or slim to 128 features; persistent tiles"
+           " (BM,BN,BK,stages,waves m,waves n) " RS_STR(RS_GEMM_CFG) ", three activation stages when K >= 2048, when K >= 1536 and the last"
+           " round is more than 0.5 full (0.6 below K = 3072), and for the whole rounds when K >= 2048 and it is at most 1/6 full, the rows"
+           " behind them apart; rs_linear_fwd: weights in rows; slim (256x128 up to 1.45 rounds of 256x256 when K < 2048), persistent, ring"
+           " tiles 128x128x32 and 128x256x32 beyond one round when K <= 384, rows behind whole rounds apart when K >= 2048 and the last round"
+           " is at most 0.5 full";
 }
 
 // `count` independent products out_p[M, N] = a_p[M, K] @ wt_p[N, K]^T (bf16, no bias), problem p at
